@@ -609,6 +609,19 @@ symb_status launch_grad_reduce(symb_handle h, const GradReduceParams& rp, int ns
     return SYMB_OK;
 }
 
+// An elementwise pass over the rows of a chunk list (adapter_kernels.hpp, ROWPASS_*).  A grid has at most 65535 chunks in
+// y; longer lists take several launches, each from its own place in the list.
+template <class P>
+symb_status launch_row_pass(symb_handle h, void (*kfn)(P), P p, int width, size_t nchunks, hipStream_t st) {
+    for (size_t at = 0; at < nchunks; at += 65535) {
+        const unsigned n = (unsigned)std::min<size_t>(65535, nchunks - at);
+        hipLaunchKernelGGL(kfn, dim3((width / 8 + ROWPASS_COLS - 1) / ROWPASS_COLS, n, SKINNY_ROWS / ROWPASS_ROWS), dim3(ROWPASS_COLS), 0, st, p);
+        SYMB_HIP(h, hipGetLastError());
+        p.chunks += n;
+    }
+    return SYMB_OK;
+}
+
 // C[T][N] = A[T][K] Wop, T <= 16, with the weight-streaming kernels (adapter_kernels.hpp).
 //   w_kmajor: Wop is [N][K] (one workgroup per 32 columns, K split inside the workgroup);
 //   else Wop is [K][N] (column blocks x K ranges, fp32 partial sums in `partial`, then the finish kernel).
@@ -1138,8 +1151,7 @@ symb_status symb_noise_add(symb_handle h, const symb_batch* b, const void* X, co
     if ((st = upload(h, blob, s, &dev)) != SYMB_OK) return st;
     NoiseAddParams np{(const bf16*)X, (bf16*)Xn, b->d_in, (const RowChunk*)(dev + o_ch), (const int32_t*)(dev + o_off),
                       (const NoiseDesc*)(dev + o_nd)};
-    hipLaunchKernelGGL(symb_noise_add_kernel, dim3((unsigned)chunks.size()), dim3(256), 0, s, np);
-    SYMB_HIP(h, hipGetLastError());
+    if ((st = launch_row_pass(h, symb_noise_add_kernel, np, b->d_in, chunks.size(), s)) != SYMB_OK) return st;
     { guard.completed = true; return seal_slot(h, s); }
 }
 

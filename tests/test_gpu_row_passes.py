@@ -1,0 +1,31 @@
+"""Elementwise passes over the rows of a batch (noise prepass of the privacy flow): edges of the 8-row x
+1024-column blocks a workgroup takes, and a chunk list longer than one grid."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_harness as gh
+import oracle
+import synth
+from paper_2507_03220_amd import binding as sb
+
+pytestmark = pytest.mark.gpu
+
+
+def _bits(rng, shape):
+    return synth.f32_to_bf16_bits(rng.standard_normal(shape).astype(np.float32))
+
+
+@pytest.mark.parametrize("width,lens", [(8, [1]), (1024, [8, 0, 9]), (1032, [7, 33, 1, 64, 40]), (2056, [31, 5]),
+                                        (8, [2097200, 3])])        # 65538 row chunks: two launches
+def test_noise_add_bit_exact(width, lens):
+    rng = np.random.default_rng(width + len(lens))
+    off = np.zeros(len(lens) + 1, dtype=np.int32)
+    off[1:] = np.cumsum(lens)
+    X = _bits(rng, (int(off[-1]), width))
+    noise = [[_bits(rng, (n, width)), _bits(rng, (1, width)), None][i % 3] if n else None for i, n in enumerate(lens)]
+    b = sb.Batch(width, 8, off, [sb.Adapter() for _ in lens])
+    Xn = torch.full((int(off[-1]), width), float("nan"), device="cuda", dtype=torch.bfloat16)
+    sb.symb_noise_add(gh.handle(), b, gh.to_dev(X), [gh.to_dev(n) for n in noise], Xn)
+    torch.cuda.synchronize()
+    assert np.array_equal(gh.bf16_bits(Xn), oracle.noise_add(off, X, noise))
