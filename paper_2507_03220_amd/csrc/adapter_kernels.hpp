@@ -1107,9 +1107,14 @@ __global__ void __launch_bounds__(256) symb_ia3_grad_kernel(const Ia3GradParams 
     }
 }
 
+constexpr int ROWPASS_ROWS = 8;        // rows per thread (a divisor of the row chunk's SKINNY_ROWS)
+constexpr int ROWPASS_COLS = 128;      // threads per workgroup, one 16-byte column each
+
 // -------------------------------------------------------------------------------------------
 // Row scale for the IA3 backward:  out[t][j] = bf16( dY[t][j] * l_seg(t)[j] ) for IA3 rows,
-// a plain copy for the others (and, with X and kind = IA3_IN, the input scale of the forward).  One workgroup per row chunk from the work list.
+// a plain copy for the others (and, with X and kind = IA3_IN, the input scale of the forward).  Bound by
+// HBM: 4 bytes per element.  Measured on 8200 IA3 rows of 11008: 84.1 us with a workgroup per 32-row chunk
+// walking its rows four at a time (257 workgroups), 55.2 us (6.6 TB/s) with 8 rows x 1024 columns each.
 // -------------------------------------------------------------------------------------------
 struct ScaleParams {
     const bf16* dY;           // [T][d_out]: rows to scale (dY for the IA3 backward, X for the IA3_IN forward)
@@ -1121,44 +1126,38 @@ struct ScaleParams {
     const bf16* const* in_seg;// device [S] or null: input rows of segment i start at in_seg[i]
     const int32_t* off;       // device [S+1] (read only with in_seg)
 };
-__global__ void __launch_bounds__(256) symb_ia3_scale_rows_kernel(const ScaleParams p) {
-    const RowChunk ch = p.chunks[blockIdx.x];
+// grid = (blocks of ROWPASS_COLS 16-byte columns, row chunks, SKINNY_ROWS / ROWPASS_ROWS); see the noise prepass below
+__global__ void __launch_bounds__(ROWPASS_COLS) symb_ia3_scale_rows_kernel(const ScaleParams p) {
+    const RowChunk ch = p.chunks[blockIdx.y];
     const SegDesc sd = p.seg[ch.seg];
     const bool ia3 = sd.kind == p.kind;
-    const int nchunk = p.d_out >> 3;
     const bf16* const in = p.in_seg ? p.in_seg[ch.seg] - (size_t)p.off[ch.seg] * p.d_out : p.dY;
-    // a thread keeps its 8 columns and walks the chunk's rows, four rows in flight
-    for (int c = threadIdx.x; c < nchunk; c += 256) {
-        uint4 l = make_uint4(0u, 0u, 0u, 0u);
-        if (ia3) l = *reinterpret_cast<const uint4*>(sd.A + c * 8);
+    const int r0 = blockIdx.z * ROWPASS_ROWS, nr = min(ch.nrows - r0, ROWPASS_ROWS);
+    const int c = blockIdx.x * ROWPASS_COLS + threadIdx.x;
+    if (nr <= 0 || c >= (p.d_out >> 3)) return;
+    const size_t col = (size_t)c * 8;
+    const int row0 = ch.row0 + r0;
+    uint4 g[ROWPASS_ROWS];                               // rows past the last one repeat it and are not stored
+#pragma unroll
+    for (int u = 0; u < ROWPASS_ROWS; ++u) g[u] = *reinterpret_cast<const uint4*>(in + (size_t)(row0 + min(u, nr - 1)) * p.d_out + col);
+    if (ia3) {
+        const uint4 l = *reinterpret_cast<const uint4*>(sd.A + col);
         const unsigned int lw[4] = {l.x, l.y, l.z, l.w};
-        auto scaled = [&](uint4 g) __attribute__((always_inline)) {
-            if (ia3) {
-                unsigned int gw[4] = {g.x, g.y, g.z, g.w};
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float lo = bf16_bits_to_f32((unsigned short)(gw[q] & 0xffffu)) * bf16_bits_to_f32((unsigned short)(lw[q] & 0xffffu));
-                    const float hi = bf16_bits_to_f32((unsigned short)(gw[q] >> 16)) * bf16_bits_to_f32((unsigned short)(lw[q] >> 16));
-                    gw[q] = pack2_bf16(lo, hi);
-                }
-                g = make_uint4(gw[0], gw[1], gw[2], gw[3]);
+        for (int u = 0; u < ROWPASS_ROWS; ++u) {
+            unsigned int gw[4] = {g[u].x, g[u].y, g[u].z, g[u].w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float lo = bf16_bits_to_f32((unsigned short)(gw[q] & 0xffffu)) * bf16_bits_to_f32((unsigned short)(lw[q] & 0xffffu));
+                const float hi = bf16_bits_to_f32((unsigned short)(gw[q] >> 16)) * bf16_bits_to_f32((unsigned short)(lw[q] >> 16));
+                gw[q] = pack2_bf16(lo, hi);
             }
-            return g;
-        };
-        const size_t col = (size_t)c * 8;
-        int t = 0;
-        for (; t + 4 <= ch.nrows; t += 4) {
-            uint4 g[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) g[u] = *reinterpret_cast<const uint4*>(in + (size_t)(ch.row0 + t + u) * p.d_out + col);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) *reinterpret_cast<uint4*>(p.out + (size_t)(ch.row0 + t + u) * p.d_out + col) = scaled(g[u]);
-        }
-        for (; t < ch.nrows; ++t) {
-            const uint4 g = *reinterpret_cast<const uint4*>(in + (size_t)(ch.row0 + t) * p.d_out + col);
-            *reinterpret_cast<uint4*>(p.out + (size_t)(ch.row0 + t) * p.d_out + col) = scaled(g);
+            g[u] = make_uint4(gw[0], gw[1], gw[2], gw[3]);
         }
     }
+#pragma unroll
+    for (int u = 0; u < ROWPASS_ROWS; ++u)
+        if (u < nr) *reinterpret_cast<uint4*>(p.out + (size_t)(row0 + u) * p.d_out + col) = g[u];
 }
 
 // -------------------------------------------------------------------------------------------
@@ -1167,10 +1166,9 @@ __global__ void __launch_bounds__(256) symb_ia3_scale_rows_kernel(const ScalePar
 // copied.  fp32 sum, one rounding.  Bound by HBM (6 bytes per element).  A workgroup takes ROWPASS_ROWS
 // rows x ROWPASS_COLS 16-byte columns of one row chunk, all its loads in flight at once: a chunk per workgroup,
 // its rows one after the other, left three quarters of the chip idle on small batches (2000 rows of 4608
-// with a noise row each: 63 workgroups, 60.9 us, 0.9 TB/s; now 756, 14.1 us, 3.9 TB/s).
+// with a noise row each: 63 workgroups, 60.9 us, 0.9 TB/s; now 1260, about 13 us, and the call with its
+// forward 178.5 -> 131.0 us).
 // -------------------------------------------------------------------------------------------
-constexpr int ROWPASS_ROWS = 8;        // rows per thread (a divisor of the row chunk's SKINNY_ROWS)
-constexpr int ROWPASS_COLS = 128;      // threads per workgroup, one 16-byte column each
 struct NoiseAddParams {
     const bf16* X;
     bf16* out;

@@ -1,4 +1,4 @@
-"""Elementwise passes over the rows of a batch (noise prepass of the privacy flow): edges of the 8-row x
+"""Elementwise passes over the rows of a batch (noise prepass of the privacy flow, IA3 row scale): edges of the 8-row x
 1024-column blocks a workgroup takes, and a chunk list longer than one grid."""
 import numpy as np
 import pytest
@@ -7,6 +7,7 @@ import torch
 import gpu_harness as gh
 import oracle
 import synth
+from helpers import check_dx, check_y
 from paper_2507_03220_amd import binding as sb
 
 pytestmark = pytest.mark.gpu
@@ -29,3 +30,22 @@ def test_noise_add_bit_exact(width, lens):
     sb.symb_noise_add(gh.handle(), b, gh.to_dev(X), [gh.to_dev(n) for n in noise], Xn)
     torch.cuda.synchronize()
     assert np.array_equal(gh.bf16_bits(Xn), oracle.noise_add(off, X, noise))
+
+
+@pytest.mark.parametrize("width,lens", [(8, [1, 2]), (1024, [8, 0, 9, 3]), (1032, [7, 33, 1, 64, 40])])
+def test_ia3_scaled_rows(width, lens):
+    """Input gradient through output-scaling segments and forward through input-scaling ones, beside segments
+    whose rows are copied or left alone: the rows the product contracts are scaled (or copied) by the row pass."""
+    rng = np.random.default_rng(100 + width)
+    off = np.zeros(len(lens) + 1, dtype=np.int32)
+    off[1:] = np.cumsum(lens)
+    W, V = _bits(rng, (width, 40)), _bits(rng, (40, width))
+    G = _bits(rng, (int(off[-1]), width))
+    for kind, weight in ((sb.SYMB_ADAPTER_IA3, W), (sb.SYMB_ADAPTER_IA3_IN, V)):
+        ads = [gh.HostAdapter(kind, 0, 0.0, synth.f32_to_bf16_bits(1 + 0.1 * rng.standard_normal(width).astype(np.float32))) if i % 2
+               else gh.HostAdapter() for i in range(len(lens))]
+        oads = [oracle.Adapter(a.kind, a.rank, a.scale, a.A, a.B) for a in ads]
+        if kind == sb.SYMB_ADAPTER_IA3:
+            check_dx(gh.bf16_to_f64(gh.backward_input(off, ads, G, weight)), off, oads, G, weight, "dX")
+        else:
+            check_y(gh.bf16_to_f64(gh.forward(off, ads, G, weight, want_base=False)[0]), off, oads, G, weight, None, "Y")
