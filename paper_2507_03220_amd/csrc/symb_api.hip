@@ -1632,13 +1632,13 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
     if (!want_l.empty()) {
         Ia3GradParams ip{(const bf16*)dY, (const bf16*)Ybase, b->d_out, doff, dseg, (const int32_t*)(dev + o_wl), acc ? 1 : 0,
                          seg_io ? (const bf16* const*)(dev + o_gs) : nullptr, seg_io ? (const bf16* const*)(dev + o_ys) : nullptr};
-        hipLaunchKernelGGL(symb_ia3_grad_kernel, dim3((b->d_out + IA3_GRAD_COLS - 1) / IA3_GRAD_COLS, (unsigned)want_l.size()), dim3(256), 0, s, ip);
+        hipLaunchKernelGGL(symb_ia3_grad_kernel, dim3((b->d_out + IA3_GRAD_COLS - 1) / IA3_GRAD_COLS, (unsigned)want_l.size()), dim3(IA3_GRAD_THREADS), 0, s, ip);
         SYMB_HIP(h, hipGetLastError());
     }
     if (!want_lin.empty()) {     // dl_i[k] = sum_t X[t][k] * (dY W)[t][k]: the same reduction over the input width
         Ia3GradParams ip{(const bf16*)X, (const bf16*)dXbase, b->d_in, doff, dseg, (const int32_t*)(dev + o_wli), acc ? 1 : 0,
                          seg_io ? (const bf16* const*)(dev + o_xs) : nullptr, seg_io ? (const bf16* const*)(dev + o_ys) : nullptr};
-        hipLaunchKernelGGL(symb_ia3_grad_kernel, dim3((b->d_in + IA3_GRAD_COLS - 1) / IA3_GRAD_COLS, (unsigned)want_lin.size()), dim3(256), 0, s, ip);
+        hipLaunchKernelGGL(symb_ia3_grad_kernel, dim3((b->d_in + IA3_GRAD_COLS - 1) / IA3_GRAD_COLS, (unsigned)want_lin.size()), dim3(IA3_GRAD_THREADS), 0, s, ip);
         SYMB_HIP(h, hipGetLastError());
     }
     { guard.completed = true; return seal_slot(h, s); }

@@ -49,3 +49,21 @@ def test_ia3_scaled_rows(width, lens):
             check_dx(gh.bf16_to_f64(gh.backward_input(off, ads, G, weight)), off, oads, G, weight, "dX")
         else:
             check_y(gh.bf16_to_f64(gh.forward(off, ads, G, weight, want_base=False)[0]), off, oads, G, weight, None, "Y")
+
+
+@pytest.mark.parametrize("width,lens", [(8, [1, 3]), (64, [127, 128, 129]), (72, [384, 385, 16]), (136, [511, 512, 1300, 0])])
+def test_ia3_vector_gradient(width, lens):
+    """dl of output-scaling segments: edges of the 64 columns and the 128 tokens (four deep) a workgroup walks side by side."""
+    rng = np.random.default_rng(200 + width)
+    off = np.zeros(len(lens) + 1, dtype=np.int32)
+    off[1:] = np.cumsum(lens)
+    T = int(off[-1])
+    X, G, Y0 = _bits(rng, (T, 16)), _bits(rng, (T, width)), _bits(rng, (T, width))
+    ads = [gh.HostAdapter(sb.SYMB_ADAPTER_IA3, 0, 0.0, _bits(rng, (width,))) for _ in lens]
+    got = gh.adapter_grad(off, ads, X, G, Y0)
+    for i, n in enumerate(lens):
+        rows = slice(int(off[i]), int(off[i + 1]))
+        ref = (synth.bf16_bits_to_f64(G[rows]) * synth.bf16_bits_to_f64(Y0[rows])).sum(0)
+        # fp32 products and sums in any order: at most (n + 1) roundings of 2^-24 of the absolute sum
+        bound = (n + 1) * 2.0 ** -24 * np.abs(synth.bf16_bits_to_f64(G[rows]) * synth.bf16_bits_to_f64(Y0[rows])).sum(0)
+        assert np.all(np.abs(got.descs[i].dA.cpu().numpy() - ref) <= bound + 1e-300)
