@@ -161,9 +161,9 @@ symb_status symb_plan_row_tiles(const symb_batch* b, int32_t tile_m, int32_t* se
  * fp32 partial tiles: such a call computes output tiles in several workgroups, one per
  * range of the inner dimension -- every tile of a batch of a few hundred rows (which alone
  * would leave most of the chip idle), or the tiles of a last round of workgroups that
- * would be partly empty (up to 160 MiB).  Before it, for a batch of at most 16 rows, come
- * the regions of the weight-streaming kernels such calls take (a flat copy of the rows and,
- * where the weight is read N-contiguous, up to 8 MiB of fp32 partial sums per K range).  These
+ * would be partly empty (up to 160 MiB).  Before it, for a batch of at most 64 rows, come the
+ * fp32 partial sums of the weight-streaming kernels such calls take (base product and LoRA shrink, at
+ * most 16 ranges of the inner dimension each).  These
  * trailing regions are optional: a workspace that covers everything before them (in
  * particular none at all for a batch without adapters) makes the call take the tiled kernel
  * without the split, only slower; anything smaller fails with SYMB_ERR_WORKSPACE_TOO_SMALL.
@@ -329,7 +329,7 @@ symb_status symb_base_linear_fwd_static(symb_handle h, const symb_batch* b, cons
  *                                place (off: every call sends them, as a job whose batch layout
  *                                changes from call to call does)
  *   SYMB_OPT_K_SPLIT             output tiles computed by several workgroups, one per K range
- *   SYMB_OPT_SMALL_BATCH_KERNELS the weight-streaming kernels for calls of at most 16 rows
+ *   SYMB_OPT_SMALL_BATCH_KERNELS the weight-streaming kernels for calls of at most 64 rows
  *   SYMB_OPT_SKINNY_DEEP         the deep-prefetch build of the LoRA shrink for launches of few workgroups
  */
 typedef enum { SYMB_OPT_DESCRIPTOR_REUSE = 0, SYMB_OPT_K_SPLIT = 1, SYMB_OPT_SMALL_BATCH_KERNELS = 2,

@@ -17,6 +17,7 @@
 
 #include "adapter_kernels.hpp"
 #include "gemm16_kernel.hpp"
+#include "small_kernels.hpp"
 
 using namespace symb;
 
@@ -332,25 +333,48 @@ struct WsLayout {
     size_t gr_off = 0, gr_bytes = 0;      // fp32 runs of the LoRA gradients of split segments (see grad_split)
     size_t dp_off = 0, dp_bytes = 0;      // fp32 partial sums of dH per group of column blocks (one-pass dH + dB, ranks up to 16)
     // optional regions (a workspace that ends before them makes the call take the tiled kernel, unsplit):
-    size_t sg_off = 0, sg_bytes = 0;      // calls of at most 16 rows: flat copy of the activation rows [T][K] (gathered / scaled)
-    size_t sp_off = 0, sp_bytes = 0;      // calls of at most 16 rows, weight read N-contiguous: fp32 partial sums per K range
+    size_t sp_off = 0, sp_bytes = 0;      // calls of at most SMALL_MAX_ROWS rows: fp32 partial sums of the base product per K range
+    size_t sh_off = 0, sh_bytes = 0;      // ... and of the LoRA shrink
     size_t tp_off = 0, tp_bytes = 0;      // fp32 partial tiles of a K-split GEMM (see gemm_split_plan); last
     size_t mandatory = 0;                 // end of the regions a call cannot do without
     size_t total = 0;
 };
 
-// K ranges of the small-batch kernel that reads the weight N-contiguous: enough workgroups to fill the
-// chip (about 512 with the column blocks), at least 128 k per range, at most 8 MiB of partial sums
-// (they are written and read back once: traffic beside the weight's own bytes).
-constexpr int kSmallRows = 16;
-int small_k_ranges(int K, int N) {
-    const int nblk = (N + COLGEMV_CT - 1) / COLGEMV_CT;
-    const long cap = std::max<long>(1, ((long)8 << 20) / ((long)kSmallRows * N * 4));
-    return (int)std::max<long>(1, std::min<long>({(512 + nblk - 1) / nblk, (long)K / 128, cap}));
-}
-int small_k_per_range(int K, int N) {
-    const int r = small_k_ranges(K, N);
-    return (int)align_up((size_t)(K + r - 1) / r, 32);
+// The grid of a call of at most SMALL_MAX_ROWS rows (small_kernels.hpp): column tiles x K ranges of the base product beside
+// shrink pieces x K ranges, at most 16 ranges of either (the finish kernel reads them back).
+struct SmallPlan {
+    int tiles = 0, ranges = 0, items = 0, h_ranges = 0;
+    bool direct = false;      // no LoRA term, one range: no partial sums, no finish kernel
+    size_t base_bytes = 0, h_bytes = 0;
+};
+SmallPlan small_plan(const symb_batch* b, const BatchInfo& bi, int op, bool lora, bool staged) {
+    SmallPlan s;
+    // the contraction runs over d_in in the forward, over d_out in the input gradient; the weight is read N-contiguous by the
+    // forward of an input-major weight and by the input gradient of an nn.Linear one
+    const int K = op == SYMB_OP_FWD ? b->d_in : b->d_out, N = op == SYMB_OP_FWD ? b->d_out : b->d_in;
+    const bool shrink_nn = op == SYMB_OP_BWD_INPUT, base_nn = (op == SYMB_OP_FWD) == (b->weight_layout == SYMB_WEIGHT_CONV1D);
+    if (lora)
+        for (int i = 0; i < bi.S; ++i)
+            if (b->adapters[i].kind == SYMB_ADAPTER_LORA && b->seg_offsets[i + 1] > b->seg_offsets[i])
+                s.items += shrink_nn ? 1 : rpad_of(b->adapters[i].rank) / 16;
+    s.tiles = (N + small_cols(base_nn) - 1) / small_cols(base_nn);
+    // Ranges per tile: the launch runs in rounds of 256 workgroups (one per CU), each of a 1 / ranges share of a tile's strip of the
+    // weight plus what a round costs besides (first loads, the wavefronts' sums, partial sums): about a quarter of a strip.  Measured
+    // over 1 to 16 ranges: a count just past a round loses (input gradient of 4608 -> 36864, 36 tiles, one row: 65.5 us at 6
+    // ranges, 82.2 at 8, 66.5 at 12), and a second workgroup per CU gains nothing (4096 -> 11008, 172 tiles: 19.4 us at 1, 22.8 at 2).
+    double best = 1e30;
+    for (int r = 1; r <= std::max(1, std::min(K / 256, 16)); ++r) {
+        const double cost = (double)((s.tiles * r + 255) / 256) * (1.0 / r + 0.25);
+        if (cost < best) { best = cost; s.ranges = r; }
+    }
+    // (not where outputs overlap inputs: every row must be read before any is written)
+    if (!s.items && !staged && K <= 2048) s.ranges = 1;
+    s.direct = !s.items && !staged && s.ranges == 1;
+    s.base_bytes = s.direct ? 0 : (size_t)s.ranges * bi.T * N * 4;
+    if (!s.items) return s;
+    s.h_ranges = std::max(1, std::min({256 / s.items, K / 512, 16}));      // at most a round of its own, two slices per wavefront
+    s.h_bytes = (size_t)s.h_ranges * bi.T * bi.max_rpad * 4;
+    return s;
 }
 
 WsLayout ws_layout(const symb_batch* b, const BatchInfo& bi, int op, bool full_bwd, bool any_lora_grad, bool staged_out = false) {
@@ -391,15 +415,10 @@ WsLayout ws_layout(const symb_batch* b, const BatchInfo& bi, int op, bool full_b
     if (staged_out && op != SYMB_OP_ADAPTER_GRAD)
         take(w.so_off, w.so_bytes, (size_t)bi.T * (op == SYMB_OP_FWD ? b->d_out : b->d_in) * 2);
     w.mandatory = cur;
-    if (op != SYMB_OP_ADAPTER_GRAD && bi.T > 0 && bi.T <= kSmallRows) {
-        // the contraction runs over d_in in the forward, over d_out in the input gradient; the weight is
-        // read N-contiguous by the forward of an input-major weight and by the input gradient of an nn.Linear one
-        const int K = op == SYMB_OP_FWD ? b->d_in : b->d_out, N = op == SYMB_OP_FWD ? b->d_out : b->d_in;
-        take(w.sg_off, w.sg_bytes, (size_t)bi.T * K * 2);
-        if ((op == SYMB_OP_FWD) == conv1d) {
-            const int kpr = small_k_per_range(K, N);
-            take(w.sp_off, w.sp_bytes, (size_t)((K + kpr - 1) / kpr) * kSmallRows * N * 4);
-        }
+    if (op != SYMB_OP_ADAPTER_GRAD && bi.T > 0 && bi.T <= SMALL_MAX_ROWS) {
+        const SmallPlan sm = small_plan(b, bi, op, op == SYMB_OP_FWD || full_bwd, staged_out);
+        take(w.sp_off, w.sp_bytes, sm.base_bytes);
+        take(w.sh_off, w.sh_bytes, sm.h_bytes);
     }
     if (op == SYMB_OP_FWD) {
         const SplitPlan sp = gemm_split_plan(bi.T, b->d_out, b->d_in);
@@ -622,37 +641,123 @@ symb_status launch_row_pass(symb_handle h, void (*kfn)(P), P p, int width, size_
     return SYMB_OK;
 }
 
-// C[T][N] = A[T][K] Wop, T <= 16, with the weight-streaming kernels (adapter_kernels.hpp).
-//   w_kmajor: Wop is [N][K] (one workgroup per 32 columns, K split inside the workgroup);
-//   else Wop is [K][N] (column blocks x K ranges, fp32 partial sums in `partial`, then the finish kernel).
-symb_status launch_small(symb_handle h, const bf16* A, const bf16* Wop, bool w_kmajor, int K, const SmallEpilogue& epi,
-                         float* partial, hipStream_t st) {
-    if (w_kmajor) {
-        RowGemvParams rp{Wop, A, K, epi};
-        hipLaunchKernelGGL(symb_rowgemv_kernel<1>, dim3((epi.N + SKINNY_ROWS - 1) / SKINNY_ROWS), dim3(256), 0, st, rp);
-        SYMB_HIP(h, hipGetLastError());
-        return SYMB_OK;
-    }
-    const int kpr = small_k_per_range(K, epi.N), ranges = (K + kpr - 1) / kpr;
-    ColGemvParams cp{Wop, A, partial, K, epi.N, epi.T, kpr};
-    hipLaunchKernelGGL(symb_colgemv_kernel, dim3((epi.N + COLGEMV_CT - 1) / COLGEMV_CT, ranges), dim3(256), 0, st, cp);
-    SYMB_HIP(h, hipGetLastError());
-    SmallFinishParams fp{partial, ranges, epi};
-    hipLaunchKernelGGL(symb_small_finish_kernel, dim3((epi.N + 255) / 256, epi.T), dim3(256), 0, st, fp);
-    SYMB_HIP(h, hipGetLastError());
-    return SYMB_OK;
+template <bool BASE_NN, bool SHRINK_NN>
+void launch_small_stream(const SmallStreamParams& p, hipStream_t st) {
+    const dim3 grid((unsigned)(p.num_items * p.h_ranges + p.tiles * p.ranges));
+    if (p.T <= 16) hipLaunchKernelGGL((symb_small_stream_kernel<1, BASE_NN, SHRINK_NN>), grid, dim3(256), 0, st, p);
+    else if (p.T <= 32) hipLaunchKernelGGL((symb_small_stream_kernel<2, BASE_NN, SHRINK_NN>), grid, dim3(256), 0, st, p);
+    else hipLaunchKernelGGL((symb_small_stream_kernel<4, BASE_NN, SHRINK_NN>), grid, dim3(256), 0, st, p);
 }
 
-// Whether a call of T rows takes the small-batch kernels: a handful of rows, the optional workspace
-// regions present, and, for a weight read K-contiguous, a layer of moderate size (one workgroup per 32
-// columns holds 152 KiB of LDS: on 4096 x 11008 the 344 workgroups make a second, third-full round and
-// the tiled kernel with its K-split is faster at any row count).
-bool small_path(symb_handle h, int T, bool w_kmajor, long long weights, bool second_output, const WsLayout& wl, const void* ws,
-                size_t ws_bytes) {
-    if (!h->opt_small_rows || T > kSmallRows || !wl.sg_bytes || !ws) return false;
-    if (ws_bytes < (wl.sp_bytes ? wl.sp_off + wl.sp_bytes : wl.sg_off + wl.sg_bytes)) return false;
-    // (a call with a pre-adapter output cannot split K in the tiled kernel: there the streaming kernel wins on any layer)
-    return !w_kmajor || weights <= 24ll << 20 || second_output;
+// Whether a call takes the small-batch kernels: at most SMALL_MAX_ROWS rows, and a workspace with the optional regions.  Measured
+// against the tiled kernels (us per call, the weight read K- / N-contiguous, 1, 16 and 64 rows of rank-16 LoRA clients of one row each):
+// 4096 x 4096 14 / 28, 15 / 34, 20 / 54 and 14 / 35, 15 / 38, 24 / 62; 4096 x 11008 22 / 39, 25 / 49, 41 / 79 and 23 / 48, 25 / 57,
+// 38 / 95; with clients of ranks 4 to 128 the tiled kernels take 2 to 5 times as long.  The tiled kernels stay the faster ones for more than 32
+// rows of at most a few clients on a wide output, K-contiguous, where the finish kernel's pass over the fp32 sums weighs more than the
+// streaming saves (64 rows of one client: 4608 -> 36864 119 / 106, 4096 -> 24576 74 / 69, 256 -> 11008 18.5 / 14; 4096 -> 16384 still 48 / 51).
+bool small_path(symb_handle h, const symb_batch* b, const BatchInfo& bi, int op, bool lora, const WsLayout& wl, const void* ws, size_t ws_bytes) {
+    const size_t need = wl.sh_off + wl.sh_bytes;
+    if (!h->opt_small_rows || bi.T > SMALL_MAX_ROWS || ws_bytes < need || (!ws && need)) return false;
+    const int K = op == SYMB_OP_FWD ? b->d_in : b->d_out, N = op == SYMB_OP_FWD ? b->d_out : b->d_in;
+    const bool base_nn = (op == SYMB_OP_FWD) == (b->weight_layout == SYMB_WEIGHT_CONV1D);
+    return base_nn || bi.T <= 32 || !lora || bi.n_lora == 0 || bi.n_lora > 4 || !(N >= 24576 || (N >= 8192 && K < 1024));
+}
+
+// One call of the small-batch kernels, forward or input gradient: what differs between the two comes in through the
+// arguments.  x_flat: the rows to multiply (or null with x_seg); scale: those rows are first copied, rows of that kind scaled by their vector
+// (0: no copy); h_rows: where H is left as value + residual; take_h: H is there already.
+struct SmallCall {
+    int op;
+    const void *x_flat, *W, *bias, *out, *out_base;
+    const void* const* x_seg;
+    void* const* out_seg;
+    const NoiseDesc* neff;    // HOST, S entries, or null
+    int scale;
+    bf16 *copy, *h_rows;
+    bool lora, take_h, staged;
+};
+symb_status run_small(symb_handle h, const symb_batch* b, const BatchInfo& bi, const WsLayout& wl, unsigned char* wsb, const SmallCall& c, hipStream_t s) {
+    symb_status st;
+    const bool fwd = c.op == SYMB_OP_FWD;
+    const int K = fwd ? b->d_in : b->d_out, N = fwd ? b->d_out : b->d_in;
+    const SmallPlan plan = small_plan(b, bi, c.op, c.lora, c.staged);
+    SmallRows rows{};
+    for (int i = 0; i < bi.S; ++i)
+        for (int t = b->seg_offsets[i]; t < b->seg_offsets[i + 1]; ++t) rows.at[t] = (uint32_t)i << 8 | (uint32_t)(t - b->seg_offsets[i]);
+    const bool shrink = plan.items > 0 && !c.take_h;
+    std::vector<SmallItem> items;
+    if (shrink)
+        for (int i = 0; i < bi.S; ++i) {
+            const int n = b->seg_offsets[i + 1] - b->seg_offsets[i];
+            if (b->adapters[i].kind != SYMB_ADAPTER_LORA || !n) continue;
+            for (int p0 = 0; p0 < (fwd ? rpad_of(b->adapters[i].rank) : 1); p0 += 16) items.push_back(SmallItem{i, p0, b->seg_offsets[i], n});
+        }
+    std::vector<RowChunk> chunks;
+    if (c.scale) plan_chunks(b, kSkinnyRows, -1, chunks);
+    const std::vector<SegDesc> sd = make_segdesc(b);
+    Blob blob;
+    const size_t o_seg = blob.add(sd.data(), sd.size());
+    const size_t o_it = blob.add(items.data(), items.size());
+    const size_t o_nd = blob.add(c.neff, c.neff ? (size_t)bi.S : 0);
+    const size_t o_xs = blob.add(c.x_seg, c.x_seg ? (size_t)bi.S : 0);
+    const size_t o_cs = blob.add(c.out_seg, c.out_seg ? (size_t)bi.S : 0);
+    const size_t o_off = blob.add(b->seg_offsets, c.scale ? (size_t)bi.S + 1 : 0);
+    const size_t o_ch = blob.add(chunks.data(), chunks.size());
+    // as many segments as the tiled kernels' descriptors have room for: a batch is refused or accepted whatever its row count
+    const size_t tiled = (2 * sizeof(SegDesc) + sizeof(int32_t) + sizeof(int64_t) + (c.neff ? sizeof(NoiseDesc) : 0) + (c.x_seg ? 16 : 0)) * (size_t)bi.S;
+    if (tiled > kSlotBytes) return fail(h, SYMB_ERR_UNSUPPORTED, "batch descriptors need %zu bytes, capacity is %zu", tiled, kSlotBytes);
+    unsigned char* dev = nullptr;
+    if ((st = upload(h, blob, s, &dev)) != SYMB_OK) return st;
+    const SegDesc* const dseg = (const SegDesc*)(dev + o_seg);
+
+    SmallStreamParams sp{};
+    sp.W = (const bf16*)c.W;
+    sp.X = (const bf16*)c.x_flat;
+    sp.x_seg = c.x_seg ? (const bf16* const*)(dev + o_xs) : nullptr;
+    if (c.scale) {
+        ScaleParams sc{sp.X, c.copy, K, (const RowChunk*)(dev + o_ch), dseg, c.scale, sp.x_seg, (const int32_t*)(dev + o_off)};
+        if ((st = launch_row_pass(h, symb_ia3_scale_rows_kernel, sc, K, chunks.size(), s)) != SYMB_OK) return st;
+        sp.X = c.copy;
+        sp.x_seg = nullptr;
+    }
+    sp.N = N;
+    sp.K = K;
+    sp.T = bi.T;
+    sp.tiles = plan.tiles;
+    sp.ranges = plan.ranges;
+    sp.partial = (float*)(wsb + wl.sp_off);
+    sp.items = (const SmallItem*)(dev + o_it);
+    sp.num_items = (int)items.size();
+    sp.h_ranges = plan.h_ranges;
+    sp.seg = dseg;
+    sp.h_partial = (float*)(wsb + wl.sh_off);
+    sp.h_pitch = bi.max_rpad;
+    sp.rows = rows;
+    sp.direct = plan.direct;
+    sp.out = SmallOut{(bf16*)c.out, (bf16*)c.out_base, c.out_seg ? (bf16* const*)(dev + o_cs) : nullptr, (const bf16*)c.bias,
+                      c.neff ? (const NoiseDesc*)(dev + o_nd) : nullptr, fwd ? (bi.n_ia3 ? KIND_IA3 : 0) : c.lora && bi.n_ia3in ? KIND_IA3_IN : 0};
+    const bool conv1d = b->weight_layout == SYMB_WEIGHT_CONV1D;
+    if (fwd) conv1d ? launch_small_stream<true, false>(sp, s) : launch_small_stream<false, false>(sp, s);
+    else conv1d ? launch_small_stream<false, true>(sp, s) : launch_small_stream<true, true>(sp, s);
+    SYMB_HIP(h, hipGetLastError());
+    if (plan.direct) return seal_slot(h, s);
+
+    SmallFinishParams fp{};
+    fp.partial = sp.partial;
+    fp.h_partial = c.take_h ? nullptr : sp.h_partial;
+    fp.ranges = plan.ranges;
+    fp.h_ranges = plan.h_ranges;
+    fp.h_pitch = bi.max_rpad;
+    fp.h_rows = c.h_rows;
+    fp.lora_term = plan.items > 0;
+    fp.out = sp.out;
+    fp.N = N;
+    fp.T = bi.T;
+    fp.seg = dseg;
+    fp.rows = rows;
+    hipLaunchKernelGGL(fwd ? symb_small_finish_kernel<false> : symb_small_finish_kernel<true>, dim3((N + 255) / 256, bi.T), dim3(128), 0, s, fp);
+    SYMB_HIP(h, hipGetLastError());
+    return seal_slot(h, s);
 }
 
 symb_status check_handle(symb_handle h) {
@@ -944,6 +1049,14 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     const SplitPlan ksp = gemm_split_plan(bi.T, b->d_out, b->d_in);
     const bool k_split = wl.tp_bytes && ws && ws_bytes >= wl.total && !Ybase && h->opt_k_split && h->xcd_rule;
     hipStream_t s = (hipStream_t)stream;
+    if (small_path(h, b, bi, SYMB_OP_FWD, true, wl, ws, ws_bytes)) {     // (partial sums between: overlapping buffers need no flat copy)
+        unsigned char* const base = (unsigned char*)ws;
+        const SmallCall c{SYMB_OP_FWD, X, W, bias, Y, Ybase, X_seg, Y_seg, nd.empty() ? nullptr : nd.data(), bi.n_ia3in ? (int)KIND_IA3_IN : 0,
+                          (bf16*)(base + wl.sc_off), (bf16*)(base + wl.h_off), true, false, staged};
+        if ((st = run_small(h, b, bi, wl, base, c, s)) != SYMB_OK) return st;
+        guard.completed = true;
+        return SYMB_OK;
+    }
 
     const int bm = gemm_tile_m(bi.T, b->d_out);
     std::vector<int32_t> lo, hi;
@@ -953,8 +1066,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     // Input-major weight: the forward is the N-contiguous GEMM, whose LoRA steps read the adapter
     // side as [rank][d_out] rows: B_i^T, packed into the workspace; a second descriptor set points there.
     const bool conv1d = b->weight_layout == SYMB_WEIGHT_CONV1D;
-    const bool small = small_path(h, bi.T, !conv1d, (long long)b->d_in * b->d_out, Ybase != nullptr, wl, ws, ws_bytes);
-    const bool copy_rows = bi.n_ia3in > 0 || (small && seg_io);      // the product reads a flat copy of X (scaled / gathered)
+    const bool copy_rows = bi.n_ia3in > 0;      // the product reads a flat copy of X (IA3_IN rows scaled)
     if (copy_rows || staged) plan_chunks(b, kSkinnyRows, -1, all_chunks);
     const std::vector<SegDesc> sd = make_segdesc(b);
     unsigned char* wsb = (unsigned char*)ws;
@@ -992,7 +1104,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     // (LoRA segments, if any, still shrink the caller's X: their rows are not touched by the copy)
     const bf16* x_op = (const bf16*)X;
     if (copy_rows) {
-        bf16* const copy = (bf16*)(wsb + (bi.n_ia3in ? wl.sc_off : wl.sg_off));
+        bf16* const copy = (bf16*)(wsb + wl.sc_off);
         ScaleParams sc{(const bf16*)X, copy, b->d_in, (const RowChunk*)(dev + o_all),
                        (const SegDesc*)(dev + o_seg), KIND_IA3_IN, seg_io ? (const bf16* const*)(dev + o_xs) : nullptr,
                        (const int32_t*)(dev + o_off)};
@@ -1000,7 +1112,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
         x_op = copy;
     }
     bf16* Hs = bi.n_lora ? (bf16*)(wsb + wl.h_off) : nullptr;
-    if (conv1d && bi.n_lora && !small) {
+    if (conv1d && bi.n_lora) {
         PackParams pp{(const SegDesc*)(dev + o_seg), (bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk), b->d_out};
         hipLaunchKernelGGL(symb_pack_bt_kernel, dim3((b->d_out + 255) / 256, bi.S), dim3(256), 0, s, pp);
         SYMB_HIP(h, hipGetLastError());
@@ -1019,28 +1131,6 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
             sp.off = (const int32_t*)(dev + o_off);
         }
         if ((st = launch_skinny(h, sp, (int)chunks.size(), bi.max_rpad, s)) != SYMB_OK) return st;
-    }
-    // A handful of rows (decode steps): the weight-streaming kernels instead of the tiled GEMM.  Measured
-    // against the tiled kernel with its K-split (33-40 us per call from 4 to 64 rows): 17-20 us up to 16 rows on
-    // 4096 x 4096 (descriptors in place), but slower from 24 rows on.
-    if (small) {
-        SmallEpilogue ep{};
-        ep.C = (bf16*)Y;
-        ep.Cbase = (bf16*)Ybase;
-        ep.c_seg = seg_io ? (bf16* const*)(dev + o_ys) : nullptr;
-        ep.bias = (const bf16*)bias;
-        ep.N = b->d_out;
-        ep.T = bi.T;
-        ep.S = bi.S;
-        ep.off = (const int32_t*)(dev + o_off);
-        ep.seg = (const SegDesc*)(dev + o_seg);
-        ep.ext = Hs;
-        ep.ext_pitch = 2 * bi.max_rpad;
-        ep.backward = 0;
-        ep.lora_term = 1;
-        ep.neff = nd.empty() ? nullptr : (const NoiseDesc*)(dev + o_nd);
-        if ((st = launch_small(h, x_op, (const bf16*)W, !conv1d, b->d_in, ep, (float*)(wsb + wl.sp_off), s)) != SYMB_OK) return st;
-        { guard.completed = true; return seal_slot(h, s); }
     }
     GemmParams gp{};
     gp.Aop = x_op;
@@ -1209,7 +1299,14 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     const bool k_split = wl.tp_bytes && ws && ws_bytes >= wl.total && !dXbase && h->opt_k_split && h->xcd_rule;
     hipStream_t s = (hipStream_t)stream;
     const bool lora = full && bi.n_lora > 0, ia3 = full && bi.n_ia3 > 0;
-    const bool conv1d_early = b->weight_layout == SYMB_WEIGHT_CONV1D;
+    if (small_path(h, b, bi, SYMB_OP_BWD_INPUT, full, wl, ws, ws_bytes)) {     // (partial sums between: overlapping buffers need no flat copy)
+        unsigned char* const base = (unsigned char*)ws;
+        const SmallCall c{SYMB_OP_BWD_INPUT, dY, W, nullptr, dX, dXbase, dY_seg, dX_seg, nullptr, ia3 ? (int)KIND_IA3 : 0,
+                          (bf16*)(base + wl.sc_off), (bf16*)(base + wl.dh_off), full, take_dh, staged};
+        if ((st = run_small(h, b, bi, wl, base, c, s)) != SYMB_OK) return st;
+        guard.completed = true;
+        return SYMB_OK;
+    }
 
     const int bm = gemm_tile_m(bi.T, b->d_in);
     std::vector<int32_t> lo, hi;
@@ -1223,13 +1320,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     unsigned char* const wsb0 = (unsigned char*)ws;
     std::vector<const void*> mix;           // per segment: where the GEMM reads its rows
     bool ia3_mixed = false;
-    // a handful of rows: the weight-streaming kernels, which read one flat copy of the rows (gathered from
-    // per-segment buffers, IA3 rows scaled) in the workspace
-    const bool small = small_path(h, bi.T, conv1d_early, (long long)b->d_in * b->d_out, dXbase != nullptr, wl, ws, ws_bytes);
-    const bool small_copy = small && (seg_io || ia3);
-    if (small_copy) {
-        plan_chunks(b, kSkinnyRows, -1, all_chunks);
-    } else if (ia3) {
+    if (ia3) {
         mix.assign(bi.S, nullptr);
         uintptr_t lo_a = UINTPTR_MAX, hi_a = 0;
         for (int i = 0; i < bi.S; ++i) {
@@ -1291,7 +1382,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
 
     const bf16* a_op = (const bf16*)dY;
     bf16* dH = nullptr;
-    if (lora && conv1d && !small) {
+    if (lora && conv1d) {
         PackAtParams pa{(const SegDesc*)(dev + o_seg), (bf16*)(wsb + wl.pa_off), (const int64_t*)(dev + o_pa), b->d_in};
         hipLaunchKernelGGL(symb_pack_at_kernel, dim3((b->d_in + 255) / 256, bi.S), dim3(256), 0, s, pa);
         SYMB_HIP(h, hipGetLastError());
@@ -1318,32 +1409,14 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
         if ((st = launch_skinny(h, sp, (int)chunks.size(), bi.max_rpad, s)) != SYMB_OK) return st;
     }
     bool a_from_seg = seg_io;
-    if (ia3 || small_copy) {
+    if (ia3) {
         a_from_seg = ia3_mixed;
-        bf16* const copy = (bf16*)(wsb + (small_copy ? wl.sg_off : wl.sc_off));
+        bf16* const copy = (bf16*)(wsb + wl.sc_off);
         ScaleParams sc{(const bf16*)dY, copy, b->d_out, (const RowChunk*)(dev + o_all), (const SegDesc*)(dev + o_seg),
-                       ia3 ? (int)KIND_IA3 : -1, seg_io ? (const bf16* const*)(dev + o_gs) : nullptr, (const int32_t*)(dev + o_off)};
+                       KIND_IA3, seg_io ? (const bf16* const*)(dev + o_gs) : nullptr, (const int32_t*)(dev + o_off)};
         // (every IA3 segment of the batch may be empty: nothing to scale then)
         if ((st = launch_row_pass(h, symb_ia3_scale_rows_kernel, sc, sc.d_out, all_chunks.size(), s)) != SYMB_OK) return st;
         a_op = copy;
-    }
-    if (small) {
-        SmallEpilogue ep{};
-        ep.C = (bf16*)dX;
-        ep.Cbase = (bf16*)dXbase;
-        ep.c_seg = seg_io ? (bf16* const*)(dev + o_xs) : nullptr;
-        ep.N = b->d_in;
-        ep.T = bi.T;
-        ep.S = bi.S;
-        ep.off = (const int32_t*)(dev + o_off);
-        ep.seg = (const SegDesc*)(dev + o_seg);
-        ep.ext = dH;
-        ep.ext_pitch = 2 * bi.max_rpad;
-        ep.backward = 1;
-        ep.lora_term = full ? 1 : 0;
-        // W [d_out][d_in] is the [K][N] operand of dX = dY W; an input-major weight [d_in][d_out] is [N][K]
-        if ((st = launch_small(h, a_op, (const bf16*)W, conv1d, b->d_out, ep, (float*)(wsb + wl.sp_off), s)) != SYMB_OK) return st;
-        { guard.completed = true; return seal_slot(h, s); }
     }
     GemmParams gp{};
     gp.Aop = a_op;

@@ -1,0 +1,80 @@
+"""Calls of at most 64 rows (the weight-streaming kernels): row counts around the blocks of 16 and the limit, inner and output
+widths around the slices and tiles, ranks that are and are not multiples of 4 and 8, an adapter matrix that is not 16-byte
+aligned, and the workspace hand-over to a gradient call."""
+import pytest
+import torch
+
+import gpu_harness as gh
+import oracle
+import test_gpu_parity as tp
+from helpers import assert_close, check_dx, check_y
+from paper_2507_03220_amd import binding as sb
+from test_gpu_parity import L, I, N, make_problem, oracle_ads
+
+pytestmark = pytest.mark.gpu
+tp.gh, tp.sb = gh, sb                    # what its problem maker uses
+
+
+@pytest.mark.parametrize("dims", [(8, 8), (40, 136), (136, 40), (72, 264), (584, 520), (2056, 128)])
+@pytest.mark.parametrize("lens", [[16], [17], [1] * 32, [33], [20, 1, 0, 43], [64], [63, 2]])
+def test_edges_of_rows_and_widths(dims, lens):
+    d_in, d_out = dims
+    p = make_problem(sum(lens) + d_in, d_in, d_out, lens, [L, L, I, L, N, 3], [1, 16, 12, 128, 40, 5, 64, 99])
+    off, oads = p["off"], oracle_ads(p["ads"])
+    base = [gh.HostAdapter() for _ in lens]
+    for conv1d in (False, True):
+        for want_base in (False, True):
+            Y, _ = gh.forward(off, p["ads"], p["X"], p["W"], p["bias"], want_base=want_base, conv1d=conv1d)
+            check_y(gh.bf16_to_f64(Y), off, oads, p["X"], p["W"], p["bias"], f"Y {dims} {lens} conv1d={conv1d}")
+        Y, _ = gh.forward(off, base, p["X"], p["W"], p["bias"], want_base=False, conv1d=conv1d)        # no adapters: finished in one kernel
+        check_y(gh.bf16_to_f64(Y), off, oracle_ads(base), p["X"], p["W"], p["bias"], f"base Y {dims} {lens} conv1d={conv1d}")
+        for base_only in (False, True):
+            dX = gh.backward_input(off, p["ads"], p["dY"], p["W"], base_only=base_only, conv1d=conv1d)
+            check_dx(gh.bf16_to_f64(dX), off, oads, p["dY"], p["W"], f"dX {dims} {lens} conv1d={conv1d}", base_only=base_only)
+
+
+@pytest.mark.parametrize("rank", [4, 12, 20])
+def test_adapter_matrix_off_its_16_byte_alignment(rank):
+    """B of a rank that is no multiple of 8 need only be 2-byte aligned."""
+    p = make_problem(rank, 520, 392, [5, 30], [L], [rank])
+    off, oads = p["off"], oracle_ads(p["ads"])
+    dev = gh.upload_adapters(p["ads"], 520, 392, grads=False)
+    for d, shift in zip(dev.descs, (1, 3)):
+        room = torch.zeros(d.B.numel() + 8, device="cuda", dtype=torch.bfloat16)
+        room[shift:shift + d.B.numel()] = d.B.reshape(-1)
+        d.B = room[shift:shift + d.B.numel()]
+    b = sb.Batch(520, 392, off, dev.descs)
+    Xd, Gd, Wd = gh.to_dev(p["X"]), gh.to_dev(p["dY"]), gh.to_dev(p["W"])
+    Y = torch.empty(35, 392, device="cuda", dtype=torch.bfloat16)
+    dX = torch.empty(35, 520, device="cuda", dtype=torch.bfloat16)
+    sb.symb_base_linear_fwd(gh.handle(), b, Xd, Wd, None, Y, None, gh.workspace(b, sb.SYMB_OP_FWD))
+    sb.symb_base_linear_bwd_input(gh.handle(), b, Gd, Wd, dX, sb.SYMB_BWD_FULL, gh.workspace(b, sb.SYMB_OP_BWD_INPUT))
+    torch.cuda.synchronize()
+    check_y(gh.bf16_to_f64(Y), off, oads, p["X"], p["W"], None, "Y")
+    check_dx(gh.bf16_to_f64(dX), off, oads, p["dY"], p["W"], "dX")
+
+
+@pytest.mark.parametrize("lens", [[16], [9, 30, 0, 25]])
+def test_gradients_take_hs_and_dh_from_the_streaming_calls(lens):
+    p = make_problem(77, 584, 392, lens, [L], [16, 5, 8, 40])
+    off, oads = p["off"], oracle_ads(p["ads"])
+    dev = gh.upload_adapters(p["ads"], 584, 392, grads=True)
+    b = sb.Batch(584, 392, off, dev.descs)
+    ws = torch.full((max(sb.symb_workspace_bytes(b, op) for op in range(3)),), 0x7f, device="cuda", dtype=torch.uint8)
+    Xd, Gd, Wd = gh.to_dev(p["X"]), gh.to_dev(p["dY"]), gh.to_dev(p["W"])
+    Y, dX = torch.empty(p["T"], 392, device="cuda", dtype=torch.bfloat16), torch.empty(p["T"], 584, device="cuda", dtype=torch.bfloat16)
+    h = gh.handle()
+    sb.symb_base_linear_fwd(h, b, Xd, Wd, None, Y, None, ws)
+    sb.symb_base_linear_bwd_input(h, b, Gd, Wd, dX, sb.SYMB_BWD_FULL, ws)
+    sb.symb_adapter_grad(h, b, Xd, Gd, None, sb.SYMB_GRAD_REUSE_DH | sb.SYMB_GRAD_REUSE_HS, ws)
+    torch.cuda.synchronize()
+    for i, n in enumerate(lens):
+        dAr, dBr = oracle.lora_grad(off, oads, p["X"], p["dY"], i)
+        assert_close(dev.descs[i].dA.cpu().numpy(), dAr, f"dA[{i}]")
+        assert_close(dev.descs[i].dB.cpu().numpy(), dBr, f"dB[{i}]")
+    # ... and the input gradient the dH a gradient call left
+    sb.symb_adapter_grad(h, b, Xd, Gd, None, sb.SYMB_GRAD_OVERWRITE, ws)
+    dX.fill_(float("nan"))
+    sb.symb_base_linear_bwd_input(h, b, Gd, Wd, dX, sb.SYMB_BWD_REUSE_DH, ws)
+    torch.cuda.synchronize()
+    check_dx(gh.bf16_to_f64(dX), off, oads, p["dY"], p["W"], "dX from the gradient call's dH")

@@ -1,0 +1,30 @@
+"""The small-batch kernels read LDS from assembly statements with a wait of their own: nothing the compiler generates between
+such a read and the wait may touch the registers still in flight (see test_gemm16_registers.py; no GPU needed)."""
+import re
+
+from test_gemm16_registers import _regs, device_asm  # noqa: F401
+
+
+def test_lds_reads_of_the_streaming_kernel_are_untouched_until_their_wait(device_asm):  # noqa: F811
+    checked = 0
+    for m in re.finditer(r"^(_ZN4symb24symb_small_stream_kernel\w+):(.*?)^\.Lfunc_end", device_asm, re.S | re.M):
+        pending, inside = set(), False
+        for raw in m.group(2).splitlines():
+            if "ASMSTART" in raw or "ASMEND" in raw:
+                inside = "ASMSTART" in raw
+                continue
+            s = raw.split(";")[0].strip()
+            if not s or s.startswith(".") or s.endswith(":"):
+                if s.endswith(":"):
+                    pending.clear()              # checked per straight-line stretch
+                continue
+            op, _, rest = s.partition(" ")
+            if inside and op in ("ds_read_b128", "ds_read_b64_tr_b16"):
+                pending |= _regs(rest.split(",")[0].strip())
+                checked += 1
+            elif inside and op == "s_waitcnt":
+                pending.clear()
+            else:
+                touched = set().union(*[_regs(t) for t in re.findall(r"v\[\d+:\d+\]|v\d+", rest)] or [set()])
+                assert not (touched & pending), (m.group(1), s)
+    assert checked > 200
