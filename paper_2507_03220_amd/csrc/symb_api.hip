@@ -213,11 +213,13 @@ BatchInfo inspect(const symb_batch* b) {
 
 // Tile variants of the GEMM kernel (gemm16_kernel.hpp): 3 = 256x256 tile, taken when the problem has
 // enough such tiles to fill the chip; 2 = 128x128 tile, for everything smaller.
-int gemm_variant(int M, int N) {
+int gemm_variant(int M, int N, int K) {
     const long big = (long)((M + 255) / 256) * ((N + 255) / 256);
-    return big >= 128 ? 3 : 2;
+    // 128 tiles of 256x256 leave half the CUs idle; as 512 of 128x128 they are one round of two per CU: 62.5 / 74.5 us on 2048 rows
+    // of 4096 x 4096, 69 / 79 on 4608 -> 4096, but 108 / 95 for 1024 on 6144 -> 8192 and 177 / 154 for 2048 on 11008 -> 4096 (twice the LDS traffic per flop)
+    return big > 128 || (big == 128 && K > 4608) ? 3 : 2;
 }
-int gemm_tile_m(int M, int N) { return gemm_variant(M, N) == 3 ? 256 : 128; }
+int gemm_tile_m(int M, int N, int K) { return gemm_variant(M, N, K) == 3 ? 256 : 128; }
 
 // Row tiles per group of the tile walk (a group is walked column by column, so the 32 tiles an XCD runs
 // at once are g row tiles x 32 / g column tiles).  Measured on the Gemma2-27B-shaped launches (80 row
@@ -245,14 +247,17 @@ int gemm_group_m(int num_m_tiles, int num_n_tiles, const std::vector<int32_t>& s
 //  * 128x128 tiles, launches that leave most of the chip idle (batches of a few hundred rows on a
 //    4096-wide layer: 96 tiles for 256 CUs, each workgroup walking the whole K extent alone, a chain
 //    of load and LDS latencies of about 0.5 us per 64 k): all tiles split (whole = 0),
-//    parts = 320 / tiles: three parts for 96 tiles, none from 161 tiles on.
+//    parts = 320 / tiles: three parts for 96 tiles, none from 161 tiles on; at least 12 stages per part
+//    (96 rows of 4096 x 4096: 20.6 us in 5 parts, 23.4 in 8; 2000 rows of 1024 x 1024: 13.6 us whole, 17.4 in 2); twice
+//    as many where a part would have 64 stages or more and a second workgroup per CU finds room (397 rows of
+//    11008 -> 4096: 57.8 us in 4 parts, 73 in 2).
 //  * 256x256 tiles, one workgroup per CU, 32 CUs per XCD: a run of per_xcd tiles ends in a round of
 //    rem = per_xcd % 32 tiles that takes as long as a full one.  These last tiles are split into the
 //    number of parts (at most 4) that makes the round shortest by a simple model of its time: e.g.
 //    4 parts for 8 tiles (a quarter of a tile's time), 3 parts for 20 tiles of a long K (60
 //    workgroups in two passes of a third each), none where the sum of the partial tiles (256 KiB
 //    each) would cost what the split saves.
-// parts is at most 8 and at most one per 8 stages of 64 k.  A pure function of the shape: the
+// parts is at most 8.  A pure function of the shape: the
 // workspace figure does not depend on the process environment or on the handle.
 struct SplitPlan {
     int parts = 1;        // K ranges per split tile (1: no split)
@@ -265,10 +270,11 @@ SplitPlan gemm_split_plan(int M, int N, int K) {
     constexpr int target = 320, tail_max = 4;
     if (M <= 0) return s;
     const int KF = K / 64;
-    if (gemm_variant(M, N) == 2) {
+    if (gemm_variant(M, N, K) == 2) {
         const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
-        const int P = std::min({8, KF / 8, (int)(target / tiles)});
+        int P = std::min({8, KF / 12, (int)(target / tiles)});
         if (P < 2) return s;
+        if (P <= 4 && KF / P >= 64 && 2 * P * tiles <= 512) P *= 2;
         s.parts = P;
         s.slots = (int)tiles;                  // whole = 0: a tile's slot is its number in the walk
         s.bytes = (size_t)tiles * P * 128 * 128 * 4;
@@ -579,7 +585,7 @@ double gemm_flops(const symb_batch* b, int N, int K, bool lora) {
 template <bool NN>
 symb_status launch_gemm(symb_handle h, const GemmParams& gp, hipStream_t st) {
     const bool plain = !gp.bias && !gp.epi_ia3 && !gp.Cbase && !gp.neff;
-    if (gemm_variant(gp.M, gp.N) == 3) return plain ? launch_gemm16_t<8, NN, true>(h, gp, st) : launch_gemm16_t<8, NN, false>(h, gp, st);
+    if (gemm_variant(gp.M, gp.N, gp.K) == 3) return plain ? launch_gemm16_t<8, NN, true>(h, gp, st) : launch_gemm16_t<8, NN, false>(h, gp, st);
     return plain ? launch_gemm16_t<4, NN, true>(h, gp, st) : launch_gemm16_t<4, NN, false>(h, gp, st);
 }
 
@@ -1058,7 +1064,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
         return SYMB_OK;
     }
 
-    const int bm = gemm_tile_m(bi.T, b->d_out);
+    const int bm = gemm_tile_m(bi.T, b->d_out, b->d_in);
     std::vector<int32_t> lo, hi;
     plan_row_tiles(b, bm, lo, hi);
     std::vector<RowChunk> chunks, all_chunks;
@@ -1308,7 +1314,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
         return SYMB_OK;
     }
 
-    const int bm = gemm_tile_m(bi.T, b->d_in);
+    const int bm = gemm_tile_m(bi.T, b->d_in, b->d_out);
     std::vector<int32_t> lo, hi;
     plan_row_tiles(b, bm, lo, hi);
     std::vector<RowChunk> chunks, all_chunks;

@@ -6,6 +6,7 @@ import torch
 
 import gpu_harness as gh
 import oracle
+import synth
 import test_gpu_parity as tp
 from helpers import assert_close, check_dx, check_y
 from paper_2507_03220_amd import binding as sb
@@ -78,3 +79,14 @@ def test_gradients_take_hs_and_dh_from_the_streaming_calls(lens):
     sb.symb_base_linear_bwd_input(h, b, Gd, Wd, dX, sb.SYMB_BWD_REUSE_DH, ws)
     torch.cuda.synchronize()
     check_dx(gh.bf16_to_f64(dX), off, oads, p["dY"], p["W"], "dX from the gradient call's dH")
+
+
+@pytest.mark.parametrize("T,d_in,d_out", [(2048, 264, 4096), (4096, 328, 2000), (397, 8320, 520), (100, 2056, 1032)])
+def test_tile_and_split_rules_of_mid_sized_batches(T, d_in, d_out):
+    """128 tiles of 256x256 run as 128x128 ones; a long inner dimension in twice the parts; at least 12 stages per part."""
+    p = make_problem(T, d_in, d_out, [T // 2, T // 4, T - T // 2 - T // 4], [L, I, N], [16])
+    rows = synth.sample_rows(p["off"], 12, f"mid{T}", block=128)
+    oads = oracle_ads(p["ads"])
+    for conv1d in (False, True):
+        Y, _ = gh.forward(p["off"], p["ads"], p["X"], p["W"], p["bias"], want_base=False, conv1d=conv1d)
+        check_y(gh.bf16_to_f64(Y)[rows], p["off"], oads, p["X"], p["W"], p["bias"], "Y", rows=rows)
