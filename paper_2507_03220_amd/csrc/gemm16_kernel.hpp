@@ -35,6 +35,13 @@
 
 namespace symb {
 
+// Rows of a row tile whose LoRA term comes ready-made (see symb_lora_delta_kernel): row r of the tile is such a row if bit r of mask is
+// set, and its term is row first + (number of set bits below r) of GemmParams::delta.
+struct TileDelta {
+    int32_t first;
+    uint32_t mask[8];
+};
+
 struct GemmParams {
     const bf16* Aop;            // [M][K] (null when the rows come from per-segment buffers, see a_seg)
     const bf16* Bop;            // NT: [N][K]   NN: [K][N]
@@ -63,6 +70,8 @@ struct GemmParams {
     // K-split (k_parts <= 1: off): of every XCD's run of tiles, those from number k_whole on are computed
     // by k_parts workgroups each; partial holds k_parts fp32 tiles per split tile, k_count one zeroed
     // arrival counter per split tile.
+    const float* delta;         // [rows][N] fp32 or null: LoRA terms of rows of short segments (whose kind here is not KIND_LORA)
+    const TileDelta* tile_delta;// device [num_m_tiles], with delta
     int k_parts, k_whole;
     float* partial;
     int* k_count;
@@ -647,6 +656,38 @@ symb_gemm16_kernel(const GemmParams p) {
                 static_for<0, 16>([&](auto B) __attribute__((always_inline)) {
                     constexpr int b = decltype(B)::value;
                     acc16_write4<4 * (g * 16 + b)>(sum[b].x, sum[b].y, sum[b].z, sum[b].w);
+                });
+            });
+        }
+    }
+
+    // ---- LoRA terms that were computed beforehand, row blocks that have any
+    if constexpr (!PLAIN) {
+        if (p.delta) {
+            const TileDelta* const td = p.tile_delta + tm;
+            int before = td->first;                  // terms of the tile's rows above the block
+            for (int w = 0; w < wm0 / 32; ++w) before += __builtin_popcount(td->mask[w]);
+            static_for<0, NBLK>([&](auto I) __attribute__((always_inline)) {
+                constexpr int i = decltype(I)::value;
+                const unsigned bits = (td->mask[(wm0 + i * 16) >> 5] >> ((i & 1) * 16)) & 0xffffu;       // uniform
+                if (!bits) return;
+                const bool has = (bits >> l15) & 1;
+                const int row = before + (has ? __builtin_popcount(bits & ((1u << l15) - 1)) : 0);
+                before += __builtin_popcount(bits);
+                const int nq0 = n0 + wn0 + lg * 4;
+                const float* const d = p.delta + (size_t)row * p.N + nq0;
+                static_for<0, NBLK / 4>([&](auto Q) __attribute__((always_inline)) {
+                    constexpr int q = decltype(Q)::value;
+                    float4 v[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        v[j] = has && nq0 + (q * 4 + j) * 16 < p.N ? *reinterpret_cast<const float4*>(d + (q * 4 + j) * 16) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    static_for<0, 4>([&](auto J) __attribute__((always_inline)) {
+                        constexpr int j = decltype(J)::value, at = 4 * (NBLK * i + q * 4 + j);
+                        float a0, a1, a2, a3;
+                        acc16_read4<at>(a0, a1, a2, a3);
+                        acc16_write4<at>(a0 + v[j].x, a1 + v[j].y, a2 + v[j].z, a3 + v[j].w);
+                    });
                 });
             });
         }

@@ -341,6 +341,7 @@ struct WsLayout {
     // optional regions (a workspace that ends before them makes the call take the tiled kernel, unsplit):
     size_t sp_off = 0, sp_bytes = 0;      // calls of at most SMALL_MAX_ROWS rows: fp32 partial sums of the base product per K range
     size_t sh_off = 0, sh_bytes = 0;      // ... and of the LoRA shrink
+    size_t de_off = 0, de_bytes = 0;      // fp32 LoRA terms of short segments of a batch for the tiled kernels (see DeltaPlan)
     size_t tp_off = 0, tp_bytes = 0;      // fp32 partial tiles of a K-split GEMM (see gemm_split_plan); last
     size_t mandatory = 0;                 // end of the regions a call cannot do without
     size_t total = 0;
@@ -381,6 +382,54 @@ SmallPlan small_plan(const symb_batch* b, const BatchInfo& bi, int op, bool lora
     s.h_ranges = std::max(1, std::min({256 / s.items, K / 512, 16}));      // at most a round of its own, two slices per wavefront
     s.h_bytes = (size_t)s.h_ranges * bi.T * bi.max_rpad * 4;
     return s;
+}
+
+// Short LoRA segments (at most kDeltaRows rows) whose term the tiled kernels add from memory (symb_lora_delta_kernel) instead of running a
+// chain of k-steps for each: all of them that meet a row tile with at least delta_steps() such steps, about the time of the extra
+// launch (6 to 16 us: a step costs up to 1.6 us in the 256x256 tile, about 0.45 in the 128x128 one).  Batches of thousands of segments keep the steps: their descriptors have to fit as before.
+constexpr int kDeltaRows = 16, kDeltaSegments = 4096;
+int delta_steps(int tile_m) { return tile_m == 256 ? 8 : 16; }
+struct DeltaPlan {
+    std::vector<RowChunk> items;          // the segments (pad: first row of their terms)
+    int rows = 0;                         // rows of terms
+};
+DeltaPlan delta_plan(const symb_batch* b, int tile_m) {
+    DeltaPlan d;
+    const int S = b->num_segments, least = delta_steps(tile_m);
+    auto steps = [&](int i) {
+        const int n = b->seg_offsets[i + 1] - b->seg_offsets[i];
+        return b->adapters[i].kind == SYMB_ADAPTER_LORA && n > 0 && n <= kDeltaRows ? rpad_of(b->adapters[i].rank) / 16 : 0;
+    };
+    if (S > kDeltaSegments) return d;
+    int all = 0;
+    for (int i = 0; i < S && all < least; ++i) all += steps(i);
+    if (all < least) return d;
+    std::vector<int> tile((b->seg_offsets[S] + tile_m - 1) / tile_m, 0);
+    for (int i = 0; i < S; ++i)
+        if (const int k = steps(i)) {
+            const int u = b->seg_offsets[i] / tile_m, v = (b->seg_offsets[i + 1] - 1) / tile_m;
+            tile[u] += k;
+            if (v != u) tile[v] += k;
+        }
+    for (int i = 0; i < S; ++i)
+        if (steps(i)) {
+            const int lo = b->seg_offsets[i], n = b->seg_offsets[i + 1] - lo;
+            if (tile[lo / tile_m] < least && tile[(lo + n - 1) / tile_m] < least) continue;
+            d.items.push_back(RowChunk{i, lo, n, d.rows});
+            d.rows += n;
+        }
+    return d;
+}
+std::vector<TileDelta> delta_tiles(const DeltaPlan& d, int num_m_tiles, int tile_m) {
+    std::vector<TileDelta> v(d.items.empty() ? 0 : num_m_tiles, TileDelta{});
+    for (const RowChunk& it : d.items)
+        for (int t = it.row0; t < it.row0 + it.nrows; ++t) v[t / tile_m].mask[t % tile_m / 32] |= 1u << (t % 32);
+    int at = 0;
+    for (TileDelta& t : v) {
+        t.first = at;
+        for (uint32_t m : t.mask) at += __builtin_popcount(m);
+    }
+    return v;
 }
 
 WsLayout ws_layout(const symb_batch* b, const BatchInfo& bi, int op, bool full_bwd, bool any_lora_grad, bool staged_out = false) {
@@ -425,6 +474,11 @@ WsLayout ws_layout(const symb_batch* b, const BatchInfo& bi, int op, bool full_b
         const SmallPlan sm = small_plan(b, bi, op, op == SYMB_OP_FWD || full_bwd, staged_out);
         take(w.sp_off, w.sp_bytes, sm.base_bytes);
         take(w.sh_off, w.sh_bytes, sm.h_bytes);
+    }
+    if (bi.n_lora && (op == SYMB_OP_FWD || (op == SYMB_OP_BWD_INPUT && full_bwd))) {
+        const int N = op == SYMB_OP_FWD ? b->d_out : b->d_in, K = op == SYMB_OP_FWD ? b->d_in : b->d_out;
+        const int rows = delta_plan(b, gemm_tile_m(bi.T, N, K)).rows;
+        if (rows) take(w.de_off, w.de_bytes, (size_t)rows * N * 4);
     }
     if (op == SYMB_OP_FWD) {
         const SplitPlan sp = gemm_split_plan(bi.T, b->d_out, b->d_in);
@@ -584,7 +638,7 @@ double gemm_flops(const symb_batch* b, int N, int K, bool lora) {
 
 template <bool NN>
 symb_status launch_gemm(symb_handle h, const GemmParams& gp, hipStream_t st) {
-    const bool plain = !gp.bias && !gp.epi_ia3 && !gp.Cbase && !gp.neff;
+    const bool plain = !gp.bias && !gp.epi_ia3 && !gp.Cbase && !gp.neff && !gp.delta;
     if (gemm_variant(gp.M, gp.N, gp.K) == 3) return plain ? launch_gemm16_t<8, NN, true>(h, gp, st) : launch_gemm16_t<8, NN, false>(h, gp, st);
     return plain ? launch_gemm16_t<4, NN, true>(h, gp, st) : launch_gemm16_t<4, NN, false>(h, gp, st);
 }
@@ -644,6 +698,20 @@ symb_status launch_row_pass(symb_handle h, void (*kfn)(P), P p, int width, size_
         SYMB_HIP(h, hipGetLastError());
         p.chunks += n;
     }
+    return SYMB_OK;
+}
+
+// The terms of a DeltaPlan, from the rows of H in the workspace.
+symb_status launch_delta(symb_handle h, bool backward, const SegDesc* seg, const RowChunk* items, int nitems, int N, bf16* h_rows, int h_pitch, float* out, hipStream_t st) {
+    LoraDeltaParams dp{};
+    dp.f.h_rows = h_rows;
+    dp.f.h_pitch = h_pitch;
+    dp.f.N = N;
+    dp.f.seg = seg;
+    dp.items = items;
+    dp.out = out;
+    hipLaunchKernelGGL(backward ? symb_lora_delta_kernel<true> : symb_lora_delta_kernel<false>, dim3((N + 255) / 256, nitems), dim3(128), 0, st, dp);
+    SYMB_HIP(h, hipGetLastError());
     return SYMB_OK;
 }
 
@@ -1078,6 +1146,9 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     unsigned char* wsb = (unsigned char*)ws;
     std::vector<SegDesc> sd_gemm = sd;
     std::vector<int64_t> pk_off(bi.S, 0);
+    DeltaPlan delta;
+    if (wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm);
+    const std::vector<TileDelta> tile_delta = delta_tiles(delta, (int)lo.size(), bm);
     if (conv1d && bi.n_lora) {
         int64_t cur = 0;
         for (int i = 0; i < bi.S; ++i)
@@ -1087,12 +1158,15 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
                 cur += (int64_t)sd[i].rpad * b->d_out;
             }
     }
+    for (const RowChunk& it : delta.items) sd_gemm[it.seg].kind = KIND_DELTA;
     Blob blob;
     const size_t o_seg = blob.add(sd.data(), sd.size());
     const size_t o_segg = blob.add(sd_gemm.data(), sd_gemm.size());
     const size_t o_off = blob.add(b->seg_offsets, (size_t)bi.S + 1);
     const size_t o_lo = blob.add(lo.data(), lo.size());
     const size_t o_hi = blob.add(hi.data(), hi.size());
+    const size_t o_de = blob.add(delta.items.data(), delta.items.size());
+    const size_t o_td = blob.add(tile_delta.data(), tile_delta.size());
     const std::vector<int32_t> tile_epi = plan_tile_kind(b, lo, hi, SYMB_ADAPTER_IA3);
     const size_t o_te = blob.add(tile_epi.data(), tile_epi.size());
     const size_t o_ch = blob.add(chunks.data(), chunks.size());
@@ -1138,7 +1212,13 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
         }
         if ((st = launch_skinny(h, sp, (int)chunks.size(), bi.max_rpad, s)) != SYMB_OK) return st;
     }
+    if (!delta.items.empty() && (st = launch_delta(h, false, (const SegDesc*)(dev + o_seg), (const RowChunk*)(dev + o_de), (int)delta.items.size(), b->d_out,
+                                                   Hs, bi.max_rpad, (float*)(wsb + wl.de_off), s)) != SYMB_OK) return st;
     GemmParams gp{};
+    if (!delta.items.empty()) {
+        gp.delta = (const float*)(wsb + wl.de_off);
+        gp.tile_delta = (const TileDelta*)(dev + o_td);
+    }
     gp.Aop = x_op;
     if (seg_io) {
         if (!copy_rows) {          // (a flat copy of the rows, scaled for IA3_IN, is read as one tensor)
@@ -1349,6 +1429,9 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     // whose LoRA steps read the adapter side as [d_in][rank] rows: A_i^T, packed into the workspace.
     const bool conv1d = b->weight_layout == SYMB_WEIGHT_CONV1D;
     std::vector<SegDesc> sd_gemm = sd;
+    DeltaPlan delta;
+    if (lora && wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm);
+    const std::vector<TileDelta> tile_delta = delta_tiles(delta, (int)lo.size(), bm);
     std::vector<int64_t> pk_off(bi.S, 0), pa_off(bi.S, 0);
     {
         int64_t cur = 0, cura = 0;
@@ -1363,12 +1446,15 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
                 }
             }
     }
+    for (const RowChunk& it : delta.items) sd_gemm[it.seg].kind = KIND_DELTA;
     Blob blob;
     const size_t o_seg = blob.add(sd.data(), sd.size());
     const size_t o_segg = blob.add(sd_gemm.data(), sd_gemm.size());
     const size_t o_off = blob.add(b->seg_offsets, (size_t)bi.S + 1);
     const size_t o_lo = blob.add(lo.data(), lo.size());
     const size_t o_hi = blob.add(hi.data(), hi.size());
+    const size_t o_de = blob.add(delta.items.data(), delta.items.size());
+    const size_t o_td = blob.add(tile_delta.data(), tile_delta.size());
     const std::vector<int32_t> tile_epi = plan_tile_kind(b, lo, hi, SYMB_ADAPTER_IA3_IN);
     const size_t o_te = blob.add(tile_epi.data(), tile_epi.size());
     const size_t o_ch = blob.add(chunks.data(), chunks.size());
@@ -1424,7 +1510,13 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
         if ((st = launch_row_pass(h, symb_ia3_scale_rows_kernel, sc, sc.d_out, all_chunks.size(), s)) != SYMB_OK) return st;
         a_op = copy;
     }
+    if (!delta.items.empty() && (st = launch_delta(h, true, (const SegDesc*)(dev + o_seg), (const RowChunk*)(dev + o_de), (int)delta.items.size(), b->d_in,
+                                                   dH, bi.max_rpad, (float*)(wsb + wl.de_off), s)) != SYMB_OK) return st;
     GemmParams gp{};
+    if (!delta.items.empty()) {
+        gp.delta = (const float*)(wsb + wl.de_off);
+        gp.tile_delta = (const TileDelta*)(dev + o_td);
+    }
     gp.Aop = a_op;
     gp.Bop = (const bf16*)W;
     gp.C = (bf16*)dX;

@@ -12,7 +12,8 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short shortx4;
 
-enum : int32_t { KIND_NONE = 0, KIND_LORA = 1, KIND_IA3 = 2, KIND_IA3_IN = 3 };
+enum : int32_t { KIND_NONE = 0, KIND_LORA = 1, KIND_IA3 = 2, KIND_IA3_IN = 3,
+                KIND_DELTA = 4 /* in the GEMM's descriptors only: a LoRA segment whose term is added from memory */ };
 
 // Per-segment descriptor as the kernels see it (device memory, one per segment).
 struct SegDesc {

@@ -90,3 +90,23 @@ def test_tile_and_split_rules_of_mid_sized_batches(T, d_in, d_out):
     for conv1d in (False, True):
         Y, _ = gh.forward(p["off"], p["ads"], p["X"], p["W"], p["bias"], want_base=False, conv1d=conv1d)
         check_y(gh.bf16_to_f64(Y)[rows], p["off"], oads, p["X"], p["W"], p["bias"], "Y", rows=rows)
+
+
+@pytest.mark.parametrize("d_in,d_out", [(264, 392), (200, 6216)])                  # 128x128 and 256x256 tiles
+def test_short_segments_of_a_larger_batch(d_in, d_out):
+    """LoRA terms of short segments are added from memory where a row tile holds many of their steps: scattered over the tiles,
+    across a tile's edge, beside long segments, empty ones and other kinds; with the pre-adapter output; in both directions."""
+    lens = [1] * 9 + [300, 16, 3, 0, 17] + [1, 2] * 8 + [200, 1, 40] + [1] * 5 + [5, 16, 260]
+    kinds = [L, L, L, I, L, N, L]
+    p = make_problem(5 + d_out, d_in, d_out, lens, kinds, [16, 128, 5, 40, 8, 33])
+    off, oads = p["off"], oracle_ads(p["ads"])
+    for conv1d in (False, True):
+        for want_base in (False, True):
+            Y, Yb = gh.forward(off, p["ads"], p["X"], p["W"], p["bias"], want_base=want_base, conv1d=conv1d)
+            Y0r, _ = check_y(gh.bf16_to_f64(Y), off, oads, p["X"], p["W"], p["bias"], f"Y conv1d={conv1d}")
+            if want_base:
+                assert_close(gh.bf16_to_f64(Yb), Y0r, "Ybase", out_bf16=True)
+    q = make_problem(6 + d_out, d_out, d_in, lens, kinds, [16, 128, 5, 40, 8, 33])
+    for conv1d in (False, True):
+        dX = gh.backward_input(off, q["ads"], q["dY"], q["W"], conv1d=conv1d)
+        check_dx(gh.bf16_to_f64(dX), off, oracle_ads(q["ads"]), q["dY"], q["W"], f"dX conv1d={conv1d}")
