@@ -18,7 +18,8 @@ struct RowChunk {
 // Skinny projection:  out[t][p] = s_i * sum_k L[t][k] * R_i[p][k],  p < rpad_i, stored as a bf16
 // value plus a bf16 residual (out[t][rpad_i + p])
 //   forward shrink : L = X  [T][K=d_in],  R_i = A_i  [r][d_in]
-//   backward dH    : L = dY [T][K=d_out], R_i = B_i^T packed [rpad][d_out] (see pack kernel)
+//   backward dH    : L = dY [T][K=d_out], R_i = B_i^T: read from B_i [d_out][r] as it lies (BT), or, where a rank is no multiple
+//                    of 4 or a B_i not 16-byte aligned, from a packed copy [rpad][d_out] (see pack kernel)
 // A workgroup owns 32 rows; its 4 wavefronts split K in interleaved slices, bring the rows in
 // through LDS (see SkinnyStage below), take the adapter rows from L2, and meet in LDS for the
 // final sum.  RB = max rank blocks of 16.
@@ -29,7 +30,7 @@ struct SkinnyParams {
     int K, out_pitch;
     const RowChunk* chunks;   // device
     const SegDesc* seg;       // device
-    const bf16* packed;       // backward: base of packed B^T area, else null
+    const bf16* packed;       // backward through a packed copy: base of packed B^T area, else null
     const int64_t* packed_off;// backward: element offset of segment i's [rpad][K] block
     int use_packed;
     const bf16* const* L_seg; // device [S] or null: rows of segment i start at L_seg[i] instead of L + off[i] * K
@@ -79,7 +80,13 @@ __device__ __forceinline__ u32x4 ld_glb16(const bf16* p) {
 // loop holds no conditional load: the compiler's wait counts for the adapter rows are then exact).
 // lrow / rrow point at the lane's first 8 elements (row start + kq*8); src[i] at the 16 bytes this
 // lane brings in with DMA request i of a slice (at k = 0); wbuf = this wavefront's slice buffers.
-template <int RB, int NB, class ST = SkinnyStage<RB>>
+// BT: rbase is B_i [K][rrows].  The SK k-rows of a slice are one contiguous run of it, brought in as it lies and read back
+// through the transposing LDS read.  Rows of 128 or 256 bytes (ranks 64, 128) would put the 8 k-rows such a read serves at a time
+// on the same banks: their 32-byte pieces are stored at piece ^ skinny_bt_swz.
+__device__ __forceinline__ int skinny_bt_swz(int r, int k) {
+    return r == 128 ? ((((k >> 3) & 1) << 2) | (k & 3)) : r == 64 ? ((((k >> 3) & 1) << 1) | ((k >> 1) & 1)) : 0;
+}
+template <int RB, int NB, bool BT, class ST = SkinnyStage<RB>>
 __device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[SKINNY_BLKS], const bf16* (&rrow)[RB], const bool (&r_ok)[RB],
                                               const bf16* (&src)[ST::DPS], const bf16* rbase, int rrows,
                                               unsigned char* wbuf, int K, int wave, int lane, floatx4 (&acc)[SKINNY_BLKS][RB]) {
@@ -97,16 +104,24 @@ __device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[SKINNY_BLKS], 
         }
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-            const int r = j * 16 + trow;
-            roff[j][h] = (unsigned)(size_t)rbuf + (unsigned)(r * ST::ROW_BYTES + (((h * 4 + kq) ^ ST::swz(r)) * 16));
+            const int r = j * 16 + trow, k = h * 32 + kq * 8 + (trow >> 2);      // BT: first of the two reads; the second is 4 k-rows further
+            roff[j][h] = (unsigned)(size_t)rbuf + (BT ? (unsigned)(k * rrows * 2 + ((j ^ skinny_bt_swz(rrows, k)) * 32) + (trow & 3) * 8)
+                                                      : (unsigned)(r * ST::ROW_BYTES + (((h * 4 + kq) ^ ST::swz(r)) * 16)));
         }
     }
     // The adapter rows (from L2) come in by LDS DMA as well, whole row pieces per request: fragment loads
     // straight from global memory are 64-byte pieces of 16 rows each, twice the requests for the bytes.
     // Rows past the adapter's last are read from row 0 and count as zero (r_ok).
     const bf16* rsrc[NRD];
+    const size_t rstep = BT ? (size_t)rrows : 1;         // adapter elements from one k to the next
 #pragma unroll
     for (int i = 0; i < NRD; ++i) {
+        if constexpr (BT) {                              // (past the run's end: its last 16 bytes again)
+            const int c = min(i * 64 + lane, ST::SK * rrows / 8 - 1), per = rrows >> 3;        // 16-byte chunk of the run
+            const int f = rrows == 64 || rrows == 128 ? skinny_bt_swz(rrows, c / per) : 0;
+            rsrc[i] = rbase + (c ^ (f << 1)) * 8;
+            continue;
+        }
         const int r = i * ST::RPI + lane / ST::LPR;
         rsrc[i] = rbase + (size_t)(r < rrows ? r : 0) * K + (((lane % ST::LPR) ^ ST::swz(r)) * 8);
     }
@@ -118,7 +133,7 @@ __device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[SKINNY_BLKS], 
     auto dma_r = [&](int buf, int k) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < NRD; ++i)
-            __builtin_amdgcn_global_load_lds((glb_void_t*)(rsrc[i] + k), (lds_void_t*)(rbuf + (ST::RDEEP ? buf * ST::RSLICE : 0) + i * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((glb_void_t*)(rsrc[i] + k * rstep), (lds_void_t*)(rbuf + (ST::RDEEP ? buf * ST::RSLICE : 0) + i * 1024), 16, 0, 0);
     };
     // The fragment reads are assembly statements with a wait of their own: while an LDS DMA request is in
     // flight the compiler makes every load result it can see wait for all memory traffic of the
@@ -126,13 +141,23 @@ __device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[SKINNY_BLKS], 
     // covers it, so no use can move in front of that wait.  mul() returns with its LDS reads
     // complete: both buffers it read may be requested again.
     auto mul = [&](int buf) __attribute__((always_inline)) {
-        u32x4 lv[SKINNY_BLKS][NH], rv[NB][NH];
+        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+        u32x4 lv[SKINNY_BLKS][NH], rv[BT ? 1 : NB][NH];
+        u32x2 rt[BT ? NB : 1][NH][2];
 #pragma unroll
         for (int h = 0; h < NH; ++h) {
 #pragma unroll
             for (int b = 0; b < SKINNY_BLKS; ++b) asm volatile("ds_read_b128 %0, %1" : "=v"(lv[b][h]) : "v"(foff[b][h] + buf * ST::SLICE));
 #pragma unroll
-            for (int j = 0; j < NB; ++j) asm volatile("ds_read_b128 %0, %1" : "=v"(rv[j][h]) : "v"(roff[j][h] + (ST::RDEEP ? buf * ST::RSLICE : 0)));
+            for (int j = 0; j < NB; ++j) {
+                const unsigned at = roff[j][h] + (ST::RDEEP ? buf * ST::RSLICE : 0);
+                if constexpr (BT) {
+                    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(rt[j][h][0]) : "v"(at));
+                    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(rt[j][h][1]) : "v"(at + 8 * rrows));
+                } else {
+                    asm volatile("ds_read_b128 %0, %1" : "=v"(rv[j][h]) : "v"(at));
+                }
+            }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
 #pragma unroll
@@ -140,13 +165,19 @@ __device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[SKINNY_BLKS], 
 #pragma unroll
             for (int b = 0; b < SKINNY_BLKS; ++b) asm volatile("" : "+v"(lv[b][h]));
 #pragma unroll
-            for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(rv[j][h]));
+            for (int j = 0; j < NB; ++j) {
+                if constexpr (BT) { asm volatile("" : "+v"(rt[j][h][0])); asm volatile("" : "+v"(rt[j][h][1])); }
+                else asm volatile("" : "+v"(rv[j][h]));
+            }
         }
 #pragma unroll
         for (int h = 0; h < NH; ++h)
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
-                const bf16x8 rf = __builtin_bit_cast(bf16x8, r_ok[j] ? rv[j][h] : u32x4{0u, 0u, 0u, 0u});
+                u32x4 raw;
+                if constexpr (BT) raw = __builtin_shufflevector(rt[j][h][0], rt[j][h][1], 0, 1, 2, 3);
+                else raw = rv[j][h];
+                const bf16x8 rf = __builtin_bit_cast(bf16x8, r_ok[j] ? raw : u32x4{0u, 0u, 0u, 0u});
 #pragma unroll
                 for (int b = 0; b < SKINNY_BLKS; ++b)
                     acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rf, __builtin_bit_cast(bf16x8, lv[b][h]), acc[b][j], 0, 0, 0);
@@ -198,7 +229,16 @@ __device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[SKINNY_BLKS], 
             for (int b = 0; b < SKINNY_BLKS; ++b) lv[b] = kok ? ld_glb16(lrow[b] + k0 + h * 32) : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
-                const u32x4 rv = (kok && r_ok[j]) ? ld_glb16(rrow[j] + k0 + h * 32) : u32x4{0u, 0u, 0u, 0u};
+                u32x4 rv = u32x4{0u, 0u, 0u, 0u};
+                if (kok && r_ok[j]) {
+                    if constexpr (BT) {                  // column j*16 + trow of 8 k-rows
+                        const unsigned short* const e = reinterpret_cast<const unsigned short*>(rbase) + (size_t)(k0 + h * 32 + kq * 8) * rrows + j * 16 + trow;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) rv[q] = e[(size_t)(2 * q) * rrows] | ((unsigned)e[(size_t)(2 * q + 1) * rrows] << 16);
+                    } else {
+                        rv = ld_glb16(rrow[j] + k0 + h * 32);
+                    }
+                }
 #pragma unroll
                 for (int b = 0; b < SKINNY_BLKS; ++b)
                     acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rv), __builtin_bit_cast(bf16x8, lv[b]), acc[b][j], 0, 0, 0);
@@ -208,16 +248,16 @@ __device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[SKINNY_BLKS], 
 }
 
 // Calls skinny_stream<RB, nb> for the run-time nb in 1..RB.
-template <int RB, class ST, int NB = 1, typename... Args>
+template <int RB, bool BT, class ST, int NB = 1, typename... Args>
 __device__ __forceinline__ void skinny_stream_dispatch(int nb, Args&&... args) {
-    if (nb == NB) skinny_stream<RB, NB, ST>(args...);
-    else if constexpr (NB < RB) skinny_stream_dispatch<RB, ST, NB + 1>(nb, args...);
+    if (nb == NB) skinny_stream<RB, NB, BT, ST>(args...);
+    else if constexpr (NB < RB) skinny_stream_dispatch<RB, BT, ST, NB + 1>(nb, args...);
 }
 
 // DEEP: three buffers with the adapter rows beside each slice, two slices in flight per wavefront.  For
 // launches of few chunks, where a workgroup has a compute unit to itself and its time is the chain of
 // memory latencies along K rather than bandwidth.
-template <int RB, bool DEEP = false>
+template <int RB, bool DEEP, bool BT>
 __global__ void __launch_bounds__(256)
 symb_skinny_kernel(const SkinnyParams p) {
     using ST = SkinnyStage<RB, DEEP ? 3 : 2, DEEP>;
@@ -241,8 +281,8 @@ symb_skinny_kernel(const SkinnyParams p) {
         const int r = i * ST::RPI + lane / ST::LPR;
         src[i] = lbase + (size_t)(ch.row0 + min(r, ch.nrows - 1)) * p.K + (((lane % ST::LPR) ^ ST::swz(r)) * 8);
     }
-    const bf16* rbase = p.use_packed ? (p.packed + p.packed_off[ch.seg]) : sd.A;
-    const int rrows = p.use_packed ? sd.rpad : sd.rank;  // valid adapter rows; the rest count as zero
+    const bf16* rbase = BT ? sd.B : p.use_packed ? (p.packed + p.packed_off[ch.seg]) : sd.A;
+    const int rrows = !BT && p.use_packed ? sd.rpad : sd.rank;     // valid adapter rows; the rest count as zero
     const bf16* rrow[RB];
     bool r_ok[RB];
 #pragma unroll
@@ -257,7 +297,7 @@ symb_skinny_kernel(const SkinnyParams p) {
 #pragma unroll
         for (int j = 0; j < RB; ++j) acc[b][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    skinny_stream_dispatch<RB, ST>(nb, lrow, rrow, r_ok, src, rbase, rrows, smem + wave * ST::WAVE_BYTES, p.K, wave, lane, acc);
+    skinny_stream_dispatch<RB, BT, ST>(nb, lrow, rrow, r_ok, src, rbase, rrows, smem + wave * ST::WAVE_BYTES, p.K, wave, lane, acc);
     __syncthreads();                                     // every wavefront is done with its slice buffers
     // lane holds out[t = b*16 + trow][p = j*16 + 4*kq + q]
     if (wave > 0) {
@@ -534,8 +574,8 @@ symb_lora_grad_kernel(const GradParams p) {
 // (a segment, or a run of a long one) and walks its tokens 32 at a time; per step it visits its
 // column blocks in turn: the dY tile goes through LDS as in symb_lora_grad_kernel and feeds
 // (a) the dB accumulators of that block (transposing LDS reads, token-contracted) and (b) a
-// 32 x 16 partial of dH over the block's columns (plain LDS reads, B_i^T fragments from the
-// packed copy, held in registers).  After the last block of a step the four wavefronts' dH partials
+// 32 x 16 partial of dH over the block's columns (plain LDS reads, B_i^T fragments held
+// in registers).  After the last block of a step the four wavefronts' dH partials
 // meet in LDS and the sum goes to dh_partial[group][t][16]; symb_dh_finish_kernel adds the
 // groups in order, scales by s_i and writes dH as value + residual.  Fixed summation order
 // everywhere: deterministic, no atomics.  dB comes out bit-identical to symb_lora_grad_kernel's.
@@ -543,8 +583,6 @@ symb_lora_grad_kernel(const GradParams p) {
 struct DhDbParams {
     const bf16* R;            // dY [T][ncols]
     const bf16* L;            // Hs [T][l_pitch]: per row 16 values then 16 residuals
-    const bf16* packed;       // B_i^T [16][ncols] per LoRA segment (symb_pack_bt_kernel), at packed_off[i]
-    const int64_t* packed_off;
     int ncols, l_pitch;
     const int32_t* off;
     const SegDesc* seg;
@@ -578,7 +616,6 @@ symb_lora_dhdb_kernel(const DhDbParams p) {
     const SegDesc sd = p.seg[s];
     const int t_lo = it.t_lo, t_hi = it.t_hi;
     const bf16* const rbase = p.R_seg ? p.R_seg[s] - (size_t)p.off[s] * p.ncols : p.R;
-    const bf16* const bt = p.packed + p.packed_off[s];
     const int nblk = (p.ncols + CT - 1) / CT;
     const int cb0 = blockIdx.x * G, ncb = min(G, nblk - cb0);     // this workgroup's column blocks (uniform)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -597,8 +634,12 @@ symb_lora_dhdb_kernel(const DhDbParams p) {
         for (int ks = 0; ks < 2; ++ks) {
             const int c = (cb0 + g) * CT + wave * 64 + ks * 32 + (lane >> 4) * 8;
             const bool ok = g < ncb && c < p.ncols;
-            btf[g][ks] = ld_glb16(bt + (size_t)(lane & 15) * p.ncols + (ok ? c : 0));
-            if (!ok) btf[g][ks] = u32x4{0u, 0u, 0u, 0u};
+            // (element loads from B_i [ncols][rank]: once per workgroup)
+            const int pr = lane & 15;
+            const unsigned short* const e = reinterpret_cast<const unsigned short*>(sd.B) + (size_t)(ok ? c : 0) * sd.rank + min(pr, sd.rank - 1);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) btf[g][ks][q] = e[(size_t)(2 * q) * sd.rank] | ((unsigned)e[(size_t)(2 * q + 1) * sd.rank] << 16);
+            if (!ok || pr >= sd.rank) btf[g][ks] = u32x4{0u, 0u, 0u, 0u};
         }
 
     struct Stage { u32x4 rr[NRC]; u32x4 lv; };

@@ -644,25 +644,46 @@ symb_status launch_gemm(symb_handle h, const GemmParams& gp, hipStream_t st) {
 }
 
 // Up to one workgroup per compute unit the deep-prefetch build is used (where its buffers fit in LDS).
-template <int RB>
+template <int RB, bool BT>
 void launch_skinny_rb(const SkinnyParams& sp, int nchunks, bool deep_ok, hipStream_t st) {
     if constexpr (RB <= 4) {
         if (deep_ok && nchunks <= 256) {
-            hipLaunchKernelGGL((symb_skinny_kernel<RB, true>), dim3(nchunks), dim3(256), 0, st, sp);
+            hipLaunchKernelGGL((symb_skinny_kernel<RB, true, BT>), dim3(nchunks), dim3(256), 0, st, sp);
             return;
         }
     }
-    hipLaunchKernelGGL((symb_skinny_kernel<RB, false>), dim3(nchunks), dim3(256), 0, st, sp);
+    hipLaunchKernelGGL((symb_skinny_kernel<RB, false, BT>), dim3(nchunks), dim3(256), 0, st, sp);
 }
+template <bool BT>
 symb_status launch_skinny(symb_handle h, const SkinnyParams& sp, int nchunks, int max_rpad, hipStream_t st) {
     if (nchunks == 0) return SYMB_OK;
     const bool deep = h->opt_skinny_deep;
-    if (max_rpad <= 16) launch_skinny_rb<1>(sp, nchunks, deep, st);
-    else if (max_rpad <= 32) launch_skinny_rb<2>(sp, nchunks, deep, st);
-    else if (max_rpad <= 64) launch_skinny_rb<4>(sp, nchunks, deep, st);
-    else launch_skinny_rb<8>(sp, nchunks, deep, st);
+    if (max_rpad <= 16) launch_skinny_rb<1, BT>(sp, nchunks, deep, st);
+    else if (max_rpad <= 32) launch_skinny_rb<2, BT>(sp, nchunks, deep, st);
+    else if (max_rpad <= 64) launch_skinny_rb<4, BT>(sp, nchunks, deep, st);
+    else launch_skinny_rb<8, BT>(sp, nchunks, deep, st);
     SYMB_HIP(h, hipGetLastError());
     return SYMB_OK;
+}
+// Whether the shrink of the backward reads every B_i [d_out][r] of these segments as it lies: 64 k of it must be whole 16-byte
+// chunks at 8-byte aligned rows.  Otherwise one launch packs all of them first (4 us on a 4096-wide layer, 29 on a 36864-wide one).
+bool reads_bt(const symb_batch* b) {
+    for (int i = 0; i < b->num_segments; ++i) {
+        const symb_adapter& a = b->adapters[i];
+        if (a.kind == SYMB_ADAPTER_LORA && b->seg_offsets[i + 1] > b->seg_offsets[i] && ((a.rank & 3) || ((uintptr_t)a.B & 15))) return false;
+    }
+    return true;
+}
+// dH = s dY B of the rows in sp.chunks (sp: everything but the adapter side).
+symb_status launch_skinny_dh(symb_handle h, const symb_batch* b, SkinnyParams sp, bf16* packed, const int64_t* packed_off, int nchunks, int max_rpad, hipStream_t st) {
+    if (reads_bt(b)) return launch_skinny<true>(h, sp, nchunks, max_rpad, st);
+    PackParams pp{sp.seg, packed, packed_off, b->d_out};
+    hipLaunchKernelGGL(symb_pack_bt_kernel, dim3((b->d_out + 255) / 256, b->num_segments), dim3(256), 0, st, pp);
+    SYMB_HIP(h, hipGetLastError());
+    sp.packed = packed;
+    sp.packed_off = packed_off;
+    sp.use_packed = 1;
+    return launch_skinny<false>(h, sp, nchunks, max_rpad, st);
 }
 
 template <int RB, bool CM>
@@ -1210,7 +1231,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
             sp.L_seg = (const bf16* const*)(dev + o_xs);
             sp.off = (const int32_t*)(dev + o_off);
         }
-        if ((st = launch_skinny(h, sp, (int)chunks.size(), bi.max_rpad, s)) != SYMB_OK) return st;
+        if ((st = launch_skinny<false>(h, sp, (int)chunks.size(), bi.max_rpad, s)) != SYMB_OK) return st;
     }
     if (!delta.items.empty() && (st = launch_delta(h, false, (const SegDesc*)(dev + o_seg), (const RowChunk*)(dev + o_de), (int)delta.items.size(), b->d_out,
                                                    Hs, bi.max_rpad, (float*)(wsb + wl.de_off), s)) != SYMB_OK) return st;
@@ -1481,9 +1502,6 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     }
     if (lora) dH = (bf16*)(wsb + wl.dh_off);
     if (lora && !take_dh) {
-        PackParams pp{(const SegDesc*)(dev + o_seg), (bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk), b->d_out};
-        hipLaunchKernelGGL(symb_pack_bt_kernel, dim3((b->d_out + 255) / 256, bi.S), dim3(256), 0, s, pp);
-        SYMB_HIP(h, hipGetLastError());
         SkinnyParams sp{};
         sp.L = (const bf16*)dY;
         sp.out = dH;
@@ -1491,14 +1509,11 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
         sp.out_pitch = 2 * bi.max_rpad;
         sp.chunks = (const RowChunk*)(dev + o_ch);
         sp.seg = (const SegDesc*)(dev + o_seg);
-        sp.packed = (const bf16*)(wsb + wl.pk_off);
-        sp.packed_off = (const int64_t*)(dev + o_pk);
-        sp.use_packed = 1;
         if (seg_io) {
             sp.L_seg = (const bf16* const*)(dev + o_gs);
             sp.off = (const int32_t*)(dev + o_off);
         }
-        if ((st = launch_skinny(h, sp, (int)chunks.size(), bi.max_rpad, s)) != SYMB_OK) return st;
+        if ((st = launch_skinny_dh(h, b, sp, (bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk), (int)chunks.size(), bi.max_rpad, s)) != SYMB_OK) return st;
     }
     bool a_from_seg = seg_io;
     if (ia3) {
@@ -1735,13 +1750,7 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
             sp.L_seg = (const bf16* const*)(dev + o_xs);
             sp.off = doff;
         }
-        return launch_skinny(h, sp, (int)ch_h.size(), grad_max_rpad, s);
-    };
-    auto run_pack = [&]() -> symb_status {
-        PackParams pp{dseg, (bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk), b->d_out};
-        hipLaunchKernelGGL(symb_pack_bt_kernel, dim3((b->d_out + 255) / 256, bi.S), dim3(256), 0, s, pp);
-        SYMB_HIP(h, hipGetLastError());
-        return SYMB_OK;
+        return launch_skinny<false>(h, sp, (int)ch_h.size(), grad_max_rpad, s);
     };
     // One pass over dY for dB and dH: when both gradients are wanted of the same segments, dH has to be
     // computed here anyway, and the ranks fit one rank block.  The pass leaves dH in the workspace where an
@@ -1750,9 +1759,7 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
     bool have_dh = reuse_dh;
     if (one_pass) {
         if (!reuse_hs && (st = run_skinny_h()) != SYMB_OK) return st;
-        if ((st = run_pack()) != SYMB_OK) return st;
-        DhDbParams dp{(const bf16*)dY, (const bf16*)(wsb + wl.h_off), (const bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk),
-                      b->d_out, 2 * bi.max_rpad, doff, dseg, (const GradItem*)(dev + o_itb), acc ? 1 : 0,
+        DhDbParams dp{(const bf16*)dY, (const bf16*)(wsb + wl.h_off), b->d_out, 2 * bi.max_rpad, doff, dseg, (const GradItem*)(dev + o_itb), acc ? 1 : 0,
                       seg_io ? (const bf16* const*)(dev + o_gs) : nullptr, (float*)(wsb + wl.gr_off), (float*)(wsb + wl.dp_off), bi.T};
         const int groups = dhdb_groups(b->d_out);
         if (dhdb_blocks_per_group(b->d_out) == 2) hipLaunchKernelGGL(symb_lora_dhdb_kernel<2>, dim3(groups, (unsigned)it_b.size()), dim3(256), 0, s, dp);
@@ -1776,7 +1783,6 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
     }
     if (!want_a.empty()) {       // dA_i = dH_i^T X_i
         if (!have_dh) {
-            if ((st = run_pack()) != SYMB_OK) return st;
             SkinnyParams sp{};
             sp.L = (const bf16*)dY;
             sp.out = (bf16*)(wsb + wl.dh_off);
@@ -1784,14 +1790,11 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
             sp.out_pitch = 2 * bi.max_rpad;
             sp.chunks = (const RowChunk*)(dev + o_chd);
             sp.seg = dseg;
-            sp.packed = (const bf16*)(wsb + wl.pk_off);
-            sp.packed_off = (const int64_t*)(dev + o_pk);
-            sp.use_packed = 1;
             if (seg_io) {
                 sp.L_seg = (const bf16* const*)(dev + o_gs);
                 sp.off = doff;
             }
-            if ((st = launch_skinny(h, sp, (int)ch_dh.size(), grad_max_rpad, s)) != SYMB_OK) return st;
+            if ((st = launch_skinny_dh(h, b, sp, (bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk), (int)ch_dh.size(), grad_max_rpad, s)) != SYMB_OK) return st;
         }
         GradParams gp{(const bf16*)X, (const bf16*)(wsb + wl.dh_off), b->d_in, 2 * bi.max_rpad, doff, dseg,
                       (const GradItem*)(dev + o_ita), acc ? 1 : 0, seg_io ? (const bf16* const*)(dev + o_xs) : nullptr,

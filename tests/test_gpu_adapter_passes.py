@@ -1,0 +1,40 @@
+"""The shrink of the backward (dH = s dY B) reads B_i [d_out][r] as it lies: every way it can lie (rows of 8 to 256 bytes, with and
+without the swizzle of ranks 64 and 128), slices and remainders of the inner dimension, launches of few and many chunks, and
+the packed copy that ranks that are no multiple of 4 still take."""
+import pytest
+
+import gpu_harness as gh
+import oracle
+import test_gpu_parity as tp
+from helpers import assert_close, check_dx
+from paper_2507_03220_amd import binding as sb
+from test_gpu_parity import L, make_problem, oracle_ads
+
+pytestmark = pytest.mark.gpu
+tp.gh, tp.sb = gh, sb                    # what its problem maker uses
+
+
+def _check(p, tag):
+    off, oads = p["off"], oracle_ads(p["ads"])
+    check_dx(gh.bf16_to_f64(gh.backward_input(off, p["ads"], p["dY"], p["W"])), off, oads, p["dY"], p["W"], f"dX {tag}")
+    dev = gh.adapter_grad(off, p["ads"], p["X"], p["dY"])
+    for i, d in enumerate(dev.descs):
+        dAr, dBr = oracle.lora_grad(off, oads, p["X"], p["dY"], i)
+        assert_close(d.dA.cpu().numpy(), dAr, f"dA[{i}] {tag}")
+        assert_close(d.dB.cpu().numpy(), dBr, f"dB[{i}] {tag}")
+
+
+@pytest.mark.parametrize("ranks", [[4], [8, 16, 12], [32, 20], [64, 48, 4], [128, 64, 100, 32, 16, 8], [16, 5]])
+@pytest.mark.parametrize("d_out", [40, 136, 1096])
+def test_shrink_of_the_backward_for_every_rank(ranks, d_out):
+    _check(make_problem(sum(ranks) + d_out, 72, d_out, [33, 64, 1, 100, 31, 70], [L], ranks), f"ranks {ranks} d_out {d_out}")
+
+
+@pytest.mark.parametrize("rank", [8, 16, 32, 64, 128])
+def test_shrink_of_the_backward_over_many_chunks(rank):
+    _check(make_problem(rank, 72, 328, [8300], [L], [rank]), f"rank {rank}")          # more than 256 row chunks: the two-buffer build
+
+
+@pytest.mark.parametrize("rank", [5, 12, 16])
+def test_db_and_dh_in_one_pass_over_a_wide_layer(rank):
+    _check(make_problem(rank, 72, 16392, [40, 33], [L], [rank]), f"rank {rank}")
