@@ -426,18 +426,21 @@ struct GradParams {
 template <int RB> constexpr int GRAD_CT = RB <= 2 ? 256 : 128;   // columns per workgroup (512-byte row pieces where the registers allow)
 constexpr int GRAD_TT = 32;        // tokens per step
 
+template <int RB>
+struct GradWalk {
+    static constexpr int CT = GRAD_CT<RB>;
+    static constexpr int RPITCH = CT * 2 + 16;             // LDS row pitch of the R tile in bytes
+    static constexpr int LP = 2 * RB * 16 * 2 + 16;        // LDS row pitch of the L tile (value | residual) in bytes
+    static constexpr int BYTES = GRAD_TT * (RPITCH + LP);
+};
 template <int RB, bool CMAJOR>
-__global__ void __launch_bounds__(256)
-symb_lora_grad_kernel(const GradParams p) {
-    constexpr int CT = GRAD_CT<RB>, NI = CT / 64;           // columns per workgroup, 16-column blocks per wavefront
-    constexpr int RPITCH = CT * 2 + 16;                    // LDS row pitch of the R tile in bytes
+__device__ __forceinline__ void lora_grad_walk(const GradParams& p, const GradItem& it, const SegDesc& sd, unsigned char* smem) {
+    constexpr int CT = GradWalk<RB>::CT, NI = CT / 64;      // columns per workgroup, 16-column blocks per wavefront
+    constexpr int RPITCH = GradWalk<RB>::RPITCH, LP = GradWalk<RB>::LP;
     constexpr int LPRW = CT / 8, NRC = GRAD_TT * LPRW / 256;   // 16-byte chunks per R row, R chunks per thread
-    constexpr int LP = 2 * RB * 16 * 2 + 16;           // LDS row pitch of the L tile (value | residual) in bytes
-    __shared__ __attribute__((aligned(16))) unsigned char sR[GRAD_TT * RPITCH];
-    __shared__ __attribute__((aligned(16))) unsigned char sL[GRAD_TT * LP];
-    const GradItem it = p.items[blockIdx.y];
+    unsigned char* const sR = smem;
+    unsigned char* const sL = smem + GRAD_TT * RPITCH;
     const int s = it.seg;
-    const SegDesc sd = p.seg[s];
     const int t_lo = it.t_lo, t_hi = it.t_hi;
     const bf16* const rbase = p.R_seg ? p.R_seg[s] - (size_t)p.off[s] * p.ncols : p.R;
     const int c0 = blockIdx.x * CT;
@@ -563,6 +566,215 @@ symb_lora_grad_kernel(const GradParams p) {
                 }
             }
         }
+}
+
+template <int RB, bool CMAJOR>
+__global__ void __launch_bounds__(256)
+symb_lora_grad_kernel(const GradParams p) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[GradWalk<RB>::BYTES];
+    const GradItem it = p.items[blockIdx.y];
+    lora_grad_walk<RB, CMAJOR>(p, it, p.seg[it.seg], smem);
+}
+
+// -------------------------------------------------------------------------------------------
+// The same gradients for ranks up to 64, with the tokens of a work item dealt out over the wavefronts: each takes every fourth
+// slice of 32 tokens, brings its rows of R and L in by LDS DMA into two buffers of its own (no workgroup barrier in the loop) and
+// accumulates all 128 columns; the wavefronts' sums meet in LDS in a fixed order at the end.  Bound by HBM (R once); a launch of
+// few workgroups lasts as long as its longest walk, which is a quarter as many steps as in symb_lora_grad_kernel.  Measured, before /
+// now: dB of 16 segments of 1024 tokens, 256 columns, rank 8, 25.3 / 12.2 us; dA of 20 segments, 4608 columns, 45 / 41.
+// 13 runs of 5120 tokens of ranks 8 to 64, 4096 columns, dB 43.5 / 34.3, dA 35.5 / 26.9 (in launches of their own, ranks to 16 and the
+// rest: 49 and 41).
+// Above rank 64 the L rows, re-read by every column block, outweigh R and their LDS halves the tile (20 clients of 1024 tokens at rank 128
+// on 6144 -> 256: the gradient call 387 us against 300): those segments keep symb_lora_grad_kernel's walk.  So does dB of layers of
+// GRAD_WIDE columns and more, where one pass over dY forms dB and dH in that kernel's order, and the two ways to a gradient give the
+// same bits.  The choice rests on the segment's own rank and the width: a client's gradient bits do not depend on the rest of the batch
+// (RB, the widest rank of the launch, only sizes the LDS).
+// R slice: 32 token rows of 128 columns, L slice: 32 rows of 2 rpad, 32-byte pieces of row t stored at piece ^ skinny_bt_swz (rows of
+// 64 elements and more).  Tokens past the item's last one repeat it and are masked in the fragments of the last slice.
+// -------------------------------------------------------------------------------------------
+constexpr int GRAD_WIDE = 63 * 256 + 1;       // more than 63 blocks of 256 columns
+constexpr int GRAD_WAVE_CT = 128, GRAD_WAVE_RANK = 64;
+template <int RB>
+struct GradWave {
+    static constexpr int CT = GRAD_WAVE_CT, RREQ = CT / 16, LREQ = 2 * RB, REQ = RREQ + LREQ, NBUF = 2;
+    static constexpr int SLICE = REQ * 1024, WAVE = NBUF * SLICE, BYTES = 4 * WAVE, NI = CT / 16;
+    static_assert(4 * NI * RB * 1024 <= BYTES, "the wavefronts' sums fit the slice buffers");
+};
+template <int RB, bool CMAJOR>
+__device__ __forceinline__ void lora_grad_wave(const GradParams& p, const GradItem& it, const SegDesc& sd, unsigned char* smem) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    using GW = GradWave<RB>;
+    constexpr int CT = GW::CT, NI = GW::NI;
+    const int s = it.seg;
+    const int t_lo = it.t_lo, t_hi = it.t_hi;
+    const bf16* const rbase = p.R_seg ? p.R_seg[s] - (size_t)p.off[s] * p.ncols : p.R;
+    const int c0 = blockIdx.x * CT, nb = sd.rpad >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l15 = lane & 15, kq = lane >> 4;
+    unsigned char* const wbuf = smem + wave * GW::WAVE;
+    // this lane's 16 bytes of every DMA request of a slice: token of the slice and column
+    constexpr int RPR = 512 / CT;                        // R rows per request
+    int rcol[GW::RREQ], ltok[GW::LREQ], lcol[GW::LREQ];
+#pragma unroll
+    for (int i = 0; i < GW::RREQ; ++i) {
+        const int t = i * RPR + lane / (CT / 8), slot = lane % (CT / 8);
+        rcol[i] = min(c0 + ((slot ^ (skinny_bt_swz(CT, t) << 1)) * 8), p.ncols - 8);
+    }
+    const int lw = sd.rpad >> 2;                         // 16-byte chunks per L row
+#pragma unroll
+    for (int i = 0; i < GW::LREQ; ++i) {
+        const int x = min(i * 64 + lane, 32 * lw - 1);
+        ltok[i] = x / lw;
+        lcol[i] = ((x - ltok[i] * lw) ^ (skinny_bt_swz(2 * sd.rpad, ltok[i]) << 1)) * 8;
+    }
+    unsigned roff[NI], loff[RB][2];
+    const int k0 = kq * 8 + (l15 >> 2);                  // first of the two transposing reads; the second is 4 tokens further
+#pragma unroll
+    for (int i = 0; i < NI; ++i) roff[i] = (unsigned)(size_t)wbuf + (unsigned)(k0 * CT * 2 + ((i ^ skinny_bt_swz(CT, k0)) * 32) + (l15 & 3) * 8);
+#pragma unroll
+    for (int j = 0; j < RB; ++j)
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+            loff[j][half] = (unsigned)(size_t)wbuf + (unsigned)(GW::RREQ * 1024 + k0 * 4 * sd.rpad + (((half * nb + min(j, nb - 1)) ^ skinny_bt_swz(2 * sd.rpad, k0)) * 32) + (l15 & 3) * 8);
+    floatx4 acc[NI][RB];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < RB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto dma = [&](int buf, int t0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < GW::RREQ; ++i)
+            __builtin_amdgcn_global_load_lds((glb_void_t*)(rbase + (size_t)min(t0 + i * RPR + lane / (CT / 8), t_hi - 1) * p.ncols + rcol[i]),
+                                             (lds_void_t*)(wbuf + buf * GW::SLICE + i * 1024), 16, 0, 0);
+#pragma unroll
+        for (int i = 0; i < GW::LREQ; ++i)
+            __builtin_amdgcn_global_load_lds((glb_void_t*)(p.L + (size_t)min(t0 + ltok[i], t_hi - 1) * p.l_pitch + lcol[i]),
+                                             (lds_void_t*)(wbuf + buf * GW::SLICE + (GW::RREQ + i) * 1024), 16, 0, 0);
+    };
+    // fragment reads with a wait of their own (see the skinny kernel); returns with the buffer free again
+    auto mul = [&](int buf, int t0) __attribute__((always_inline)) {
+        u32x2 rt[NI][2], lt[RB][2][2];
+        const unsigned at = (unsigned)(buf * GW::SLICE), lrow = 16 * sd.rpad;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(rt[i][0]) : "v"(roff[i] + at));
+            asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(rt[i][1]) : "v"(roff[i] + at), "n"(CT * 8));
+        }
+#pragma unroll
+        for (int j = 0; j < RB; ++j)
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(lt[j][half][0]) : "v"(loff[j][half] + at));
+                asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(lt[j][half][1]) : "v"(loff[j][half] + at + lrow));
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+#pragma unroll
+        for (int i = 0; i < NI; ++i) { asm volatile("" : "+v"(rt[i][0])); asm volatile("" : "+v"(rt[i][1])); }
+#pragma unroll
+        for (int j = 0; j < RB; ++j)
+#pragma unroll
+            for (int half = 0; half < 2; ++half) { asm volatile("" : "+v"(lt[j][half][0])); asm volatile("" : "+v"(lt[j][half][1])); }
+        u32x4 rf[NI], lf[RB][2];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) rf[i] = __builtin_shufflevector(rt[i][0], rt[i][1], 0, 1, 2, 3);
+#pragma unroll
+        for (int j = 0; j < RB; ++j)
+#pragma unroll
+            for (int half = 0; half < 2; ++half) lf[j][half] = __builtin_shufflevector(lt[j][half][0], lt[j][half][1], 0, 1, 2, 3);
+        if (t0 + 32 > t_hi) {                            // a lane holds tokens t0 + 8 kq + 0..7: those past the end count as zero, in both operands
+            const int left = t_hi - (t0 + kq * 8);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const unsigned keep = 2 * q + 1 < left ? 0xffffffffu : 2 * q < left ? 0xffffu : 0u;
+#pragma unroll
+                for (int i = 0; i < NI; ++i) rf[i][q] &= keep;
+#pragma unroll
+                for (int j = 0; j < RB; ++j) { lf[j][0][q] &= keep; lf[j][1][q] &= keep; }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < RB; ++j)
+            if (j < nb) {
+#pragma unroll
+                for (int half = 0; half < 2; ++half)     // bf16 value, then its rounding residual
+#pragma unroll
+                    for (int i = 0; i < NI; ++i) {
+                        const bf16x8 l = __builtin_bit_cast(bf16x8, lf[j][half]), r = __builtin_bit_cast(bf16x8, rf[i]);
+                        acc[i][j] = CMAJOR ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(l, r, acc[i][j], 0, 0, 0)
+                                           : __builtin_amdgcn_mfma_f32_16x16x32_bf16(r, l, acc[i][j], 0, 0, 0);
+                    }
+            }
+    };
+    const int nsl = (t_hi - t_lo + 31) >> 5, ns = nsl > wave ? (nsl - wave + 3) >> 2 : 0;
+    int t = t_lo + wave * 32;
+    if (ns > 0) dma(0, t);
+    if (ns > 1) dma(1, t + 128);
+    for (int q = 0; q < ns; ++q, t += 128) {
+        if (q + 1 < ns) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(GW::REQ) : "memory");       // the next slice may still be in flight
+        else asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+        mul(q & 1, t);
+        if (q + 2 < ns) dma(q & 1, t + 256);
+    }
+    floatx4* const red = reinterpret_cast<floatx4*>(smem);
+    __syncthreads();                                     // every wavefront is done with its slice buffers
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < RB; ++j) red[((wave * NI + i) * RB + j) * 64 + lane] = acc[i][j];
+    __syncthreads();
+    float* const out = it.direct ? (CMAJOR ? sd.dB : sd.dA) : p.partial + it.partial_off;
+    const bool accumulate = it.direct && p.accumulate;
+#pragma unroll
+    for (int b = 0; b < NI * RB; ++b) {
+        const int i = b / RB, j = b % RB;
+        if ((b & 3) != wave || j >= nb) continue;
+        floatx4 v = red[b * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) v += red[(w * NI * RB + b) * 64 + lane];
+        if constexpr (CMAJOR) {
+            // lane: column c = .. + l15; registers: pp = 16 j + 4 kq + q
+            const int c = c0 + i * 16 + l15, pp0 = j * 16 + kq * 4;
+            if (c < p.ncols) {
+                float* const dst = out + (size_t)c * sd.rank + pp0;
+                float old[4] = {0.f, 0.f, 0.f, 0.f};     // all four read before the first store
+                if (accumulate) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (pp0 + q < sd.rank) old[q] = dst[q];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (pp0 + q < sd.rank) dst[q] = old[q] + v[q];
+            }
+        } else {
+            // lane: pp = 16 j + l15; registers: column c = .. + 4 kq + q
+            const int pp = j * 16 + l15, c = c0 + i * 16 + kq * 4;
+            if (pp < sd.rank && c < p.ncols) {
+                floatx4* const dst = reinterpret_cast<floatx4*>(out + (size_t)pp * p.ncols + c);
+                *dst = accumulate ? v + *dst : v;
+            }
+        }
+    }
+}
+
+// RB: rank blocks of the widest segment of the launch.  The segments' own ones decide what each workgroup runs (above rank 64 the other
+// kernel's walk): one launch lets the short walks of low ranks fill the CUs beside the long ones.
+template <int RB, bool CMAJOR>
+__global__ void __launch_bounds__(256)
+symb_lora_grad_wave_kernel(const GradParams p) {
+    constexpr int WB = RB < 4 ? RB : 4;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[GradWave<WB>::BYTES];
+    static_assert(GRAD_CT<8> == GRAD_WAVE_CT && GradWalk<8>::BYTES <= GradWave<4>::BYTES, "both walks share a grid and the LDS");
+    const GradItem it = p.items[blockIdx.y];
+    const SegDesc sd = p.seg[it.seg];
+    if (sd.rpad <= 16) lora_grad_wave<1, CMAJOR>(p, it, sd, smem);
+    else if constexpr (RB >= 2) {
+        if (sd.rpad <= 32) lora_grad_wave<2, CMAJOR>(p, it, sd, smem);
+        else if constexpr (RB >= 4) {
+            if (sd.rpad <= GRAD_WAVE_RANK) lora_grad_wave<4, CMAJOR>(p, it, sd, smem);
+            else if constexpr (RB >= 8) lora_grad_walk<8, CMAJOR>(p, it, sd, smem);
+        }
+    }
 }
 
 // -------------------------------------------------------------------------------------------

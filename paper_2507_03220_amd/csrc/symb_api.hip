@@ -303,7 +303,7 @@ SplitPlan gemm_split_plan(int M, int N, int K) {
 // One-pass dH + dB kernel: column blocks of 256 columns per workgroup (0: the layer is too narrow for it:
 // with few column blocks the launch has too few workgroups, each walking its tokens alone, and the two
 // separate passes are faster), and the number of workgroups along d_out.
-int dhdb_blocks_per_group(int d_out) { return (d_out + 255) / 256 >= 64 ? 2 : 0; }
+int dhdb_blocks_per_group(int d_out) { return d_out >= GRAD_WIDE ? 2 : 0; }
 int dhdb_groups(int d_out) {
     const int g = dhdb_blocks_per_group(d_out);
     return g ? ((d_out + 255) / 256 + g - 1) / g : 0;
@@ -690,13 +690,29 @@ template <int RB, bool CM>
 void launch_grad_rb(const GradParams& gp, int nitems, hipStream_t st) {
     hipLaunchKernelGGL((symb_lora_grad_kernel<RB, CM>), dim3((gp.ncols + GRAD_CT<RB> - 1) / GRAD_CT<RB>, nitems), dim3(256), 0, st, gp);
 }
+template <int RB, bool CM>
+void launch_grad_wave(const GradParams& gp, int nitems, hipStream_t st) {
+    hipLaunchKernelGGL((symb_lora_grad_wave_kernel<RB, CM>), dim3((gp.ncols + GRAD_WAVE_CT - 1) / GRAD_WAVE_CT, nitems), dim3(256), 0, st, gp);
+}
+// wave_rpad: the items take the kernel that deals tokens out over the wavefronts, this is their widest rank (plan_items; 0: the other one).
 template <bool CM>
-symb_status launch_grad(symb_handle h, const GradParams& gp, int nseg, int max_rpad, hipStream_t st) {
-    if (nseg == 0) return SYMB_OK;
-    if (max_rpad <= 16) launch_grad_rb<1, CM>(gp, nseg, st);
-    else if (max_rpad <= 32) launch_grad_rb<2, CM>(gp, nseg, st);
-    else if (max_rpad <= 64) launch_grad_rb<4, CM>(gp, nseg, st);
-    else launch_grad_rb<8, CM>(gp, nseg, st);
+symb_status launch_grad(symb_handle h, const GradParams& gp, int wave_rpad, int nitems, int max_rpad, hipStream_t st) {
+    if (nitems == 0) return SYMB_OK;
+    if (wave_rpad > 0) {
+        if (wave_rpad <= 16) launch_grad_wave<1, CM>(gp, nitems, st);
+        else if (wave_rpad <= 32) launch_grad_wave<2, CM>(gp, nitems, st);
+        else if (wave_rpad <= 64) launch_grad_wave<4, CM>(gp, nitems, st);
+        else launch_grad_wave<8, CM>(gp, nitems, st);
+    } else {
+        if constexpr (CM) {                  // (wide dB; everything else comes here above rank 64 only)
+            if (max_rpad <= 16) launch_grad_rb<1, CM>(gp, nitems, st);
+            else if (max_rpad <= 32) launch_grad_rb<2, CM>(gp, nitems, st);
+            else if (max_rpad <= 64) launch_grad_rb<4, CM>(gp, nitems, st);
+            else launch_grad_rb<8, CM>(gp, nitems, st);
+        } else {
+            launch_grad_rb<8, CM>(gp, nitems, st);
+        }
+    }
     SYMB_HIP(h, hipGetLastError());
     return SYMB_OK;
 }
@@ -1697,7 +1713,12 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
             }
     }
     // Work items of the two gradient launches: whole segments, or the runs of long ones (see grad_runs).
-    auto plan_items = [&](const std::vector<int32_t>& want, int ncols, std::vector<GradItem>& items, std::vector<GradReduceItem>& red) {
+    // Widest ranks (the longest walks) first.  Returns the widest rank (padded) if the items take the kernel that deals tokens out over the
+    // wavefronts; 0, for the other one, in a wide layer's dB and where every rank is above that kernel's limit.
+    auto plan_items = [&](std::vector<int32_t> want, int ncols, bool of_b, std::vector<GradItem>& items, std::vector<GradReduceItem>& red) {
+        const auto rpad = [&](int i) { return rpad_of(b->adapters[i].rank); };
+        std::stable_sort(want.begin(), want.end(), [&](int x, int y) { return rpad(x) > rpad(y); });
+        const int wave_rpad = want.empty() || (of_b && ncols >= GRAD_WIDE) || rpad(want.back()) > GRAD_WAVE_RANK ? 0 : rpad(want[0]);
         int64_t cur = 0;
         for (int i : want) {
             const int lo = b->seg_offsets[i], hi = b->seg_offsets[i + 1], runs = grad_runs(hi - lo);
@@ -1710,11 +1731,11 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
             for (int q = 0; q < runs; ++q, cur += n)
                 items.push_back(GradItem{i, lo + q * GRAD_SPLIT, std::min(hi, lo + (q + 1) * GRAD_SPLIT), 0, cur});
         }
+        return wave_rpad;
     };
     std::vector<GradItem> it_a, it_b;
     std::vector<GradReduceItem> red_a, red_b;
-    plan_items(want_b, b->d_out, it_b, red_b);
-    plan_items(want_a, b->d_in, it_a, red_a);
+    const int wave_rpad_b = plan_items(want_b, b->d_out, true, it_b, red_b), wave_rpad_a = plan_items(want_a, b->d_in, false, it_a, red_a);
     Blob blob;
     const size_t o_seg = blob.add(sd.data(), sd.size());
     const size_t o_off = blob.add(b->seg_offsets, (size_t)bi.S + 1);
@@ -1777,7 +1798,7 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
         GradParams gp{(const bf16*)dY, (const bf16*)(wsb + wl.h_off), b->d_out, 2 * bi.max_rpad, doff, dseg,
                       (const GradItem*)(dev + o_itb), acc ? 1 : 0, seg_io ? (const bf16* const*)(dev + o_gs) : nullptr,
                       (float*)(wsb + wl.gr_off)};
-        if ((st = launch_grad<true>(h, gp, (int)it_b.size(), grad_max_rpad, s)) != SYMB_OK) return st;
+        if ((st = launch_grad<true>(h, gp, wave_rpad_b, (int)it_b.size(), grad_max_rpad, s)) != SYMB_OK) return st;
         if ((st = launch_grad_reduce(h, GradReduceParams{dseg, (const GradReduceItem*)(dev + o_rdb), (const float*)(wsb + wl.gr_off), b->d_out, 1, acc ? 1 : 0},
                                      (int)red_b.size(), s)) != SYMB_OK) return st;
     }
@@ -1799,7 +1820,7 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
         GradParams gp{(const bf16*)X, (const bf16*)(wsb + wl.dh_off), b->d_in, 2 * bi.max_rpad, doff, dseg,
                       (const GradItem*)(dev + o_ita), acc ? 1 : 0, seg_io ? (const bf16* const*)(dev + o_xs) : nullptr,
                       (float*)(wsb + wl.gr_off)};
-        if ((st = launch_grad<false>(h, gp, (int)it_a.size(), grad_max_rpad, s)) != SYMB_OK) return st;
+        if ((st = launch_grad<false>(h, gp, wave_rpad_a, (int)it_a.size(), grad_max_rpad, s)) != SYMB_OK) return st;
         if ((st = launch_grad_reduce(h, GradReduceParams{dseg, (const GradReduceItem*)(dev + o_rda), (const float*)(wsb + wl.gr_off), b->d_in, 0, acc ? 1 : 0},
                                      (int)red_a.size(), s)) != SYMB_OK) return st;
     }

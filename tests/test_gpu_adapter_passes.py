@@ -38,3 +38,20 @@ def test_shrink_of_the_backward_over_many_chunks(rank):
 @pytest.mark.parametrize("rank", [5, 12, 16])
 def test_db_and_dh_in_one_pass_over_a_wide_layer(rank):
     _check(make_problem(rank, 72, 16392, [40, 33], [L], [rank]), f"rank {rank}")
+
+
+@pytest.mark.parametrize("lens,ranks", [([31, 32, 33, 127, 128, 129], [16, 5, 8]), ([1, 160, 257, 1537], [32, 17]), ([300, 95], [64, 40]), ([520, 64], [128, 72, 4])])
+@pytest.mark.parametrize("dims", [(8, 136), (120, 64), (264, 392)])
+def test_gradients_over_slices_of_tokens(lens, ranks, dims):
+    """Edges of the 32-token slices dealt over four wavefronts, of the column blocks and of a segment walked in runs; accumulation."""
+    p = make_problem(sum(lens) + dims[0], dims[0], dims[1], lens, [L], ranks)
+    off, oads = p["off"], oracle_ads(p["ads"])
+    dev = gh.adapter_grad(off, p["ads"], p["X"], p["dY"])
+    once = [(d.dA.clone(), d.dB.clone()) for d in dev.descs]
+    gh.adapter_grad(off, p["ads"], p["X"], p["dY"], accumulate_into=dev)
+    for i, (d, (dA, dB)) in enumerate(zip(dev.descs, once)):
+        dAr, dBr = oracle.lora_grad(off, oads, p["X"], p["dY"], i)
+        assert_close(dA.cpu().numpy(), dAr, f"dA[{i}]")
+        assert_close(dB.cpu().numpy(), dBr, f"dB[{i}]")
+        assert_close(d.dA.cpu().numpy(), 2 * dAr, f"accumulated dA[{i}]")
+        assert_close(d.dB.cpu().numpy(), 2 * dBr, f"accumulated dB[{i}]")
