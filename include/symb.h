@@ -163,7 +163,8 @@ symb_status symb_plan_row_tiles(const symb_batch* b, int32_t tile_m, int32_t* se
  * would leave most of the chip idle), or the tiles of a last round of workgroups that
  * would be partly empty (up to 160 MiB).  Before it, for a batch of at most 64 rows, come the
  * fp32 partial sums of the weight-streaming kernels such calls take (base product and LoRA shrink, at
- * most 16 ranges of the inner dimension each).  These
+ * most 16 ranges of the inner dimension each), and, for larger ones with many LoRA segments of at most
+ * 16 rows in one row tile, those rows' LoRA terms in fp32 (rows x output width x 4 bytes).  These
  * trailing regions are optional: a workspace that covers everything before them (in
  * particular none at all for a batch without adapters) makes the call take the tiled kernel
  * without the split, only slower; anything smaller fails with SYMB_ERR_WORKSPACE_TOO_SMALL.

@@ -92,7 +92,7 @@ def test_tile_and_split_rules_of_mid_sized_batches(T, d_in, d_out):
         check_y(gh.bf16_to_f64(Y)[rows], p["off"], oads, p["X"], p["W"], p["bias"], "Y", rows=rows)
 
 
-@pytest.mark.parametrize("d_in,d_out", [(264, 392), (200, 6216)])                  # 128x128 and 256x256 tiles
+@pytest.mark.parametrize("d_in,d_out", [(264, 392), (2056, 264), (200, 6216)])     # 128x128 tiles, split over K, 256x256 tiles
 def test_short_segments_of_a_larger_batch(d_in, d_out):
     """LoRA terms of short segments are added from memory where a row tile holds many of their steps: scattered over the tiles,
     across a tile's edge, beside long segments, empty ones and other kinds; with the pre-adapter output; in both directions."""
