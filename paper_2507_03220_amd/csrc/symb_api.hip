@@ -1773,6 +1773,20 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
         }
         return launch_skinny<false>(h, sp, (int)ch_h.size(), grad_max_rpad, s);
     };
+    auto skinny_dh = [&]() {                            // dH = s dY B of the segments that want dA
+        SkinnyParams sp{};
+        sp.L = (const bf16*)dY;
+        sp.out = (bf16*)(wsb + wl.dh_off);
+        sp.K = b->d_out;
+        sp.out_pitch = 2 * bi.max_rpad;
+        sp.chunks = (const RowChunk*)(dev + o_chd);
+        sp.seg = dseg;
+        if (seg_io) {
+            sp.L_seg = (const bf16* const*)(dev + o_gs);
+            sp.off = doff;
+        }
+        return sp;
+    };
     // One pass over dY for dB and dH: when both gradients are wanted of the same segments, dH has to be
     // computed here anyway, and the ranks fit one rank block.  The pass leaves dH in the workspace where an
     // input-gradient call with SYMB_BWD_REUSE_DH (same batch, same dY, same workspace) takes it.
@@ -1794,28 +1808,30 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
         SYMB_HIP(h, hipGetLastError());
         have_dh = true;
     } else if (!want_b.empty()) {       // dB_i = s_i * dY_i^T H_i  ==  dY_i^T Hs_i
+        // small calls: dH beside dB in one launch (at most one workgroup per CU)
+        const int col_blocks = (b->d_out + GRAD_WAVE_CT - 1) / GRAD_WAVE_CT;
+        const bool pair = !have_dh && !want_a.empty() && wave_rpad_b > 0 && grad_max_rpad <= GRAD_WAVE_RANK && h->opt_skinny_deep && reads_bt(b) &&
+                          (long long)ch_dh.size() + (long long)col_blocks * (long long)it_b.size() <= 256;
         if (!reuse_hs && (st = run_skinny_h()) != SYMB_OK) return st;
         GradParams gp{(const bf16*)dY, (const bf16*)(wsb + wl.h_off), b->d_out, 2 * bi.max_rpad, doff, dseg,
                       (const GradItem*)(dev + o_itb), acc ? 1 : 0, seg_io ? (const bf16* const*)(dev + o_gs) : nullptr,
                       (float*)(wsb + wl.gr_off)};
-        if ((st = launch_grad<true>(h, gp, wave_rpad_b, (int)it_b.size(), grad_max_rpad, s)) != SYMB_OK) return st;
+        if (pair) {
+            const dim3 grid((unsigned)(ch_dh.size() + (size_t)col_blocks * it_b.size()));
+            const SkinnyParams sp = skinny_dh();
+            auto launch = [&](auto kfn) { hipLaunchKernelGGL(kfn, grid, dim3(256), 0, s, sp, (int)ch_dh.size(), gp, col_blocks); };
+            if (grad_max_rpad <= 16) launch(symb_lora_grad_pair_kernel<1>);
+            else if (grad_max_rpad <= 32) launch(symb_lora_grad_pair_kernel<2>);
+            else launch(symb_lora_grad_pair_kernel<4>);
+            SYMB_HIP(h, hipGetLastError());
+            have_dh = true;
+        } else if ((st = launch_grad<true>(h, gp, wave_rpad_b, (int)it_b.size(), grad_max_rpad, s)) != SYMB_OK) return st;
         if ((st = launch_grad_reduce(h, GradReduceParams{dseg, (const GradReduceItem*)(dev + o_rdb), (const float*)(wsb + wl.gr_off), b->d_out, 1, acc ? 1 : 0},
                                      (int)red_b.size(), s)) != SYMB_OK) return st;
     }
     if (!want_a.empty()) {       // dA_i = dH_i^T X_i
         if (!have_dh) {
-            SkinnyParams sp{};
-            sp.L = (const bf16*)dY;
-            sp.out = (bf16*)(wsb + wl.dh_off);
-            sp.K = b->d_out;
-            sp.out_pitch = 2 * bi.max_rpad;
-            sp.chunks = (const RowChunk*)(dev + o_chd);
-            sp.seg = dseg;
-            if (seg_io) {
-                sp.L_seg = (const bf16* const*)(dev + o_gs);
-                sp.off = doff;
-            }
-            if ((st = launch_skinny_dh(h, b, sp, (bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk), (int)ch_dh.size(), grad_max_rpad, s)) != SYMB_OK) return st;
+            if ((st = launch_skinny_dh(h, b, skinny_dh(), (bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk), (int)ch_dh.size(), grad_max_rpad, s)) != SYMB_OK) return st;
         }
         GradParams gp{(const bf16*)X, (const bf16*)(wsb + wl.dh_off), b->d_in, 2 * bi.max_rpad, doff, dseg,
                       (const GradItem*)(dev + o_ita), acc ? 1 : 0, seg_io ? (const bf16* const*)(dev + o_xs) : nullptr,
