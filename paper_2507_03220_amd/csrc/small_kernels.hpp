@@ -576,11 +576,13 @@ __device__ __forceinline__ void small_finish_sums(const SmallFinishParams& p, co
         float d[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            const float hq = hs[i * 4 + g];              // (rank rows past the last repeat it, against a zero)
+            const float hq = hs[i * 4 + g];
+            const unsigned keep = i * 4 + g < sd.rank ? 0xffffffffu : 0u;        // rank rows past the last repeated it: zero (an infinity times hq = 0 is none)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                d[2 * e] += hq * bf16_bits_to_f32((unsigned short)(bw[i][e] & 0xffffu));
-                d[2 * e + 1] += hq * bf16_bits_to_f32((unsigned short)(bw[i][e] >> 16));
+                const unsigned w = bw[i][e] & keep;
+                d[2 * e] += hq * bf16_bits_to_f32((unsigned short)(w & 0xffffu));
+                d[2 * e + 1] += hq * bf16_bits_to_f32((unsigned short)(w >> 16));
             }
         }
         // row groups 264 floats apart: the stores and the column reads stay off each other's banks

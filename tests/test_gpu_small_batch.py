@@ -1,6 +1,7 @@
 """Calls of at most 64 rows (the weight-streaming kernels): row counts around the blocks of 16 and the limit, inner and output
 widths around the slices and tiles, ranks that are and are not multiples of 4 and 8, an adapter matrix that is not 16-byte
 aligned, and the workspace hand-over to a gradient call."""
+import numpy as np
 import pytest
 import torch
 
@@ -53,6 +54,20 @@ def test_adapter_matrix_off_its_16_byte_alignment(rank):
     torch.cuda.synchronize()
     check_y(gh.bf16_to_f64(Y), off, oads, p["X"], p["W"], None, "Y")
     check_dx(gh.bf16_to_f64(dX), off, oads, p["dY"], p["W"], "dX")
+
+
+@pytest.mark.parametrize("rank", [8, 12, 20, 40, 100])
+@pytest.mark.parametrize("lens", [[5, 30], [1] * 150])              # the streaming kernels; short segments of a tiled call
+def test_an_infinity_in_the_last_row_of_a(rank, lens):
+    """The rank rows that pad A_i to whole blocks count as zero: an infinity in its last row stays one in dX."""
+    p = make_problem(rank, 392, 264, lens, [L], [rank])
+    p["ads"][0].A[rank - 1, 3] = 0x7f80
+    off, oads = p["off"], oracle_ads(p["ads"])
+    got = gh.bf16_to_f64(gh.backward_input(off, p["ads"], p["dY"], p["W"]))
+    ref = oracle.backward_input(off, oads, p["dY"], p["W"])
+    assert np.isinf(ref[:lens[0], 3]).all() and np.array_equal(got[:lens[0], 3], ref[:lens[0], 3])
+    got[:lens[0], 3] = ref[:lens[0], 3] = 0.0
+    assert_close(got, ref, f"dX rank {rank}", out_bf16=True)
 
 
 @pytest.mark.parametrize("lens", [[16], [9, 30, 0, 25]])
