@@ -386,7 +386,8 @@ SmallPlan small_plan(const symb_batch* b, const BatchInfo& bi, int op, bool lora
 
 // Short LoRA segments (at most kDeltaRows rows) whose term the tiled kernels add from memory (symb_lora_delta_kernel) instead of running a
 // chain of k-steps for each: all of them that meet a row tile with at least delta_steps() such steps, about the time of the extra
-// launch (6 to 16 us: a step costs up to 1.6 us in the 256x256 tile, about 0.45 in the 128x128 one).  Batches of thousands of segments keep the steps: their descriptors have to fit as before.
+// launch (6 to 16 us: a step costs up to 1.6 us in the 256x256 tile, about 0.45 in the 128x128 one).  Batches of more than kDeltaSegments segments keep the
+// steps, as does one whose descriptors have no room for the terms' (add_gemm_desc).
 constexpr int kDeltaRows = 16, kDeltaSegments = 4096;
 int delta_steps(int tile_m) { return tile_m == 256 ? 8 : 16; }
 struct DeltaPlan {
@@ -502,6 +503,25 @@ struct Blob {
         return off;
     }
 };
+
+// The last descriptors of a GEMM call: the segments as the GEMM reads them and, with a DeltaPlan, its items and the tiles' masks.  The
+// masks are 36 bytes for every row tile: a plan whose descriptors do not fit beside the others is dropped (its segments keep their
+// steps), so that a batch is refused or accepted as it would be without one.
+struct DeltaBlob {
+    size_t seg = 0, items = 0, tiles = 0;
+};
+DeltaBlob add_gemm_desc(Blob& blob, std::vector<SegDesc>& sd_gemm, DeltaPlan& delta, int num_m_tiles, int tile_m) {
+    const size_t extra = sd_gemm.size() * sizeof(SegDesc) + delta.items.size() * sizeof(RowChunk) + (size_t)num_m_tiles * sizeof(TileDelta) + 3 * 16;
+    if (blob.bytes.size() + extra > kSlotBytes) delta = DeltaPlan{};
+    for (const RowChunk& it : delta.items) sd_gemm[it.seg].kind = KIND_DELTA;
+    DeltaBlob d;
+    d.seg = blob.add(sd_gemm.data(), sd_gemm.size());
+    if (delta.items.empty()) return d;
+    const std::vector<TileDelta> tiles = delta_tiles(delta, num_m_tiles, tile_m);
+    d.items = blob.add(delta.items.data(), delta.items.size());
+    d.tiles = blob.add(tiles.data(), tiles.size());
+    return d;
+}
 
 symb_status upload(symb_handle h, const Blob& blob, hipStream_t st, unsigned char** dev_base) {
     if (blob.bytes.size() > kSlotBytes)
@@ -1185,7 +1205,6 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     std::vector<int64_t> pk_off(bi.S, 0);
     DeltaPlan delta;
     if (wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm);
-    const std::vector<TileDelta> tile_delta = delta_tiles(delta, (int)lo.size(), bm);
     if (conv1d && bi.n_lora) {
         int64_t cur = 0;
         for (int i = 0; i < bi.S; ++i)
@@ -1195,15 +1214,11 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
                 cur += (int64_t)sd[i].rpad * b->d_out;
             }
     }
-    for (const RowChunk& it : delta.items) sd_gemm[it.seg].kind = KIND_DELTA;
     Blob blob;
     const size_t o_seg = blob.add(sd.data(), sd.size());
-    const size_t o_segg = blob.add(sd_gemm.data(), sd_gemm.size());
     const size_t o_off = blob.add(b->seg_offsets, (size_t)bi.S + 1);
     const size_t o_lo = blob.add(lo.data(), lo.size());
     const size_t o_hi = blob.add(hi.data(), hi.size());
-    const size_t o_de = blob.add(delta.items.data(), delta.items.size());
-    const size_t o_td = blob.add(tile_delta.data(), tile_delta.size());
     const std::vector<int32_t> tile_epi = plan_tile_kind(b, lo, hi, SYMB_ADAPTER_IA3);
     const size_t o_te = blob.add(tile_epi.data(), tile_epi.size());
     const size_t o_ch = blob.add(chunks.data(), chunks.size());
@@ -1214,6 +1229,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     const size_t o_ys = blob.add(Y_seg, seg_io ? (size_t)bi.S : 0);
     const std::vector<int32_t> k_zero(k_split ? ksp.slots : 0, 0);
     const size_t o_kc = blob.add(k_zero.data(), k_zero.size());   // arrival counters of the K-split tiles
+    const DeltaBlob db = add_gemm_desc(blob, sd_gemm, delta, (int)lo.size(), bm);
     unsigned char* dev = nullptr;
     if ((st = upload(h, blob, s, &dev)) != SYMB_OK) return st;
 
@@ -1249,12 +1265,12 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
         }
         if ((st = launch_skinny<false>(h, sp, (int)chunks.size(), bi.max_rpad, s)) != SYMB_OK) return st;
     }
-    if (!delta.items.empty() && (st = launch_delta(h, false, (const SegDesc*)(dev + o_seg), (const RowChunk*)(dev + o_de), (int)delta.items.size(), b->d_out,
+    if (!delta.items.empty() && (st = launch_delta(h, false, (const SegDesc*)(dev + o_seg), (const RowChunk*)(dev + db.items), (int)delta.items.size(), b->d_out,
                                                    Hs, bi.max_rpad, (float*)(wsb + wl.de_off), s)) != SYMB_OK) return st;
     GemmParams gp{};
     if (!delta.items.empty()) {
         gp.delta = (const float*)(wsb + wl.de_off);
-        gp.tile_delta = (const TileDelta*)(dev + o_td);
+        gp.tile_delta = (const TileDelta*)(dev + db.tiles);
     }
     gp.Aop = x_op;
     if (seg_io) {
@@ -1273,7 +1289,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     gp.N = b->d_out;
     gp.K = b->d_in;
     gp.off = (const int32_t*)(dev + o_off);
-    gp.seg = (const SegDesc*)(dev + o_segg);
+    gp.seg = (const SegDesc*)(dev + db.seg);
     gp.tile_seg_lo = (const int32_t*)(dev + o_lo);
     gp.tile_seg_hi = (const int32_t*)(dev + o_hi);
     gp.ext = Hs;
@@ -1468,7 +1484,6 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     std::vector<SegDesc> sd_gemm = sd;
     DeltaPlan delta;
     if (lora && wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm);
-    const std::vector<TileDelta> tile_delta = delta_tiles(delta, (int)lo.size(), bm);
     std::vector<int64_t> pk_off(bi.S, 0), pa_off(bi.S, 0);
     {
         int64_t cur = 0, cura = 0;
@@ -1483,15 +1498,11 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
                 }
             }
     }
-    for (const RowChunk& it : delta.items) sd_gemm[it.seg].kind = KIND_DELTA;
     Blob blob;
     const size_t o_seg = blob.add(sd.data(), sd.size());
-    const size_t o_segg = blob.add(sd_gemm.data(), sd_gemm.size());
     const size_t o_off = blob.add(b->seg_offsets, (size_t)bi.S + 1);
     const size_t o_lo = blob.add(lo.data(), lo.size());
     const size_t o_hi = blob.add(hi.data(), hi.size());
-    const size_t o_de = blob.add(delta.items.data(), delta.items.size());
-    const size_t o_td = blob.add(tile_delta.data(), tile_delta.size());
     const std::vector<int32_t> tile_epi = plan_tile_kind(b, lo, hi, SYMB_ADAPTER_IA3_IN);
     const size_t o_te = blob.add(tile_epi.data(), tile_epi.size());
     const size_t o_ch = blob.add(chunks.data(), chunks.size());
@@ -1506,6 +1517,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     const size_t o_rows = blob.add(row_chunks.data(), row_chunks.size());
     const std::vector<int32_t> k_zero(k_split ? ksp.slots : 0, 0);
     const size_t o_kc = blob.add(k_zero.data(), k_zero.size());   // arrival counters of the K-split tiles
+    const DeltaBlob db = add_gemm_desc(blob, sd_gemm, delta, (int)lo.size(), bm);
     unsigned char* dev = nullptr;
     if ((st = upload(h, blob, s, &dev)) != SYMB_OK) return st;
 
@@ -1541,12 +1553,12 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
         if ((st = launch_row_pass(h, symb_ia3_scale_rows_kernel, sc, sc.d_out, all_chunks.size(), s)) != SYMB_OK) return st;
         a_op = copy;
     }
-    if (!delta.items.empty() && (st = launch_delta(h, true, (const SegDesc*)(dev + o_seg), (const RowChunk*)(dev + o_de), (int)delta.items.size(), b->d_in,
+    if (!delta.items.empty() && (st = launch_delta(h, true, (const SegDesc*)(dev + o_seg), (const RowChunk*)(dev + db.items), (int)delta.items.size(), b->d_in,
                                                    dH, bi.max_rpad, (float*)(wsb + wl.de_off), s)) != SYMB_OK) return st;
     GemmParams gp{};
     if (!delta.items.empty()) {
         gp.delta = (const float*)(wsb + wl.de_off);
-        gp.tile_delta = (const TileDelta*)(dev + o_td);
+        gp.tile_delta = (const TileDelta*)(dev + db.tiles);
     }
     gp.Aop = a_op;
     gp.Bop = (const bf16*)W;
@@ -1563,7 +1575,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     gp.N = b->d_in;
     gp.K = b->d_out;
     gp.off = (const int32_t*)(dev + o_off);
-    gp.seg = (const SegDesc*)(dev + o_segg);
+    gp.seg = (const SegDesc*)(dev + db.seg);
     gp.tile_seg_lo = (const int32_t*)(dev + o_lo);
     gp.tile_seg_hi = (const int32_t*)(dev + o_hi);
     gp.ext = dH;

@@ -125,3 +125,16 @@ def test_short_segments_of_a_larger_batch(d_in, d_out):
     for conv1d in (False, True):
         dX = gh.backward_input(off, q["ads"], q["dY"], q["W"], conv1d=conv1d)
         check_dx(gh.bf16_to_f64(dX), off, oracle_ads(q["ads"]), q["dY"], q["W"], f"dX conv1d={conv1d}")
+
+
+def test_short_segments_beside_more_rows_than_their_masks_have_room_for():
+    """The terms of short segments cost 36 bytes of descriptors per row tile: a batch of 3.4 million rows, whose other descriptors fit
+    the 2 MiB slot, is accepted and its short segments keep their steps inside the GEMM."""
+    lens = [3_400_000] + [1] * 20
+    p = make_problem(31, 8, 8, lens, [L], [16])
+    off, oads = p["off"], oracle_ads(p["ads"])
+    rows = np.concatenate([np.arange(0, 3_400_000, 170_001), np.arange(3_399_990, p["T"])])
+    Y, _ = gh.forward(off, p["ads"], p["X"], p["W"], p["bias"], want_base=False)
+    check_y(gh.bf16_to_f64(Y[rows]), off, oads, p["X"], p["W"], p["bias"], "Y", rows=rows)
+    dX = gh.backward_input(off, p["ads"], p["dY"], p["W"])
+    check_dx(gh.bf16_to_f64(dX[rows]), off, oads, p["dY"], p["W"], "dX", rows=rows)
