@@ -158,17 +158,18 @@ symb_status symb_plan_row_tiles(const symb_batch* b, int32_t tile_m, int32_t* se
                                 int32_t* seg_hi, int32_t* num_tiles);
 
 /* Bytes of caller-owned device workspace an operation needs for this batch (may be 0).
- * Host-only.  For some forward and input-gradient calls the figure ends with a region for
- * fp32 partial tiles: such a call computes output tiles in several workgroups, one per
- * range of the inner dimension -- every tile of a batch of a few hundred rows (which alone
- * would leave most of the chip idle), or the tiles of a last round of workgroups that
- * would be partly empty (up to 160 MiB).  Before it, for a batch of at most 64 rows, come the
- * fp32 partial sums of the weight-streaming kernels such calls take (base product and LoRA shrink, at
- * most 16 ranges of the inner dimension each), and, for larger ones with many LoRA segments of at most
- * 16 rows in one row tile, those rows' LoRA terms in fp32 (rows x output width x 4 bytes).  These
- * trailing regions are optional: a workspace that covers everything before them (in
- * particular none at all for a batch without adapters) makes the call take the tiled kernel
- * without the split, only slower; anything smaller fails with SYMB_ERR_WORKSPACE_TOO_SMALL.
+ * Host-only.  For some forward and input-gradient calls the figure ends with optional regions: a
+ * workspace that covers everything before them (in particular none at all for a batch without adapters)
+ * makes the call take the tiled kernel, whole, only slower; anything smaller fails with
+ * SYMB_ERR_WORKSPACE_TOO_SMALL.  They are
+ *   - for a batch of at most 64 rows that takes the weight-streaming kernels, the fp32 partial sums of base
+ *     product and LoRA shrink (at most 16 ranges of the inner dimension each);
+ *   - in the same place, for the tiled kernel, fp32 partial tiles: such a call computes output tiles in
+ *     several workgroups, one per range of the inner dimension -- every tile of a batch of a few hundred
+ *     rows (which alone would leave most of the chip idle), or the tiles of a last round of workgroups that
+ *     would be partly empty (up to 160 MiB);
+ *   - after them, for a batch with many LoRA segments of at most 16 rows in one row tile, those rows'
+ *     LoRA terms in fp32 (rows x output width x 4 bytes).
  * The figure depends on the batch and the operation alone (not on the handle or its options).  Every call is deterministic (the same arguments give the
  * same bits, whatever order the workgroups finish in); a split call sums the inner dimension
  * in a different order than an unsplit one, so the two can differ in the last rounding.  For

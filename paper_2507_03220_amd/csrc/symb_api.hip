@@ -264,6 +264,7 @@ struct SplitPlan {
     int whole = 0;        // tiles per XCD that stay whole
     int slots = 0;        // split tiles of the launch (over all XCDs): arrival counters
     size_t bytes = 0;     // partial tiles: slots * parts * tile rows * tile columns * 4
+    bool doubled = false; // half the parts would do as well (see above)
 };
 SplitPlan gemm_split_plan(int M, int N, int K) {
     SplitPlan s;
@@ -274,7 +275,10 @@ SplitPlan gemm_split_plan(int M, int N, int K) {
         const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
         int P = std::min({8, KF / 12, (int)(target / tiles)});
         if (P < 2) return s;
-        if (P <= 4 && KF / P >= 64 && 2 * P * tiles <= 512) P *= 2;
+        if (P <= 4 && KF / P >= 64 && 2 * P * tiles <= 512) {
+            P *= 2;
+            s.doubled = true;
+        }
         s.parts = P;
         s.slots = (int)tiles;                  // whole = 0: a tile's slot is its number in the walk
         s.bytes = (size_t)tiles * P * 128 * 128 * 4;
@@ -298,6 +302,16 @@ SplitPlan gemm_split_plan(int M, int N, int K) {
         s.bytes = (size_t)s.slots * P * 256 * 256 * 4;
     }
     return s;
+}
+
+// The split of a launch whose workspace has `room` bytes for partial tiles: doubled parts that do not fit (397 rows of 11008 -> 4096 with an
+// adapter in the 32 MiB static scratch) are halved again, any other plan runs unsplit.
+SplitPlan split_within(SplitPlan s, size_t room) {
+    if (s.bytes > room && s.doubled) {
+        s.parts /= 2;
+        s.bytes /= 2;
+    }
+    return s.bytes <= room ? s : SplitPlan{};
 }
 
 // One-pass dH + dB kernel: column blocks of 256 columns per workgroup (0: the layer is too narrow for it:
@@ -338,11 +352,13 @@ struct WsLayout {
     size_t so_off = 0, so_bytes = 0;      // flat output [T][width] bf16 of a per-segment call whose outputs overlap its inputs
     size_t gr_off = 0, gr_bytes = 0;      // fp32 runs of the LoRA gradients of split segments (see grad_split)
     size_t dp_off = 0, dp_bytes = 0;      // fp32 partial sums of dH per group of column blocks (one-pass dH + dB, ranks up to 16)
-    // optional regions (a workspace that ends before them makes the call take the tiled kernel, unsplit):
+    // optional regions (a workspace that ends before them makes the call take the tiled kernel, unsplit); those of the small-batch
+    // kernels and those of the tiled ones share their place, a call uses one or the other:
     size_t sp_off = 0, sp_bytes = 0;      // calls of at most SMALL_MAX_ROWS rows: fp32 partial sums of the base product per K range
     size_t sh_off = 0, sh_bytes = 0;      // ... and of the LoRA shrink
-    size_t de_off = 0, de_bytes = 0;      // fp32 LoRA terms of short segments of a batch for the tiled kernels (see DeltaPlan)
-    size_t tp_off = 0, tp_bytes = 0;      // fp32 partial tiles of a K-split GEMM (see gemm_split_plan); last
+    size_t tp_off = 0, tp_bytes = 0;      // tiled: fp32 partial tiles of a K-split GEMM (see gemm_split_plan)
+    size_t de_off = 0, de_bytes = 0;      // ... fp32 LoRA terms of short segments of the batch (see DeltaPlan); after the partial tiles: a
+                                          // workspace of a fixed size loses the terms before it loses the split
     size_t mandatory = 0;                 // end of the regions a call cannot do without
     size_t total = 0;
 };
@@ -476,19 +492,16 @@ WsLayout ws_layout(const symb_batch* b, const BatchInfo& bi, int op, bool full_b
         take(w.sp_off, w.sp_bytes, sm.base_bytes);
         take(w.sh_off, w.sh_bytes, sm.h_bytes);
     }
-    if (bi.n_lora && (op == SYMB_OP_FWD || (op == SYMB_OP_BWD_INPUT && full_bwd))) {
+    const size_t small_end = cur;
+    cur = w.mandatory;
+    if (op != SYMB_OP_ADAPTER_GRAD) {
         const int N = op == SYMB_OP_FWD ? b->d_out : b->d_in, K = op == SYMB_OP_FWD ? b->d_in : b->d_out;
-        const int rows = delta_plan(b, gemm_tile_m(bi.T, N, K)).rows;
+        const SplitPlan sp = gemm_split_plan(bi.T, N, K);
+        if (sp.parts > 1) take(w.tp_off, w.tp_bytes, sp.bytes);
+        const int rows = bi.n_lora && (op == SYMB_OP_FWD || full_bwd) ? delta_plan(b, gemm_tile_m(bi.T, N, K)).rows : 0;
         if (rows) take(w.de_off, w.de_bytes, (size_t)rows * N * 4);
     }
-    if (op == SYMB_OP_FWD) {
-        const SplitPlan sp = gemm_split_plan(bi.T, b->d_out, b->d_in);
-        if (sp.parts > 1) take(w.tp_off, w.tp_bytes, sp.bytes);
-    } else if (op == SYMB_OP_BWD_INPUT) {
-        const SplitPlan sp = gemm_split_plan(bi.T, b->d_in, b->d_out);
-        if (sp.parts > 1) take(w.tp_off, w.tp_bytes, sp.bytes);
-    }
-    w.total = cur;
+    w.total = std::max(small_end, cur);
     return w;
 }
 
@@ -1177,8 +1190,8 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     if (ws_need > ws_bytes || (ws_need && !ws))
         return fail(h, SYMB_ERR_WORKSPACE_TOO_SMALL, "forward needs %zu workspace bytes, got %zu%s", ws_need, ws_bytes,
                     staged ? " (output buffers overlap input buffers: size the workspace with SYMB_OP_FWD_INPLACE)" : "");
-    const SplitPlan ksp = gemm_split_plan(bi.T, b->d_out, b->d_in);
-    const bool k_split = wl.tp_bytes && ws && ws_bytes >= wl.total && !Ybase && h->opt_k_split && h->xcd_rule;
+    const SplitPlan ksp = split_within(gemm_split_plan(bi.T, b->d_out, b->d_in), ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
+    const bool k_split = ksp.parts > 1 && !Ybase && h->opt_k_split && h->xcd_rule;
     hipStream_t s = (hipStream_t)stream;
     if (small_path(h, b, bi, SYMB_OP_FWD, true, wl, ws, ws_bytes)) {     // (partial sums between: overlapping buffers need no flat copy)
         unsigned char* const base = (unsigned char*)ws;
@@ -1434,8 +1447,8 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     if (ws_need > ws_bytes || (ws_need && !ws))
         return fail(h, SYMB_ERR_WORKSPACE_TOO_SMALL, "backward needs %zu workspace bytes, got %zu%s", ws_need, ws_bytes,
                     staged ? " (output buffers overlap input buffers: size the workspace with SYMB_OP_BWD_INPUT_INPLACE)" : "");
-    const SplitPlan ksp = gemm_split_plan(bi.T, b->d_in, b->d_out);
-    const bool k_split = wl.tp_bytes && ws && ws_bytes >= wl.total && !dXbase && h->opt_k_split && h->xcd_rule;
+    const SplitPlan ksp = split_within(gemm_split_plan(bi.T, b->d_in, b->d_out), ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
+    const bool k_split = ksp.parts > 1 && !dXbase && h->opt_k_split && h->xcd_rule;
     hipStream_t s = (hipStream_t)stream;
     const bool lora = full && bi.n_lora > 0, ia3 = full && bi.n_ia3 > 0;
     if (small_path(h, b, bi, SYMB_OP_BWD_INPUT, full, wl, ws, ws_bytes)) {     // (partial sums between: overlapping buffers need no flat copy)

@@ -138,3 +138,29 @@ def test_short_segments_beside_more_rows_than_their_masks_have_room_for():
     check_y(gh.bf16_to_f64(Y[rows]), off, oads, p["X"], p["W"], p["bias"], "Y", rows=rows)
     dX = gh.backward_input(off, p["ads"], p["dY"], p["W"])
     check_dx(gh.bf16_to_f64(dX[rows]), off, oads, p["dY"], p["W"], "dX", rows=rows)
+
+
+@pytest.mark.parametrize("T,d_in,d_out,short", [(397, 11008, 4096, 0),       # 128 tiles: four parts do not fit beside H, two do
+                                                (2560, 4096, 7168, 600)])    # a last round in three parts, which do not fit behind the short segments' terms
+def test_k_split_within_the_static_scratch(T, d_in, d_out, short):
+    """A workspace of a fixed size too small for all optional regions still splits the inner dimension: the bits show it, as a split sums in
+    another order."""
+    lens = [T - short] + [1] * short
+    p = make_problem(T, d_in, d_out, lens, [L] if not short else [N] + [L] * short, [16])
+    dev = gh.upload_adapters(p["ads"], d_in, d_out, grads=False)
+    b = sb.Batch(d_in, d_out, p["off"], dev.descs)
+    assert sb.symb_workspace_bytes(b, sb.SYMB_OP_FWD) > sb.SYMB_STATIC_SCRATCH_BYTES
+    Xd, Wd = gh.to_dev(p["X"]), gh.to_dev(p["W"])
+    got = []
+    try:
+        for split in (1, 0):
+            sb.symb_debug_set_option(gh.handle(), sb.SYMB_OPT_K_SPLIT, split)
+            Y = torch.empty(T, d_out, device="cuda", dtype=torch.bfloat16)
+            sb.symb_base_linear_fwd_static(gh.handle(), b, Xd, Wd, None, Y, None)
+            torch.cuda.synchronize()
+            got.append(Y)
+    finally:
+        sb.symb_debug_set_option(gh.handle(), sb.SYMB_OPT_K_SPLIT, 1)
+    assert not torch.equal(got[0].view(torch.int16), got[1].view(torch.int16)), "not split"
+    rows = synth.sample_rows(p["off"], 1, f"static{T}", block=128)[:48]
+    check_y(gh.bf16_to_f64(got[0][rows]), p["off"], oracle_ads(p["ads"]), p["X"], p["W"], None, "Y", rows=rows)
