@@ -248,7 +248,9 @@ int gemm_group_m(int num_m_tiles, int num_n_tiles, const std::vector<int32_t>& s
 //    4096-wide layer: 96 tiles for 256 CUs, each workgroup walking the whole K extent alone, a chain
 //    of load and LDS latencies of about 0.5 us per 64 k): all tiles split (whole = 0),
 //    parts = 320 / tiles: three parts for 96 tiles, none from 161 tiles on; at least 12 stages per part
-//    (96 rows of 4096 x 4096: 20.6 us in 5 parts, 23.4 in 8; 2000 rows of 1024 x 1024: 13.6 us whole, 17.4 in 2); twice
+//    (96 rows of 4096 x 4096: 20.6 us in 5 parts, 23.4 in 8; 2000 rows of 1024 x 1024: 13.6 us whole, 17.4 in 2); up to four parts
+//    from 8 stages on, where all of them together are at most 160 workgroups (2048 x 2048: 64 rows 13.9 us in 4 parts, 15.4 in 2,
+//    256 rows 15.5 / 17.2; in 6 parts 14.6 / 16.3); twice
 //    as many where a part would have 64 stages or more and a second workgroup per CU finds room (397 rows of
 //    11008 -> 4096: 57.8 us in 4 parts, 73 in 2).
 //  * 256x256 tiles, one workgroup per CU, 32 CUs per XCD: a run of per_xcd tiles ends in a round of
@@ -274,6 +276,7 @@ SplitPlan gemm_split_plan(int M, int N, int K) {
     if (gemm_variant(M, N, K) == 2) {
         const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
         int P = std::min({8, KF / 12, (int)(target / tiles)});
+        if (KF >= 24) P = std::max(P, std::min({4, KF / 8, (int)(160 / tiles)}));
         if (P < 2) return s;
         if (P <= 4 && KF / P >= 64 && 2 * P * tiles <= 512) {
             P *= 2;

@@ -165,6 +165,15 @@ def test_workspace_includes_partial_tiles_of_a_k_split():
     assert sb.symb_workspace_bytes(sb.Batch(4096, 4608, [0, 20480], [sb.Adapter()]), sb.SYMB_OP_FWD) == 0
 
 
+def test_parts_of_a_k_split_on_narrow_layers():
+    # 32 stages of 64: four parts of 8 where few tiles leave the chip idle, two for 64 tiles; 16 stages: whole
+    part = 128 * 128 * 4
+    for rows, parts in ((128, 4), (200, 4), (300, 3), (512, 2)):
+        tiles = -(-rows // 128) * 16
+        assert sb.symb_workspace_bytes(sb.Batch(2048, 2048, [0, rows], [sb.Adapter()]), sb.SYMB_OP_FWD) == tiles * parts * part, rows
+    assert sb.symb_workspace_bytes(sb.Batch(1024, 4096, [0, 200], [sb.Adapter()]), sb.SYMB_OP_FWD) == 0
+
+
 def test_unknown_weight_layout_is_rejected():
     b = sb.Batch(64, 64, [0, 4], [sb.Adapter()], weight_layout=7)
     assert sb.lib().symb_validate_batch(b.ref()) == sb.SYMB_ERR_INVALID_ARG
