@@ -27,6 +27,8 @@ namespace symb {
 constexpr int SMALL_MAX_ROWS = 64;
 constexpr int small_cols(bool nn) { return nn ? 128 : 64; }     // columns of a tile of the base product (weight read N-contiguous, K-contiguous)
 
+constexpr int SMALL_NARROW_COLS = 32;    // ... of symb_small_narrow_kernel
+
 // The segment of each row and the row's index inside it, carried in the launch arguments (a search on the device is a chain
 // of dependent loads).
 struct SmallRows {
@@ -86,8 +88,10 @@ struct SmallTile {
     static constexpr int SLICE = REQ * 1024, WAVE = NBUF * SLICE, BYTES = 4 * WAVE;
     static_assert(4 * CB * MB * 1024 <= BYTES, "the partial sums of the wavefronts fit the slice buffers");
 };
-// Buffers of a base tile, and of a piece of shrink work (little per slice, so more of them).
-constexpr int small_base_nbuf(int mb, bool nn) { return nn && mb == 4 ? 3 : 2; }
+// Buffers of a base tile, and of a piece of shrink work (little per slice, so more of them).  ONE: a single buffer, for long N-contiguous strips of at most
+// 16 rows with about one workgroup per CU: there fewer requests in flight stream faster (one row, us with 2 buffers / 1: 8192 -> 28672 84.5 / 79.3,
+// 28672 -> 8192 91.3 / 81.9, 4096 -> 16384 30.7 / 29.7), while short strips need both (4608 -> 2048 12.2 / 13.0).
+constexpr int small_base_nbuf(int mb, bool nn, bool one = false) { return one ? 1 : nn && mb == 4 ? 3 : 2; }
 constexpr int small_shrink_nbuf(int mb) { return mb == 1 ? 4 : 2; }
 __device__ __forceinline__ int small_nn_swz(int k) { return (((k >> 3) & 1) << 2) | (k & 3); }
 
@@ -422,14 +426,14 @@ __device__ __forceinline__ void small_direct(const SmallStreamParams& p, int t, 
 // grid = num_items * h_ranges + tiles * ranges workgroups.  MB: row blocks of 16 (T <= 16 MB).  BASE_NN / SHRINK_NN: the weight / the
 // adapter matrix is read N-contiguous (forward: the weight of a Conv1D layer, never A_i; input gradient: the weight of an
 // nn.Linear layer, always B_i).
-template <int MB, bool BASE_NN, bool SHRINK_NN>
+template <int MB, bool BASE_NN, bool SHRINK_NN, bool ONE>
 __global__ void __launch_bounds__(256)
 symb_small_stream_kernel(const SmallStreamParams p) {
-    constexpr int CB = small_cols(BASE_NN) / 16, NB = small_base_nbuf(MB, BASE_NN), SNB1 = small_shrink_nbuf(1), SNB = small_shrink_nbuf(MB);
-    constexpr int BASE_BYTES = SmallTile<CB, MB, NB, BASE_NN>::BYTES, ONE = SmallTile<1, 1, SNB1, false>::BYTES, ALL = SmallTile<1, MB, SNB, false>::BYTES;
-    // (SHRINK_NN: one slice of rank 128 per wavefront at least, 16 KiB and the activation rows, and the partial sums: both fit BASE_BYTES)
-    constexpr int SHRINK_BYTES = SHRINK_NN ? 0 : ONE > ALL ? ONE : ALL;
-    static_assert(!SHRINK_NN || (BASE_BYTES >= 4 * (16 + 2 * MB) * 1024 && BASE_BYTES >= 4 * 8 * MB * 1024), "LDS of small_bt");
+    static_assert(!ONE || (MB == 1 && BASE_NN), "one buffer: see small_base_nbuf");
+    constexpr int CB = small_cols(BASE_NN) / 16, NB = small_base_nbuf(MB, BASE_NN, ONE), SNB1 = small_shrink_nbuf(1), SNB = small_shrink_nbuf(MB);
+    constexpr int BASE_BYTES = SmallTile<CB, MB, NB, BASE_NN>::BYTES, ROWS16 = SmallTile<1, 1, SNB1, false>::BYTES, ALL = SmallTile<1, MB, SNB, false>::BYTES;
+    // SHRINK_NN: one slice of rank 128 per wavefront at least, 16 KiB and the activation rows; the partial sums fit there too
+    constexpr int SHRINK_BYTES = SHRINK_NN ? 4 * (16 + 2 * MB) * 1024 : ROWS16 > ALL ? ROWS16 : ALL;
     __shared__ __attribute__((aligned(16))) unsigned char smem[BASE_BYTES > SHRINK_BYTES ? BASE_BYTES : SHRINK_BYTES];
     const int nshrink = p.num_items * p.h_ranges;
     if ((int)blockIdx.x < nshrink) {
@@ -466,6 +470,23 @@ symb_small_stream_kernel(const SmallStreamParams p) {
     } else {
         small_store<CB, MB>(acc, smem, 0, p.T, p.partial + (size_t)range * p.T * p.N + n0, p.N, p.N - n0);
     }
+}
+
+// Calls without a LoRA term on a small layer whose weight is read K-contiguous: tiles of 32 columns over the whole inner dimension, finished
+// here.  Such a call is one chain of latencies; half the columns per workgroup are twice the workgroups, with up to four slices in flight
+// per wavefront.  One row, us with 64 columns / 32: 2048 x 2048 9.1 / 8.0, 3072 -> 768 10.3 / 8.5 (in K ranges), 4608 -> 2048 11.7 / 9.9, 1024 -> 8192 8.3 / 8.0,
+// but 4096 x 4096 12.5 / 14.9 and 16 rows of 256 -> 11008 7.6 / 8.2; 64 rows of 2048 x 2048 14.3 / 11.1.  grid = tiles; ranges, items and partial sums of p are not used.
+template <int MB>
+__global__ void __launch_bounds__(256)
+symb_small_narrow_kernel(const SmallStreamParams p) {
+    constexpr int CB = SMALL_NARROW_COLS / 16, NBUF = MB == 4 ? 3 : 4;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SmallTile<CB, MB, NBUF, false>::BYTES];
+    const int n0 = blockIdx.x * SMALL_NARROW_COLS;
+    floatx4 acc[CB][MB];
+    small_tile<CB, MB, NBUF, false>(p, p.W + (size_t)n0 * p.K, p.K, p.N - n0, 0, p.T, 0, 1, smem, acc);
+    small_sum<CB, MB>(acc, smem, [&](int t, int n, const floatx4& v) __attribute__((always_inline)) {
+        if (t < p.T && n0 + n < p.N) small_direct(p, t, n0 + n, v);
+    });
 }
 
 struct SmallFinishParams {

@@ -362,6 +362,7 @@ struct WsLayout {
     size_t tp_off = 0, tp_bytes = 0;      // tiled: fp32 partial tiles of a K-split GEMM (see gemm_split_plan)
     size_t de_off = 0, de_bytes = 0;      // ... fp32 LoRA terms of short segments of the batch (see DeltaPlan); after the partial tiles: a
                                           // workspace of a fixed size loses the terms before it loses the split
+    bool small = false;                   // the call takes the small-batch kernels if their regions are there
     size_t mandatory = 0;                 // end of the regions a call cannot do without
     size_t total = 0;
 };
@@ -371,8 +372,33 @@ struct WsLayout {
 struct SmallPlan {
     int tiles = 0, ranges = 0, items = 0, h_ranges = 0;
     bool direct = false;      // no LoRA term, one range: no partial sums, no finish kernel
+    bool narrow = false;      // direct, in symb_small_narrow_kernel
+    bool one_buffer = false;  // see small_base_nbuf
+    bool wins = false;        // faster than the tiled kernels
     size_t base_bytes = 0, h_bytes = 0;
 };
+// Whether the small-batch kernels are faster than the tiled ones for T <= SMALL_MAX_ROWS rows: measured both ways over 22 layers of 256 to 36864
+// columns, 1 to 64 rows, both weight layouts, without LoRA, with one or four clients, and a client per row.  With up to 16 rows, or more than a
+// few LoRA clients, always (4096 x 4096, rank-16 clients of one row each, us per call, the weight read K- / N-contiguous: 14 / 28, 15 / 34, 20 / 54
+// and 14 / 35, 15 / 38, 24 / 62 for 1, 16 and 64 rows).  Else the tiled kernels keep (us streamed / tiled):
+//  * short inner dimensions, where there is little to stream: without LoRA, 32 rows of 256 -> 6144 N-contiguous 9.2 / 8.6; beyond 32 rows
+//    256 -> 11008 11.4 / 8.7 and 9.8 / 8.7 (K-contiguous), 1024 -> 4096 N-contiguous 12.5 to 16 / 12.5, 2048 -> 4608 19.1 / 16.5 (4096 -> 1024 13.5 / 15.7);
+//    with one LoRA client, 64 rows of 256 -> 11008 18.8 / 13.6 N-contiguous, 18.5 / 14 K-contiguous;
+//  * wide outputs where the partial sums, written and read back, weigh more than a tenth of the weight (8 r T N bytes of 2 K N): 64 rows without LoRA of 4608 -> 36864 N-contiguous 107.5 / 98, of 4096 -> 16384 40 / 37.4, of 4096 -> 24576 K-contiguous 63.8 / 61 (but 6144 -> 24576 90 / 99, 8192 -> 28672
+//    N-contiguous 103 / 111); with one LoRA client 4608 -> 36864 123 / 106;
+//  * K-contiguous with one to four LoRA clients, N >= 24576: 64 rows of 4608 -> 36864 119 / 106, of 4096 -> 24576 74 / 69.
+bool small_wins(bool base_nn, int K, int N, int T, int n_lora, int ranges) {
+    if (T <= 16 || n_lora > 4) return true;
+    const bool sums_weigh = 40LL * ranges * T > K;
+    if (n_lora == 0) {
+        if (K <= 512 && (base_nn || T > 32)) return false;
+        if (base_nn && K <= 2048 && T > 32) return false;
+        return !(sums_weigh && K >= 4096 && N >= (base_nn ? 16384 : 24576));
+    }
+    if (T <= 32) return true;
+    if (N >= 8192 && K < 1024) return base_nn && T <= 40;
+    return N < 24576 || (base_nn && !sums_weigh);
+}
 SmallPlan small_plan(const symb_batch* b, const BatchInfo& bi, int op, bool lora, bool staged) {
     SmallPlan s;
     // the contraction runs over d_in in the forward, over d_out in the input gradient; the weight is read N-contiguous by the
@@ -390,12 +416,30 @@ SmallPlan small_plan(const symb_batch* b, const BatchInfo& bi, int op, bool lora
     // ranges, 82.2 at 8, 66.5 at 12), and a second workgroup per CU gains nothing (4096 -> 11008, 172 tiles: 19.4 us at 1, 22.8 at 2).
     double best = 1e30;
     for (int r = 1; r <= std::max(1, std::min(K / 256, 16)); ++r) {
-        const double cost = (double)((s.tiles * r + 255) / 256) * (1.0 / r + 0.25);
+        double cost = (double)((s.tiles * r + 255) / 256) * (1.0 / r + 0.25);
+        // More N-contiguous tiles than CUs: the CUs with a tile more than the others set a third of the time, against the traffic of the partial
+        // sums (8 r T N bytes for 2 K N) and the finish kernel (about 4 us, the time of 19 MB).  4608 -> 36864, 288 tiles: one row 71.5 us at 2 ranges, 65.3 at 6; 16 rows 79.0 / 76.3; 32 rows
+        // 85.5, 83.6 at 3; 2048 -> 36864, one row 39.1 at 1, 34.9 at 4; 4608 -> 49152, 384 tiles, stays at 2, 2048 -> 65536, 512 tiles, at 1.
+        if (base_nn && s.tiles > 256)
+            cost = 0.65 + 0.35 * ((s.tiles * r + 255) / 256) * 256.0 / ((double)s.tiles * r) + 4.0 * r * bi.T / K + (r > 1 ? 9.4e6 / ((double)K * N) : 0.0);
         if (cost < best) { best = cost; s.ranges = r; }
     }
-    // (not where outputs overlap inputs: every row must be read before any is written)
-    if (!s.items && !staged && K <= 2048) s.ranges = 1;
-    s.direct = !s.items && !staged && s.ranges == 1;
+    // One buffer: long strips, at most 16 rows, N-contiguous; less than a full round of workgroups is faster there (64 tiles of 28672 -> 8192, one row: 81.9 us
+    // at 3 ranges, 86.4 at 4; 36 of 36864 -> 4608 62.7 at 6, with two buffers 64.7 at 7).
+    if (base_nn && bi.T <= 16) {
+        const int r = s.tiles <= 112 ? std::min(224 / s.tiles, 16) : s.ranges, n = s.tiles * r;
+        s.one_buffer = K / r >= 2048 && n >= 160 && n <= 256;
+        if (s.one_buffer) s.ranges = r;
+    }
+    // Without a LoRA term, in one kernel where what a second one costs outweighs the ranges (not where outputs overlap inputs: every row must be
+    // read before any is written).  N-contiguous, us in one kernel / in 8 ranges: 1024 -> 4096 one row 9.8 / 10.0, 17 rows 11.8 / 10.5; 2048 x 2048 one row
+    // 11.9 / 10.3, 64 rows 22.1 / 13.9.  K-contiguous in tiles of 32 columns: see symb_small_narrow_kernel.
+    const bool can_direct = !s.items && !staged;
+    s.narrow = can_direct && !base_nn && N <= 8192 && (long long)K * N <= 10 << 20 && K <= (bi.T <= 32 ? 4608 : 2048);
+    if (s.narrow) s.tiles = (N + SMALL_NARROW_COLS - 1) / SMALL_NARROW_COLS;
+    if (s.narrow || (can_direct && K <= (!base_nn ? 2048 : bi.T <= 16 ? 1024 : 768))) s.ranges = 1;
+    s.direct = can_direct && s.ranges == 1;
+    s.wins = small_wins(base_nn, K, N, bi.T, s.items ? bi.n_lora : 0, s.ranges);
     s.base_bytes = s.direct ? 0 : (size_t)s.ranges * bi.T * N * 4;
     if (!s.items) return s;
     s.h_ranges = std::max(1, std::min({256 / s.items, K / 512, 16}));      // at most a round of its own, two slices per wavefront
@@ -492,8 +536,11 @@ WsLayout ws_layout(const symb_batch* b, const BatchInfo& bi, int op, bool full_b
     w.mandatory = cur;
     if (op != SYMB_OP_ADAPTER_GRAD && bi.T > 0 && bi.T <= SMALL_MAX_ROWS) {
         const SmallPlan sm = small_plan(b, bi, op, op == SYMB_OP_FWD || full_bwd, staged_out);
-        take(w.sp_off, w.sp_bytes, sm.base_bytes);
-        take(w.sh_off, w.sh_bytes, sm.h_bytes);
+        if (sm.wins) {
+            w.small = true;
+            take(w.sp_off, w.sp_bytes, sm.base_bytes);
+            take(w.sh_off, w.sh_bytes, sm.h_bytes);
+        }
     }
     const size_t small_end = cur;
     cur = w.mandatory;
@@ -789,25 +836,20 @@ symb_status launch_delta(symb_handle h, bool backward, const SegDesc* seg, const
 }
 
 template <bool BASE_NN, bool SHRINK_NN>
-void launch_small_stream(const SmallStreamParams& p, hipStream_t st) {
+void launch_small_stream(const SmallStreamParams& p, bool one_buffer, hipStream_t st) {
     const dim3 grid((unsigned)(p.num_items * p.h_ranges + p.tiles * p.ranges));
-    if (p.T <= 16) hipLaunchKernelGGL((symb_small_stream_kernel<1, BASE_NN, SHRINK_NN>), grid, dim3(256), 0, st, p);
-    else if (p.T <= 32) hipLaunchKernelGGL((symb_small_stream_kernel<2, BASE_NN, SHRINK_NN>), grid, dim3(256), 0, st, p);
-    else hipLaunchKernelGGL((symb_small_stream_kernel<4, BASE_NN, SHRINK_NN>), grid, dim3(256), 0, st, p);
+    if (one_buffer) {
+        if constexpr (BASE_NN) hipLaunchKernelGGL((symb_small_stream_kernel<1, true, SHRINK_NN, true>), grid, dim3(256), 0, st, p);
+    } else if (p.T <= 16) hipLaunchKernelGGL((symb_small_stream_kernel<1, BASE_NN, SHRINK_NN, false>), grid, dim3(256), 0, st, p);
+    else if (p.T <= 32) hipLaunchKernelGGL((symb_small_stream_kernel<2, BASE_NN, SHRINK_NN, false>), grid, dim3(256), 0, st, p);
+    else hipLaunchKernelGGL((symb_small_stream_kernel<4, BASE_NN, SHRINK_NN, false>), grid, dim3(256), 0, st, p);
 }
 
-// Whether a call takes the small-batch kernels: at most SMALL_MAX_ROWS rows, and a workspace with the optional regions.  Measured
-// against the tiled kernels (us per call, the weight read K- / N-contiguous, 1, 16 and 64 rows of rank-16 LoRA clients of one row each):
-// 4096 x 4096 14 / 28, 15 / 34, 20 / 54 and 14 / 35, 15 / 38, 24 / 62; 4096 x 11008 22 / 39, 25 / 49, 41 / 79 and 23 / 48, 25 / 57,
-// 38 / 95; with clients of ranks 4 to 128 the tiled kernels take 2 to 5 times as long.  The tiled kernels stay the faster ones for more than 32
-// rows of at most a few clients on a wide output, K-contiguous, where the finish kernel's pass over the fp32 sums weighs more than the
-// streaming saves (64 rows of one client: 4608 -> 36864 119 / 106, 4096 -> 24576 74 / 69, 256 -> 11008 18.5 / 14; 4096 -> 16384 still 48 / 51).
-bool small_path(symb_handle h, const symb_batch* b, const BatchInfo& bi, int op, bool lora, const WsLayout& wl, const void* ws, size_t ws_bytes) {
+// Whether a call takes the small-batch kernels: at most SMALL_MAX_ROWS rows, a shape on which they are the faster ones (small_wins), and a
+// workspace with their regions.
+bool small_path(symb_handle h, const BatchInfo& bi, const WsLayout& wl, const void* ws, size_t ws_bytes) {
     const size_t need = wl.sh_off + wl.sh_bytes;
-    if (!h->opt_small_rows || bi.T > SMALL_MAX_ROWS || ws_bytes < need || (!ws && need)) return false;
-    const int K = op == SYMB_OP_FWD ? b->d_in : b->d_out, N = op == SYMB_OP_FWD ? b->d_out : b->d_in;
-    const bool base_nn = (op == SYMB_OP_FWD) == (b->weight_layout == SYMB_WEIGHT_CONV1D);
-    return base_nn || bi.T <= 32 || !lora || bi.n_lora == 0 || bi.n_lora > 4 || !(N >= 24576 || (N >= 8192 && K < 1024));
+    return h->opt_small_rows && bi.T <= SMALL_MAX_ROWS && wl.small && ws_bytes >= need && (ws || !need);
 }
 
 // One call of the small-batch kernels, forward or input gradient: what differs between the two comes in through the
@@ -884,8 +926,12 @@ symb_status run_small(symb_handle h, const symb_batch* b, const BatchInfo& bi, c
     sp.out = SmallOut{(bf16*)c.out, (bf16*)c.out_base, c.out_seg ? (bf16* const*)(dev + o_cs) : nullptr, (const bf16*)c.bias,
                       c.neff ? (const NoiseDesc*)(dev + o_nd) : nullptr, fwd ? (bi.n_ia3 ? KIND_IA3 : 0) : c.lora && bi.n_ia3in ? KIND_IA3_IN : 0};
     const bool conv1d = b->weight_layout == SYMB_WEIGHT_CONV1D;
-    if (fwd) conv1d ? launch_small_stream<true, false>(sp, s) : launch_small_stream<false, false>(sp, s);
-    else conv1d ? launch_small_stream<false, true>(sp, s) : launch_small_stream<true, true>(sp, s);
+    if (plan.narrow) {
+        if (bi.T <= 16) hipLaunchKernelGGL(symb_small_narrow_kernel<1>, dim3(plan.tiles), dim3(256), 0, s, sp);
+        else if (bi.T <= 32) hipLaunchKernelGGL(symb_small_narrow_kernel<2>, dim3(plan.tiles), dim3(256), 0, s, sp);
+        else hipLaunchKernelGGL(symb_small_narrow_kernel<4>, dim3(plan.tiles), dim3(256), 0, s, sp);
+    } else if (fwd) conv1d ? launch_small_stream<true, false>(sp, plan.one_buffer, s) : launch_small_stream<false, false>(sp, false, s);
+    else conv1d ? launch_small_stream<false, true>(sp, false, s) : launch_small_stream<true, true>(sp, plan.one_buffer, s);
     SYMB_HIP(h, hipGetLastError());
     if (plan.direct) return seal_slot(h, s);
 
@@ -1196,7 +1242,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     const SplitPlan ksp = split_within(gemm_split_plan(bi.T, b->d_out, b->d_in), ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
     const bool k_split = ksp.parts > 1 && !Ybase && h->opt_k_split && h->xcd_rule;
     hipStream_t s = (hipStream_t)stream;
-    if (small_path(h, b, bi, SYMB_OP_FWD, true, wl, ws, ws_bytes)) {     // (partial sums between: overlapping buffers need no flat copy)
+    if (small_path(h, bi, wl, ws, ws_bytes)) {     // (partial sums between: overlapping buffers need no flat copy)
         unsigned char* const base = (unsigned char*)ws;
         const SmallCall c{SYMB_OP_FWD, X, W, bias, Y, Ybase, X_seg, Y_seg, nd.empty() ? nullptr : nd.data(), bi.n_ia3in ? (int)KIND_IA3_IN : 0,
                           (bf16*)(base + wl.sc_off), (bf16*)(base + wl.h_off), true, false, staged};
@@ -1454,7 +1500,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     const bool k_split = ksp.parts > 1 && !dXbase && h->opt_k_split && h->xcd_rule;
     hipStream_t s = (hipStream_t)stream;
     const bool lora = full && bi.n_lora > 0, ia3 = full && bi.n_ia3 > 0;
-    if (small_path(h, b, bi, SYMB_OP_BWD_INPUT, full, wl, ws, ws_bytes)) {     // (partial sums between: overlapping buffers need no flat copy)
+    if (small_path(h, bi, wl, ws, ws_bytes)) {     // (partial sums between: overlapping buffers need no flat copy)
         unsigned char* const base = (unsigned char*)ws;
         const SmallCall c{SYMB_OP_BWD_INPUT, dY, W, nullptr, dX, dXbase, dY_seg, dX_seg, nullptr, ia3 ? (int)KIND_IA3 : 0,
                           (bf16*)(base + wl.sc_off), (bf16*)(base + wl.dh_off), full, take_dh, staged};

@@ -35,6 +35,16 @@ def test_edges_of_rows_and_widths(dims, lens):
             check_dx(gh.bf16_to_f64(dX), off, oads, p["dY"], p["W"], f"dX {dims} {lens} conv1d={conv1d}", base_only=base_only)
 
 
+@pytest.mark.parametrize("d_in,d_out,lens", [(5000, 10248, [1, 9, 6]),       # 40 tiles in 5 long ranges: one buffer
+                                             (33000, 2056, [3, 9]), (33000, 2056, [20, 17])])      # more tiles than CUs
+def test_large_n_contiguous_weights(d_in, d_out, lens):
+    p = make_problem(d_in + len(lens), d_in, d_out, lens, [L, N, L], [16, 40])
+    oads = oracle_ads(p["ads"])
+    for base_only in (False, True):
+        dX = gh.backward_input(p["off"], p["ads"], p["dY"], p["W"], base_only=base_only)
+        check_dx(gh.bf16_to_f64(dX), p["off"], oads, p["dY"], p["W"], f"dX base_only={base_only}", base_only=base_only)
+
+
 @pytest.mark.parametrize("rank", [4, 12, 20])
 def test_adapter_matrix_off_its_16_byte_alignment(rank):
     """B of a rank that is no multiple of 8 need only be 2-byte aligned."""

@@ -174,6 +174,25 @@ def test_parts_of_a_k_split_on_narrow_layers():
     assert sb.symb_workspace_bytes(sb.Batch(1024, 4096, [0, 200], [sb.Adapter()]), sb.SYMB_OP_FWD) == 0
 
 
+def test_small_batches_on_which_the_tiled_kernels_are_faster():
+    """Their workspace holds the tiled kernel's regions alone (the figure is the larger of the two routes')."""
+    fake = 0x1000
+    lora = [sb.Adapter(sb.SYMB_ADAPTER_LORA, 16, 1.0, fake, fake)]
+    up = lambda n: (n + 255) // 256 * 256
+    one = sb.Batch(36864, 4608, [0, 64], [sb.Adapter()])
+    # input gradient of 36864 -> 4608: 288 tiles of 128x128, whole; up to 38 rows partial sums over 3 ranges
+    assert sb.symb_workspace_bytes(one, sb.SYMB_OP_BWD_INPUT) == 0
+    assert sb.symb_workspace_bytes(sb.Batch(36864, 4608, [0, 33], [sb.Adapter()]), sb.SYMB_OP_BWD_INPUT) == up(3 * 33 * 36864 * 4)
+    h = 64 * 2 * 16 * 2
+    assert sb.symb_workspace_bytes(sb.Batch(36864, 4608, [0, 64], lora), sb.SYMB_OP_BWD_INPUT) == 2 * up(h) + up(16 * 4608 * 2)
+    # 4096 -> 16384, input-major: 128 tiles in two parts; with 32 rows two ranges of partial sums, less than those
+    for rows in (32, 64):
+        assert sb.symb_workspace_bytes(sb.Batch(4096, 16384, [0, rows], [sb.Adapter()], sb.SYMB_WEIGHT_CONV1D), sb.SYMB_OP_FWD) == 128 * 2 * 65536
+    # 2048 -> 4608, input-major: 33 rows tiled (36 tiles in four parts), 32 rows 7 ranges
+    for rows in (32, 33):
+        assert sb.symb_workspace_bytes(sb.Batch(2048, 4608, [0, rows], [sb.Adapter()], sb.SYMB_WEIGHT_CONV1D), sb.SYMB_OP_FWD) == 36 * 4 * 65536
+
+
 def test_unknown_weight_layout_is_rejected():
     b = sb.Batch(64, 64, [0, 4], [sb.Adapter()], weight_layout=7)
     assert sb.lib().symb_validate_batch(b.ref()) == sb.SYMB_ERR_INVALID_ARG

@@ -7,7 +7,7 @@ from test_gemm16_registers import _regs, device_asm  # noqa: F401
 
 def test_lds_reads_are_untouched_until_their_wait(device_asm):  # noqa: F811
     checked = 0
-    for m in re.finditer(r"^(_ZN4symb(?:24symb_small_stream_kernel|18symb_skinny_kernel|26symb_lora_grad_(?:wave|pair)_kernel)\w+):(.*?)^\.Lfunc_end", device_asm, re.S | re.M):
+    for m in re.finditer(r"^(_ZN4symb(?:24symb_small_(?:stream|narrow)_kernel|18symb_skinny_kernel|26symb_lora_grad_(?:wave|pair)_kernel)\w+):(.*?)^\.Lfunc_end", device_asm, re.S | re.M):
         pending, inside = set(), False
         for raw in m.group(2).splitlines():
             if "ASMSTART" in raw or "ASMEND" in raw:
