@@ -657,35 +657,106 @@ symb_small_finish_kernel(const SmallFinishParams p) {
     *reinterpret_cast<unsigned*>(out + n) = pack2_bf16(v0, v1);
 }
 
-// LoRA terms of short segments of a larger batch, in fp32, for the tiled kernel to add: out[d][n] = sum_q H[t][q] B_i[n][q] (forward) or
-// A_i[q][n] (input gradient), H from the rows the skinny kernel left.  Inside the tiled kernel every LoRA segment that meets a row tile
-// is a chain of 2 rpad / 32 register-staged steps of 1 to 1.6 us, whatever few rows it has, and the launch waits for the row
-// tile that holds the most of them; here the segments run side by side.  Measured on the mixed batch (48 one-token clients beside
-// 16 long ones, 9049 rows, 4096 -> 11008): the tiled kernel 961 -> 757 us, this one 16.
-// grid = (blocks of 256 columns, segments).
+// LoRA terms of short segments (at most 16 rows) of a larger batch, in fp32, for the tiled kernel to add: out[d][n] = sum_q H[t][q] B_i[n][q]
+// (forward) or A_i[q][n] (input gradient), H from the rows the skinny kernel left.  Inside the tiled kernel every LoRA segment that meets
+// a row tile is a chain of 2 rpad / 32 register-staged steps of 1 to 1.6 us, whatever few rows it has, and the launch waits for the
+// row tile that holds the most of them; here the segments run side by side.  All rows of a segment are one block of 16 for the
+// matrix cores, against value and residual of H as in the tiled kernel's steps: the adapter is read once per segment, and a wavefront needs neither
+// LDS nor a barrier.  A wavefront owns 64 columns: lane l15 holds columns 4 l15 .. + 3 as fragments of four products, so that the
+// result of a row is one 16-byte store per lane.  Bound by the fp32 terms it writes.
+// grid = (blocks of 256 columns, segments).  NS: 32-wide steps over the ranks (padded rank <= 32 NS).
 struct LoraDeltaParams {
-    SmallFinishParams f;      // h_rows, h_pitch, N, seg; no ranges, no partial sums
+    const bf16* h_rows;       // [T][2 * h_pitch]
+    int h_pitch, N;
+    const SegDesc* seg;
     const RowChunk* items;    // device: segment, first row, rows, pad = first row of out
     float* out;               // [.][N]
 };
-template <bool BACKWARD>
-__global__ void __launch_bounds__(128)
-symb_lora_delta_kernel(const LoraDeltaParams p) {
-    __shared__ __attribute__((aligned(16))) float hs[128], us[4096 + 128];
-    const RowChunk it = p.items[blockIdx.y];
-    const SegDesc sd = p.f.seg[it.seg];
-    const int c0 = blockIdx.x * 256, n = c0 + 2 * (int)threadIdx.x;
-    for (int r = 0; r < it.nrows; ++r) {
-        float v0 = 0.f, v1 = 0.f;
-        auto sums = [&](auto NCH) __attribute__((always_inline)) { small_finish_sums<BACKWARD, decltype(NCH)::value>(p.f, sd, it.row0 + r, c0, hs, us, v0, v1); };
-        if (!BACKWARD && (sd.rank & 7)) sums(std::integral_constant<int, -1>{});
-        else if (sd.rank <= 16) sums(std::integral_constant<int, 4>{});
-        else if (sd.rank <= 32) sums(std::integral_constant<int, 8>{});
-        else if (sd.rank <= 64) sums(std::integral_constant<int, 16>{});
-        else sums(std::integral_constant<int, 32>{});
-        if (n < p.f.N) *reinterpret_cast<float2*>(p.out + (size_t)(it.pad + r) * p.f.N + n) = make_float2(v0, v1);
-        __syncthreads();                                 // hs and us are written again
+template <bool BACKWARD, int NS>
+__device__ __forceinline__ void lora_delta(const LoraDeltaParams& p, const RowChunk& it, const SegDesc& sd) {
+    const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, kq = lane >> 4;
+    const int n = blockIdx.x * 256 + (tid >> 6) * 64 + l15 * 4;           // this lane's columns n .. n + 3 (N is a multiple of 8)
+    if (n - l15 * 4 >= p.N) return;
+    u32x4 h[NS][2];
+    const bf16* const hrow = p.h_rows + (size_t)(it.row0 + min(l15, it.nrows - 1)) * 2 * p.h_pitch;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int q0 = s * 32 + kq * 8, at = min(q0, sd.rpad - 8);        // ranks past the padded one count as zero, in both operands
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            h[s][half] = ld_glb16(hrow + half * sd.rpad + at);
+            if (q0 >= sd.rpad) h[s][half] = u32x4{0u, 0u, 0u, 0u};
+        }
     }
+    u32x4 w[NS][4];                                      // column n + j, ranks q0 .. q0 + 7
+    if constexpr (BACKWARD) {
+        uint2 x[NS][8];
+        const bf16* const col = sd.A + min(n, p.N - 4);
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[s][e] = *reinterpret_cast<const uint2*>(col + (size_t)min(s * 32 + kq * 8 + e, sd.rank - 1) * p.N);
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                uint2 a = x[s][2 * e], b = x[s][2 * e + 1];
+                const int q = s * 32 + kq * 8 + 2 * e;
+                if (q >= sd.rank) a = make_uint2(0u, 0u);
+                if (q + 1 >= sd.rank) b = make_uint2(0u, 0u);
+                w[s][0][e] = (a.x & 0xffffu) | (b.x << 16);
+                w[s][1][e] = (a.x >> 16) | (b.x & 0xffff0000u);
+                w[s][2][e] = (a.y & 0xffffu) | (b.y << 16);
+                w[s][3][e] = (a.y >> 16) | (b.y & 0xffff0000u);
+            }
+    } else if ((sd.rank & 7) == 0) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int q0 = s * 32 + kq * 8;
+                w[s][j] = ld_glb16(sd.B + (size_t)min(n + j, p.N - 1) * sd.rank + min(q0, sd.rank - 8));
+                if (q0 >= sd.rank) w[s][j] = u32x4{0u, 0u, 0u, 0u};
+            }
+    } else {
+        // rows of B_i that are no whole 16-byte chunks: element loads
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const unsigned short* const b = reinterpret_cast<const unsigned short*>(sd.B) + (size_t)min(n + j, p.N - 1) * sd.rank;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int q = s * 32 + kq * 8 + 2 * e;
+                    const unsigned a = b[min(q, sd.rank - 1)], c = b[min(q + 1, sd.rank - 1)];
+                    w[s][j][e] = (q < sd.rank ? a : 0u) | (q + 1 < sd.rank ? c << 16 : 0u);
+                }
+            }
+    }
+    floatx4 acc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, h[s][half]), __builtin_bit_cast(bf16x8, w[s][j]), acc[j], 0, 0, 0);
+    if (n >= p.N) return;
+    float* const out = p.out + (size_t)(it.pad + kq * 4) * p.N + n;        // rows 4 kq .. + 3 of the block
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (kq * 4 + q < it.nrows) *reinterpret_cast<float4*>(out + (size_t)q * p.N) = make_float4(acc[0][q], acc[1][q], acc[2][q], acc[3][q]);
+}
+template <bool BACKWARD>
+__global__ void __launch_bounds__(256)
+symb_lora_delta_kernel(const LoraDeltaParams p) {
+    const RowChunk it = p.items[blockIdx.y];
+    const SegDesc sd = p.seg[it.seg];
+    if (sd.rpad <= 32) lora_delta<BACKWARD, 1>(p, it, sd);                 // uniform over the workgroup
+    else if (sd.rpad <= 64) lora_delta<BACKWARD, 2>(p, it, sd);
+    else lora_delta<BACKWARD, 4>(p, it, sd);
 }
 
 }  // namespace symb

@@ -447,27 +447,40 @@ SmallPlan small_plan(const symb_batch* b, const BatchInfo& bi, int op, bool lora
     return s;
 }
 
-// Short LoRA segments (at most kDeltaRows rows) whose term the tiled kernels add from memory (symb_lora_delta_kernel) instead of running a
-// chain of k-steps for each: all of them that meet a row tile with at least delta_steps() such steps, about the time of the extra
-// launch (6 to 16 us: a step costs up to 1.6 us in the 256x256 tile, about 0.45 in the 128x128 one).  Batches of more than kDeltaSegments segments keep the
-// steps, as does one whose descriptors have no room for the terms' (add_gemm_desc).
+// Short LoRA segments (at most kDeltaRows rows) whose term the tiled kernels add from memory (symb_lora_delta_kernel) instead of running a chain of k-steps
+// for each: all of them that meet a row tile with at least delta_steps() such steps.  The steps of the row tile with the most set what the
+// chains cost, a launch and the traffic of the fp32 terms (8 bytes per row and output column) what they cost from memory.  Measured over clients
+// of 1 to 16 rows and ranks 8 to 128, 96 to 2048 such rows alone or beside long segments, 1024 to 11008 columns, both directions, us from
+// memory / in steps: 4096 x 4096, 96 rows, 24 steps 40.8 / 37.4, 48 steps 42.3 / 43.4, 96 steps 53.7 / 61.8; 1024 x 1024, 24 steps 24.7 / 34.4; 2048 rows of
+// 4096 -> 11008 (256x256 tile) 16 steps 232 / 205, 64 steps 270 / 317.  By the line below nothing of the sweep is more than 4 % slower than in steps.
+// Batches of more than kDeltaSegments segments, or of more terms than kDeltaBytes, keep the steps, as does one whose descriptors have no
+// room for the terms' (add_gemm_desc).
 constexpr int kDeltaRows = 16, kDeltaSegments = 4096;
-int delta_steps(int tile_m) { return tile_m == 256 ? 8 : 16; }
+constexpr size_t kDeltaBytes = (size_t)160 << 20;
+int delta_steps(int tile_m, int rows, int N) {
+    const double elems = 1e-6 * rows * N;
+    return (int)(tile_m == 256 ? 8 + 1.5 * elems : 6 + 0.005 * N + 3 * elems);
+}
 struct DeltaPlan {
     std::vector<RowChunk> items;          // the segments (pad: first row of their terms)
     int rows = 0;                         // rows of terms
 };
-DeltaPlan delta_plan(const symb_batch* b, int tile_m) {
+DeltaPlan delta_plan(const symb_batch* b, int tile_m, int N) {
     DeltaPlan d;
-    const int S = b->num_segments, least = delta_steps(tile_m);
+    const int S = b->num_segments;
     auto steps = [&](int i) {
         const int n = b->seg_offsets[i + 1] - b->seg_offsets[i];
         return b->adapters[i].kind == SYMB_ADAPTER_LORA && n > 0 && n <= kDeltaRows ? rpad_of(b->adapters[i].rank) / 16 : 0;
     };
     if (S > kDeltaSegments) return d;
-    int all = 0;
-    for (int i = 0; i < S && all < least; ++i) all += steps(i);
-    if (all < least) return d;
+    int all = 0, rows = 0;
+    for (int i = 0; i < S; ++i)
+        if (const int k = steps(i)) {
+            all += k;
+            rows += b->seg_offsets[i + 1] - b->seg_offsets[i];
+        }
+    const int least = delta_steps(tile_m, rows, N);
+    if (all < least || (size_t)rows * N * 4 > kDeltaBytes) return d;
     std::vector<int> tile((b->seg_offsets[S] + tile_m - 1) / tile_m, 0);
     for (int i = 0; i < S; ++i)
         if (const int k = steps(i)) {
@@ -548,7 +561,7 @@ WsLayout ws_layout(const symb_batch* b, const BatchInfo& bi, int op, bool full_b
         const int N = op == SYMB_OP_FWD ? b->d_out : b->d_in, K = op == SYMB_OP_FWD ? b->d_in : b->d_out;
         const SplitPlan sp = gemm_split_plan(bi.T, N, K);
         if (sp.parts > 1) take(w.tp_off, w.tp_bytes, sp.bytes);
-        const int rows = bi.n_lora && (op == SYMB_OP_FWD || full_bwd) ? delta_plan(b, gemm_tile_m(bi.T, N, K)).rows : 0;
+        const int rows = bi.n_lora && (op == SYMB_OP_FWD || full_bwd) ? delta_plan(b, gemm_tile_m(bi.T, N, K), N).rows : 0;
         if (rows) take(w.de_off, w.de_bytes, (size_t)rows * N * 4);
     }
     w.total = std::max(small_end, cur);
@@ -822,15 +835,9 @@ symb_status launch_row_pass(symb_handle h, void (*kfn)(P), P p, int width, size_
 }
 
 // The terms of a DeltaPlan, from the rows of H in the workspace.
-symb_status launch_delta(symb_handle h, bool backward, const SegDesc* seg, const RowChunk* items, int nitems, int N, bf16* h_rows, int h_pitch, float* out, hipStream_t st) {
-    LoraDeltaParams dp{};
-    dp.f.h_rows = h_rows;
-    dp.f.h_pitch = h_pitch;
-    dp.f.N = N;
-    dp.f.seg = seg;
-    dp.items = items;
-    dp.out = out;
-    hipLaunchKernelGGL(backward ? symb_lora_delta_kernel<true> : symb_lora_delta_kernel<false>, dim3((N + 255) / 256, nitems), dim3(128), 0, st, dp);
+symb_status launch_delta(symb_handle h, bool backward, const SegDesc* seg, const RowChunk* items, int nitems, int N, const bf16* h_rows, int h_pitch, float* out, hipStream_t st) {
+    const LoraDeltaParams dp{h_rows, h_pitch, N, seg, items, out};
+    hipLaunchKernelGGL(backward ? symb_lora_delta_kernel<true> : symb_lora_delta_kernel<false>, dim3((N + 255) / 256, nitems), dim3(256), 0, st, dp);
     SYMB_HIP(h, hipGetLastError());
     return SYMB_OK;
 }
@@ -1266,7 +1273,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     std::vector<SegDesc> sd_gemm = sd;
     std::vector<int64_t> pk_off(bi.S, 0);
     DeltaPlan delta;
-    if (wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm);
+    if (wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm, b->d_out);
     if (conv1d && bi.n_lora) {
         int64_t cur = 0;
         for (int i = 0; i < bi.S; ++i)
@@ -1545,7 +1552,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     const bool conv1d = b->weight_layout == SYMB_WEIGHT_CONV1D;
     std::vector<SegDesc> sd_gemm = sd;
     DeltaPlan delta;
-    if (lora && wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm);
+    if (lora && wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm, b->d_in);
     std::vector<int64_t> pk_off(bi.S, 0), pa_off(bi.S, 0);
     {
         int64_t cur = 0, cura = 0;

