@@ -449,23 +449,25 @@ SmallPlan small_plan(const symb_batch* b, const BatchInfo& bi, int op, bool lora
 
 // Short LoRA segments (at most kDeltaRows rows) whose term the tiled kernels add from memory (symb_lora_delta_kernel) instead of running a chain of k-steps
 // for each: all of them that meet a row tile with at least delta_steps() such steps.  The steps of the row tile with the most set what the
-// chains cost, a launch and the traffic of the fp32 terms (8 bytes per row and output column) what they cost from memory.  Measured over clients
-// of 1 to 16 rows and ranks 8 to 128, 96 to 2048 such rows alone or beside long segments, 1024 to 11008 columns, both directions, us from
-// memory / in steps: 4096 x 4096, 96 rows, 24 steps 40.8 / 37.4, 48 steps 42.3 / 43.4, 96 steps 53.7 / 61.8; 1024 x 1024, 24 steps 24.7 / 34.4; 2048 rows of
-// 4096 -> 11008 (256x256 tile) 16 steps 232 / 205, 64 steps 270 / 317.  By the line below nothing of the sweep is more than 4 % slower than in steps.
+// chains cost (the K parts of a split tile share them), a launch and the traffic of the fp32 terms (8 bytes per row and output column) what they
+// cost from memory.  Measured over clients of 1 to 16 rows and ranks 8 to 128, 96 to 2048 such rows alone or beside long segments, 1024 to 11008
+// columns, both directions, us from memory / in steps: 4096 x 4096, 96 rows (five parts), 24 steps 40.8 / 37.4, 48 steps 42.3 / 43.4, 96 steps
+// 53.7 / 61.8; 64 rows beside 1984 (whole), 16 steps 9 us less, 8 steps equal; 512 rows of 11008 -> 4096 (four parts) 32 steps 108 / 99, 64 steps equal; 2048
+// rows of 4096 -> 11008 (256x256 tile) 16 steps 232 / 205, 64 steps 270 / 317.  By the lines below what is chosen is at most 3 %, what is not
+// at most 5 % slower than the other way, over the whole sweep.
 // Batches of more than kDeltaSegments segments, or of more terms than kDeltaBytes, keep the steps, as does one whose descriptors have no
 // room for the terms' (add_gemm_desc).
 constexpr int kDeltaRows = 16, kDeltaSegments = 4096;
 constexpr size_t kDeltaBytes = (size_t)160 << 20;
-int delta_steps(int tile_m, int rows, int N) {
+int delta_steps(int tile_m, int parts, int rows, int N) {
     const double elems = 1e-6 * rows * N;
-    return (int)(tile_m == 256 ? 8 + 1.5 * elems : 6 + 0.005 * N + 3 * elems);
+    return (int)(tile_m == 256 ? 8 + 1.5 * elems : 8 * parts + 5 * elems);
 }
 struct DeltaPlan {
     std::vector<RowChunk> items;          // the segments (pad: first row of their terms)
     int rows = 0;                         // rows of terms
 };
-DeltaPlan delta_plan(const symb_batch* b, int tile_m, int N) {
+DeltaPlan delta_plan(const symb_batch* b, int tile_m, int N, int K) {
     DeltaPlan d;
     const int S = b->num_segments;
     auto steps = [&](int i) {
@@ -479,7 +481,7 @@ DeltaPlan delta_plan(const symb_batch* b, int tile_m, int N) {
             all += k;
             rows += b->seg_offsets[i + 1] - b->seg_offsets[i];
         }
-    const int least = delta_steps(tile_m, rows, N);
+    const int least = delta_steps(tile_m, gemm_split_plan(b->seg_offsets[S], N, K).parts, rows, N);
     if (all < least || (size_t)rows * N * 4 > kDeltaBytes) return d;
     std::vector<int> tile((b->seg_offsets[S] + tile_m - 1) / tile_m, 0);
     for (int i = 0; i < S; ++i)
@@ -561,7 +563,7 @@ WsLayout ws_layout(const symb_batch* b, const BatchInfo& bi, int op, bool full_b
         const int N = op == SYMB_OP_FWD ? b->d_out : b->d_in, K = op == SYMB_OP_FWD ? b->d_in : b->d_out;
         const SplitPlan sp = gemm_split_plan(bi.T, N, K);
         if (sp.parts > 1) take(w.tp_off, w.tp_bytes, sp.bytes);
-        const int rows = bi.n_lora && (op == SYMB_OP_FWD || full_bwd) ? delta_plan(b, gemm_tile_m(bi.T, N, K), N).rows : 0;
+        const int rows = bi.n_lora && (op == SYMB_OP_FWD || full_bwd) ? delta_plan(b, gemm_tile_m(bi.T, N, K), N, K).rows : 0;
         if (rows) take(w.de_off, w.de_bytes, (size_t)rows * N * 4);
     }
     w.total = std::max(small_end, cur);
@@ -1273,7 +1275,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     std::vector<SegDesc> sd_gemm = sd;
     std::vector<int64_t> pk_off(bi.S, 0);
     DeltaPlan delta;
-    if (wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm, b->d_out);
+    if (wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm, b->d_out, b->d_in);
     if (conv1d && bi.n_lora) {
         int64_t cur = 0;
         for (int i = 0; i < bi.S; ++i)
@@ -1552,7 +1554,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     const bool conv1d = b->weight_layout == SYMB_WEIGHT_CONV1D;
     std::vector<SegDesc> sd_gemm = sd;
     DeltaPlan delta;
-    if (lora && wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm, b->d_in);
+    if (lora && wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm, b->d_in, b->d_out);
     std::vector<int64_t> pk_off(bi.S, 0), pa_off(bi.S, 0);
     {
         int64_t cur = 0, cura = 0;

@@ -211,6 +211,8 @@ def test_terms_of_short_segments_in_the_workspace():
     assert figure(1, 8, 128, 2000, 1024, 1024) == 128 * 1024 * 4
     assert figure(16, 128, 96, 0, 4096, 4096) == 96 * 4096 * 4
     assert figure(16, 16, 96, 0, 4096, 4096) == 0              # 6 steps
+    assert figure(16, 64, 64, 1984, 4096, 4096) == 64 * 4096 * 4        # 16 steps of a whole tile; of one in five K parts: none
+    assert figure(16, 64, 96, 0, 4096, 4096) == 0
     assert figure(1, 128, 3600, 8, 64, 36864) == 0             # more than 160 MiB of terms
 
 
