@@ -214,10 +214,14 @@ BatchInfo inspect(const symb_batch* b) {
 // Tile variants of the GEMM kernel (gemm16_kernel.hpp): 3 = 256x256 tile, taken when the problem has
 // enough such tiles to fill the chip; 2 = 128x128 tile, for everything smaller.
 int gemm_variant(int M, int N, int K) {
-    const long big = (long)((M + 255) / 256) * ((N + 255) / 256);
-    // 128 tiles of 256x256 leave half the CUs idle; as 512 of 128x128 they are one round of two per CU: 62.5 / 74.5 us on 2048 rows
-    // of 4096 x 4096, 69 / 79 on 4608 -> 4096, but 108 / 95 for 1024 on 6144 -> 8192 and 177 / 154 for 2048 on 11008 -> 4096 (twice the LDS traffic per flop)
-    return big > 128 || (big == 128 && K > 4608) ? 3 : 2;
+    const long big = (long)((M + 255) / 256) * ((N + 255) / 256), small = (long)((M + 127) / 128) * ((N + 127) / 128);
+    if (big < 128) return 2;
+    // From 128 tiles of 256x256 on, as long as the 128x128 ones are one round of two per CU, those fill the chip where the others leave up to half the CUs
+    // idle, but they read twice the LDS bytes per flop, and lose on a long inner dimension, sooner the wider the output.  Weights from HBM, us in
+    // small / big tiles: 2048 rows, 4096 wide, K = 4096 70 / 76, 4608 80 / 81, 5120 90 / 88, 8192 128 / 119; 8192 rows, 1024 wide, K = 4608 80 / 81; 1024 rows, 8192 wide,
+    // K = 2048 42 / 55, 4096 77 / 77, 4608 87 / 81; 512 rows, 16384 wide, K = 2048 45 / 54, 4096 84 / 79; ragged: 1800 rows, 4096 wide, K = 4608 74 / 81;
+    // 3700 rows, 2056 wide (135 big tiles, 493 small) K = 4096 65 / 79; 3840 rows, 2184 wide (135, 540) K = 2048 52 / 46.
+    return small <= 512 && K <= (N <= 4096 ? 4608 : N <= 8192 ? 4096 : 3072) ? 2 : 3;
 }
 int gemm_tile_m(int M, int N, int K) { return gemm_variant(M, N, K) == 3 ? 256 : 128; }
 

@@ -133,3 +133,15 @@ def adapter_grad(off, ads: Sequence[HostAdapter], X, dY, Ybase=None, d_in=None, 
                          ws, stream_ptr())
     torch.cuda.synchronize()
     return dev
+
+
+def gemm_launches(call):
+    """How often call() launches each GEMM instantiation: {variant: launches}, variants as in symb_debug_gemm_timing_read (bit 0: weight read
+    N-contiguous, bit 1: 128x128 tile, bit 2: full epilogue); empty if another kernel did the product."""
+    sb.symb_debug_gemm_timing_enable(handle(), 1)
+    try:
+        call()
+        n = {v: sb.symb_debug_gemm_timing_read(handle(), v)[1] for v in range(8)}
+    finally:
+        sb.symb_debug_gemm_timing_enable(handle(), 0)
+    return {v: k for v, k in n.items() if k}

@@ -119,6 +119,19 @@ def test_tile_and_split_rules_of_mid_sized_batches(T, d_in, d_out):
         check_y(gh.bf16_to_f64(Y)[rows], p["off"], oads, p["X"], p["W"], p["bias"], "Y", rows=rows)
 
 
+@pytest.mark.parametrize("T,d_in,d_out,small", [
+    (2048, 4608, 4096, True), (2048, 4616, 4096, False), (1800, 512, 4096, True), (1024, 4096, 8192, True), (1024, 4104, 8192, False),
+    (512, 3072, 16384, True), (512, 4096, 16384, False), (3700, 512, 2056, True), (3840, 512, 2184, False), (1792, 8192, 4096, True)])
+def test_tile_size(T, d_in, d_out, small):
+    """Which tile a product runs in, around 128 tiles of 256x256 and 512 of 128x128."""
+    X, W, Y = (torch.zeros(s, device="cuda", dtype=torch.bfloat16) for s in ((T, d_in), (d_out, d_in), (T, d_out)))
+    for conv1d in (0, 1):
+        b = sb.Batch(d_in, d_out, [0, T], [sb.Adapter()], conv1d)
+        ws = gh.workspace(b, sb.SYMB_OP_FWD)
+        ran = gh.gemm_launches(lambda: sb.symb_base_linear_fwd(gh.handle(), b, X, W, None, Y, None, ws))
+        assert ran == {conv1d + (2 if small else 0): 1}
+
+
 @pytest.mark.parametrize("d_in,d_out", [(264, 392), (2056, 264), (200, 6216)])     # 128x128 tiles, split over K, 256x256 tiles
 def test_short_segments_of_a_larger_batch(d_in, d_out):
     """LoRA terms of short segments are added from memory where a row tile holds many of their steps: scattered over the tiles,
