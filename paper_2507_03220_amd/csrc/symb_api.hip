@@ -321,14 +321,11 @@ SplitPlan split_within(SplitPlan s, size_t room) {
     return s.bytes <= room ? s : SplitPlan{};
 }
 
-// One-pass dH + dB kernel: column blocks of 256 columns per workgroup (0: the layer is too narrow for it:
+// One-pass dH + dB kernel: the number of workgroups along d_out, kDhDbBlocks blocks of 256 columns each (0: the layer is too narrow for it:
 // with few column blocks the launch has too few workgroups, each walking its tokens alone, and the two
-// separate passes are faster), and the number of workgroups along d_out.
-int dhdb_blocks_per_group(int d_out) { return d_out >= GRAD_WIDE ? 2 : 0; }
-int dhdb_groups(int d_out) {
-    const int g = dhdb_blocks_per_group(d_out);
-    return g ? ((d_out + 255) / 256 + g - 1) / g : 0;
-}
+// separate passes are faster).
+constexpr int kDhDbBlocks = 2;
+int dhdb_groups(int d_out) { return d_out >= GRAD_WIDE ? ((d_out + 255) / 256 + kDhDbBlocks - 1) / kDhDbBlocks : 0; }
 
 // LoRA gradients of long segments: a segment of more than GRAD_SPLIT_MIN tokens is walked in runs of
 // GRAD_SPLIT tokens, each by workgroups of its own, which leave fp32 sums of the result's size in the
@@ -1884,8 +1881,7 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
         DhDbParams dp{(const bf16*)dY, (const bf16*)(wsb + wl.h_off), b->d_out, 2 * bi.max_rpad, doff, dseg, (const GradItem*)(dev + o_itb), acc ? 1 : 0,
                       seg_io ? (const bf16* const*)(dev + o_gs) : nullptr, (float*)(wsb + wl.gr_off), (float*)(wsb + wl.dp_off), bi.T};
         const int groups = dhdb_groups(b->d_out);
-        if (dhdb_blocks_per_group(b->d_out) == 2) hipLaunchKernelGGL(symb_lora_dhdb_kernel<2>, dim3(groups, (unsigned)it_b.size()), dim3(256), 0, s, dp);
-        else hipLaunchKernelGGL(symb_lora_dhdb_kernel<4>, dim3(groups, (unsigned)it_b.size()), dim3(256), 0, s, dp);
+        hipLaunchKernelGGL(symb_lora_dhdb_kernel<kDhDbBlocks>, dim3(groups, (unsigned)it_b.size()), dim3(256), 0, s, dp);
         SYMB_HIP(h, hipGetLastError());
         if ((st = launch_grad_reduce(h, GradReduceParams{dseg, (const GradReduceItem*)(dev + o_rdb), (const float*)(wsb + wl.gr_off), b->d_out, 1, acc ? 1 : 0},
                                      (int)red_b.size(), s)) != SYMB_OK) return st;
