@@ -303,7 +303,8 @@ symb_status symb_adapter_grad_ex(symb_handle h, const symb_batch* b, const void*
  * read synchronises on the recorded events and returns the totals since the last
  * enable call (which clears them).  At most 4096 launches are recorded after an
  * enable; later ones are not timed.  `flops_total` is the algorithmic work of those launches
- * (2*M*N*K plus the fused LoRA term 2*n_i*r_i*N per segment).
+ * (2*M*N*K plus the fused LoRA term 2*n_i*r_i*N per segment, without short segments whose term another
+ * kernel computes).
  */
 symb_status symb_debug_gemm_timing_enable(symb_handle h, int32_t on);
 symb_status symb_debug_gemm_timing_read(symb_handle h, int32_t variant, double* ms_total,

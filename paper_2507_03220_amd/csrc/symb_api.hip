@@ -724,13 +724,13 @@ symb_status launch_gemm16_t(symb_handle h, const GemmParams& gp, hipStream_t st)
     return launch_gemm_fn(h, gp, st, symb_gemm16_kernel<NBLK, NN, PLAIN>, TT::BM, TT::BN, TT::NT, TT::SMEM, variant);
 }
 
-// Algorithmic work of one GEMM launch: 2 M N K plus the fused LoRA term.
-double gemm_flops(const symb_batch* b, int N, int K, bool lora) {
+// Algorithmic work of one GEMM launch: 2 M N K plus the LoRA term of the segments that have their steps in it.
+double gemm_flops(const symb_batch* b, const std::vector<SegDesc>& sd_gemm, int N, int K, bool lora) {
     const int S = b->num_segments;
     double f = 2.0 * b->seg_offsets[S] * (double)N * K;
     if (lora)
         for (int i = 0; i < S; ++i)
-            if (b->adapters[i].kind == SYMB_ADAPTER_LORA)
+            if (sd_gemm[i].kind == KIND_LORA)
                 f += 2.0 * (b->seg_offsets[i + 1] - b->seg_offsets[i]) * (double)b->adapters[i].rank * N;
     return f;
 }
@@ -1369,7 +1369,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     gp.epi_ia3 = bi.n_ia3 > 0 ? KIND_IA3 : 0;
     gp.tile_epi = (const int32_t*)(dev + o_te);
     gp.neff = nd.empty() ? nullptr : (const NoiseDesc*)(dev + o_nd);
-    gp.timing_flops = gemm_flops(b, b->d_out, b->d_in, bi.n_lora > 0);
+    gp.timing_flops = gemm_flops(b, sd_gemm, b->d_out, b->d_in, bi.n_lora > 0);
     gp.group_m = gemm_group_m((bi.T + bm - 1) / bm, (b->d_out + bm - 1) / bm, lo, hi);
     if (k_split) {
         gp.k_parts = ksp.parts;
@@ -1654,7 +1654,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     gp.ext_pitch = 2 * bi.max_rpad;
     gp.epi_ia3 = (full && bi.n_ia3in > 0) ? KIND_IA3_IN : 0;      // dX rows of IA3_IN segments: l_i * (dY W)
     gp.tile_epi = (const int32_t*)(dev + o_te);
-    gp.timing_flops = gemm_flops(b, b->d_in, b->d_out, lora);
+    gp.timing_flops = gemm_flops(b, sd_gemm, b->d_in, b->d_out, lora);
     gp.group_m = gemm_group_m((bi.T + bm - 1) / bm, (b->d_in + bm - 1) / bm, lo, hi);
     if (k_split) {
         gp.k_parts = ksp.parts;

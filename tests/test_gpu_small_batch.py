@@ -152,6 +152,24 @@ def test_short_segments_of_a_larger_batch(d_in, d_out):
         check_dx(gh.bf16_to_f64(dX), off, oracle_ads(q["ads"]), q["dY"], q["W"], f"dX conv1d={conv1d}")
 
 
+def test_timed_work_of_a_gemm_leaves_out_the_terms_from_memory():
+    lens = [1] * 40 + [300]
+    p = make_problem(8, 264, 392, lens, [L], [16] * 40 + [8])
+    dev = gh.upload_adapters(p["ads"], 264, 392, grads=False)
+    b = sb.Batch(264, 392, p["off"], dev.descs)
+    X, W = gh.to_dev(p["X"]), gh.to_dev(p["W"])
+    Y = torch.empty(p["T"], 392, device="cuda", dtype=torch.bfloat16)
+    full = gh.workspace(b, sb.SYMB_OP_FWD)
+    for ws, rows in ((full, 300 * 8), (full[:p["T"] * 2 * 16 * 2], 40 * 16 + 300 * 8)):          # with the terms' region, and without
+        sb.symb_debug_gemm_timing_enable(gh.handle(), 1)
+        try:
+            sb.symb_base_linear_fwd(gh.handle(), b, X, W, None, Y, None, ws)
+            work = sum(sb.symb_debug_gemm_timing_read(gh.handle(), v)[2] for v in range(8))
+        finally:
+            sb.symb_debug_gemm_timing_enable(gh.handle(), 0)
+        assert work == 2.0 * 392 * (p["T"] * 264 + rows)
+
+
 def test_short_segments_beside_more_rows_than_their_masks_have_room_for():
     """The terms of short segments cost 36 bytes of descriptors per row tile: a batch of 3.4 million rows, whose other descriptors fit
     the 2 MiB slot, is accepted and its short segments keep their steps inside the GEMM."""
