@@ -1069,13 +1069,15 @@ __global__ void __launch_bounds__(256) symb_grad_reduce_kernel(const GradReduceP
 
 // -------------------------------------------------------------------------------------------
 // IA3 vector gradient:  dl_i[j] = sum_{t in segment i} dY[t][j] * Y0[t][j]
-// grid.x covers d_out in blocks of IA3_GRAD_COLS columns, grid.y indexes the IA3 segments that want it.
-// A thread owns 8 columns (16-byte loads) and every IA3_GRAD_LANES-th token, four tokens per step in flight;
-// partial sums meet in LDS in a fixed order.  Bound by HBM (4 bytes per element).  A launch lasts as long as
-// its longest segment's walk, so a workgroup is 1024 threads, 128 tokens side by side, on 64 columns (one
-// 128-byte line per row).  Measured on 11 segments of 8200 tokens together, 11008 wide: 96 us with 256 threads
-// on 128 columns (16 tokens side by side), 84 us now (4.3 TB/s; 87 on 128 columns, 105 on 256; starting the longest
-// segments first changes nothing).
+// grid.x covers d_out in blocks of COLS columns, grid.y indexes the IA3 segments that want it.
+// A thread owns 8 columns (16-byte loads) and every LN-th token, four tokens per step in flight;
+// partial sums meet in LDS in a fixed order.  Bound by HBM (4 bytes per element).  Two shapes:
+//   long   1024 threads, 128 tokens side by side on 64 columns (one 128-byte line per row): a launch lasts as long as its longest
+//          segment's walk.  11 segments of 8200 tokens together, 11008 wide: 84 us (4.3 TB/s), 96 in the short shape; one segment of 4096 tokens on
+//          4096 columns 22 / 39.
+//   short  256 threads, 16 tokens side by side on 128 columns: an eighth of the threads per segment.  64 segments of 16 tokens, 11008 wide:
+//          13 us, 71 in the long shape; 16 of 256 tokens, 4096 wide, 1.12 times the long shape's speed.
+// (Long shape on 128 columns 87 us, on 256 105; starting the longest segments first changes nothing.)
 // -------------------------------------------------------------------------------------------
 struct Ia3GradParams {
     const bf16* dY;
@@ -1088,17 +1090,19 @@ struct Ia3GradParams {
     const bf16* const* dY_seg;   // device [S] or null: per-segment buffers of the first / second operand
     const bf16* const* Y0_seg;
 };
-constexpr int IA3_GRAD_COLS = 64, IA3_GRAD_THREADS = 1024;
-constexpr int IA3_GRAD_CHUNKS = IA3_GRAD_COLS / 8, IA3_GRAD_LANES = IA3_GRAD_THREADS / IA3_GRAD_CHUNKS;
-__global__ void __launch_bounds__(IA3_GRAD_THREADS) symb_ia3_grad_kernel(const Ia3GradParams p) {
-    constexpr int LN = IA3_GRAD_LANES, WL = 64 / IA3_GRAD_CHUNKS, NW = IA3_GRAD_THREADS / 64;   // token lanes, of them per wavefront; wavefronts
-    __shared__ float red[NW][IA3_GRAD_COLS];
+constexpr int ia3_grad_cols(bool lng) { return lng ? 64 : 128; }
+constexpr int ia3_grad_threads(bool lng) { return lng ? 1024 : 256; }
+template <bool LONG>
+__global__ void __launch_bounds__(ia3_grad_threads(LONG)) symb_ia3_grad_kernel(const Ia3GradParams p) {
+    constexpr int COLS = ia3_grad_cols(LONG), THREADS = ia3_grad_threads(LONG), CHUNKS = COLS / 8, LN = THREADS / CHUNKS;
+    constexpr int WL = 64 / CHUNKS, NW = THREADS / 64;   // token lanes per wavefront; wavefronts
+    __shared__ float red[NW][COLS];
     const int s = p.seg_list[blockIdx.y];
     const int t_lo = p.off[s], t_hi = p.off[s + 1];
     const bf16* const gbase = p.dY_seg ? p.dY_seg[s] - (size_t)t_lo * p.d_out : p.dY;
     const bf16* const ybase = p.Y0_seg ? p.Y0_seg[s] - (size_t)t_lo * p.d_out : p.Y0;
-    const int cc = threadIdx.x % IA3_GRAD_CHUNKS, tl = threadIdx.x / IA3_GRAD_CHUNKS;
-    const int c = blockIdx.x * IA3_GRAD_COLS + cc * 8;
+    const int cc = threadIdx.x % CHUNKS, tl = threadIdx.x / CHUNKS;
+    const int c = blockIdx.x * COLS + cc * 8;
     float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     auto fma8 = [&](const uint4& g, const uint4& y) __attribute__((always_inline)) {
         const unsigned int gw[4] = {g.x, g.y, g.z, g.w}, yw[4] = {y.x, y.y, y.z, y.w};
@@ -1126,19 +1130,19 @@ __global__ void __launch_bounds__(IA3_GRAD_THREADS) symb_ia3_grad_kernel(const I
             fma8(g, y);
         }
     }
-    // the token lanes of a wavefront first (lanes 8 apart hold the same columns), then the wavefronts
+    // the token lanes of a wavefront first (lanes CHUNKS apart hold the same columns), then the wavefronts
 #pragma unroll
     for (int q = 0; q < 8; ++q)
 #pragma unroll
-        for (int m = IA3_GRAD_CHUNKS; m < 64; m *= 2) a[q] += __shfl_xor(a[q], m);
-    static_assert(WL * IA3_GRAD_CHUNKS == 64, "whole rows of chunks per wavefront");
+        for (int m = CHUNKS; m < 64; m *= 2) a[q] += __shfl_xor(a[q], m);
+    static_assert(WL * CHUNKS == 64, "whole rows of chunks per wavefront");
     if ((tl % WL) == 0) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) red[tl / WL][cc * 8 + q] = a[q];
     }
     __syncthreads();
-    const int j = blockIdx.x * IA3_GRAD_COLS + threadIdx.x;
-    if (threadIdx.x < IA3_GRAD_COLS && j < p.d_out) {
+    const int j = blockIdx.x * COLS + threadIdx.x;
+    if (threadIdx.x < COLS && j < p.d_out) {
         float v = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) v += red[w][threadIdx.x];

@@ -817,6 +817,35 @@ symb_status launch_grad(symb_handle h, const GradParams& gp, int wave_rpad, int 
 }
 // Adds up the runs of the split segments (none: nothing to do).  At most 128 * 36864 floats per segment
 // at 1024 per workgroup and pass.
+// Stable sort of a list that mostly is sorted: calls of many small segments are bound by the host.
+template <class LESS>
+void sort_once(std::vector<int32_t>& v, LESS&& less) {
+    if (!std::is_sorted(v.begin(), v.end(), less)) std::stable_sort(v.begin(), v.end(), less);
+}
+
+// IA3 gradients of the segments `want` (the list p.seg_list holds on the device).  The long shape of the kernel where the longest walk sets the
+// time: from 1024 tokens on, or from 192 where the short shape would have at most 128 workgroups (2 segments of 256 tokens, 4096 wide: 0.84
+// of the short shape's time, 8 segments 1.15; 768 wide, 16 segments 0.93).  Segments of both kinds share the long shape's launch unless the
+// short ones would be more than 2048 workgroups of it.
+symb_status launch_ia3_grad(symb_handle h, const symb_batch* b, Ia3GradParams p, const std::vector<int32_t>& want, hipStream_t st) {
+    const auto tokens = [&](int i) { return b->seg_offsets[i + 1] - b->seg_offsets[i]; };
+    const auto blocks = [&](bool lng) { return (unsigned)((p.d_out + ia3_grad_cols(lng) - 1) / ia3_grad_cols(lng)); };
+    const int least = blocks(false) * want.size() <= 128 ? 192 : 1024;
+    size_t n_long = 0;                                   // (the list is sorted by it)
+    while (n_long < want.size() && tokens(want[n_long]) >= least) ++n_long;
+    if (n_long && (want.size() - n_long) * blocks(true) <= 2048) n_long = want.size();
+    if (n_long) {
+        hipLaunchKernelGGL(symb_ia3_grad_kernel<true>, dim3(blocks(true), (unsigned)n_long), dim3(ia3_grad_threads(true)), 0, st, p);
+        SYMB_HIP(h, hipGetLastError());
+    }
+    if (n_long < want.size()) {
+        p.seg_list += n_long;
+        hipLaunchKernelGGL(symb_ia3_grad_kernel<false>, dim3(blocks(false), (unsigned)(want.size() - n_long)), dim3(ia3_grad_threads(false)), 0, st, p);
+        SYMB_HIP(h, hipGetLastError());
+    }
+    return SYMB_OK;
+}
+
 symb_status launch_grad_reduce(symb_handle h, const GradReduceParams& rp, int nsplit, hipStream_t st) {
     if (nsplit == 0) return SYMB_OK;
     hipLaunchKernelGGL(symb_grad_reduce_kernel, dim3(1024, nsplit), dim3(256), 0, st, rp);
@@ -1763,6 +1792,8 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
         return fail(h, SYMB_ERR_INVALID_ARG, "an IA3_IN segment wants dl but dXbase (the input gradient before the input scale) is null");
     if (!want_l.empty() && !(seg_io ? (const void*)Ybase_seg : Ybase))
         return fail(h, SYMB_ERR_INVALID_ARG, "an IA3 segment wants dl but Ybase (the pre-adapter output) is null");
+    for (auto* w : {&want_l, &want_lin})                 // longest first (launch_ia3_grad)
+        sort_once(*w, [&](int x, int y) { return b->seg_offsets[x + 1] - b->seg_offsets[x] > b->seg_offsets[y + 1] - b->seg_offsets[y]; });
     const bool any_lora = !want_a.empty() || !want_b.empty();
     const WsLayout wl = ws_layout(b, bi, SYMB_OP_ADAPTER_GRAD, true, any_lora);
     if (wl.total > ws_bytes || (wl.total && !ws))
@@ -1926,14 +1957,12 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
     if (!want_l.empty()) {
         Ia3GradParams ip{(const bf16*)dY, (const bf16*)Ybase, b->d_out, doff, dseg, (const int32_t*)(dev + o_wl), acc ? 1 : 0,
                          seg_io ? (const bf16* const*)(dev + o_gs) : nullptr, seg_io ? (const bf16* const*)(dev + o_ys) : nullptr};
-        hipLaunchKernelGGL(symb_ia3_grad_kernel, dim3((b->d_out + IA3_GRAD_COLS - 1) / IA3_GRAD_COLS, (unsigned)want_l.size()), dim3(IA3_GRAD_THREADS), 0, s, ip);
-        SYMB_HIP(h, hipGetLastError());
+        if ((st = launch_ia3_grad(h, b, ip, want_l, s)) != SYMB_OK) return st;
     }
     if (!want_lin.empty()) {     // dl_i[k] = sum_t X[t][k] * (dY W)[t][k]: the same reduction over the input width
         Ia3GradParams ip{(const bf16*)X, (const bf16*)dXbase, b->d_in, doff, dseg, (const int32_t*)(dev + o_wli), acc ? 1 : 0,
                          seg_io ? (const bf16* const*)(dev + o_xs) : nullptr, seg_io ? (const bf16* const*)(dev + o_ys) : nullptr};
-        hipLaunchKernelGGL(symb_ia3_grad_kernel, dim3((b->d_in + IA3_GRAD_COLS - 1) / IA3_GRAD_COLS, (unsigned)want_lin.size()), dim3(IA3_GRAD_THREADS), 0, s, ip);
-        SYMB_HIP(h, hipGetLastError());
+        if ((st = launch_ia3_grad(h, b, ip, want_lin, s)) != SYMB_OK) return st;
     }
     { guard.completed = true; return seal_slot(h, s); }
 }

@@ -7,7 +7,7 @@ import torch
 import gpu_harness as gh
 import oracle
 import synth
-from helpers import check_dx, check_y
+from helpers import assert_close, check_dx, check_y
 from paper_2507_03220_amd import binding as sb
 
 pytestmark = pytest.mark.gpu
@@ -67,3 +67,25 @@ def test_ia3_vector_gradient(width, lens):
         # fp32 products and sums in any order: at most (n + 1) roundings of 2^-24 of the absolute sum
         bound = (n + 1) * 2.0 ** -24 * np.abs(synth.bf16_bits_to_f64(G[rows]) * synth.bf16_bits_to_f64(Y0[rows])).sum(0)
         assert np.all(np.abs(got.descs[i].dA.cpu().numpy() - ref) <= bound + 1e-300)
+
+
+@pytest.mark.parametrize("width,lens", [(72, [1, 15, 16, 17, 63, 64, 65]), (264, [191, 192, 193]), (136, [1023, 1024, 1025, 2]), (40, [200] * 3 + [1, 0]),
+                                        (2248, [3] * 60 + [1100])])        # both shapes of the kernel, in one launch and (last) in two
+def test_ia3_gradient(width, lens):
+    rng = np.random.default_rng(width)
+    off = np.zeros(len(lens) + 1, dtype=np.int32)
+    off[1:] = np.cumsum(lens)
+    T = int(off[-1])
+    dY, Y0 = _bits(rng, (T, width)), _bits(rng, (T, width))
+    l = gh.to_dev(_bits(rng, (width,)))
+    dl = [torch.full((width,), float("nan"), device="cuda") for _ in lens]
+    b = sb.Batch(8, width, off, [sb.Adapter(sb.SYMB_ADAPTER_IA3, 0, 0.0, l, None, d) for d in dl])
+    X = torch.zeros(T, 8, device="cuda", dtype=torch.bfloat16)
+    dYd, Yd = gh.to_dev(dY), gh.to_dev(Y0)
+    for times, flag in ((1, sb.SYMB_GRAD_OVERWRITE), (2, sb.SYMB_GRAD_ACCUMULATE)):
+        sb.symb_adapter_grad(gh.handle(), b, X, dYd, Yd, flag, None)
+        torch.cuda.synchronize()
+        for i, n in enumerate(lens):
+            rows = slice(off[i], off[i + 1])
+            ref = times * (synth.bf16_bits_to_f64(dY[rows]) * synth.bf16_bits_to_f64(Y0[rows])).sum(0)
+            assert_close(dl[i].cpu().numpy(), ref, f"dl[{i}] x{times}")
