@@ -174,9 +174,10 @@ symb_status symb_plan_row_tiles(const symb_batch* b, int32_t tile_m, int32_t* se
  * same bits, whatever order the workgroups finish in); a split call sums the inner dimension
  * in a different order than an unsplit one, so the two can differ in the last rounding.  For
  * SYMB_OP_ADAPTER_GRAD the figure includes room for the partial sums of LoRA gradients of
- * segments longer than 1536 tokens (summed in runs of 1024 tokens, the runs added in order: a
- * segment's gradient does not depend on what else is in the batch) and, for ranks up to 16 on
- * layers at least 16384 wide, for the partial sums of dH of the pass that forms dB and dH together. */
+ * segments longer than 1536 tokens (summed in runs of 1024 tokens, the runs added in order)
+ * and, for ranks up to 16 on layers at least 16384 wide, for the partial sums of dH of the pass that
+ * forms dB and dH together.  Kernels are chosen for a call as a whole: what else is in the batch can
+ * change a segment's outputs and gradients in the last rounding. */
 symb_status symb_workspace_bytes(const symb_batch* b, int32_t op, size_t* out);
 
 /*

@@ -409,8 +409,7 @@ __global__ void __launch_bounds__(256) symb_pack_at_kernel(const PackAtParams p)
 // tokens, one of its runs of GRAD_SPLIT tokens: a long segment walked by one workgroup per
 // column block would set the time of the whole launch.  Such a run leaves its sum in the
 // workspace (same layout as the result) and symb_grad_reduce_kernel adds the runs up in
-// order.  Fixed summation order, a function of the segment's length alone: results do not
-// depend on the launch or on the rest of the batch.
+// order.  Fixed summation order within this kernel, a function of the segment's length alone.
 // -------------------------------------------------------------------------------------------
 constexpr int GRAD_SPLIT = 1024;       // tokens per run of a split segment (a multiple of GRAD_TT)
 constexpr int GRAD_SPLIT_MIN = 1536;   // segments up to this length stay whole
@@ -439,19 +438,17 @@ struct GradWalk {
     static constexpr int CT = GRAD_CT<RB>;
     static constexpr int RPITCH = CT * 2 + 16;             // LDS row pitch of the R tile in bytes
     static constexpr int LP = 2 * RB * 16 * 2 + 16;        // LDS row pitch of the L tile (value | residual) in bytes
-    static constexpr int BYTES = GRAD_TT * (RPITCH + LP);
+    static constexpr int R_BYTES = GRAD_TT * RPITCH, L_BYTES = GRAD_TT * LP, BYTES = R_BYTES + L_BYTES;
 };
 template <int RB, bool CMAJOR>
-__device__ __forceinline__ void lora_grad_walk(const GradParams& p, const GradItem& it, const SegDesc& sd, unsigned char* smem) {
+__device__ __forceinline__ void lora_grad_walk(const GradParams& p, const GradItem& it, const SegDesc& sd, int block, unsigned char* sR, unsigned char* sL) {
     constexpr int CT = GradWalk<RB>::CT, NI = CT / 64;      // columns per workgroup, 16-column blocks per wavefront
     constexpr int RPITCH = GradWalk<RB>::RPITCH, LP = GradWalk<RB>::LP;
     constexpr int LPRW = CT / 8, NRC = GRAD_TT * LPRW / 256;   // 16-byte chunks per R row, R chunks per thread
-    unsigned char* const sR = smem;
-    unsigned char* const sL = smem + GRAD_TT * RPITCH;
     const int s = it.seg;
     const int t_lo = it.t_lo, t_hi = it.t_hi;
     const bf16* const rbase = p.R_seg ? p.R_seg[s] - (size_t)p.off[s] * p.ncols : p.R;
-    const int c0 = blockIdx.x * CT;
+    const int c0 = block * CT;
     const int nb = sd.rpad >> 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
@@ -579,24 +576,24 @@ __device__ __forceinline__ void lora_grad_walk(const GradParams& p, const GradIt
 template <int RB, bool CMAJOR>
 __global__ void __launch_bounds__(256)
 symb_lora_grad_kernel(const GradParams p) {
-    __shared__ __attribute__((aligned(16))) unsigned char smem[GradWalk<RB>::BYTES];
+    __shared__ __attribute__((aligned(16))) unsigned char sR[GradWalk<RB>::R_BYTES], sL[GradWalk<RB>::L_BYTES];
     const GradItem it = p.items[blockIdx.y];
-    lora_grad_walk<RB, CMAJOR>(p, it, p.seg[it.seg], smem);
+    const SegDesc sd = p.seg[it.seg];
+    lora_grad_walk<RB, CMAJOR>(p, it, sd, blockIdx.x, sR, sL);
 }
 
 // -------------------------------------------------------------------------------------------
 // The same gradients for ranks up to 64, with the tokens of a work item dealt out over the wavefronts: each takes every fourth
 // slice of 32 tokens, brings its rows of R and L in by LDS DMA into two buffers of its own (no workgroup barrier in the loop) and
-// accumulates all 128 columns; the wavefronts' sums meet in LDS in a fixed order at the end.  Bound by HBM (R once); a launch of
-// few workgroups lasts as long as its longest walk, which is a quarter as many steps as in symb_lora_grad_kernel.  Measured, before /
-// now: dB of 16 segments of 1024 tokens, 256 columns, rank 8, 25.3 / 12.2 us; dA of 20 segments, 4608 columns, 45 / 41.
-// 13 runs of 5120 tokens of ranks 8 to 64, 4096 columns, dB 43.5 / 34.3, dA 35.5 / 26.9 (in launches of their own, ranks to 16 and the
-// rest: 49 and 41).
-// Above rank 64 the L rows, re-read by every column block, outweigh R and their LDS halves the tile (20 clients of 1024 tokens at rank 128
-// on 6144 -> 256: the gradient call 387 us against 300): those segments keep symb_lora_grad_kernel's walk.  So does dB of layers of
+// accumulates all 128 columns; the wavefronts' sums meet in LDS in a fixed order at the end.  Bound by HBM (R once).  A launch of few
+// workgroups lasts as long as its longest walk, which is a quarter as many steps as in symb_lora_grad_kernel: dB of 16 segments of 1024 tokens,
+// 256 columns, rank 8, 25.3 -> 12.2 us; 13 runs of 5120 tokens of ranks 8 to 64, 4096 columns, dB 43.5 -> 34.3, dA 35.5 -> 26.9.  But a workgroup
+// takes 80 to 128 KiB of LDS, where the other kernel's takes 17 to 19, and adds four sets of sums up, so launches of many workgroups, and short
+// segments, are that kernel's (16-row segments, 64 of them, dA + dB on 4096 columns: rank 8 17 us against 30, rank 32 34 / 77): grad_wave()
+// in the host code has the line.  Above rank 64 the L rows, re-read by every column block, outweigh R and their LDS halves the tile (20 clients of
+// 1024 tokens at rank 128 on 6144 -> 256: the gradient call 387 us against 300): those segments always keep that walk.  So does dB of layers of
 // GRAD_WIDE columns and more, where one pass over dY forms dB and dH in that kernel's order, and the two ways to a gradient give the
-// same bits.  The choice rests on the segment's own rank and the width: a client's gradient bits do not depend on the rest of the batch
-// (RB, the widest rank of the launch, only sizes the LDS).
+// same bits.
 // R slice: 32 token rows of 128 columns, L slice: 32 rows of 2 rpad, 32-byte pieces of row t stored at piece ^ skinny_bt_swz (rows of
 // 64 elements and more).  Tokens past the item's last one repeat it and are masked in the fragments of the last slice.
 // -------------------------------------------------------------------------------------------
@@ -780,16 +777,17 @@ symb_lora_grad_wave_kernel(const GradParams p) {
         if (sd.rpad <= 32) lora_grad_wave<2, CMAJOR>(p, it, sd, blockIdx.x, smem);
         else if constexpr (RB >= 4) {
             if (sd.rpad <= GRAD_WAVE_RANK) lora_grad_wave<4, CMAJOR>(p, it, sd, blockIdx.x, smem);
-            else if constexpr (RB >= 8) lora_grad_walk<8, CMAJOR>(p, it, sd, smem);
+            else if constexpr (RB >= 8) lora_grad_walk<8, CMAJOR>(p, it, sd, blockIdx.x, smem, smem + GradWalk<8>::R_BYTES);
         }
     }
 }
 
 // dH of a gradient call beside its dB, ranks up to 64: nchunks workgroups of the backward shrink, then those of dB.  Neither needs the
-// other's result, and a small call's time is its launches: training step of 4 x 64 tokens on 768 columns 46.9 -> 43.0 us.
+// other's result, and a small call's time is its launches: training step of 4 x 64 tokens on 768 columns 46.9 -> 43.0 us.  wave: see grad_wave()
+// in the host code (without it ranks above 32, whose walk has blocks of 128 columns too).
 template <int RB>
 __global__ void __launch_bounds__(256)
-symb_lora_grad_pair_kernel(const SkinnyParams sp, int nchunks, const GradParams gp, int col_blocks) {
+symb_lora_grad_pair_kernel(const SkinnyParams sp, int nchunks, const GradParams gp, int col_blocks, int wave) {
     constexpr int BYTES = skinny_lds<RB, true>() > GradWave<RB>::BYTES ? skinny_lds<RB, true>() : GradWave<RB>::BYTES;
     __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES];
     if ((int)blockIdx.x < nchunks) {
@@ -799,6 +797,13 @@ symb_lora_grad_pair_kernel(const SkinnyParams sp, int nchunks, const GradParams 
     const int g = blockIdx.x - nchunks, block = g % col_blocks;
     const GradItem it = gp.items[g / col_blocks];
     const SegDesc sd = gp.seg[it.seg];
+    if constexpr (RB == 4) {
+        static_assert(GRAD_CT<4> == GRAD_WAVE_CT && GradWalk<4>::BYTES <= BYTES, "both walks share a grid and the LDS");
+        if (!wave) {
+            lora_grad_walk<4, true>(gp, it, sd, block, smem, smem + GradWalk<4>::R_BYTES);
+            return;
+        }
+    }
     if (sd.rpad <= 16) lora_grad_wave<1, true>(gp, it, sd, block, smem);
     else if constexpr (RB >= 2) {
         if (sd.rpad <= 32) lora_grad_wave<2, true>(gp, it, sd, block, smem);

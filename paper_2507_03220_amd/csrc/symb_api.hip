@@ -793,6 +793,26 @@ template <int RB, bool CM>
 void launch_grad_wave(const GradParams& gp, int nitems, hipStream_t st) {
     hipLaunchKernelGGL((symb_lora_grad_wave_kernel<RB, CM>), dim3((gp.ncols + GRAD_WAVE_CT - 1) / GRAD_WAVE_CT, nitems), dim3(256), 0, st, gp);
 }
+// Whether a launch takes the kernel that deals tokens out over the wavefronts.  `w` is about the launch's workgroups at its widest rank: with more than one
+// per CU (two, for ranks to 16) the other kernel, which fits many of them on one, is faster unless the walks are long; and a workgroup of the
+// widest kernel (128 KiB of LDS) needs a long walk to pay for its sums.  Measured on both gradients of 2 to 64 segments of 16 to 1024 tokens, 768, 4096 and 11008
+// columns, time against the other kernel's: rank 8, 512 workgroups 1.05 (32 tokens) 0.94 (64 to 512), 1376 1.35 (16) 1.05 (192) 1.00 (512); rank 32, 256
+// workgroups 0.82 to 1.04, 384 1.5 to 1.2, 688 1.36 (16) 1.13 (192) 0.93 (1024); rank 64, 64 workgroups 1.34 (16) 1.01 (256) 0.82 (1024), 512 1.7 to 1.2.
+bool grad_wave(const symb_batch* b, const std::vector<GradItem>& items, int ncols) {
+    int most = 0, least = INT32_MAX;
+    long long tokens = 0, ranks = 0;
+    for (const GradItem& it : items) {
+        const int r = rpad_of(b->adapters[it.seg].rank);
+        most = std::max(most, r);
+        least = std::min(least, r);
+        tokens += it.t_hi - it.t_lo;
+        ranks += r;
+    }
+    if (items.empty() || least > GRAD_WAVE_RANK) return false;
+    const double w = (double)((ncols + GRAD_WAVE_CT - 1) / GRAD_WAVE_CT) * (double)ranks / most, mean = (double)tokens / (double)items.size();
+    if (most <= 16) return w <= 256 || mean >= 256 || (w <= 512 && mean >= 64);
+    return w <= 256 && (most <= 32 || mean >= 384);
+}
 // wave_rpad: the items take the kernel that deals tokens out over the wavefronts, this is their widest rank (plan_items; 0: the other one).
 template <bool CM>
 symb_status launch_grad(symb_handle h, const GradParams& gp, int wave_rpad, int nitems, int max_rpad, hipStream_t st) {
@@ -803,14 +823,10 @@ symb_status launch_grad(symb_handle h, const GradParams& gp, int wave_rpad, int 
         else if (wave_rpad <= 64) launch_grad_wave<4, CM>(gp, nitems, st);
         else launch_grad_wave<8, CM>(gp, nitems, st);
     } else {
-        if constexpr (CM) {                  // (wide dB; everything else comes here above rank 64 only)
-            if (max_rpad <= 16) launch_grad_rb<1, CM>(gp, nitems, st);
-            else if (max_rpad <= 32) launch_grad_rb<2, CM>(gp, nitems, st);
-            else if (max_rpad <= 64) launch_grad_rb<4, CM>(gp, nitems, st);
-            else launch_grad_rb<8, CM>(gp, nitems, st);
-        } else {
-            launch_grad_rb<8, CM>(gp, nitems, st);
-        }
+        if (max_rpad <= 16) launch_grad_rb<1, CM>(gp, nitems, st);
+        else if (max_rpad <= 32) launch_grad_rb<2, CM>(gp, nitems, st);
+        else if (max_rpad <= 64) launch_grad_rb<4, CM>(gp, nitems, st);
+        else launch_grad_rb<8, CM>(gp, nitems, st);
     }
     SYMB_HIP(h, hipGetLastError());
     return SYMB_OK;
@@ -1829,11 +1845,10 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
     }
     // Work items of the two gradient launches: whole segments, or the runs of long ones (see grad_runs).
     // Widest ranks (the longest walks) first.  Returns the widest rank (padded) if the items take the kernel that deals tokens out over the
-    // wavefronts; 0, for the other one, in a wide layer's dB and where every rank is above that kernel's limit.
+    // wavefronts (grad_wave); 0, for the other one, also in a wide layer's dB.
     auto plan_items = [&](std::vector<int32_t> want, int ncols, bool of_b, std::vector<GradItem>& items, std::vector<GradReduceItem>& red) {
         const auto rpad = [&](int i) { return rpad_of(b->adapters[i].rank); };
-        std::stable_sort(want.begin(), want.end(), [&](int x, int y) { return rpad(x) > rpad(y); });
-        const int wave_rpad = want.empty() || (of_b && ncols >= GRAD_WIDE) || rpad(want.back()) > GRAD_WAVE_RANK ? 0 : rpad(want[0]);
+        sort_once(want, [&](int x, int y) { return rpad(x) > rpad(y); });
         int64_t cur = 0;
         for (int i : want) {
             const int lo = b->seg_offsets[i], hi = b->seg_offsets[i + 1], runs = grad_runs(hi - lo);
@@ -1846,7 +1861,7 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
             for (int q = 0; q < runs; ++q, cur += n)
                 items.push_back(GradItem{i, lo + q * GRAD_SPLIT, std::min(hi, lo + (q + 1) * GRAD_SPLIT), 0, cur});
         }
-        return wave_rpad;
+        return want.empty() || (of_b && ncols >= GRAD_WIDE) || !grad_wave(b, items, ncols) ? 0 : rpad(want[0]);
     };
     std::vector<GradItem> it_a, it_b;
     std::vector<GradReduceItem> red_a, red_b;
@@ -1924,7 +1939,7 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
     } else if (!want_b.empty()) {       // dB_i = s_i * dY_i^T H_i  ==  dY_i^T Hs_i
         // small calls: dH beside dB in one launch (at most one workgroup per CU)
         const int col_blocks = (b->d_out + GRAD_WAVE_CT - 1) / GRAD_WAVE_CT;
-        const bool pair = !have_dh && !want_a.empty() && wave_rpad_b > 0 && grad_max_rpad <= GRAD_WAVE_RANK && h->opt_skinny_deep && reads_bt(b) &&
+        const bool pair = !have_dh && !want_a.empty() && b->d_out < GRAD_WIDE && (wave_rpad_b > 0 || grad_max_rpad > 32) && grad_max_rpad <= GRAD_WAVE_RANK && h->opt_skinny_deep && reads_bt(b) &&
                           (long long)ch_dh.size() + (long long)col_blocks * (long long)it_b.size() <= 256;
         if (!reuse_hs && (st = run_skinny_h()) != SYMB_OK) return st;
         GradParams gp{(const bf16*)dY, (const bf16*)(wsb + wl.h_off), b->d_out, 2 * bi.max_rpad, doff, dseg,
@@ -1933,7 +1948,7 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
         if (pair) {
             const dim3 grid((unsigned)(ch_dh.size() + (size_t)col_blocks * it_b.size()));
             const SkinnyParams sp = skinny_dh();
-            auto launch = [&](auto kfn) { hipLaunchKernelGGL(kfn, grid, dim3(256), 0, s, sp, (int)ch_dh.size(), gp, col_blocks); };
+            auto launch = [&](auto kfn) { hipLaunchKernelGGL(kfn, grid, dim3(256), 0, s, sp, (int)ch_dh.size(), gp, col_blocks, wave_rpad_b > 0 ? 1 : 0); };
             if (grad_max_rpad <= 16) launch(symb_lora_grad_pair_kernel<1>);
             else if (grad_max_rpad <= 32) launch(symb_lora_grad_pair_kernel<2>);
             else launch(symb_lora_grad_pair_kernel<4>);

@@ -55,3 +55,16 @@ def test_gradients_over_slices_of_tokens(lens, ranks, dims):
         assert_close(dB.cpu().numpy(), dBr, f"dB[{i}]")
         assert_close(d.dA.cpu().numpy(), 2 * dAr, f"accumulated dA[{i}]")
         assert_close(d.dB.cpu().numpy(), 2 * dBr, f"accumulated dB[{i}]")
+
+
+@pytest.mark.parametrize("ranks", [[8], [32], [64, 48], [8, 16, 32, 64], [5, 100]])
+@pytest.mark.parametrize("lens", [[16] * 40, [1, 33, 7] * 8, [400, 390, 16]])
+def test_gradients_of_many_short_segments(lens, ranks):
+    """Launches of more workgroups than CUs, of few and of short walks: both gradient kernels, dB alone and beside dH."""
+    p = make_problem(len(lens) + sum(ranks), 264, 1032, lens, [L], ranks)
+    off, oads = p["off"], oracle_ads(p["ads"])
+    dev = gh.adapter_grad(off, p["ads"], p["X"], p["dY"])
+    for i, d in enumerate(dev.descs):
+        dAr, dBr = oracle.lora_grad(off, oads, p["X"], p["dY"], i)
+        assert_close(d.dA.cpu().numpy(), dAr, f"dA[{i}]")
+        assert_close(d.dB.cpu().numpy(), dBr, f"dB[{i}]")
