@@ -791,10 +791,11 @@ def test_one_buffer_per_client_for_input_and_output(case):
     check_dx(gather(d_in), off, oads, p["dY"], p["W"], "in-place dX")
 
 
-@pytest.mark.parametrize("lens", [[1], [16], [9, 0, 7], [1, 1, 5, 1, 1, 4], [3, 1, 2, 1, 1, 2, 1, 1]])
+@pytest.mark.parametrize("lens", [[1], [16], [9, 0, 7], [1, 1, 5, 1, 1, 4], [3, 1, 2, 1, 1, 2, 1, 1],
+                                  [17], [20, 0, 1, 3, 4], [33], [40, 2, 11, 1, 0, 6], [64], [7, 9, 20, 1, 16, 8, 2, 1]])
 @pytest.mark.parametrize("dims", [(200, 392), (392, 200), (4096, 4096)])
 def test_a_handful_of_rows_in_every_call_form(lens, dims):
-    """Calls of at most 16 rows take the weight-streaming kernels in every form: forward with the
+    """Calls of at most 64 rows take the weight-streaming kernels in every form: forward with the
     pre-adapter output, input-major weight, IA3 on the input, the privacy flow's epilogue, per-client
     buffers (also one buffer for input and output); input gradient, full and base-only, with the
     pre-adapter gradient, through either weight layout and from per-client buffers.  Every adapter kind,
@@ -802,11 +803,11 @@ def test_a_handful_of_rows_in_every_call_form(lens, dims):
     d_in, d_out = dims
     big = d_in * d_out > 1 << 20
     if big and len(lens) not in (1, 6):
-        pytest.skip("the real layer width runs two of the row mixes")
+        pytest.skip("the real layer width runs the row mixes of one and of six segments")
     kinds = [L, I, N, L, 3, I, L, 3]
     p = make_problem(400 + len(lens) + d_in, d_in, d_out, lens, kinds, [1, 128, 24, 8, 100] if not big else [16, 8, 64])
     off, T, S = p["off"], p["T"], len(p["ads"])
-    assert 0 < T <= 16
+    assert 0 < T <= 64
     oads = oracle_ads(p["ads"])
     h = gh.handle()
     Y0r, Yr = oracle.forward(off, oads, p["X"], p["W"], p["bias"])
@@ -814,7 +815,10 @@ def test_a_handful_of_rows_in_every_call_form(lens, dims):
     kind_of_row = np.array([p["ads"][int(np.searchsorted(off, t, side="right") - 1)].kind for t in range(T)])
     plain_in = np.flatnonzero(kind_of_row != 3)       # rows of input-scaling segments hold the product of the scaled input in Ybase
     for conv1d in (False, True):
-        Y, Yb = gh.forward(off, p["ads"], p["X"], p["W"], p["bias"], want_base=True, conv1d=conv1d)
+        res = []
+        ran = gh.gemm_launches(lambda: res.append(gh.forward(off, p["ads"], p["X"], p["W"], p["bias"], want_base=True, conv1d=conv1d)))
+        assert ran == {}, "the streaming kernels did not run"
+        Y, Yb = res[0]
         assert_close_client(gh.bf16_to_f64(Y), Yr, Yc, f"small Y conv1d={conv1d}")
         assert_close(gh.bf16_to_f64(Yb)[plain_in], Y0r[plain_in], f"small Ybase conv1d={conv1d}", out_bf16=True)
         if (kind_of_row == 3).any():
@@ -966,7 +970,7 @@ def test_gradient_call_first_then_the_input_gradient_takes_its_dh(case):
     # the 256x256 tile in the forward (one LoRA step fetched while another multiplies), about 110 segments per row tile
     dict(seed=102, S=1000, d_in=136, d_out=6208),
 ])
-def test_thousands_of_clients_of_a_few_tokens_each(case):
+def test_thousands_of_clients_of_a_few_tokens_each(case, monkeypatch):
     """A decode-heavy batch (Sec. 3.7: many inference clients, a token or a few each, batched per layer):
     thousands of segments of 0..9 rows with every adapter kind and ranks 3..16, each with buffers of its
     own, so that every row tile holds dozens of segments.  Everything against the oracle in full."""
@@ -975,6 +979,28 @@ def test_thousands_of_clients_of_a_few_tokens_each(case):
     p = make_problem(case["seed"], case["d_in"], case["d_out"], lens, [L, L, I, N, L], [4, 8, 16, 3])
     print(f"[many clients] S={case['S']} T={p['T']} {case['d_in']}->{case['d_out']}", flush=True)
     check_all(p, f"{case['S']} clients")
+    # the short segments' terms come from memory; without room for them (the end of the workspace) they are steps inside the GEMM
+    rows = sum(n for n, x in zip(lens, p["ads"]) if x.kind == L)
+    room = {sb.SYMB_OP_FWD: (rows * case["d_out"] * 4 + 255) // 256 * 256, sb.SYMB_OP_BWD_INPUT: (rows * case["d_in"] * 4 + 255) // 256 * 256}
+    whole_ws, off, oads = gh.workspace, p["off"], oracle_ads(p["ads"])
+
+    def timed(call):
+        sb.symb_debug_gemm_timing_enable(gh.handle(), 1)
+        try:
+            out = call()
+            return out, sum(sb.symb_debug_gemm_timing_read(gh.handle(), v)[2] for v in range(8))
+        finally:
+            sb.symb_debug_gemm_timing_enable(gh.handle(), 0)
+    forward = lambda: gh.forward(off, p["ads"], p["X"], p["W"], p["bias"], want_base=False)[0]
+    backward = lambda: gh.backward_input(off, p["ads"], p["dY"], p["W"])
+    (_, fwd_work), (_, bwd_work) = timed(forward), timed(backward)
+    monkeypatch.setattr(gh, "workspace", lambda b, op: whole_ws(b, op)[:-room[op]])
+    Y, work = timed(forward)
+    assert work > fwd_work
+    check_y(gh.bf16_to_f64(Y), off, oads, p["X"], p["W"], p["bias"], "Y, steps in the GEMM")
+    dX, work = timed(backward)
+    assert work > bwd_work or case["d_in"] < case["d_out"] // 8          # a long K's parts share the steps: no terms, and now no parts either
+    check_dx(gh.bf16_to_f64(dX), off, oads, p["dY"], p["W"], "dX, steps in the GEMM")
 
 
 def test_more_segments_than_the_descriptor_slot_holds_are_refused():

@@ -35,6 +35,94 @@ def test_edges_of_rows_and_widths(dims, lens):
             check_dx(gh.bf16_to_f64(dX), off, oads, p["dY"], p["W"], f"dX {dims} {lens} conv1d={conv1d}", base_only=base_only)
 
 
+@pytest.mark.parametrize("lens", [[1], [5, 0, 12, 15], [40, 0, 24]])
+@pytest.mark.parametrize("dims", [(520, 2048), (2000, 648)])
+def test_calls_without_lora_in_every_form(dims, lens):
+    """Base products finished in the streaming kernel itself (K up to 2048), the same calls in the tiled kernels, and which of them runs:
+    matrices, a buffer per client, one buffer for input and output, noise effects taken off."""
+    d_in, d_out = dims
+    p = make_problem(700 + d_in + sum(lens), d_in, d_out, lens, [I, N], [1])
+    off, T, S, oads, h = p["off"], p["T"], len(lens), oracle_ads(p["ads"]), gh.handle()
+    _, Yr = oracle.forward(off, oads, p["X"], p["W"], p["bias"])
+    dXr = oracle.backward_input(off, oads, p["dY"], p["W"])
+    rng = np.random.default_rng(17)
+    neff = [None if off[i + 1] == off[i] else synth.f32_to_bf16_bits(rng.standard_normal((1 if i % 2 else lens[i], d_out)).astype(np.float32)) for i in range(S)]
+    Ydr = oracle.forward_denoise(off, oads, p["X"], p["W"], p["bias"], neff)
+    Xd, Gd, bd = gh.to_dev(p["X"]), gh.to_dev(p["dY"]), gh.to_dev(p["bias"])
+    dev = gh.upload_adapters(p["ads"], d_in, d_out, grads=False)
+
+    def pieces(M, width):                # a buffer per segment, in one arena of rows wide enough for both sides
+        arena = torch.full((T + S, max(dims)), float("nan"), device="cuda", dtype=torch.bfloat16)
+        v = [arena[off[i] + i:off[i + 1] + i].view(-1)[:lens[i] * width].view(lens[i], width) if lens[i] else None for i in range(S)]
+        if M is not None:
+            for i in range(S):
+                if lens[i]:
+                    v[i].copy_(M[off[i]:off[i + 1]])
+        return v, lambda w: [None if x is None else torch.as_strided(x, (x.shape[0], w), (w, 1)) for x in v]
+
+    def joined(v):
+        return gh.bf16_to_f64(torch.cat([x for x in v if x is not None]))
+    try:
+        for conv1d in (0, 1):
+            b = sb.Batch(d_in, d_out, off, dev.descs, conv1d)
+            Wd = gh.weight_to_dev(p["W"], bool(conv1d))
+            fwd_ws, bwd_ws = gh.workspace(b, sb.SYMB_OP_FWD), gh.workspace(b, sb.SYMB_OP_BWD_INPUT)
+            for on in (1, 0):
+                sb.symb_debug_set_option(h, sb.SYMB_OPT_SMALL_BATCH_KERNELS, on)
+                Y, Yd = (torch.full((T, d_out), float("nan"), device="cuda", dtype=torch.bfloat16) for _ in range(2))
+                dX = torch.full((T, d_in), float("nan"), device="cuda", dtype=torch.bfloat16)
+                xin, _ = pieces(Xd, d_in)
+                yout, _ = pieces(None, d_out)
+                xy, xy_as = pieces(Xd, d_in)
+                gin, _ = pieces(Gd, d_out)
+                gout, _ = pieces(None, d_in)
+                gx, gx_as = pieces(Gd, d_out)
+                calls = {
+                    "Y": lambda: sb.symb_base_linear_fwd(h, b, Xd, Wd, bd, Y, None, fwd_ws),
+                    "denoised": lambda: sb.symb_base_linear_fwd_denoise(h, b, Xd, Wd, bd, [gh.to_dev(n) for n in neff], Yd, fwd_ws),
+                    "seg Y": lambda: sb.symb_base_linear_fwd_seg(h, b, xin, Wd, bd, yout, fwd_ws),
+                    "in-place Y": lambda: sb.symb_base_linear_fwd_seg(h, b, xy, Wd, bd, xy_as(d_out), gh.workspace(b, sb.SYMB_OP_FWD_INPLACE)),
+                    "dX": lambda: sb.symb_base_linear_bwd_input(h, b, Gd, Wd, dX, sb.SYMB_BWD_FULL, bwd_ws),
+                    "seg dX": lambda: sb.symb_base_linear_bwd_input_seg(h, b, gin, Wd, gout, sb.SYMB_BWD_FULL, bwd_ws),
+                    "in-place dX": lambda: sb.symb_base_linear_bwd_input_seg(h, b, gx, Wd, gx_as(d_in), sb.SYMB_BWD_FULL, gh.workspace(b, sb.SYMB_OP_BWD_INPUT_INPLACE))}
+                for name, call in calls.items():
+                    forward = "Y" in name or name == "denoised"
+                    across = forward == bool(conv1d)             # the weight is read across its rows: tiled above 32 rows
+                    streams = bool(on) and (T <= 32 or not across)
+                    ran = gh.gemm_launches(call)
+                    assert (ran == {}) == streams, f"{name} conv1d={conv1d} on={on}: {ran}"
+                torch.cuda.synchronize()
+                tag = f"conv1d={conv1d} on={on}"
+                assert_close(gh.bf16_to_f64(Y), Yr, f"Y {tag}", out_bf16=True)
+                assert_close(gh.bf16_to_f64(Yd), Ydr, f"denoised {tag}", out_bf16=True)
+                assert_close(joined(yout), Yr, f"seg Y {tag}", out_bf16=True)
+                assert_close(joined(xy_as(d_out)), Yr, f"in-place Y {tag}", out_bf16=True)
+                for got, what in ((gh.bf16_to_f64(dX), "dX"), (joined(gout), "seg dX"), (joined(gx_as(d_in)), "in-place dX")):
+                    assert_close(got, dXr, f"{what} {tag}", out_bf16=True)
+    finally:
+        sb.symb_debug_set_option(h, sb.SYMB_OPT_SMALL_BATCH_KERNELS, 1)
+
+
+def test_workspaces_at_their_limits():
+    """The exact figure takes the streaming kernels; one byte less the tiled one, down to H alone; less than that is refused."""
+    lens, d_in, d_out = [60, 4], 4104, 520
+    p = make_problem(77, d_in, d_out, lens, [L, I], [8])
+    off, oads, h = p["off"], oracle_ads(p["ads"]), gh.handle()
+    dev = gh.upload_adapters(p["ads"], d_in, d_out, grads=False)
+    b = sb.Batch(d_in, d_out, off, dev.descs)
+    X, W, bias = gh.to_dev(p["X"]), gh.to_dev(p["W"]), gh.to_dev(p["bias"])
+    ws = gh.workspace(b, sb.SYMB_OP_FWD)
+    hs = p["T"] * 2 * 16 * 2
+    for n, streams in ((ws.numel(), True), (ws.numel() - 1, False), (hs, False)):
+        Y = torch.full((p["T"], d_out), float("nan"), device="cuda", dtype=torch.bfloat16)
+        ran = gh.gemm_launches(lambda: sb.symb_base_linear_fwd(h, b, X, W, bias, Y, None, ws[:n]))
+        assert (ran == {}) == streams, f"{n} bytes: {ran}"
+        check_y(gh.bf16_to_f64(Y), off, oads, p["X"], p["W"], p["bias"], f"Y with {n} bytes")
+    with pytest.raises(sb.SymbError) as e:
+        sb.symb_base_linear_fwd(h, b, X, W, bias, Y, None, ws[:hs - 1])
+    assert e.value.status == sb.SYMB_ERR_WORKSPACE_TOO_SMALL
+
+
 @pytest.mark.parametrize("d_in,d_out,lens", [(5000, 10248, [1, 9, 6]),       # 40 tiles in 5 long ranges: one buffer
                                              (33000, 2056, [3, 9]), (33000, 2056, [20, 17])])      # more tiles than CUs
 def test_large_n_contiguous_weights(d_in, d_out, lens):
@@ -108,15 +196,24 @@ def test_gradients_take_hs_and_dh_from_the_streaming_calls(lens):
     check_dx(gh.bf16_to_f64(dX), off, oads, p["dY"], p["W"], "dX from the gradient call's dH")
 
 
-@pytest.mark.parametrize("T,d_in,d_out", [(2048, 264, 4096), (4096, 328, 2000), (397, 8320, 520), (100, 2056, 1032)])
-def test_tile_and_split_rules_of_mid_sized_batches(T, d_in, d_out):
-    """128 tiles of 256x256 run as 128x128 ones; a long inner dimension in twice the parts; at least 12 stages per part."""
+@pytest.mark.parametrize("T,d_in,d_out,tile,parts", [
+    (2048, 264, 4096, 128, 1), (4096, 328, 2000, 128, 1),         # 128 tiles of 256x256, as 512 of 128x128
+    (2048, 4680, 4096, 256, 2),                                   # above that rule's inner dimension: every tile in two parts
+    (100, 2056, 1032, 128, 4), (397, 8320, 520, 128, 8),
+    (397, 8200, 3400, 128, 4), (397, 12296, 2600, 128, 6)])       # parts of 64 stages: twice two and twice three
+def test_tile_and_split_rules_of_mid_sized_batches(T, d_in, d_out, tile, parts):
+    """The tile and the K parts a product of each rule runs in (by the partial tiles' bytes), and its results."""
+    plain = sb.Batch(d_in, d_out, [0, T], [sb.Adapter()])
+    partial = -(-T // tile) * -(-d_out // tile) * parts * tile * tile * 4 if parts > 1 else 0
+    assert sb.symb_workspace_bytes(plain, sb.SYMB_OP_FWD) == partial
     p = make_problem(T, d_in, d_out, [T // 2, T // 4, T - T // 2 - T // 4], [L, I, N], [16])
     rows = synth.sample_rows(p["off"], 12, f"mid{T}", block=128)
     oads = oracle_ads(p["ads"])
     for conv1d in (False, True):
-        Y, _ = gh.forward(p["off"], p["ads"], p["X"], p["W"], p["bias"], want_base=False, conv1d=conv1d)
-        check_y(gh.bf16_to_f64(Y)[rows], p["off"], oads, p["X"], p["W"], p["bias"], "Y", rows=rows)
+        res = []
+        ran = gh.gemm_launches(lambda: res.append(gh.forward(p["off"], p["ads"], p["X"], p["W"], p["bias"], want_base=False, conv1d=conv1d)[0]))
+        assert ran == {conv1d + (2 if tile == 128 else 0) + 4: 1}
+        check_y(gh.bf16_to_f64(res[0])[rows], p["off"], oads, p["X"], p["W"], p["bias"], "Y", rows=rows)
 
 
 @pytest.mark.parametrize("T,d_in,d_out,small", [
@@ -132,23 +229,33 @@ def test_tile_size(T, d_in, d_out, small):
         assert ran == {conv1d + (2 if small else 0): 1}
 
 
-@pytest.mark.parametrize("d_in,d_out", [(264, 392), (2056, 264), (200, 6216)])     # 128x128 tiles, split over K, 256x256 tiles
-def test_short_segments_of_a_larger_batch(d_in, d_out):
+@pytest.mark.parametrize("d_in,d_out,tile", [(264, 392, 128), (2056, 264, 128), (200, 9480, 256)])     # whole, split over K, large tiles
+def test_short_segments_of_a_larger_batch(d_in, d_out, tile):
     """LoRA terms of short segments are added from memory where a row tile holds many of their steps: scattered over the tiles,
     across a tile's edge, beside long segments, empty ones and other kinds; with the pre-adapter output; in both directions."""
     lens = [1] * 9 + [300, 16, 3, 0, 17] + [1, 2] * 8 + [200, 1, 40] + [1] * 5 + [5, 16, 260]
     kinds = [L, L, L, I, L, N, L]
     p = make_problem(5 + d_out, d_in, d_out, lens, kinds, [16, 128, 5, 40, 8, 33])
     off, oads = p["off"], oracle_ads(p["ads"])
+    b = sb.Batch(d_in, d_out, off, gh.upload_adapters(p["ads"], d_in, d_out, grads=False).descs)
+    steps_only = p["T"] * 2 * 128 * 2 + sb.symb_workspace_bytes(sb.Batch(d_in, d_out, [0, p["T"]], [sb.Adapter()]), sb.SYMB_OP_FWD)
+    assert sb.symb_workspace_bytes(b, sb.SYMB_OP_FWD) > steps_only + 16 * d_out * 4           # room for terms of more than 16 rows
+    small = 2 if tile == 128 else 0
+
+    def run(call):
+        res = []
+        ran = gh.gemm_launches(lambda: res.append(call()))
+        assert len(ran) == 1 and next(iter(ran)) & 2 == small
+        return res[0]
     for conv1d in (False, True):
         for want_base in (False, True):
-            Y, Yb = gh.forward(off, p["ads"], p["X"], p["W"], p["bias"], want_base=want_base, conv1d=conv1d)
+            Y, Yb = run(lambda: gh.forward(off, p["ads"], p["X"], p["W"], p["bias"], want_base=want_base, conv1d=conv1d))
             Y0r, _ = check_y(gh.bf16_to_f64(Y), off, oads, p["X"], p["W"], p["bias"], f"Y conv1d={conv1d}")
             if want_base:
                 assert_close(gh.bf16_to_f64(Yb), Y0r, "Ybase", out_bf16=True)
     q = make_problem(6 + d_out, d_out, d_in, lens, kinds, [16, 128, 5, 40, 8, 33])
     for conv1d in (False, True):
-        dX = gh.backward_input(off, q["ads"], q["dY"], q["W"], conv1d=conv1d)
+        dX = run(lambda: gh.backward_input(off, q["ads"], q["dY"], q["W"], conv1d=conv1d))
         check_dx(gh.bf16_to_f64(dX), off, oracle_ads(q["ads"]), q["dY"], q["W"], f"dX conv1d={conv1d}")
 
 
