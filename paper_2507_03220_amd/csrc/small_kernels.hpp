@@ -12,13 +12,14 @@
 //                              it also leaves H in the workspace as value + residual, as the skinny kernel does, for
 //                              a gradient call that takes it from there.
 //
-// A call without a LoRA term whose tiles need no K ranges is finished by the first kernel alone.
+// A call without a LoRA term whose tiles need no K ranges is finished by the first kernel alone, or, on a K-contiguous weight of at most 8192
+// columns and 10 M elements, by symb_small_narrow_kernel, whose tiles are narrower.  Which of these calls stay in the tiled kernels: small_wins.
 //
 // Bound by HBM: 2 K N bytes of weight plus 2 r (K + N) of each LoRA client.  What these calls spent their time on
 // before was one launch after the other (shrink, weight, for the input gradient also a transposed copy of B_i),
 // each a chain of memory latencies on a part of the chip, and from 17 rows on, in the tiled kernel, a chain of small steps for each
-// client's adapter.  Measured per call, before / now: one client on 4096 x 4096 21.9 / 14.3 us (7.8 us the first kernel, 4.3 TB/s; 4.2 the
-// second), 16 mixed clients on 4096 -> 11008 68.9 / 29.8, 48 clients of ranks to 128 on 11008 -> 4096 134.6 / 43.0.
+// client's adapter.  Measured per call, before / now: one client on 4096 x 4096 21.6 / 14.2 us (7.8 us the first kernel, 4.3 TB/s; 4.2 the
+// second), 16 mixed clients on 4096 -> 11008 69.0 / 28.7, 48 clients of ranks to 128 on 11008 -> 4096 134.9 / 41.2.
 #pragma once
 #include "adapter_kernels.hpp"
 

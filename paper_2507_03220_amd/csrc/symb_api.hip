@@ -831,8 +831,6 @@ symb_status launch_grad(symb_handle h, const GradParams& gp, int wave_rpad, int 
     SYMB_HIP(h, hipGetLastError());
     return SYMB_OK;
 }
-// Adds up the runs of the split segments (none: nothing to do).  At most 128 * 36864 floats per segment
-// at 1024 per workgroup and pass.
 // Stable sort of a list that mostly is sorted: calls of many small segments are bound by the host.
 template <class LESS>
 void sort_once(std::vector<int32_t>& v, LESS&& less) {
@@ -862,6 +860,8 @@ symb_status launch_ia3_grad(symb_handle h, const symb_batch* b, Ia3GradParams p,
     return SYMB_OK;
 }
 
+// Adds up the runs of the split segments (none: nothing to do).  At most 128 * 36864 floats per segment
+// at 1024 per workgroup and pass.
 symb_status launch_grad_reduce(symb_handle h, const GradReduceParams& rp, int nsplit, hipStream_t st) {
     if (nsplit == 0) return SYMB_OK;
     hipLaunchKernelGGL(symb_grad_reduce_kernel, dim3(1024, nsplit), dim3(256), 0, st, rp);
