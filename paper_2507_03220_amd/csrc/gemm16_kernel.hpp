@@ -11,10 +11,14 @@
 // and an epilogue with the optional bias, the optional store of the pre-adapter output, the IA3
 // per-channel scale of each row's own segment and the privacy flow's noise effect.
 //
-// One kernel on v_mfma_f32_16x16x32_bf16: 4 wavefronts (2x2), each NBLK x NBLK blocks of 16x16 of C.
-// NBLK = 8: 256x256 tile of the workgroup, all 256 accumulation registers per wavefront, 160 KiB of
-// LDS, for launches with enough such tiles to fill the chip.  NBLK = 4: 128x128 tile, 64 accumulation
-// registers, 80 KiB of LDS, two workgroups per CU, for everything smaller.  The text below describes
+// One kernel on v_mfma_f32_16x16x32_bf16: 4 wavefronts (2x2), each MBLK x NBLK blocks of 16x16 of C.
+// 8 x 8: 256x256 tile of the workgroup, all 256 accumulation registers per wavefront, 160 KiB of
+// LDS, for launches with enough such tiles to fill the chip.  4 x 4: 128x128 tile, 64 accumulation
+// registers, 80 KiB of LDS, two workgroups per CU, for everything smaller.  8 x 4: 256x128 tile, 128 accumulation
+// registers, 160 KiB of LDS, for launches in between: one full round of such tiles (gemm_plan has the rule and the figures).  Its bound is the rate at
+// which a CU's loads arrive: per 64-k stage 48 KiB for 1024 cycles of MFMAs; 0.56 us per stage with both operands in the Infinity Cache, 0.65 to 0.8
+// from HBM, 0.47 without any loads.  Hence the deeper ring (three A and four B units), the loads spread evenly over a stage (in one burst per stage they hold up
+// the matrix instructions: 0.65 us) and the rotated K walk below.  The text below describes
 // the 256x256 case; the 128x128 one is the same code with half the extents.  Why this instruction:
 // with Gaussian operands the power-limited chip sustains about 12 % more flops on the 16x16x32 form
 // than on the 32x32x16 form.
@@ -75,7 +79,8 @@ struct GemmParams {
     int k_parts, k_whole;
     float* partial;
     int* k_count;
-    double timing_flops;        // host bookkeeping for the measurement hook; unused on the device
+    int variant;                // host bookkeeping: which tile,
+    double timing_flops;        // and the measurement hook's figure; unused on the device
 };
 
 // 16-byte chunk swizzle of a K-contiguous tile row (8 chunks of 8 bf16 per row).
@@ -90,14 +95,15 @@ __device__ __forceinline__ uint4 ld_global_16(const bf16* p, bool ok) {
     return v;
 }
 
-template <int NBLK>
+template <int MBLK, int NBLK>
 struct Gemm16Tile {
-    static_assert(NBLK == 8 || NBLK == 4, "256x256 or 128x128 tile");
-    static constexpr int BM = 32 * NBLK, BN = 32 * NBLK, NT = 256, BK = 64;
-    static constexpr int WT = 16 * NBLK;                 // rows and columns of a wavefront's part
-    static constexpr int UNIT = BM * 128;                // one operand's 64-k stage
+    static_assert(NBLK == 4 ? MBLK == 4 || MBLK == 8 : NBLK == 8 && MBLK == 8, "256x256, 128x128 or 256x128 tile");
+    static constexpr bool TALL = MBLK != NBLK;
+    static constexpr int BM = 32 * MBLK, BN = 32 * NBLK, NT = 256, BK = 64;
+    static constexpr int WM = 16 * MBLK, WN = 16 * NBLK; // rows and columns of a wavefront's part
+    static constexpr int UNIT_A = BM * 128, UNIT_B = BN * 128;   // one operand's 64-k stage
     static constexpr int C_PITCH = BN * 2 + 16, C_BYTES = BM * C_PITCH;
-    static constexpr int SMEM = 5 * UNIT;                // three A units, two B units
+    static constexpr int SMEM = 3 * UNIT_A + (TALL ? 4 : 2) * UNIT_B;
     static_assert(C_BYTES <= SMEM, "the staged output tile must fit the ring");
 };
 
@@ -135,15 +141,14 @@ __device__ __forceinline__ void acc16_write4(float v0, float v1, float v2, float
 }
 
 // PLAIN: no bias, no IA3 scale, no noise effect, no pre-adapter output (checked by the host).
-template <int NBLK, bool NN, bool PLAIN>
-__global__ void __launch_bounds__(256)
-symb_gemm16_kernel(const GemmParams p) {
-    using TT = Gemm16Tile<NBLK>;
-    constexpr int BM = TT::BM, BN = TT::BN, NT = TT::NT, CP = TT::C_PITCH, WT = TT::WT;
+template <int MBLK, int NBLK, bool NN, bool PLAIN>
+__device__ __forceinline__ void gemm16_tile(const GemmParams p) {
+    using TT = Gemm16Tile<MBLK, NBLK>;
+    constexpr int BM = TT::BM, BN = TT::BN, NT = TT::NT, CP = TT::C_PITCH, WM = TT::WM, WN = TT::WN;
     constexpr int CA = BM * 8 / NT, CB = BN * 8 / NT;      // 16-byte chunks per thread of a register-staged tile
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned char* const sA = smem;                        // register-staged tiles (K remainder, LoRA term)
-    unsigned char* const sB = smem + TT::UNIT;
+    unsigned char* const sB = smem + TT::UNIT_A;
 
     // ---- tile of this workgroup
     // Every XCD (blockIdx & 7) walks a contiguous run of per_xcd tiles.  With a K-split (k_parts > 1)
@@ -176,7 +181,7 @@ symb_gemm16_kernel(const GemmParams p) {
     const int tn = (lin % width) / gsz;
     const int m0 = tm * BM, n0 = tn * BN;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave >> 1) * WT, wn0 = (wave & 1) * WT;
+    const int wm0 = (wave >> 1) * WM, wn0 = (wave & 1) * WN;
     const int l15 = lane & 15, lg = lane >> 4;
     const int seg_lo = p.tile_seg_lo[tm], seg_hi = p.tile_seg_hi[tm];
     auto a_row = [&](int m) __attribute__((always_inline)) -> const bf16* {
@@ -227,12 +232,12 @@ symb_gemm16_kernel(const GemmParams p) {
     // (segment es, first extended column ekc); ext_seek moves es to the next LoRA segment with rows
     // in this tile, ext_load fetches the step.  The first step is fetched here, so that its latency
     // hides under the main loop.
-    constexpr int EC = BM / 64;                              // 16-byte chunks per thread of a 32-k tile
+    constexpr int EC = BM / 64, EB = BN / 64;                // 16-byte chunks per thread of a 32-k tile
     // K-contiguous 32-k tile: chunk i sits 64 rows below chunk 0.  Steps alternate between the two 32-k
     // halves of the 64-k tile, so a step's stores never meet the reads of the step before it.
     const int e_lds[2] = {lds_off_kmajor(tid >> 2, tid & 3), lds_off_kmajor(tid >> 2, 4 + (tid & 3))};
     constexpr int ESETS = (NN ? 1 : 2) + (NBLK == 8 ? 0 : 1);  // steps in flight (register sets): what fits without spilling
-    uint4 ea[ESETS][EC], eb[ESETS][EC];
+    uint4 ea[ESETS][EC], eb[ESETS][EB];
     int e_rlo[ESETS] = {}, e_rhi[ESETS] = {};                // the rows of the segment of the step in each set
     bool e_have[ESETS] = {};                                 // the set holds a step that has not run yet
     int es = seg_lo, ekc = 0, e_lo = 0, e_hi = 0;
@@ -279,7 +284,7 @@ symb_gemm16_kernel(const GemmParams p) {
         }
         // adapter-side tile; both halves of the extended columns meet the same adapter matrix
 #pragma unroll
-        for (int i = 0; i < EC; ++i) {
+        for (int i = 0; i < EB; ++i) {
             if constexpr (!NN) {       // B_i [N][rank], rank-contiguous
                 const int n = n0 + (tid >> 2) + i * 64;
                 const int pk = ekc + (tid & 3) * 8, pp = pk >= esd.rpad ? pk - esd.rpad : pk;
@@ -339,21 +344,27 @@ symb_gemm16_kernel(const GemmParams p) {
         for (int ks = ks0; ks < ks0 + nks; ++ks) {
             const unsigned va0 = lds0 + frag_a(ks, 0), va1 = lds0 + frag_a(ks, 1);
             if constexpr (!NN) {
-                const unsigned vb0 = lds0 + TT::UNIT + frag_b_nt(ks, 0), vb1 = lds0 + TT::UNIT + frag_b_nt(ks, 1);
+                const unsigned vb0 = lds0 + TT::UNIT_A + frag_b_nt(ks, 0), vb1 = lds0 + TT::UNIT_A + frag_b_nt(ks, 1);
                 if constexpr (NBLK == 8)
                     asm volatile(SYMB_GEMM16_KSTEP32_NT : : "v"(va0), "v"(va1), "v"(vb0), "v"(vb1), "s"(rows)
                                  : "memory", "scc", SYMB_GEMM16_VCLOBBERS, SYMB_GEMM16_ACLOBBERS);
+                else if constexpr (TT::TALL)
+                    asm volatile(SYMB_GEMM16T_KSTEP32_NT : : "v"(va0), "v"(va1), "v"(vb0), "v"(vb1), "s"(rows)
+                                 : "memory", "scc", SYMB_GEMM16T_VCLOBBERS, SYMB_GEMM16T_ACLOBBERS);
                 else
                     asm volatile(SYMB_GEMM16S_KSTEP32_NT : : "v"(va0), "v"(va1), "v"(vb0), "v"(vb1), "s"(rows)
                                  : "memory", "scc", SYMB_GEMM16S_VCLOBBERS, SYMB_GEMM16S_ACLOBBERS);
             } else {
                 unsigned vb[NBLK];
 #pragma unroll
-                for (int j = 0; j < NBLK; ++j) vb[j] = lds0 + TT::UNIT + frag_b_nn(j) + ks * 32 * (BN * 2);
+                for (int j = 0; j < NBLK; ++j) vb[j] = lds0 + TT::UNIT_A + frag_b_nn(j) + ks * 32 * (BN * 2);
                 if constexpr (NBLK == 8)
                     asm volatile(SYMB_GEMM16_KSTEP32_NN : : "v"(va0), "v"(va1), "v"(vb[0]), "v"(vb[1]), "v"(vb[2]), "v"(vb[3]),
                                  "v"(vb[4]), "v"(vb[5]), "v"(vb[6]), "v"(vb[7]), "s"(rows)
                                  : "memory", "scc", SYMB_GEMM16_VCLOBBERS, SYMB_GEMM16_ACLOBBERS);
+                else if constexpr (TT::TALL)
+                    asm volatile(SYMB_GEMM16T_KSTEP32_NN : : "v"(va0), "v"(va1), "v"(vb[0]), "v"(vb[1]), "v"(vb[2]), "v"(vb[3]), "s"(rows)
+                                 : "memory", "scc", SYMB_GEMM16T_VCLOBBERS, SYMB_GEMM16T_ACLOBBERS);
                 else
                     asm volatile(SYMB_GEMM16S_KSTEP32_NN : : "v"(va0), "v"(va1), "v"(vb[0]), "v"(vb[1]), "v"(vb[2]), "v"(vb[3]), "s"(rows)
                                  : "memory", "scc", SYMB_GEMM16S_VCLOBBERS, SYMB_GEMM16S_ACLOBBERS);
@@ -367,6 +378,7 @@ symb_gemm16_kernel(const GemmParams p) {
     const int KF = (int)((long long)KFT * (part + 1) / nparts) - st0;   // this workgroup's stages: [st0, st0 + KF)
     if (KF == 0) {                                         // otherwise the main loop zeroes them
         if constexpr (NBLK == 8) asm volatile(SYMB_GEMM16_ZERO ::: SYMB_GEMM16_ACLOBBERS);
+        else if constexpr (TT::TALL) asm volatile(SYMB_GEMM16T_ZERO ::: SYMB_GEMM16T_ACLOBBERS);
         else asm volatile(SYMB_GEMM16S_ZERO ::: SYMB_GEMM16S_ACLOBBERS);
     }
     if (KF > 0) {
@@ -380,24 +392,47 @@ symb_gemm16_kernel(const GemmParams p) {
         // fills 1 KiB of consecutive LDS: 8 rows of a K-contiguous unit or 1024 / (2 BN) k-rows of the
         // N-contiguous unit; the lane -> chunk map is the inverse of the LDS swizzle.  Rows / columns
         // outside the problem are clamped onto the last valid one and never stored.
-        unsigned ab[NBLK], bb[NBLK];
+        // (In the 256x128 loop four loads share one m0 write, and the instruction's offset, 1024 (j % 4), counts for both
+        // addresses: the lane offsets are lower by it, from bases 4096 lower.)
+        constexpr unsigned LOWER = TT::TALL ? 4096u : 0u;
+        auto lower = [](int j) { return LOWER ? LOWER - 1024u * (unsigned)(j & 3) : 0u; };
+        unsigned ab[MBLK], bb[NBLK];
+#pragma unroll
+        for (int j = 0; j < MBLK; ++j) {
+            const int row = (wave * MBLK + j) * 8 + (lane >> 3), kc = (lane & 7) ^ swz_row(row);
+            ab[j] = ((unsigned)(a_row(min(m0 + row, p.M - 1)) - a_tile) + kc * 8) * 2u + lower(j);
+        }
 #pragma unroll
         for (int j = 0; j < NBLK; ++j) {
-            const int row = (wave * NBLK + j) * 8 + (lane >> 3), kc = (lane & 7) ^ swz_row(row);
-            ab[j] = ((unsigned)(a_row(min(m0 + row, p.M - 1)) - a_tile) + kc * 8) * 2u;
             if constexpr (!NN) {
-                bb[j] = ((unsigned)(min(n0 + row, p.N - 1) - n0) * (unsigned)p.K + kc * 8) * 2u;
+                const int row = (wave * NBLK + j) * 8 + (lane >> 3), kc = (lane & 7) ^ swz_row(row);
+                bb[j] = ((unsigned)(min(n0 + row, p.N - 1) - n0) * (unsigned)p.K + kc * 8) * 2u + lower(j);
             } else {
                 constexpr int CPR = BN / 8;                     // 16-byte chunks per k-row
                 const int krow = (wave * NBLK + j) * (64 / CPR) + lane / CPR, nc = (lane % CPR) ^ swz_nmajor16(krow);
-                bb[j] = ((unsigned)krow * (unsigned)p.N + (unsigned)min(nc * 8, p.N - 8 - n0)) * 2u;
+                bb[j] = ((unsigned)krow * (unsigned)p.N + (unsigned)min(nc * 8, p.N - 8 - n0)) * 2u + lower(j);
             }
         }
-        const unsigned long long ga = (unsigned long long)(a_tile + (size_t)st0 * 64);
-        const unsigned long long gb = (unsigned long long)(b_tile + (NN ? (size_t)st0 * 64 * p.N : (size_t)st0 * 64));
+        // In the 256x128 loop every XCD starts at another eighth of the K range and walks around its end: the XCDs' tiles read the same rows of one
+        // operand, and in step all of them would wait for the same lines from HBM (397 rows of 4096 -> 11008: 56.8 us in step, 50.8 this way).
+        const int first = TT::TALL ? (int)((blockIdx.x & 7) * (unsigned)KF / 8) : 0;
+        const unsigned long long ga = (unsigned long long)(a_tile + (size_t)(st0 + first) * 64) - LOWER;
+        const unsigned long long gb = (unsigned long long)(b_tile + (size_t)(st0 + first) * 64 * (NN ? p.N : 1)) - LOWER;
         const unsigned stride_b = NN ? 128u * (unsigned)p.N : 128u;
-        const unsigned swa = (unsigned)__builtin_amdgcn_readfirstlane((int)lds0 + wave * (1024 * NBLK));
-        if constexpr (NBLK == 8) {
+        const unsigned swa = (unsigned)__builtin_amdgcn_readfirstlane((int)lds0 + wave * (1024 * MBLK));
+        if constexpr (TT::TALL) {
+            const unsigned swb = (unsigned)__builtin_amdgcn_readfirstlane((int)lds0 + wave * (1024 * NBLK));
+#define SYMB_GEMM16T_LOOP_OPERANDS                                                                                  \
+    :                                                                                                              \
+    : "v"(vA[0]), "v"(vA[1]), "v"(vA[2]), "v"(vA[3]), "v"(vB[0]), "v"(vB[1]), "v"(vB[2]), "v"(vB[3]),              \
+      "v"(ab[0]), "v"(ab[1]), "v"(ab[2]), "v"(ab[3]), "v"(ab[4]), "v"(ab[5]), "v"(ab[6]), "v"(ab[7]),              \
+      "v"(bb[0]), "v"(bb[1]), "v"(bb[2]), "v"(bb[3]),                                                              \
+      "s"(ga), "s"(gb), "s"(stride_b), "s"(KF), "s"(swa), "s"(swb), "s"(first)                                                 \
+    : "memory", "scc", SYMB_GEMM16T_SCLOBBERS, SYMB_GEMM16T_VCLOBBERS, SYMB_GEMM16T_ACLOBBERS
+            if constexpr (NN) asm volatile(SYMB_GEMM16T_LOOP_NN SYMB_GEMM16T_LOOP_OPERANDS);
+            else asm volatile(SYMB_GEMM16T_LOOP_NT SYMB_GEMM16T_LOOP_OPERANDS);
+#undef SYMB_GEMM16T_LOOP_OPERANDS
+        } else if constexpr (NBLK == 8) {
 #define SYMB_GEMM16_LOOP_OPERANDS                                                                                   \
     :                                                                                                              \
     : "v"(vA[0]), "v"(vA[1]), "v"(vA[2]), "v"(vA[3]), "v"(vB[0]), "v"(vB[1]), "v"(vB[2]), "v"(vB[3]), "v"(vB[4]),  \
@@ -426,7 +461,7 @@ symb_gemm16_kernel(const GemmParams p) {
         lds_store_a();
         lds_store_b();
         __syncthreads();
-        compute(0, (p.K - KFT * 64 + 31) >> 5, (1u << NBLK) - 1);
+        compute(0, (p.K - KFT * 64 + 31) >> 5, (1u << MBLK) - 1);
         __syncthreads();
     }
 
@@ -434,7 +469,8 @@ symb_gemm16_kernel(const GemmParams p) {
     const unsigned c_lane = (unsigned)((wm0 + l15) * CP + (wn0 + lg * 4) * 2);   // this lane's C[.][.] of block (0, 0)
     auto stage_out = [&](bf16* __restrict__ dst, bool scale_ia3) __attribute__((always_inline)) {
         if (PLAIN || (!p.bias && !scale_ia3 && !p.neff)) {
-            if constexpr (NBLK == 8) asm volatile(SYMB_GEMM16_STAGE_OUT : : "v"(lds0 + c_lane) : "memory", SYMB_GEMM16_VCLOBBERS);
+            if constexpr (TT::TALL) asm volatile(SYMB_GEMM16T_STAGE_OUT : : "v"(lds0 + c_lane) : "memory", SYMB_GEMM16T_VCLOBBERS);
+            else if constexpr (NBLK == 8) asm volatile(SYMB_GEMM16_STAGE_OUT : : "v"(lds0 + c_lane) : "memory", SYMB_GEMM16_VCLOBBERS);
             else asm volatile(SYMB_GEMM16S_STAGE_OUT : : "v"(lds0 + c_lane) : "memory", SYMB_GEMM16S_VCLOBBERS);
         } else if constexpr (!PLAIN) {
             // bias of this lane's column quads, once; IA3 vector and noise effect of each row's own
@@ -446,7 +482,7 @@ symb_gemm16_kernel(const GemmParams p) {
                 const int n = nq0 + j * 16;
                 bv[j] = (p.bias && n < p.N) ? *reinterpret_cast<const uint2*>(p.bias + n) : make_uint2(0u, 0u);
             }
-            static_for<0, NBLK>([&](auto I) __attribute__((always_inline)) {
+            static_for<0, MBLK>([&](auto I) __attribute__((always_inline)) {
                 constexpr int i = decltype(I)::value;
                 const int m = m0 + wm0 + i * 16 + l15;
                 const bf16* lrow = nullptr;
@@ -558,14 +594,15 @@ symb_gemm16_kernel(const GemmParams p) {
             constexpr int SET = decltype(SETC)::value, HALF = decltype(HALFC)::value;
             // this wavefront's 16-row blocks that hold rows of the step's segment (the other rows of the
             // activation-side tile are zero)
-            constexpr unsigned ALL = (1u << NBLK) - 1;
+            constexpr unsigned ALL = (1u << MBLK) - 1;
             const int r_lo = e_rlo[SET], r_hi = e_rhi[SET];
-            const int b_lo = max(r_lo - (m0 + wm0), 0) >> 4, b_hi = min((r_hi - 1 - (m0 + wm0)) >> 4, NBLK - 1);
+            const int b_lo = max(r_lo - (m0 + wm0), 0) >> 4, b_hi = min((r_hi - 1 - (m0 + wm0)) >> 4, MBLK - 1);
             const unsigned rows = (unsigned)__builtin_amdgcn_readfirstlane(
-                (r_hi > m0 + wm0 && b_lo <= b_hi) ? (int)((ALL >> (NBLK - 1 - b_hi)) & (ALL << b_lo) & ALL) : 0);
+                (r_hi > m0 + wm0 && b_lo <= b_hi) ? (int)((ALL >> (MBLK - 1 - b_hi)) & (ALL << b_lo) & ALL) : 0);
 #pragma unroll
-            for (int i = 0; i < EC; ++i) {
-                *reinterpret_cast<uint4*>(sA + e_lds[HALF] + i * 8192) = ea[SET][i];
+            for (int i = 0; i < EC; ++i) *reinterpret_cast<uint4*>(sA + e_lds[HALF] + i * 8192) = ea[SET][i];
+#pragma unroll
+            for (int i = 0; i < EB; ++i) {
                 if constexpr (!NN) *reinterpret_cast<uint4*>(sB + e_lds[HALF] + i * 8192) = eb[SET][i];
                 else *reinterpret_cast<uint4*>(sB + b_lds0 + (HALF * 32 + i * KSTEP) * (BN * 2)) = eb[SET][i];
             }
@@ -594,9 +631,10 @@ symb_gemm16_kernel(const GemmParams p) {
     if (nparts > 1) {
         constexpr int PT = BM * BN;                  // floats per partial tile
         float* const tile_parts = p.partial + (size_t)slot * nparts * PT;
-        const unsigned lane_off = (unsigned)(wave * (NBLK * NBLK * 1024) + lane * 16);
+        const unsigned lane_off = (unsigned)(wave * (MBLK * NBLK * 1024) + lane * 16);
         const unsigned long long mine = (unsigned long long)(tile_parts + (size_t)part * PT);
-        if constexpr (NBLK == 8) asm volatile(SYMB_GEMM16_STORE_PARTIAL : : "v"(lane_off), "s"(mine) : "memory", SYMB_GEMM16_VCLOBBERS);
+        if constexpr (TT::TALL) asm volatile(SYMB_GEMM16T_STORE_PARTIAL : : "v"(lane_off), "s"(mine) : "memory", SYMB_GEMM16T_VCLOBBERS);
+        else if constexpr (NBLK == 8) asm volatile(SYMB_GEMM16_STORE_PARTIAL : : "v"(lane_off), "s"(mine) : "memory", SYMB_GEMM16_VCLOBBERS);
         else asm volatile(SYMB_GEMM16S_STORE_PARTIAL : : "v"(lane_off), "s"(mine) : "memory", SYMB_GEMM16S_VCLOBBERS);
         // No device-scope fence (on this chip it writes back and invalidates the XCD's whole L2, tens
         // of microseconds with the outputs of other tiles in it).  None is needed: the parts of a tile
@@ -615,7 +653,7 @@ symb_gemm16_kernel(const GemmParams p) {
         const bool last_arrival = *flag == nparts - 1;
         __syncthreads();                             // the flag's LDS word is part of the staging tile
         if (!last_arrival) return;
-        const float4* src = reinterpret_cast<const float4*>(tile_parts) + wave * (NBLK * NBLK * 64) + lane;
+        const float4* src = reinterpret_cast<const float4*>(tile_parts) + wave * (MBLK * NBLK * 64) + lane;
         // Blocks are requested in groups (the accumulator writes below are assembly statements, which the
         // loads could not be moved across): sixteen blocks of one part at a time, or, with at most four
         // parts, eight blocks of all parts at once, which halves the number of round trips.
@@ -623,7 +661,7 @@ symb_gemm16_kernel(const GemmParams p) {
             static_for<2, 5>([&](auto NPC) __attribute__((always_inline)) {
                 constexpr int NP = decltype(NPC)::value;
                 if (nparts != NP) return;
-                static_for<0, NBLK * NBLK / 8>([&](auto G) __attribute__((always_inline)) {
+                static_for<0, MBLK * NBLK / 8>([&](auto G) __attribute__((always_inline)) {
                     constexpr int g = decltype(G)::value;
                     float4 v[NP][8];
 #pragma unroll
@@ -641,7 +679,7 @@ symb_gemm16_kernel(const GemmParams p) {
                 });
             });
         } else {
-            static_for<0, NBLK * NBLK / 16>([&](auto G) __attribute__((always_inline)) {
+            static_for<0, MBLK * NBLK / 16>([&](auto G) __attribute__((always_inline)) {
                 constexpr int g = decltype(G)::value;
                 float4 sum[16];
 #pragma unroll
@@ -667,7 +705,7 @@ symb_gemm16_kernel(const GemmParams p) {
             const TileDelta* const td = p.tile_delta + tm;
             int before = td->first;                  // terms of the tile's rows above the block
             for (int w = 0; w < wm0 / 32; ++w) before += __builtin_popcount(td->mask[w]);
-            static_for<0, NBLK>([&](auto I) __attribute__((always_inline)) {
+            static_for<0, MBLK>([&](auto I) __attribute__((always_inline)) {
                 constexpr int i = decltype(I)::value;
                 const unsigned bits = (td->mask[(wm0 + i * 16) >> 5] >> ((i & 1) * 16)) & 0xffffu;       // uniform
                 if (!bits) return;
@@ -695,6 +733,20 @@ symb_gemm16_kernel(const GemmParams p) {
 
     // ---- final output: bias, IA3 scale, noise effect, one rounding, whole-row stores
     stage_out(p.C, p.epi_ia3 != 0 && p.tile_epi[tm] != 0);
+}
+
+// The square tiles: 256x256 (NBLK 8) and 128x128 (NBLK 4).
+template <int NBLK, bool NN, bool PLAIN>
+__global__ void __launch_bounds__(256)
+symb_gemm16_kernel(const GemmParams p) {
+    gemm16_tile<NBLK, NBLK, NN, PLAIN>(p);
+}
+
+// The 256x128 tile.
+template <bool NN, bool PLAIN>
+__global__ void __launch_bounds__(256)
+symb_gemm16t_kernel(const GemmParams p) {
+    gemm16_tile<8, 4, NN, PLAIN>(p);
 }
 
 }  // namespace symb

@@ -211,8 +211,11 @@ BatchInfo inspect(const symb_batch* b) {
     return bi;
 }
 
-// Tile variants of the GEMM kernel (gemm16_kernel.hpp): 3 = 256x256 tile, taken when the problem has
-// enough such tiles to fill the chip; 2 = 128x128 tile, for everything smaller.
+// Tile variants of the GEMM kernels (gemm16_kernel.hpp): 3 = 256x256 tile, taken when the problem has
+// enough such tiles to fill the chip; 2 = 128x128 tile or, where gemm_plan says so, 4 = 256x128 tile, for everything smaller.
+constexpr int kTile128 = 2, kTile256 = 3, kTileTall = 4;
+int tile_rows(int variant) { return variant == kTile128 ? 128 : 256; }
+int tile_cols(int variant) { return variant == kTile256 ? 256 : 128; }
 int gemm_variant(int M, int N, int K) {
     const long big = (long)((M + 255) / 256) * ((N + 255) / 256), small = (long)((M + 127) / 128) * ((N + 127) / 128);
     if (big < 128) return 2;
@@ -223,7 +226,6 @@ int gemm_variant(int M, int N, int K) {
     // 3700 rows, 2056 wide (135 big tiles, 493 small) K = 4096 65 / 79; 3840 rows, 2184 wide (135, 540) K = 2048 52 / 46.
     return small <= 512 && K <= (N <= 4096 ? 4608 : N <= 8192 ? 4096 : 3072) ? 2 : 3;
 }
-int gemm_tile_m(int M, int N, int K) { return gemm_variant(M, N, K) == 3 ? 256 : 128; }
 
 // Row tiles per group of the tile walk (a group is walked column by column, so the 32 tiles an XCD runs
 // at once are g row tiles x 32 / g column tiles).  Measured on the Gemma2-27B-shaped launches (80 row
@@ -265,6 +267,7 @@ int gemm_group_m(int num_m_tiles, int num_n_tiles, const std::vector<int32_t>& s
 //    each) would cost what the split saves.
 // parts is at most 8.  A pure function of the shape: the
 // workspace figure does not depend on the process environment or on the handle.
+constexpr int kDeltaRows = 16;  // longest LoRA segment whose term may be computed beforehand (see delta_plan)
 struct SplitPlan {
     int parts = 1;        // K ranges per split tile (1: no split)
     int whole = 0;        // tiles per XCD that stay whole
@@ -311,14 +314,60 @@ SplitPlan gemm_split_plan(int M, int N, int K) {
     return s;
 }
 
-// The split of a launch whose workspace has `room` bytes for partial tiles: doubled parts that do not fit (397 rows of 11008 -> 4096 with an
-// adapter in the 32 MiB static scratch) are halved again, any other plan runs unsplit.
-SplitPlan split_within(SplitPlan s, size_t room) {
-    if (s.bytes > room && s.doubled) {
-        s.parts /= 2;
-        s.bytes /= 2;
+// The LoRA k-steps of the 256-row tile that has the most (a segment of rank r: 2 ceil16(r) / 32).  Of segments short enough
+// to be computed beforehand (kDeltaRows) no more than would be left to the steps.
+struct LoraSteps {
+    int most256 = 0;
+};
+LoraSteps lora_steps(const symb_batch* b) {
+    LoraSteps s;
+    int tile = -1, sum = 0, few = 0;
+    for (int i = 0; i < b->num_segments; ++i) {
+        const int lo = b->seg_offsets[i], n = b->seg_offsets[i + 1] - lo;
+        if (b->adapters[i].kind != SYMB_ADAPTER_LORA || !n) continue;
+        const int k = rpad_of(b->adapters[i].rank) / 16, first = lo / 256, last = (lo + n - 1) / 256;
+        for (int u : {first, last}) {                // (the tiles in between hold this segment alone)
+            if (u != tile) { tile = u; sum = few = 0; }
+            if (n > kDeltaRows) sum += k;
+            else few = std::min(few + k, 8);
+            s.most256 = std::max(s.most256, sum + few);
+            if (first == last) break;
+        }
     }
-    return s.bytes <= room ? s : SplitPlan{};
+    return s;
+}
+
+// The tile and the K split of a product.  Of the launches that gemm_variant gives to the 128x128 tile, those whose 256x128 tiles are one nearly
+// full round of one per CU, whole or in two or three K parts, take that tile: it moves three quarters of the bytes per flop from L2 to LDS and waits out
+// HBM latency with two stages in flight.  Time of the 128x128 tile over its, medians over products of 65 to 4500 rows, operands from HBM, by its
+// tiles: whole, 161 to 256 tiles, 1.12 to 1.19 for K = 1000 to 2500, 1.17 to 1.3 above, 1.0 below; 129 to 160 tiles 0.94 to 1.1; two or three parts, 65 to 128 tiles,
+// 1.1 to 1.46 for K >= 3072 and 0.93 to 0.99 below; fewer tiles 0.76 to 1.0 (and 1.15 in four parts of K > 5000).  Up to 128 rows half of every
+// such tile would be empty.  397 rows of 4096 -> 11008 with the adapters of
+// eleven clients 85.5 / 78 us, 16384 rows of 6144 -> 256 80 / 67.  Not with LoRA steps beyond a quarter of the K stages: a tile of twice the
+// rows has up to twice as many, one after the other.
+// room: bytes for partial tiles (0: no split).  Doubled parts that do not fit (397 rows of 11008 -> 4096 with an
+// adapter in the 32 MiB static scratch) are halved again, any other plan runs unsplit.
+struct GemmPlan {
+    int variant = kTile128;
+    SplitPlan split;
+};
+GemmPlan gemm_plan(int M, int N, int K, const LoraSteps& steps, size_t room) {
+    GemmPlan p;
+    p.variant = gemm_variant(M, N, K);
+    p.split = gemm_split_plan(M, N, K);
+    const long tall = (long)((M + 255) / 256) * ((N + 127) / 128);
+    if (p.variant == kTile128 && M > 128 && !p.split.doubled && 4 * steps.most256 <= K / 64) {
+        const int parts = (int)(256 / std::max(tall, 1L));
+        const size_t bytes = (size_t)tall * parts * 256 * 128 * 4;
+        if (tall > 160 && tall <= 256 && K >= 1024) return GemmPlan{kTileTall, SplitPlan{}};
+        if (tall > 64 && tall <= 128 && K >= 3072 && bytes <= room) return GemmPlan{kTileTall, SplitPlan{parts, 0, (int)tall, bytes, false}};
+    }
+    if (p.split.bytes > room && p.split.doubled) {
+        p.split.parts /= 2;
+        p.split.bytes /= 2;
+    }
+    if (p.split.bytes > room) p.split = SplitPlan{};
+    return p;
 }
 
 // One-pass dH + dB kernel: the number of workgroups along d_out, kDhDbBlocks blocks of 256 columns each (0: the layer is too narrow for it:
@@ -458,7 +507,7 @@ SmallPlan small_plan(const symb_batch* b, const BatchInfo& bi, int op, bool lora
 // at most 5 % slower than the other way, over the whole sweep.
 // Batches of more than kDeltaSegments segments, or of more terms than kDeltaBytes, keep the steps, as does one whose descriptors have no
 // room for the terms' (add_gemm_desc).
-constexpr int kDeltaRows = 16, kDeltaSegments = 4096;
+constexpr int kDeltaSegments = 4096;
 constexpr size_t kDeltaBytes = (size_t)160 << 20;
 int delta_steps(int tile_m, int parts, int rows, int N) {
     const double elems = 1e-6 * rows * N;
@@ -468,7 +517,8 @@ struct DeltaPlan {
     std::vector<RowChunk> items;          // the segments (pad: first row of their terms)
     int rows = 0;                         // rows of terms
 };
-DeltaPlan delta_plan(const symb_batch* b, int tile_m, int N, int K) {
+DeltaPlan delta_plan(const symb_batch* b, const GemmPlan& plan, int N) {
+    const int tile_m = tile_rows(plan.variant);
     DeltaPlan d;
     const int S = b->num_segments;
     auto steps = [&](int i) {
@@ -482,7 +532,7 @@ DeltaPlan delta_plan(const symb_batch* b, int tile_m, int N, int K) {
             all += k;
             rows += b->seg_offsets[i + 1] - b->seg_offsets[i];
         }
-    const int least = delta_steps(tile_m, gemm_split_plan(b->seg_offsets[S], N, K).parts, rows, N);
+    const int least = delta_steps(tile_m, plan.split.parts, rows, N);
     if (all < least || (size_t)rows * N * 4 > kDeltaBytes) return d;
     std::vector<int> tile((b->seg_offsets[S] + tile_m - 1) / tile_m, 0);
     for (int i = 0; i < S; ++i)
@@ -562,10 +612,11 @@ WsLayout ws_layout(const symb_batch* b, const BatchInfo& bi, int op, bool full_b
     cur = w.mandatory;
     if (op != SYMB_OP_ADAPTER_GRAD) {
         const int N = op == SYMB_OP_FWD ? b->d_out : b->d_in, K = op == SYMB_OP_FWD ? b->d_in : b->d_out;
-        const SplitPlan sp = gemm_split_plan(bi.T, N, K);
-        if (sp.parts > 1) take(w.tp_off, w.tp_bytes, sp.bytes);
-        const int rows = bi.n_lora && (op == SYMB_OP_FWD || full_bwd) ? delta_plan(b, gemm_tile_m(bi.T, N, K), N, K).rows : 0;
-        if (rows) take(w.de_off, w.de_bytes, (size_t)rows * N * 4);
+        const bool lora = bi.n_lora && (op == SYMB_OP_FWD || full_bwd);
+        const GemmPlan plan = gemm_plan(bi.T, N, K, lora ? lora_steps(b) : LoraSteps{}, SIZE_MAX);
+        take(w.tp_off, w.tp_bytes, plan.split.bytes);
+        const int rows = lora ? delta_plan(b, plan, N).rows : 0;
+        take(w.de_off, w.de_bytes, (size_t)rows * N * 4);
     }
     w.total = std::max(small_end, cur);
     return w;
@@ -716,12 +767,13 @@ symb_status launch_gemm_fn(symb_handle h, GemmParams gp, hipStream_t st, KFN kfn
     return SYMB_OK;
 }
 
-template <int NBLK, bool NN, bool PLAIN>
+template <int MBLK, int NBLK, bool NN, bool PLAIN>
 symb_status launch_gemm16_t(symb_handle h, const GemmParams& gp, hipStream_t st) {
-    using TT = Gemm16Tile<NBLK>;
-    // instantiation number of the measurement hook: bit 0 = N-contiguous weight, bit 1 = 128x128 tile, bit 2 = full epilogue
-    constexpr int variant = (NN ? 1 : 0) | (NBLK == 4 ? 2 : 0) | (PLAIN ? 0 : 4);
-    return launch_gemm_fn(h, gp, st, symb_gemm16_kernel<NBLK, NN, PLAIN>, TT::BM, TT::BN, TT::NT, TT::SMEM, variant);
+    using TT = Gemm16Tile<MBLK, NBLK>;
+    // instantiation number of the measurement hook: bit 0 = N-contiguous weight, bit 1 = tile of 128 columns, bit 2 = full epilogue, bit 3 = 256x128 tile
+    constexpr int variant = (NN ? 1 : 0) | (NBLK == 4 ? 2 : 0) | (PLAIN ? 0 : 4) | (TT::TALL ? 8 : 0);
+    if constexpr (TT::TALL) return launch_gemm_fn(h, gp, st, symb_gemm16t_kernel<NN, PLAIN>, TT::BM, TT::BN, TT::NT, TT::SMEM, variant);
+    else return launch_gemm_fn(h, gp, st, symb_gemm16_kernel<NBLK, NN, PLAIN>, TT::BM, TT::BN, TT::NT, TT::SMEM, variant);
 }
 
 // Algorithmic work of one GEMM launch: 2 M N K plus the LoRA term of the segments that have their steps in it.
@@ -738,8 +790,9 @@ double gemm_flops(const symb_batch* b, const std::vector<SegDesc>& sd_gemm, int 
 template <bool NN>
 symb_status launch_gemm(symb_handle h, const GemmParams& gp, hipStream_t st) {
     const bool plain = !gp.bias && !gp.epi_ia3 && !gp.Cbase && !gp.neff && !gp.delta;
-    if (gemm_variant(gp.M, gp.N, gp.K) == 3) return plain ? launch_gemm16_t<8, NN, true>(h, gp, st) : launch_gemm16_t<8, NN, false>(h, gp, st);
-    return plain ? launch_gemm16_t<4, NN, true>(h, gp, st) : launch_gemm16_t<4, NN, false>(h, gp, st);
+    if (gp.variant == kTile256) return plain ? launch_gemm16_t<8, 8, NN, true>(h, gp, st) : launch_gemm16_t<8, 8, NN, false>(h, gp, st);
+    if (gp.variant == kTileTall) return plain ? launch_gemm16_t<8, 4, NN, true>(h, gp, st) : launch_gemm16_t<8, 4, NN, false>(h, gp, st);
+    return plain ? launch_gemm16_t<4, 4, NN, true>(h, gp, st) : launch_gemm16_t<4, 4, NN, false>(h, gp, st);
 }
 
 // Up to one workgroup per compute unit the deep-prefetch build is used (where its buffers fit in LDS).
@@ -1135,7 +1188,7 @@ symb_status symb_debug_gemm_timing_read(symb_handle h, int32_t variant, double* 
     *launches = 0;
     *flops_total = 0.0;
     for (size_t i = 0; i < h->timed.size(); ++i) {
-        if (h->timed[i].variant != variant) continue;
+        if ((variant & 8 ? h->timed[i].variant : h->timed[i].variant & 7) != variant) continue;
         SYMB_HIP(h, hipEventSynchronize(h->tev[2 * i + 1]));
         float ms = 0.f;
         SYMB_HIP(h, hipEventElapsedTime(&ms, h->tev[2 * i], h->tev[2 * i + 1]));
@@ -1294,8 +1347,6 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     if (ws_need > ws_bytes || (ws_need && !ws))
         return fail(h, SYMB_ERR_WORKSPACE_TOO_SMALL, "forward needs %zu workspace bytes, got %zu%s", ws_need, ws_bytes,
                     staged ? " (output buffers overlap input buffers: size the workspace with SYMB_OP_FWD_INPLACE)" : "");
-    const SplitPlan ksp = split_within(gemm_split_plan(bi.T, b->d_out, b->d_in), ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
-    const bool k_split = ksp.parts > 1 && !Ybase && h->opt_k_split && h->xcd_rule;
     hipStream_t s = (hipStream_t)stream;
     if (small_path(h, bi, wl, ws, ws_bytes)) {     // (partial sums between: overlapping buffers need no flat copy)
         unsigned char* const base = (unsigned char*)ws;
@@ -1306,7 +1357,10 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
         return SYMB_OK;
     }
 
-    const int bm = gemm_tile_m(bi.T, b->d_out, b->d_in);
+    const GemmPlan plan = gemm_plan(bi.T, b->d_out, b->d_in, bi.n_lora > 0 ? lora_steps(b) : LoraSteps{},
+                                    !Ybase && h->opt_k_split && h->xcd_rule && ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
+    const bool k_split = plan.split.parts > 1;
+    const int bm = tile_rows(plan.variant), bn = tile_cols(plan.variant);
     std::vector<int32_t> lo, hi;
     plan_row_tiles(b, bm, lo, hi);
     std::vector<RowChunk> chunks, all_chunks;
@@ -1321,7 +1375,8 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     std::vector<SegDesc> sd_gemm = sd;
     std::vector<int64_t> pk_off(bi.S, 0);
     DeltaPlan delta;
-    if (wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm, b->d_out, b->d_in);
+    if (bi.n_lora && ws_bytes > wl.de_off) delta = delta_plan(b, plan, b->d_out);
+    if (!delta.items.empty() && ws_bytes < wl.de_off + (size_t)delta.rows * b->d_out * 4) delta = DeltaPlan{};
     if (conv1d && bi.n_lora) {
         int64_t cur = 0;
         for (int i = 0; i < bi.S; ++i)
@@ -1344,7 +1399,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     const size_t o_all = blob.add(all_chunks.data(), all_chunks.size());
     const size_t o_xs = blob.add(X_seg, seg_io ? (size_t)bi.S : 0);
     const size_t o_ys = blob.add(Y_seg, seg_io ? (size_t)bi.S : 0);
-    const std::vector<int32_t> k_zero(k_split ? ksp.slots : 0, 0);
+    const std::vector<int32_t> k_zero(k_split ? plan.split.slots : 0, 0);
     const size_t o_kc = blob.add(k_zero.data(), k_zero.size());   // arrival counters of the K-split tiles
     const DeltaBlob db = add_gemm_desc(blob, sd_gemm, delta, (int)lo.size(), bm);
     unsigned char* dev = nullptr;
@@ -1415,10 +1470,11 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     gp.tile_epi = (const int32_t*)(dev + o_te);
     gp.neff = nd.empty() ? nullptr : (const NoiseDesc*)(dev + o_nd);
     gp.timing_flops = gemm_flops(b, sd_gemm, b->d_out, b->d_in, bi.n_lora > 0);
-    gp.group_m = gemm_group_m((bi.T + bm - 1) / bm, (b->d_out + bm - 1) / bm, lo, hi);
+    gp.variant = plan.variant;
+    gp.group_m = gemm_group_m((bi.T + bm - 1) / bm, (b->d_out + bn - 1) / bn, lo, hi);
     if (k_split) {
-        gp.k_parts = ksp.parts;
-        gp.k_whole = ksp.whole;
+        gp.k_parts = plan.split.parts;
+        gp.k_whole = plan.split.whole;
         gp.partial = (float*)(wsb + wl.tp_off);
         gp.k_count = (int*)(dev + o_kc);
     }
@@ -1551,8 +1607,6 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     if (ws_need > ws_bytes || (ws_need && !ws))
         return fail(h, SYMB_ERR_WORKSPACE_TOO_SMALL, "backward needs %zu workspace bytes, got %zu%s", ws_need, ws_bytes,
                     staged ? " (output buffers overlap input buffers: size the workspace with SYMB_OP_BWD_INPUT_INPLACE)" : "");
-    const SplitPlan ksp = split_within(gemm_split_plan(bi.T, b->d_in, b->d_out), ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
-    const bool k_split = ksp.parts > 1 && !dXbase && h->opt_k_split && h->xcd_rule;
     hipStream_t s = (hipStream_t)stream;
     const bool lora = full && bi.n_lora > 0, ia3 = full && bi.n_ia3 > 0;
     if (small_path(h, bi, wl, ws, ws_bytes)) {     // (partial sums between: overlapping buffers need no flat copy)
@@ -1564,7 +1618,10 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
         return SYMB_OK;
     }
 
-    const int bm = gemm_tile_m(bi.T, b->d_in, b->d_out);
+    const GemmPlan plan = gemm_plan(bi.T, b->d_in, b->d_out, lora ? lora_steps(b) : LoraSteps{},
+                                    !dXbase && h->opt_k_split && h->xcd_rule && ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
+    const bool k_split = plan.split.parts > 1;
+    const int bm = tile_rows(plan.variant), bn = tile_cols(plan.variant);
     std::vector<int32_t> lo, hi;
     plan_row_tiles(b, bm, lo, hi);
     std::vector<RowChunk> chunks, all_chunks;
@@ -1600,7 +1657,8 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     const bool conv1d = b->weight_layout == SYMB_WEIGHT_CONV1D;
     std::vector<SegDesc> sd_gemm = sd;
     DeltaPlan delta;
-    if (lora && wl.de_bytes && ws_bytes >= wl.de_off + wl.de_bytes) delta = delta_plan(b, bm, b->d_in, b->d_out);
+    if (lora && ws_bytes > wl.de_off) delta = delta_plan(b, plan, b->d_in);
+    if (!delta.items.empty() && ws_bytes < wl.de_off + (size_t)delta.rows * b->d_in * 4) delta = DeltaPlan{};
     std::vector<int64_t> pk_off(bi.S, 0), pa_off(bi.S, 0);
     {
         int64_t cur = 0, cura = 0;
@@ -1632,7 +1690,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     std::vector<RowChunk> row_chunks;
     if (staged) plan_chunks(b, kSkinnyRows, -1, row_chunks);
     const size_t o_rows = blob.add(row_chunks.data(), row_chunks.size());
-    const std::vector<int32_t> k_zero(k_split ? ksp.slots : 0, 0);
+    const std::vector<int32_t> k_zero(k_split ? plan.split.slots : 0, 0);
     const size_t o_kc = blob.add(k_zero.data(), k_zero.size());   // arrival counters of the K-split tiles
     const DeltaBlob db = add_gemm_desc(blob, sd_gemm, delta, (int)lo.size(), bm);
     unsigned char* dev = nullptr;
@@ -1700,10 +1758,11 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     gp.epi_ia3 = (full && bi.n_ia3in > 0) ? KIND_IA3_IN : 0;      // dX rows of IA3_IN segments: l_i * (dY W)
     gp.tile_epi = (const int32_t*)(dev + o_te);
     gp.timing_flops = gemm_flops(b, sd_gemm, b->d_in, b->d_out, lora);
-    gp.group_m = gemm_group_m((bi.T + bm - 1) / bm, (b->d_in + bm - 1) / bm, lo, hi);
+    gp.variant = plan.variant;
+    gp.group_m = gemm_group_m((bi.T + bm - 1) / bm, (b->d_in + bn - 1) / bn, lo, hi);
     if (k_split) {
-        gp.k_parts = ksp.parts;
-        gp.k_whole = ksp.whole;
+        gp.k_parts = plan.split.parts;
+        gp.k_whole = plan.split.whole;
         gp.partial = (float*)(wsb + wl.tp_off);
         gp.k_count = (int*)(dev + o_kc);
     }

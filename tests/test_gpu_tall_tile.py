@@ -1,0 +1,62 @@
+"""Products that take the 256x128 GEMM tile: whole and split over K, inner dimensions with and without a
+remainder of 64, ragged edges, every epilogue, LoRA steps of ranks 5 to 128, in both directions and weight layouts."""
+import pytest
+import torch
+
+import gpu_harness as gh
+import synth
+from helpers import assert_close, check_dx, check_y
+from paper_2507_03220_amd import binding as sb
+from test_gpu_parity import I, L, N, make_problem, oracle_ads
+import test_gpu_parity as tp
+
+pytestmark = pytest.mark.gpu
+tp.gh, tp.sb = gh, sb                    # what its problem maker uses
+
+
+def launches(call, variant):
+    """Launches of one instantiation, its tile included (bit 3: 256x128), and what the call returns."""
+    sb.symb_debug_gemm_timing_enable(gh.handle(), 1)
+    try:
+        out = call()
+        return sb.symb_debug_gemm_timing_read(gh.handle(), variant)[1], out
+    finally:
+        sb.symb_debug_gemm_timing_enable(gh.handle(), 0)
+
+
+@pytest.mark.parametrize("T,d_in,d_out,parts,ranks", [
+    (1300, 1032, 4104, 1, [16, 5]), (1500, 3080, 4096, 1, [16, 40, 5]),         # whole: a remainder of 8 beyond the last stage
+    (520, 4104, 4104, 2, [16, 128, 5]), (1000, 3080, 2056, 3, [100, 16, 5])])
+def test_tall_tile(T, d_in, d_out, parts, ranks):
+    plain = sb.Batch(d_in, d_out, [0, T], [sb.Adapter()])
+    tiles = -(-T // 256) * -(-d_out // 128)
+    need = sb.symb_workspace_bytes(plain, sb.SYMB_OP_FWD)
+    assert need == (tiles * parts * 256 * 128 * 4 if parts > 1 else 0)
+    lens = [T // 3, 1, T // 4, 0, 17, T - T // 3 - T // 4 - 18]
+    p = make_problem(T + d_in, d_in, d_out, lens, [L, I, L, N, L], ranks)
+    off, oads = p["off"], oracle_ads(p["ads"])
+    rows = synth.sample_rows(off, 6, f"tall{T}", block=128)
+    base = [gh.HostAdapter() for _ in lens]
+    for conv1d in (False, True):
+        n, (Y, _) = launches(lambda: gh.forward(off, base, p["X"], p["W"], None, want_base=False, conv1d=conv1d), 8 + 2 + conv1d)
+        assert n == 1
+        check_y(gh.bf16_to_f64(Y)[rows], off, oracle_ads(base), p["X"], p["W"], None, "plain Y", rows=rows)
+        n, (Y, Yb) = launches(lambda: gh.forward(off, p["ads"], p["X"], p["W"], p["bias"], want_base=parts == 1, conv1d=conv1d), 8 + 4 + 2 + conv1d)
+        assert n == 1
+        Y0, _ = check_y(gh.bf16_to_f64(Y)[rows], off, oads, p["X"], p["W"], p["bias"], "Y", rows=rows)
+        if parts == 1:
+            assert_close(gh.bf16_to_f64(Yb)[rows], Y0, "Ybase", out_bf16=True)
+    q = make_problem(T + d_out, d_out, d_in, lens, [L, I, L, N, L], ranks)       # its input gradient has the same product
+    for conv1d in (False, True):
+        n, dX = launches(lambda: gh.backward_input(off, q["ads"], q["dY"], q["W"], conv1d=conv1d), 8 + 2 + (not conv1d))
+        assert n == 1
+        check_dx(gh.bf16_to_f64(dX)[rows], off, oracle_ads(q["ads"]), q["dY"], q["W"], "dX", rows=rows)
+    if parts > 1:                        # one byte too few for the partial tiles, and a call whose tiles cannot be split: the 128x128 tile
+        X, W = gh.to_dev(p["X"]), gh.to_dev(p["W"])
+        for ws, want_base, variant in ((need - 1, False, 2), (need, True, 4 + 2)):
+            Y = torch.full((T, d_out), float("nan"), device="cuda", dtype=torch.bfloat16)
+            Yb = torch.empty_like(Y) if want_base else None
+            buf = torch.empty(ws, device="cuda", dtype=torch.uint8)
+            call = lambda: sb.symb_base_linear_fwd(gh.handle(), plain, X, W, None, Y, Yb, buf)  # noqa: B023,E731
+            assert launches(call, variant)[0] == 1 and launches(call, variant + 8)[0] == 0
+            check_y(gh.bf16_to_f64(Y[rows]), off, oracle_ads(base), p["X"], p["W"], None, f"Y in {ws} bytes", rows=rows)
