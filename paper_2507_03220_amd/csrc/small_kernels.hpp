@@ -22,6 +22,7 @@
 // second), 16 mixed clients on 4096 -> 11008 69.0 / 28.7, 48 clients of ranks to 128 on 11008 -> 4096 134.9 / 41.2.
 #pragma once
 #include "adapter_kernels.hpp"
+#include "gemm16_kernel.hpp"
 
 namespace symb {
 
@@ -127,15 +128,16 @@ __device__ __forceinline__ void small_store(const floatx4 (&acc)[CB][MB], unsign
 
 // The accumulators of a tile over slices [KF range / ranges, ..).  w: the operand's first row (column, NN) of the tile; ld: its row
 // pitch; wvalid: its valid rows (columns, NN).
-template <int CB, int MB, int NBUF, bool NN>
-__device__ __forceinline__ void small_tile(const SmallStreamParams& p, const bf16* w, int ld, int wvalid, int row0, int nrows, int range,
-                                           int ranges, unsigned char* smem, floatx4 (&acc)[CB][MB]) {
+// xrow(t): row t of the activations; meanwhile(acc): adds to the zeroed accumulators while the first slices are on their way.
+template <int CB, int MB, int NBUF, bool NN, class XROW, class MEANWHILE>
+__device__ __forceinline__ void small_tile_of(int K, XROW&& xrow, const bf16* w, int ld, int wvalid, int row0, int nrows, int range,
+                                              int ranges, unsigned char* smem, floatx4 (&acc)[CB][MB], MEANWHILE&& meanwhile) {
     static_assert(!NN || CB == 8, "an N-contiguous tile is 128 columns wide");
     typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
     using ST = SmallTile<CB, MB, NBUF, NN>;
     constexpr int NH = ST::SK / 32;                      // 32-k steps per slice
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l15 = lane & 15, kq = lane >> 4, K = p.K;
+    const int l15 = lane & 15, kq = lane >> 4;
     unsigned char* const wbuf = smem + wave * ST::WAVE;
     // this lane's 16 bytes of every DMA request of a slice, at k = 0; what lies past the last valid row or column repeats it
     const bf16* src[ST::REQ];
@@ -153,7 +155,7 @@ __device__ __forceinline__ void small_tile(const SmallStreamParams& p, const bf1
 #pragma unroll
     for (int i = 0; i < ST::XREQ; ++i) {
         const int r = NN ? i * 16 + (lane >> 2) : i * 8 + (lane >> 3);
-        src[ST::WREQ + i] = small_row(p, row0 + min(r, nrows - 1)) + (NN ? (lane & 3) ^ ((r >> 2) & 3) : (lane & 7) ^ ((r >> 1) & 7)) * 8;
+        src[ST::WREQ + i] = xrow(row0 + min(r, nrows - 1)) + (NN ? (lane & 3) ^ ((r >> 2) & 3) : (lane & 7) ^ ((r >> 1) & 7)) * 8;
     }
     unsigned woff[CB][NH], xoff[MB][NH];                 // fragment of block b, 32-k step h
 #pragma unroll
@@ -229,6 +231,7 @@ __device__ __forceinline__ void small_tile(const SmallStreamParams& p, const bf1
     const int ns = hi - lo > wave ? (hi - lo - wave + 3) >> 2 : 0;
     int k = (lo + wave) * ST::SK;                        // the next slice to request
     for (int d = 0; d < min(ns, NBUF); ++d, k += 4 * ST::SK) dma(d, k);
+    meanwhile(acc);
     int buf = 0, s = 0;
     for (; s + NBUF <= ns; ++s) {                        // NBUF slices requested and not yet used: all but the oldest may stay in flight
         asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NBUF - 1) * ST::REQ) : "memory");
@@ -251,7 +254,7 @@ __device__ __forceinline__ void small_tile(const SmallStreamParams& p, const bf1
             const bool ok = kk < K;
             u32x4 xv[MB];
 #pragma unroll
-            for (int m = 0; m < MB; ++m) xv[m] = ok ? ld_glb16(small_row(p, row0 + min(m * 16 + l15, nrows - 1)) + kk) : u32x4{0u, 0u, 0u, 0u};
+            for (int m = 0; m < MB; ++m) xv[m] = ok ? ld_glb16(xrow(row0 + min(m * 16 + l15, nrows - 1)) + kk) : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int c = 0; c < CB; ++c) {
                 u32x4 f = u32x4{0u, 0u, 0u, 0u};
@@ -270,6 +273,13 @@ __device__ __forceinline__ void small_tile(const SmallStreamParams& p, const bf1
             }
         }
     }
+}
+
+template <int CB, int MB, int NBUF, bool NN>
+__device__ __forceinline__ void small_tile(const SmallStreamParams& p, const bf16* w, int ld, int wvalid, int row0, int nrows, int range,
+                                           int ranges, unsigned char* smem, floatx4 (&acc)[CB][MB]) {
+    small_tile_of<CB, MB, NBUF, NN>(p.K, [&](int t) __attribute__((always_inline)) { return small_row(p, t); }, w, ld, wvalid, row0, nrows, range, ranges, smem, acc,
+                                    [](floatx4 (&)[CB][MB]) {});
 }
 
 // ---- shrink against an adapter matrix stored [K][r] (B_i in the input gradient): all r columns against 16 MB activation rows.  64 k of
@@ -487,6 +497,98 @@ symb_small_narrow_kernel(const SmallStreamParams p) {
     small_tile<CB, MB, NBUF, false>(p, p.W + (size_t)n0 * p.K, p.K, p.N - n0, 0, p.T, 0, 1, smem, acc);
     small_sum<CB, MB>(acc, smem, [&](int t, int n, const floatx4& v) __attribute__((always_inline)) {
         if (t < p.T && n0 + n < p.N) small_direct(p, t, n0 + n, v);
+    });
+}
+
+// ---- The tiled product of small layers: tiles of 32 rows and 64 (weight read K-contiguous) or 128 columns, the four wavefronts of a workgroup
+// splitting K.  Such a launch is one chain of latencies (launch, first loads, K, epilogue); the 128x128 tile walks its K stages one behind the other and
+// leaves the chip to a dozen workgroups.  Here a wavefront's share of K up to 768 is in flight at once, and the LoRA steps (H and the adapter straight
+// from memory, dealt out over the wavefronts) run while it arrives.  256 rows of 768 x 768 with one rank-8 step
+// per tile, us: K-contiguous 11.7 -> 6.9, N-contiguous 11.5 -> 8.4 (11.4 with the element loads of A_i under a condition).  gemm_plan has the rule.  No pre-adapter
+// output, no terms computed beforehand.
+constexpr int MID_ROWS = 32;
+template <bool NN>
+__global__ void __launch_bounds__(256)
+symb_gemm_mid_kernel(const GemmParams p) {
+    constexpr int MB = MID_ROWS / 16, CB = small_cols(NN) / 16, NBUF = NN ? 4 : 3;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SmallTile<CB, MB, NBUF, NN>::BYTES];
+    const int tm = blockIdx.x % p.num_m_tiles, tn = blockIdx.x / p.num_m_tiles, m0 = tm * MID_ROWS, n0 = tn * small_cols(NN);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l15 = lane & 15, kq = lane >> 4;
+    const int seg_lo = p.tile_seg_lo[tm], seg_hi = p.tile_seg_hi[tm];
+    auto xrow = [&](int m) __attribute__((always_inline)) -> const bf16* {
+        if (!p.a_seg) return p.Aop + (size_t)m * p.K;
+        const int s = seg_of_row(p.off, seg_lo, seg_hi, m);
+        return p.a_seg[s] + (size_t)(m - p.off[s]) * p.K;
+    };
+    auto lora = [&](floatx4 (&acc)[CB][MB]) __attribute__((always_inline)) {
+        if (!p.ext) return;
+        int no = 0;                                      // steps of the tile: number no goes to wavefront no % 4
+        for (int s = seg_lo; s <= seg_hi; ++s) {
+            const SegDesc sd = p.seg[s];
+            const int lo = max(p.off[s], m0), hi = min(min(p.off[s + 1], m0 + MID_ROWS), p.M);
+            if (sd.kind != KIND_LORA || hi <= lo) continue;
+            for (int e = 0; e < 2 * sd.rpad; e += 32, ++no) {
+                if ((no & 3) != wave) continue;
+                const int pk = e + kq * 8, pp = pk >= sd.rpad ? pk - sd.rpad : pk;     // both halves of the extended columns meet the same adapter matrix
+                // every load unconditional and in bounds, what does not belong to the step zeroed afterwards (under a condition each would be waited for)
+                u32x4 xv[MB], wv[CB];
+#pragma unroll
+                for (int m = 0; m < MB; ++m) xv[m] = ld_glb16(p.ext + (size_t)min(max(m0 + m * 16 + l15, lo), hi - 1) * p.ext_pitch + pk);
+                if (!NN && (sd.rank & 7) == 0) {
+#pragma unroll
+                    for (int c = 0; c < CB; ++c) wv[c] = ld_glb16(sd.B + (size_t)min(n0 + c * 16 + l15, p.N - 1) * sd.rank + min(pp, sd.rank - 8));
+                } else {                                 // A_i [rank][N] or B_i [N][rank], element by element
+                    const __attribute__((address_space(1))) unsigned short* const w =
+                        (const __attribute__((address_space(1))) unsigned short*)reinterpret_cast<const unsigned short*>(NN ? sd.A : sd.B);
+#pragma unroll
+                    for (int c = 0; c < CB; ++c) {
+                        const int n = min(n0 + c * 16 + l15, p.N - 1);
+                        unsigned e[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            const int r = min(pp + q, sd.rank - 1);
+                            e[q] = w[NN ? (size_t)r * p.N + n : (size_t)n * sd.rank + r];
+                        }
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) e[q] = pp + q < sd.rank ? e[q] : 0u;
+                        wv[c] = u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
+                    }
+                }
+#pragma unroll
+                for (int m = 0; m < MB; ++m) {
+                    const int t = m0 + m * 16 + l15;
+                    xv[m] = t >= lo && t < hi ? xv[m] : u32x4{0u, 0u, 0u, 0u};
+                }
+#pragma unroll
+                for (int c = 0; c < CB; ++c) wv[c] = pp < sd.rank ? wv[c] : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int c = 0; c < CB; ++c)
+#pragma unroll
+                    for (int m = 0; m < MB; ++m)
+                        acc[c][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv[c]), __builtin_bit_cast(bf16x8, xv[m]), acc[c][m], 0, 0, 0);
+            }
+        }
+    };
+    floatx4 acc[CB][MB];
+    small_tile_of<CB, MB, NBUF, NN>(p.K, xrow, p.Bop + (NN ? (size_t)n0 : (size_t)n0 * p.K), NN ? p.N : p.K, p.N - n0, m0, min(MID_ROWS, p.M - m0), 0, 1, smem, acc, lora);
+    const bool scale = p.epi_ia3 != 0 && p.tile_epi[tm] != 0;
+    small_sum<CB, MB>(acc, smem, [&](int r, int c, floatx4 v) __attribute__((always_inline)) {
+        const int t = m0 + r, n = n0 + c;
+        if (t >= p.M || n >= p.N) return;
+        auto quad = [&](const bf16* q) __attribute__((always_inline)) {
+            const uint2 b = *reinterpret_cast<const uint2*>(q);
+            return floatx4{bf16_bits_to_f32((unsigned short)(b.x & 0xffffu)), bf16_bits_to_f32((unsigned short)(b.x >> 16)),
+                           bf16_bits_to_f32((unsigned short)(b.y & 0xffffu)), bf16_bits_to_f32((unsigned short)(b.y >> 16))};
+        };
+        bf16* out = p.C + (size_t)t * p.N;
+        if (p.bias) v += quad(p.bias + n);
+        if (scale || p.neff || p.c_seg) {
+            const int s = seg_of_row(p.off, seg_lo, seg_hi, t);
+            if (scale && p.seg[s].kind == p.epi_ia3) v *= quad(p.seg[s].A + n);
+            if (p.neff && p.neff[s].ptr) v -= quad(p.neff[s].ptr + (size_t)(p.neff[s].rows == 1 ? 0 : t - p.off[s]) * p.N + n);
+            if (p.c_seg) out = p.c_seg[s] + (size_t)(t - p.off[s]) * p.N;
+        }
+        *reinterpret_cast<uint2*>(out + n) = make_uint2(pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]));
     });
 }
 

@@ -212,9 +212,9 @@ BatchInfo inspect(const symb_batch* b) {
 }
 
 // Tile variants of the GEMM kernels (gemm16_kernel.hpp): 3 = 256x256 tile, taken when the problem has
-// enough such tiles to fill the chip; 2 = 128x128 tile or, where gemm_plan says so, 4 = 256x128 tile, for everything smaller.
-constexpr int kTile128 = 2, kTile256 = 3, kTileTall = 4;
-int tile_rows(int variant) { return variant == kTile128 ? 128 : 256; }
+// enough such tiles to fill the chip; 2 = 128x128 tile or, where gemm_plan says so, 4 = 256x128 or 5 = 32-row tile, for everything smaller.
+constexpr int kTile128 = 2, kTile256 = 3, kTileTall = 4, kTileMid = 5;
+int tile_rows(int variant) { return variant == kTileMid ? MID_ROWS : variant == kTile128 ? 128 : 256; }
 int tile_cols(int variant) { return variant == kTile256 ? 256 : 128; }
 int gemm_variant(int M, int N, int K) {
     const long big = (long)((M + 255) / 256) * ((N + 255) / 256), small = (long)((M + 127) / 128) * ((N + 127) / 128);
@@ -315,22 +315,22 @@ SplitPlan gemm_split_plan(int M, int N, int K) {
 }
 
 // The LoRA k-steps of the 256-row tile that has the most (a segment of rank r: 2 ceil16(r) / 32).  Of segments short enough
-// to be computed beforehand (kDeltaRows) no more than would be left to the steps.
+// to be computed beforehand (kDeltaRows) no more than would be left to the steps; few256: those alone, all of them.
 struct LoraSteps {
-    int most256 = 0;
+    int most256 = 0, few256 = 0;
 };
 LoraSteps lora_steps(const symb_batch* b) {
     LoraSteps s;
-    int tile = -1, sum = 0, few = 0;
+    int tile = -1, sum = 0, few = 0;                 // the tile so far: steps of long and of short segments
     for (int i = 0; i < b->num_segments; ++i) {
         const int lo = b->seg_offsets[i], n = b->seg_offsets[i + 1] - lo;
         if (b->adapters[i].kind != SYMB_ADAPTER_LORA || !n) continue;
         const int k = rpad_of(b->adapters[i].rank) / 16, first = lo / 256, last = (lo + n - 1) / 256;
         for (int u : {first, last}) {                // (the tiles in between hold this segment alone)
             if (u != tile) { tile = u; sum = few = 0; }
-            if (n > kDeltaRows) sum += k;
-            else few = std::min(few + k, 8);
-            s.most256 = std::max(s.most256, sum + few);
+            (n > kDeltaRows ? sum : few) += k;
+            s.most256 = std::max(s.most256, sum + std::min(few, 8));
+            s.few256 = std::max(s.few256, few);
             if (first == last) break;
         }
     }
@@ -345,13 +345,18 @@ LoraSteps lora_steps(const symb_batch* b) {
 // such tile would be empty.  397 rows of 4096 -> 11008 with the adapters of
 // eleven clients 85.5 / 78 us, 16384 rows of 6144 -> 256 80 / 67.  Not with LoRA steps beyond a quarter of the K stages: a tile of twice the
 // rows has up to twice as many, one after the other.
+// Small layers take the tiles of 32 rows (symb_gemm_mid_kernel) as long as these are one round of workgroups: time of the 128x128 tile over theirs, 13 300 products
+// of 65 to 1500 rows, medians by K, K-contiguous weight: 1.2 (K = 256), 1.3 to 1.37 (512), 1.3 to 1.46 (768), 1.4 to 1.57 (1024), 1.55 to 1.74 (1536) up to 256
+// workgroups, 0.9 to 1.0 with 257 to 512, 0.6 beyond; where the 128x128 tiles are split over K 1.23 to 1.34 up to K = 2048, 1.03 to 1.1 above;
+// N-contiguous 1.07 to 1.25 up to 192 workgroups, 0.75 beyond 256, and 0.9 to 1.0 against split tiles.  (The workspace figure stays the split's.)  Not with
+// a pre-adapter output or with steps enough to be computed beforehand.
 // room: bytes for partial tiles (0: no split).  Doubled parts that do not fit (397 rows of 11008 -> 4096 with an
 // adapter in the 32 MiB static scratch) are halved again, any other plan runs unsplit.
 struct GemmPlan {
     int variant = kTile128;
     SplitPlan split;
 };
-GemmPlan gemm_plan(int M, int N, int K, const LoraSteps& steps, size_t room) {
+GemmPlan gemm_plan(int M, int N, int K, bool nn, const LoraSteps& steps, bool with_base, size_t room) {
     GemmPlan p;
     p.variant = gemm_variant(M, N, K);
     p.split = gemm_split_plan(M, N, K);
@@ -367,6 +372,10 @@ GemmPlan gemm_plan(int M, int N, int K, const LoraSteps& steps, size_t room) {
         p.split.bytes /= 2;
     }
     if (p.split.bytes > room) p.split = SplitPlan{};
+    const long mid = (long)((M + MID_ROWS - 1) / MID_ROWS) * ((N + small_cols(nn) - 1) / small_cols(nn));
+    if (p.variant == kTile128 && !with_base && steps.most256 <= 16 && steps.few256 < 8 &&
+        (p.split.parts == 1 ? K <= 1536 && mid <= (nn ? 192 : 256) : !nn && K <= 2048 && mid <= 192))
+        p.variant = kTileMid;
     return p;
 }
 
@@ -520,6 +529,7 @@ struct DeltaPlan {
 DeltaPlan delta_plan(const symb_batch* b, const GemmPlan& plan, int N) {
     const int tile_m = tile_rows(plan.variant);
     DeltaPlan d;
+    if (plan.variant == kTileMid) return d;
     const int S = b->num_segments;
     auto steps = [&](int i) {
         const int n = b->seg_offsets[i + 1] - b->seg_offsets[i];
@@ -613,7 +623,7 @@ WsLayout ws_layout(const symb_batch* b, const BatchInfo& bi, int op, bool full_b
     if (op != SYMB_OP_ADAPTER_GRAD) {
         const int N = op == SYMB_OP_FWD ? b->d_out : b->d_in, K = op == SYMB_OP_FWD ? b->d_in : b->d_out;
         const bool lora = bi.n_lora && (op == SYMB_OP_FWD || full_bwd);
-        const GemmPlan plan = gemm_plan(bi.T, N, K, lora ? lora_steps(b) : LoraSteps{}, SIZE_MAX);
+        const GemmPlan plan = gemm_plan(bi.T, N, K, (op == SYMB_OP_FWD) == conv1d, lora ? lora_steps(b) : LoraSteps{}, false, SIZE_MAX);
         take(w.tp_off, w.tp_bytes, plan.split.bytes);
         const int rows = lora ? delta_plan(b, plan, N).rows : 0;
         take(w.de_off, w.de_bytes, (size_t)rows * N * 4);
@@ -790,6 +800,20 @@ double gemm_flops(const symb_batch* b, const std::vector<SegDesc>& sd_gemm, int 
 template <bool NN>
 symb_status launch_gemm(symb_handle h, const GemmParams& gp, hipStream_t st) {
     const bool plain = !gp.bias && !gp.epi_ia3 && !gp.Cbase && !gp.neff && !gp.delta;
+    if (gp.variant == kTileMid) {
+        GemmParams g = gp;
+        g.num_m_tiles = (gp.M + MID_ROWS - 1) / MID_ROWS;
+        const bool timed = h->timing && (int)h->timed.size() < kMaxTimed;
+        const size_t slot = h->timed.size();
+        if (timed) SYMB_HIP(h, hipEventRecord(h->tev[2 * slot], st));
+        hipLaunchKernelGGL(symb_gemm_mid_kernel<NN>, dim3((unsigned)(g.num_m_tiles * ((gp.N + small_cols(NN) - 1) / small_cols(NN)))), dim3(256), 0, st, g);
+        SYMB_HIP(h, hipGetLastError());
+        if (timed) {
+            SYMB_HIP(h, hipEventRecord(h->tev[2 * slot + 1], st));
+            h->timed.push_back({(NN ? 1 : 0) | 2 | (plain ? 0 : 4) | 16, gp.timing_flops});
+        }
+        return SYMB_OK;
+    }
     if (gp.variant == kTile256) return plain ? launch_gemm16_t<8, 8, NN, true>(h, gp, st) : launch_gemm16_t<8, 8, NN, false>(h, gp, st);
     if (gp.variant == kTileTall) return plain ? launch_gemm16_t<8, 4, NN, true>(h, gp, st) : launch_gemm16_t<8, 4, NN, false>(h, gp, st);
     return plain ? launch_gemm16_t<4, 4, NN, true>(h, gp, st) : launch_gemm16_t<4, 4, NN, false>(h, gp, st);
@@ -1188,7 +1212,7 @@ symb_status symb_debug_gemm_timing_read(symb_handle h, int32_t variant, double* 
     *launches = 0;
     *flops_total = 0.0;
     for (size_t i = 0; i < h->timed.size(); ++i) {
-        if ((variant & 8 ? h->timed[i].variant : h->timed[i].variant & 7) != variant) continue;
+        if ((variant >= 8 ? h->timed[i].variant : h->timed[i].variant & 7) != variant) continue;
         SYMB_HIP(h, hipEventSynchronize(h->tev[2 * i + 1]));
         float ms = 0.f;
         SYMB_HIP(h, hipEventElapsedTime(&ms, h->tev[2 * i], h->tev[2 * i + 1]));
@@ -1357,9 +1381,9 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
         return SYMB_OK;
     }
 
-    const GemmPlan plan = gemm_plan(bi.T, b->d_out, b->d_in, bi.n_lora > 0 ? lora_steps(b) : LoraSteps{},
+    const GemmPlan plan = gemm_plan(bi.T, b->d_out, b->d_in, b->weight_layout == SYMB_WEIGHT_CONV1D, bi.n_lora > 0 ? lora_steps(b) : LoraSteps{}, Ybase != nullptr,
                                     !Ybase && h->opt_k_split && h->xcd_rule && ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
-    const bool k_split = plan.split.parts > 1;
+    const bool k_split = plan.split.parts > 1 && plan.variant != kTileMid;
     const int bm = tile_rows(plan.variant), bn = tile_cols(plan.variant);
     std::vector<int32_t> lo, hi;
     plan_row_tiles(b, bm, lo, hi);
@@ -1618,9 +1642,9 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
         return SYMB_OK;
     }
 
-    const GemmPlan plan = gemm_plan(bi.T, b->d_in, b->d_out, lora ? lora_steps(b) : LoraSteps{},
+    const GemmPlan plan = gemm_plan(bi.T, b->d_in, b->d_out, b->weight_layout != SYMB_WEIGHT_CONV1D, lora ? lora_steps(b) : LoraSteps{}, dXbase != nullptr,
                                     !dXbase && h->opt_k_split && h->xcd_rule && ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
-    const bool k_split = plan.split.parts > 1;
+    const bool k_split = plan.split.parts > 1 && plan.variant != kTileMid;
     const int bm = tile_rows(plan.variant), bn = tile_cols(plan.variant);
     std::vector<int32_t> lo, hi;
     plan_row_tiles(b, bm, lo, hi);
