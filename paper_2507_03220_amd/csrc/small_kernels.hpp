@@ -562,10 +562,12 @@ symb_gemm_mid_kernel(const GemmParams p) {
 #pragma unroll
                 for (int c = 0; c < CB; ++c) wv[c] = pp < sd.rank ? wv[c] : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-                for (int c = 0; c < CB; ++c)
+                for (int m = 0; m < MB; ++m) {
+                    if (lo >= m0 + m * 16 + 16 || hi <= m0 + m * 16) continue;      // 16 rows of other segments
 #pragma unroll
-                    for (int m = 0; m < MB; ++m)
+                    for (int c = 0; c < CB; ++c)
                         acc[c][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv[c]), __builtin_bit_cast(bf16x8, xv[m]), acc[c][m], 0, 0, 0);
+                }
             }
         }
     };

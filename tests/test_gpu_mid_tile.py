@@ -1,5 +1,6 @@
 """Products of small layers in tiles of 32 rows: row counts around the tile, widths around 64 and 128 columns, inner dimensions around the slices (64 and 32 k) and with
 a remainder, every epilogue, LoRA ranks of several steps, buffers per client, in both directions and weight layouts."""
+import numpy as np
 import pytest
 import torch
 
@@ -40,3 +41,11 @@ def test_small_layers(d_in, d_out, lens, ranks):
     seg = lambda t: [t[c[0]:c[1]] if c else None for c in cut]  # noqa: E731
     n, _ = launches(lambda: sb.symb_base_linear_fwd_seg(gh.handle(), b, seg(X), W, bias, seg(Z), gh.workspace(b, sb.SYMB_OP_FWD)), 16 + 4 + 2)
     assert n == 1 and torch.equal(Y.view(torch.int16), Z.view(torch.int16))
+
+
+def test_an_infinity_stays_out_of_other_blocks_of_rows():
+    """A LoRA step meets only the blocks of 16 rows that hold rows of its segment."""
+    p = make_problem(3, 264, 200, [16, 60], [L], [8])
+    p["ads"][0].B[3] = 0x7f80
+    got = gh.bf16_to_f64(gh.forward(p["off"], p["ads"], p["X"], p["W"], p["bias"], want_base=False)[0])
+    assert not np.isfinite(got[:16, 3]).any() and np.isfinite(np.delete(got, 3, 1)).all() and np.isfinite(got[16:]).all()
