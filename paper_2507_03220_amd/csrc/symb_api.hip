@@ -343,7 +343,7 @@ LoraSteps lora_steps(const symb_batch* b) {
 // tiles: whole, 161 to 256 tiles, 1.12 to 1.19 for K = 1000 to 2500, 1.17 to 1.3 above, 1.0 below; 129 to 160 tiles 0.94 to 1.1; two or three parts, 65 to 128 tiles,
 // 1.1 to 1.46 for K >= 3072 and 0.93 to 0.99 below; fewer tiles 0.76 to 1.0 (and 1.15 in four parts of K > 5000).  Up to 128 rows half of every
 // such tile would be empty.  397 rows of 4096 -> 11008 with the adapters of
-// eleven clients 85.5 / 78 us, 16384 rows of 6144 -> 256 80 / 67.  Inside calls, behind the adapter passes, the whole ones of K < 3072 only break even (6000 rows of
+// eleven clients 85.5 / 78 us, 16384 rows of 6144 -> 256 80.6 / 59.3.  Inside calls, behind the adapter passes, the whole ones of K < 3072 only break even (6000 rows of
 // 2032 -> 800 74.5 / 77.4, the call): from K = 3072 on.  At most an eighth of the 128-row halves empty: 547 rows of 4096 -> 4992 85.0 / 89.8, 288 of 2320 ->
 // 11008 55.8 / 66.9 (the calls).  Not with LoRA steps beyond a quarter of the K stages: a tile of twice the
 // rows has up to twice as many, one after the other.
