@@ -165,6 +165,13 @@ def test_workspace_includes_partial_tiles_of_a_k_split():
     assert sb.symb_workspace_bytes(sb.Batch(4096, 4608, [0, 20480], [sb.Adapter()]), sb.SYMB_OP_FWD) == 0
 
 
+def test_parts_of_256x128_tiles_fit_an_xcd():
+    """All parts of the tiles that an XCD walks are resident at once: one workgroup on each of its 32 CUs."""
+    for rows, d_out, tiles, parts in ((1300, 1720, 84, 2), (2000, 1280, 80, 3), (2999, 888, 84, 2), (700, 3640, 87, 2), (1030, 2040, 80, 3)):
+        assert -(-rows // 256) * -(-d_out // 128) == tiles and -(-tiles // 8) * parts <= 32
+        assert sb.symb_workspace_bytes(sb.Batch(8192, d_out, [0, rows], [sb.Adapter()]), sb.SYMB_OP_FWD) == tiles * parts * 256 * 128 * 4, rows
+
+
 def test_parts_of_a_k_split_on_narrow_layers():
     # 32 stages of 64: four parts of 8 where few tiles leave the chip idle, two for 64 tiles; 16 stages: whole
     part = 128 * 128 * 4
