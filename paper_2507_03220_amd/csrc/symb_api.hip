@@ -341,7 +341,8 @@ LoraSteps lora_steps(const symb_batch* b) {
 // full round of one per CU, whole or in two or three K parts, take that tile: it moves three quarters of the bytes per flop from L2 to LDS and waits out
 // HBM latency with two stages in flight.  Time of the 128x128 tile over its, medians over products of 65 to 4500 rows, operands from HBM, by its
 // tiles: whole, 161 to 256 tiles, 1.12 to 1.19 for K = 1000 to 2500, 1.17 to 1.3 above, 1.0 below; 129 to 160 tiles 0.94 to 1.1; two or three parts, 65 to 128 tiles,
-// 1.1 to 1.46 for K >= 3072 and 0.93 to 0.99 below; fewer tiles 0.76 to 1.0 (and 1.15 in four parts of K > 5000).  Up to 128 rows half of every
+// 1.1 to 1.46 for K >= 3072 and 0.93 to 0.99 below; but inside calls, with their activations in cache and the partial tiles (up to 32 MiB) pushing weights out of it, 90 calls of all
+// flows: K = 3072 to 6000 0.85 to 1.05, median 0.96 (675 rows of 4096 x 4096, forward and input gradient, 78.4 / 88.4 us, 2178 of 4608 -> 1064 82.1 / 97.0), from 6144 on 0.95 to 1.48, median 1.14: from there on; fewer tiles 0.76 to 1.0 (and 1.15 in four parts of K > 5000).  Up to 128 rows half of every
 // such tile would be empty.  The parts are as many as fit an XCD's 32 CUs: 81 to 85 tiles in three parts are 33 workgroups on most XCDs, a second
 // round (84 tiles, us in two / three parts, 128x128 tile: 2993 rows of 4608 -> 856 42.2 / 59.4, 58.3; 2855 of 11192 -> 776 109.7 / 129.2, 130.3).  397 rows of 4096 -> 11008 with the adapters of
 // eleven clients 85.5 / 78 us, 16384 rows of 6144 -> 256 80.6 / 59.3.  Inside calls, behind the adapter passes, the whole ones of K < 3072 only break even (6000 rows of
@@ -369,7 +370,7 @@ GemmPlan gemm_plan(int M, int N, int K, bool nn, const LoraSteps& steps, bool wi
         const int parts = (int)(32 / std::max((tall + 7) / 8, 1L));      // of an XCD's tiles, in its 32 CUs
         const size_t bytes = (size_t)tall * parts * 256 * 128 * 4;
         if (tall > 160 && tall <= 256) return GemmPlan{kTileTall, SplitPlan{}};
-        if (tall > 64 && tall <= 128 && bytes <= room) return GemmPlan{kTileTall, SplitPlan{parts, 0, (int)tall, bytes, false}};
+        if (tall > 64 && tall <= 128 && K >= 6144 && bytes <= room) return GemmPlan{kTileTall, SplitPlan{parts, 0, (int)tall, bytes, false}};
     }
     if (p.split.bytes > room && p.split.doubled) {
         p.split.parts /= 2;

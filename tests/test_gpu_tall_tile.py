@@ -26,7 +26,7 @@ def launches(call, variant):
 
 @pytest.mark.parametrize("T,d_in,d_out,parts,ranks", [
     (1300, 3144, 4104, 1, [16, 5]), (1500, 3080, 4096, 1, [16, 40, 5]),         # whole: a remainder of 8 beyond the last stage
-    (700, 4104, 4104, 2, [16, 128, 5]), (1000, 3080, 2056, 3, [100, 16, 5])])
+    (700, 6152, 4104, 2, [16, 128, 5]), (1000, 6152, 2056, 3, [100, 16, 5])])
 def test_tall_tile(T, d_in, d_out, parts, ranks):
     plain = sb.Batch(d_in, d_out, [0, T], [sb.Adapter()])
     tiles = -(-T // 256) * -(-d_out // 128)

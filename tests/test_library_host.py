@@ -172,6 +172,12 @@ def test_parts_of_256x128_tiles_fit_an_xcd():
         assert sb.symb_workspace_bytes(sb.Batch(8192, d_out, [0, rows], [sb.Adapter()]), sb.SYMB_OP_FWD) == tiles * parts * 256 * 128 * 4, rows
 
 
+def test_short_inner_dimensions_do_not_split_256x128_tiles():
+    # 675 rows, 4096 wide: 96 tiles of 256x128 (192 of 128x128, whole); partial tiles pay from K = 6144 on
+    for k, parts in ((4096, 0), (6136, 0), (6144, 2), (11008, 2)):
+        assert sb.symb_workspace_bytes(sb.Batch(k, 4096, [0, 675], [sb.Adapter()]), sb.SYMB_OP_FWD) == 96 * parts * 256 * 128 * 4, k
+
+
 def test_parts_of_a_k_split_on_narrow_layers():
     # 32 stages of 64: four parts of 8 where few tiles leave the chip idle, two for 64 tiles; 16 stages: whole
     part = 128 * 128 * 4
