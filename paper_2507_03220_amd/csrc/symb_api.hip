@@ -518,14 +518,16 @@ SmallPlan small_plan(const symb_batch* b, const BatchInfo& bi, int op, bool lora
 // columns, both directions, us from memory / in steps: 4096 x 4096, 96 rows (five parts), 24 steps 40.8 / 37.4, 48 steps 42.3 / 43.4, 96 steps
 // 53.7 / 61.8; 64 rows beside 1984 (whole), 16 steps 9 us less, 8 steps equal; 512 rows of 11008 -> 4096 (four parts) 32 steps 108 / 99, 64 steps equal; 2048
 // rows of 4096 -> 11008 (256x256 tile) 16 steps 232 / 205, 64 steps 270 / 317.  By the lines below what is chosen is at most 3 %, what is not
-// at most 5 % slower than the other way, over the whole sweep.
+// at most 5 % slower than the other way, over the whole sweep.  The 256x128 tile, whose parts share the steps too, has the 128x128 one's line: 400 calls of 129 to 4500 rows
+// with 3 to 150 short clients, whole and in two or three parts, are at most 4.1 % slower than the faster way, 0.16 % on average; by the 256x256 tile's line 6.5 and
+// 0.35 % (3894 rows of 9072 -> 544 in three parts, 16 steps, 101.1 from memory / 94.9 in steps; 252 of 7192 -> 16256 in two, 10 steps, 115.0 / 108.2).
 // Batches of more than kDeltaSegments segments, or of more terms than kDeltaBytes, keep the steps, as does one whose descriptors have no
 // room for the terms' (add_gemm_desc).
 constexpr int kDeltaSegments = 4096;
 constexpr size_t kDeltaBytes = (size_t)160 << 20;
-int delta_steps(int tile_m, int parts, int rows, int N) {
+int delta_steps(int variant, int parts, int rows, int N) {
     const double elems = 1e-6 * rows * N;
-    return (int)(tile_m == 256 ? 8 + 1.5 * elems : 8 * parts + 5 * elems);
+    return (int)(variant == kTile256 ? 8 + 1.5 * elems : 8 * parts + 5 * elems);
 }
 struct DeltaPlan {
     std::vector<RowChunk> items;          // the segments (pad: first row of their terms)
@@ -547,7 +549,7 @@ DeltaPlan delta_plan(const symb_batch* b, const GemmPlan& plan, int N) {
             all += k;
             rows += b->seg_offsets[i + 1] - b->seg_offsets[i];
         }
-    const int least = delta_steps(tile_m, plan.split.parts, rows, N);
+    const int least = delta_steps(plan.variant, plan.split.parts, rows, N);
     if (all < least || (size_t)rows * N * 4 > kDeltaBytes) return d;
     std::vector<int> tile((b->seg_offsets[S] + tile_m - 1) / tile_m, 0);
     for (int i = 0; i < S; ++i)

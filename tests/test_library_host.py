@@ -227,6 +227,10 @@ def test_terms_of_short_segments_in_the_workspace():
     assert figure(16, 64, 64, 1984, 4096, 4096) == 64 * 4096 * 4        # 16 steps of a whole tile; of one in five K parts: none
     assert figure(16, 64, 96, 0, 4096, 4096) == 0
     assert figure(1, 128, 3600, 8, 64, 36864) == 0             # more than 160 MiB of terms
+    # 256x128 tiles: 16 steps are worth it in a whole tile, of one in three parts 24 are
+    assert figure(8, 8, 128, 3766, 9072, 544) == 0
+    assert figure(8, 8, 256, 3638, 9072, 544) == 256 * 544 * 4
+    assert figure(8, 8, 128, 869, 4096, 6144) == 128 * 6144 * 4
 
 
 def test_unknown_weight_layout_is_rejected():
