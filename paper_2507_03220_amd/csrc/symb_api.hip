@@ -359,11 +359,13 @@ LoraSteps lora_steps(const symb_batch* b) {
 struct GemmPlan {
     int variant = kTile128;
     SplitPlan split;
+    bool unsplit_for_base = false;    // the shape would split, but the pre-adapter output is wanted
 };
 GemmPlan gemm_plan(int M, int N, int K, bool nn, const LoraSteps& steps, bool with_base, size_t room) {
     GemmPlan p;
     p.variant = gemm_variant(M, N, K);
     p.split = gemm_split_plan(M, N, K);
+    p.unsplit_for_base = with_base && p.variant == kTile128 && p.split.parts > 1;
     const long tall = (long)((M + 255) / 256) * ((N + 127) / 128);
     const long small = (long)((M + 127) / 128) * ((N + 127) / 128);
     if (p.variant == kTile128 && M > 128 && K >= 3072 && 4 * small >= 7 * tall && !p.split.doubled && 4 * steps.most256 <= K / 64) {
@@ -521,13 +523,17 @@ SmallPlan small_plan(const symb_batch* b, const BatchInfo& bi, int op, bool lora
 // at most 5 % slower than the other way, over the whole sweep.  The 256x128 tile, whose parts share the steps too, has the 128x128 one's line: 400 calls of 129 to 4500 rows
 // with 3 to 150 short clients, whole and in two or three parts, are at most 4.1 % slower than the faster way, 0.16 % on average; by the 256x256 tile's line 6.5 and
 // 0.35 % (3894 rows of 9072 -> 544 in three parts, 16 steps, 101.1 from memory / 94.9 in steps; 252 of 7192 -> 16256 in two, 10 steps, 115.0 / 108.2).
+// A launch whose shape would split, but whose pre-adapter output is wanted, has the line of two parts: 40 training steps with such calls, terms against steps, lost up to 4 % at 8
+// to 15 steps (136 rows of 6144 -> 1416, 13 steps in both directions, 255.1 us in steps, 265.6 from memory) and gained up to 18 % from 17 on (348 of 4096 -> 1104, 58
+// steps, 167.5 / 141.6).
 // Batches of more than kDeltaSegments segments, or of more terms than kDeltaBytes, keep the steps, as does one whose descriptors have no
 // room for the terms' (add_gemm_desc).
 constexpr int kDeltaSegments = 4096;
 constexpr size_t kDeltaBytes = (size_t)160 << 20;
-int delta_steps(int variant, int parts, int rows, int N) {
+int delta_steps(const GemmPlan& plan, int rows, int N) {
     const double elems = 1e-6 * rows * N;
-    return (int)(variant == kTile256 ? 8 + 1.5 * elems : 8 * parts + 5 * elems);
+    const int parts = plan.unsplit_for_base ? 2 : plan.split.parts;
+    return (int)(plan.variant == kTile256 ? 8 + 1.5 * elems : 8 * parts + 5 * elems);
 }
 struct DeltaPlan {
     std::vector<RowChunk> items;          // the segments (pad: first row of their terms)
@@ -549,7 +555,7 @@ DeltaPlan delta_plan(const symb_batch* b, const GemmPlan& plan, int N) {
             all += k;
             rows += b->seg_offsets[i + 1] - b->seg_offsets[i];
         }
-    const int least = delta_steps(plan.variant, plan.split.parts, rows, N);
+    const int least = delta_steps(plan, rows, N);
     if (all < least || (size_t)rows * N * 4 > kDeltaBytes) return d;
     std::vector<int> tile((b->seg_offsets[S] + tile_m - 1) / tile_m, 0);
     for (int i = 0; i < S; ++i)
@@ -638,6 +644,10 @@ WsLayout ws_layout(const symb_batch* b, const BatchInfo& bi, int op, bool full_b
     w.total = std::max(small_end, cur);
     return w;
 }
+
+// Where a call's terms of short segments start: right behind its own partial tiles.  A call that does not split (pre-adapter output wanted) may select
+// more rows than the figure counts for a split call, and has the place of the figure's partial tiles for them, at least twice the whole output in fp32.
+size_t terms_offset(const WsLayout& w, const GemmPlan& plan) { return w.tp_off + align_up(plan.split.bytes, 256); }
 
 // ---- descriptor blob -------------------------------------------------------------------------
 struct Blob {
@@ -1406,8 +1416,9 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     std::vector<SegDesc> sd_gemm = sd;
     std::vector<int64_t> pk_off(bi.S, 0);
     DeltaPlan delta;
-    if (bi.n_lora && ws_bytes > wl.de_off) delta = delta_plan(b, plan, b->d_out);
-    if (!delta.items.empty() && ws_bytes < wl.de_off + (size_t)delta.rows * b->d_out * 4) delta = DeltaPlan{};
+    const size_t de_off = terms_offset(wl, plan);
+    if (bi.n_lora && ws_bytes > de_off) delta = delta_plan(b, plan, b->d_out);
+    if (!delta.items.empty() && ws_bytes < de_off + (size_t)delta.rows * b->d_out * 4) delta = DeltaPlan{};
     if (conv1d && bi.n_lora) {
         int64_t cur = 0;
         for (int i = 0; i < bi.S; ++i)
@@ -1469,10 +1480,10 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
         if ((st = launch_skinny<false>(h, sp, (int)chunks.size(), bi.max_rpad, s)) != SYMB_OK) return st;
     }
     if (!delta.items.empty() && (st = launch_delta(h, false, (const SegDesc*)(dev + o_seg), (const RowChunk*)(dev + db.items), (int)delta.items.size(), b->d_out,
-                                                   Hs, bi.max_rpad, (float*)(wsb + wl.de_off), s)) != SYMB_OK) return st;
+                                                   Hs, bi.max_rpad, (float*)(wsb + de_off), s)) != SYMB_OK) return st;
     GemmParams gp{};
     if (!delta.items.empty()) {
-        gp.delta = (const float*)(wsb + wl.de_off);
+        gp.delta = (const float*)(wsb + de_off);
         gp.tile_delta = (const TileDelta*)(dev + db.tiles);
     }
     gp.Aop = x_op;
@@ -1688,8 +1699,9 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     const bool conv1d = b->weight_layout == SYMB_WEIGHT_CONV1D;
     std::vector<SegDesc> sd_gemm = sd;
     DeltaPlan delta;
-    if (lora && ws_bytes > wl.de_off) delta = delta_plan(b, plan, b->d_in);
-    if (!delta.items.empty() && ws_bytes < wl.de_off + (size_t)delta.rows * b->d_in * 4) delta = DeltaPlan{};
+    const size_t de_off = terms_offset(wl, plan);
+    if (lora && ws_bytes > de_off) delta = delta_plan(b, plan, b->d_in);
+    if (!delta.items.empty() && ws_bytes < de_off + (size_t)delta.rows * b->d_in * 4) delta = DeltaPlan{};
     std::vector<int64_t> pk_off(bi.S, 0), pa_off(bi.S, 0);
     {
         int64_t cur = 0, cura = 0;
@@ -1760,10 +1772,10 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
         a_op = copy;
     }
     if (!delta.items.empty() && (st = launch_delta(h, true, (const SegDesc*)(dev + o_seg), (const RowChunk*)(dev + db.items), (int)delta.items.size(), b->d_in,
-                                                   dH, bi.max_rpad, (float*)(wsb + wl.de_off), s)) != SYMB_OK) return st;
+                                                   dH, bi.max_rpad, (float*)(wsb + de_off), s)) != SYMB_OK) return st;
     GemmParams gp{};
     if (!delta.items.empty()) {
-        gp.delta = (const float*)(wsb + wl.de_off);
+        gp.delta = (const float*)(wsb + de_off);
         gp.tile_delta = (const TileDelta*)(dev + db.tiles);
     }
     gp.Aop = a_op;

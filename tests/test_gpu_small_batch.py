@@ -277,6 +277,39 @@ def test_timed_work_of_a_gemm_leaves_out_the_terms_from_memory():
         assert work == 2.0 * 392 * (p["T"] * 264 + rows)
 
 
+@pytest.mark.parametrize("d_in,d_out", [(4096, 4096), (6144, 2056)])         # 128x128 tiles in five parts; 256x128 tiles in two
+def test_terms_of_a_call_with_pre_adapter_output_fit_the_reported_workspace(d_in, d_out):
+    """Such a call does not split: its chains of steps are as long as they are, and it selects more rows for memory than the figure's split call."""
+    lens = [1] * 160 + ([1100] if d_in == 6144 else [])
+    p = make_problem(d_in, d_in, d_out, lens, [L] * 160 + [N], [16])
+    off, oads = p["off"], oracle_ads(p["ads"])
+    dev = gh.upload_adapters(p["ads"], d_in, d_out, grads=False)
+    b = sb.Batch(d_in, d_out, off, dev.descs)
+    X, W, dY = gh.to_dev(p["X"]), gh.to_dev(p["W"]), gh.to_dev(p["dY"])
+    rows = synth.sample_rows(off, 12, f"base{d_in}", block=128)
+    for base in (False, True):
+        for back in (False, True):
+            k, n = (d_out, d_in) if back else (d_in, d_out)
+            out = torch.empty(p["T"], n, device="cuda", dtype=torch.bfloat16)
+            extra = torch.empty_like(out) if base else None
+            ws = torch.empty(sb.symb_workspace_bytes(b, sb.SYMB_OP_BWD_INPUT if back else sb.SYMB_OP_FWD), device="cuda", dtype=torch.uint8)
+            sb.symb_debug_gemm_timing_enable(gh.handle(), 1)
+            try:
+                if back:
+                    sb.symb_base_linear_bwd_input_ex(gh.handle(), b, dY, W, out, extra, sb.SYMB_BWD_FULL, ws)
+                else:
+                    sb.symb_base_linear_fwd(gh.handle(), b, X, W, None, out, extra, ws)
+                work = sum(sb.symb_debug_gemm_timing_read(gh.handle(), v)[2] for v in range(8))
+            finally:
+                sb.symb_debug_gemm_timing_enable(gh.handle(), 0)
+            left = 32 if not base and d_in == 4096 else 0            # (the second row tile of a call in five parts keeps its 32 steps)
+            assert work == 2.0 * n * (p["T"] * k + left * 16), (base, back)
+            if back:
+                check_dx(gh.bf16_to_f64(out[rows]), off, oads, p["dY"], p["W"], "dX", rows=rows)
+            else:
+                check_y(gh.bf16_to_f64(out[rows]), off, oads, p["X"], p["W"], None, "Y", rows=rows)
+
+
 def test_short_segments_beside_more_rows_than_their_masks_have_room_for():
     """The terms of short segments cost 36 bytes of descriptors per row tile: a batch of 3.4 million rows, whose other descriptors fit
     the 2 MiB slot, is accepted and its short segments keep their steps inside the GEMM."""
