@@ -267,7 +267,6 @@ int gemm_group_m(int num_m_tiles, int num_n_tiles, const std::vector<int32_t>& s
 //    each) would cost what the split saves.
 // parts is at most 8.  A pure function of the shape: the
 // workspace figure does not depend on the process environment or on the handle.
-constexpr int kDeltaRows = 16;  // longest LoRA segment whose term may be computed beforehand (see delta_plan)
 struct SplitPlan {
     int parts = 1;        // K ranges per split tile (1: no split)
     int whole = 0;        // tiles per XCD that stay whole
@@ -314,22 +313,94 @@ SplitPlan gemm_split_plan(int M, int N, int K) {
     return s;
 }
 
-// The LoRA k-steps of the 256-row tile that has the most (a segment of rank r: 2 ceil16(r) / 32).  Of segments short enough
-// to be computed beforehand (kDeltaRows) no more than would be left to the steps; few256: those alone, all of them.
+struct DeltaPlan {
+    std::vector<RowChunk> items;          // the segments (pad: first row of their terms)
+    int rows = 0;                         // rows of terms
+};
+// The tile of a product, its K split and the terms of short segments that it adds from memory (gemm_plan).
+struct GemmPlan {
+    int variant = kTile128;
+    SplitPlan split;
+    bool unsplit_for_base = false;    // the shape would split, but the pre-adapter output is wanted
+    DeltaPlan terms;
+};
+
+// Short LoRA segments (at most kDeltaRows rows) whose term the tiled kernels add from memory (symb_lora_delta_kernel) instead of running a chain of k-steps
+// for each: all of them that meet a row tile with at least delta_steps() such steps.  The steps of the row tile with the most set what the
+// chains cost (the K parts of a split tile share them), a launch and the traffic of the fp32 terms (8 bytes per row and output column) what they
+// cost from memory.  Measured over clients of 1 to 16 rows and ranks 8 to 128, 96 to 2048 such rows alone or beside long segments, 1024 to 11008
+// columns, both directions, us from memory / in steps: 4096 x 4096, 96 rows (five parts), 24 steps 40.8 / 37.4, 48 steps 42.3 / 43.4, 96 steps
+// 53.7 / 61.8; 64 rows beside 1984 (whole), 16 steps 9 us less, 8 steps equal; 512 rows of 11008 -> 4096 (four parts) 32 steps 108 / 99, 64 steps equal; 2048
+// rows of 4096 -> 11008 (256x256 tile) 16 steps 232 / 205, 64 steps 270 / 317.  By the lines below what is chosen is at most 3 %, what is not
+// at most 5 % slower than the other way, over the whole sweep.  The 256x128 tile, whose parts share the steps too, has the 128x128 one's line: 400 calls of 129 to 4500 rows
+// with 3 to 150 short clients, whole and in two or three parts, are at most 4.1 % slower than the faster way, 0.16 % on average; by the 256x256 tile's line 6.5 and
+// 0.35 % (3894 rows of 9072 -> 544 in three parts, 16 steps, 101.1 from memory / 94.9 in steps; 252 of 7192 -> 16256 in two, 10 steps, 115.0 / 108.2).
+// A launch whose shape would split, but whose pre-adapter output is wanted, has the line of two parts: 40 training steps with such calls, terms against steps, lost up to 4 % at 8
+// to 15 steps (136 rows of 6144 -> 1416, 13 steps in both directions, 255.1 us in steps, 265.6 from memory) and gained up to 18 % from 17 on (348 of 4096 -> 1104, 58
+// steps, 167.5 / 141.6).
+// Batches of more than kDeltaSegments segments, or of more terms than kDeltaBytes, keep the steps, as does one whose descriptors have no
+// room for the terms' (add_gemm_desc).
+constexpr int kDeltaRows = 16, kDeltaSegments = 4096;
+constexpr size_t kDeltaBytes = (size_t)160 << 20;
+int delta_steps(const GemmPlan& plan, int rows, int N) {
+    const double elems = 1e-6 * rows * N;
+    const int parts = plan.unsplit_for_base ? 2 : plan.split.parts;
+    return (int)(plan.variant == kTile256 ? 8 + 1.5 * elems : 8 * parts + 5 * elems);
+}
+DeltaPlan delta_plan(const symb_batch* b, const GemmPlan& plan, int N) {
+    const int tile_m = tile_rows(plan.variant);
+    DeltaPlan d;
+    const int S = b->num_segments;
+    auto steps = [&](int i) {
+        const int n = b->seg_offsets[i + 1] - b->seg_offsets[i];
+        return b->adapters[i].kind == SYMB_ADAPTER_LORA && n > 0 && n <= kDeltaRows ? rpad_of(b->adapters[i].rank) / 16 : 0;
+    };
+    if (S > kDeltaSegments) return d;
+    int all = 0, rows = 0;
+    for (int i = 0; i < S; ++i)
+        if (const int k = steps(i)) {
+            all += k;
+            rows += b->seg_offsets[i + 1] - b->seg_offsets[i];
+        }
+    const int least = delta_steps(plan, rows, N);
+    if (all < least || (size_t)rows * N * 4 > kDeltaBytes) return d;
+    std::vector<int> tile((b->seg_offsets[S] + tile_m - 1) / tile_m, 0);
+    for (int i = 0; i < S; ++i)
+        if (const int k = steps(i)) {
+            const int u = b->seg_offsets[i] / tile_m, v = (b->seg_offsets[i + 1] - 1) / tile_m;
+            tile[u] += k;
+            if (v != u) tile[v] += k;
+        }
+    for (int i = 0; i < S; ++i)
+        if (steps(i)) {
+            const int lo = b->seg_offsets[i], n = b->seg_offsets[i + 1] - lo;
+            if (tile[lo / tile_m] < least && tile[(lo + n - 1) / tile_m] < least) continue;
+            d.items.push_back(RowChunk{i, lo, n, d.rows});
+            d.rows += n;
+        }
+    return d;
+}
+
+// The LoRA k-steps of the 256-row tile that has the most (a segment of rank r: 2 ceil16(r) / 32): those of long segments and of the short ones that
+// the terms leave out; short ones, whichever way they go, as at least min(8, their steps).  few256: short ones alone, all of them.
 struct LoraSteps {
     int most256 = 0, few256 = 0;
 };
-LoraSteps lora_steps(const symb_batch* b) {
+LoraSteps lora_steps(const symb_batch* b, const DeltaPlan& terms) {
     LoraSteps s;
-    int tile = -1, sum = 0, few = 0;                 // the tile so far: steps of long and of short segments
+    int tile = -1, sum = 0, few = 0, left = 0;       // the tile so far: steps of long and of short segments, and of the short ones that keep theirs
+    size_t at = 0;                                   // the terms are in the segments' order
     for (int i = 0; i < b->num_segments; ++i) {
+        const bool taken = at < terms.items.size() && terms.items[at].seg == i;
+        at += taken;
         const int lo = b->seg_offsets[i], n = b->seg_offsets[i + 1] - lo;
         if (b->adapters[i].kind != SYMB_ADAPTER_LORA || !n) continue;
         const int k = rpad_of(b->adapters[i].rank) / 16, first = lo / 256, last = (lo + n - 1) / 256;
         for (int u : {first, last}) {                // (the tiles in between hold this segment alone)
-            if (u != tile) { tile = u; sum = few = 0; }
+            if (u != tile) { tile = u; sum = few = left = 0; }
             (n > kDeltaRows ? sum : few) += k;
-            s.most256 = std::max(s.most256, sum + std::min(few, 8));
+            if (n <= kDeltaRows && !taken) left += k;
+            s.most256 = std::max(s.most256, sum + std::max(left, std::min(few, 8)));
             s.few256 = std::max(s.few256, few);
             if (first == last) break;
         }
@@ -348,41 +419,55 @@ LoraSteps lora_steps(const symb_batch* b) {
 // eleven clients 85.5 / 78 us, 16384 rows of 6144 -> 256 80.6 / 59.3.  Inside calls, behind the adapter passes, the whole ones of K < 3072 only break even (6000 rows of
 // 2032 -> 800 74.5 / 77.4, the call): from K = 3072 on.  At most an eighth of the 128-row halves empty: 547 rows of 4096 -> 4992 85.0 / 89.8, 288 of 2320 ->
 // 11008 55.8 / 66.9 (the calls).  Not with LoRA steps beyond a quarter of the K stages: a tile of twice the
-// rows has up to twice as many, one after the other.
+// rows has up to twice as many, one after the other (batches whose terms do not come from memory, for want of room or by their number, count in full: 2000 one-token clients on
+// 4096 x 4096 with room for nothing optional keep 128x128 tiles of 128 steps each).
 // Small layers take the tiles of 32 rows (symb_gemm_mid_kernel) as long as these are one round of workgroups: time of the 128x128 tile over theirs, 13 300 products
 // of 65 to 1500 rows, medians by K, K-contiguous weight: 1.2 (K = 256), 1.3 to 1.37 (512), 1.3 to 1.46 (768), 1.4 to 1.57 (1024), 1.55 to 1.74 (1536) up to 256
 // workgroups, 0.9 to 1.0 with 257 to 512, 0.6 beyond; where the 128x128 tiles are split over K 1.23 to 1.34 up to K = 2048, 1.03 to 1.1 above;
 // N-contiguous 1.07 to 1.25 up to 192 workgroups, 0.75 beyond 256, and 0.9 to 1.0 against split tiles.  (The workspace figure stays the split's.)  Not with
 // a pre-adapter output or with steps enough to be computed beforehand.
-// room: bytes for partial tiles (0: no split).  Doubled parts that do not fit (397 rows of 11008 -> 4096 with an
+// room: bytes behind the mandatory regions, for partial tiles (can_split) and, behind them, the terms.  Doubled parts that do not fit (397 rows of 11008 -> 4096 with an
 // adapter in the 32 MiB static scratch) are halved again, any other plan runs unsplit.
-struct GemmPlan {
-    int variant = kTile128;
-    SplitPlan split;
-    bool unsplit_for_base = false;    // the shape would split, but the pre-adapter output is wanted
-};
-GemmPlan gemm_plan(int M, int N, int K, bool nn, const LoraSteps& steps, bool with_base, size_t room) {
+GemmPlan gemm_plan(const symb_batch* b, int N, int K, bool nn, bool lora, bool with_base, bool can_split, size_t room) {
     GemmPlan p;
+    const int M = b->seg_offsets[b->num_segments];
+    const size_t split_room = can_split ? room : 0;
+    auto with_terms = [&](GemmPlan& g) {
+        if (lora) g.terms = delta_plan(b, g, N);
+        if (!g.terms.items.empty() && align_up(g.split.bytes, 256) + (size_t)g.terms.rows * N * 4 > room) g.terms = DeltaPlan{};
+    };
     p.variant = gemm_variant(M, N, K);
     p.split = gemm_split_plan(M, N, K);
     p.unsplit_for_base = with_base && p.variant == kTile128 && p.split.parts > 1;
     const long tall = (long)((M + 255) / 256) * ((N + 127) / 128);
     const long small = (long)((M + 127) / 128) * ((N + 127) / 128);
-    if (p.variant == kTile128 && M > 128 && K >= 3072 && 4 * small >= 7 * tall && !p.split.doubled && 4 * steps.most256 <= K / 64) {
+    if (p.variant == kTile128 && M > 128 && K >= 3072 && 4 * small >= 7 * tall && !p.split.doubled) {
         const int parts = (int)(32 / std::max((tall + 7) / 8, 1L));      // of an XCD's tiles, in its 32 CUs
         const size_t bytes = (size_t)tall * parts * 256 * 128 * 4;
-        if (tall > 160 && tall <= 256) return GemmPlan{kTileTall, SplitPlan{}};
-        if (tall > 64 && tall <= 128 && K >= 6144 && bytes <= room) return GemmPlan{kTileTall, SplitPlan{parts, 0, (int)tall, bytes, false}};
+        const bool whole = tall > 160 && tall <= 256, split = tall > 64 && tall <= 128 && K >= 6144 && bytes <= split_room;
+        GemmPlan t;
+        t.variant = kTileTall;
+        if (split) t.split = SplitPlan{parts, 0, (int)tall, bytes, false};
+        if (whole || split) {
+            with_terms(t);
+            if (!lora || 4 * lora_steps(b, t.terms).most256 <= K / 64) return t;
+        }
     }
-    if (p.split.bytes > room && p.split.doubled) {
+    if (p.split.bytes > split_room && p.split.doubled) {
         p.split.parts /= 2;
         p.split.bytes /= 2;
     }
-    if (p.split.bytes > room) p.split = SplitPlan{};
+    if (p.split.bytes > split_room) p.split = SplitPlan{};
     const long mid = (long)((M + MID_ROWS - 1) / MID_ROWS) * ((N + small_cols(nn) - 1) / small_cols(nn));
-    if (p.variant == kTile128 && !with_base && steps.most256 <= 16 && steps.few256 < 8 &&
-        (p.split.parts == 1 ? K <= 1536 && mid <= (nn ? 192 : 256) : !nn && K <= 2048 && mid <= 192))
-        p.variant = kTileMid;
+    if (p.variant == kTile128 && !with_base &&
+        (p.split.parts == 1 ? K <= 1536 && mid <= (nn ? 192 : 256) : !nn && K <= 2048 && mid <= 192)) {
+        const LoraSteps steps = lora ? lora_steps(b, DeltaPlan{}) : LoraSteps{};
+        if (steps.most256 <= 16 && steps.few256 < 8) {
+            p.variant = kTileMid;
+            return p;
+        }
+    }
+    with_terms(p);
     return p;
 }
 
@@ -513,66 +598,6 @@ SmallPlan small_plan(const symb_batch* b, const BatchInfo& bi, int op, bool lora
     return s;
 }
 
-// Short LoRA segments (at most kDeltaRows rows) whose term the tiled kernels add from memory (symb_lora_delta_kernel) instead of running a chain of k-steps
-// for each: all of them that meet a row tile with at least delta_steps() such steps.  The steps of the row tile with the most set what the
-// chains cost (the K parts of a split tile share them), a launch and the traffic of the fp32 terms (8 bytes per row and output column) what they
-// cost from memory.  Measured over clients of 1 to 16 rows and ranks 8 to 128, 96 to 2048 such rows alone or beside long segments, 1024 to 11008
-// columns, both directions, us from memory / in steps: 4096 x 4096, 96 rows (five parts), 24 steps 40.8 / 37.4, 48 steps 42.3 / 43.4, 96 steps
-// 53.7 / 61.8; 64 rows beside 1984 (whole), 16 steps 9 us less, 8 steps equal; 512 rows of 11008 -> 4096 (four parts) 32 steps 108 / 99, 64 steps equal; 2048
-// rows of 4096 -> 11008 (256x256 tile) 16 steps 232 / 205, 64 steps 270 / 317.  By the lines below what is chosen is at most 3 %, what is not
-// at most 5 % slower than the other way, over the whole sweep.  The 256x128 tile, whose parts share the steps too, has the 128x128 one's line: 400 calls of 129 to 4500 rows
-// with 3 to 150 short clients, whole and in two or three parts, are at most 4.1 % slower than the faster way, 0.16 % on average; by the 256x256 tile's line 6.5 and
-// 0.35 % (3894 rows of 9072 -> 544 in three parts, 16 steps, 101.1 from memory / 94.9 in steps; 252 of 7192 -> 16256 in two, 10 steps, 115.0 / 108.2).
-// A launch whose shape would split, but whose pre-adapter output is wanted, has the line of two parts: 40 training steps with such calls, terms against steps, lost up to 4 % at 8
-// to 15 steps (136 rows of 6144 -> 1416, 13 steps in both directions, 255.1 us in steps, 265.6 from memory) and gained up to 18 % from 17 on (348 of 4096 -> 1104, 58
-// steps, 167.5 / 141.6).
-// Batches of more than kDeltaSegments segments, or of more terms than kDeltaBytes, keep the steps, as does one whose descriptors have no
-// room for the terms' (add_gemm_desc).
-constexpr int kDeltaSegments = 4096;
-constexpr size_t kDeltaBytes = (size_t)160 << 20;
-int delta_steps(const GemmPlan& plan, int rows, int N) {
-    const double elems = 1e-6 * rows * N;
-    const int parts = plan.unsplit_for_base ? 2 : plan.split.parts;
-    return (int)(plan.variant == kTile256 ? 8 + 1.5 * elems : 8 * parts + 5 * elems);
-}
-struct DeltaPlan {
-    std::vector<RowChunk> items;          // the segments (pad: first row of their terms)
-    int rows = 0;                         // rows of terms
-};
-DeltaPlan delta_plan(const symb_batch* b, const GemmPlan& plan, int N) {
-    const int tile_m = tile_rows(plan.variant);
-    DeltaPlan d;
-    if (plan.variant == kTileMid) return d;
-    const int S = b->num_segments;
-    auto steps = [&](int i) {
-        const int n = b->seg_offsets[i + 1] - b->seg_offsets[i];
-        return b->adapters[i].kind == SYMB_ADAPTER_LORA && n > 0 && n <= kDeltaRows ? rpad_of(b->adapters[i].rank) / 16 : 0;
-    };
-    if (S > kDeltaSegments) return d;
-    int all = 0, rows = 0;
-    for (int i = 0; i < S; ++i)
-        if (const int k = steps(i)) {
-            all += k;
-            rows += b->seg_offsets[i + 1] - b->seg_offsets[i];
-        }
-    const int least = delta_steps(plan, rows, N);
-    if (all < least || (size_t)rows * N * 4 > kDeltaBytes) return d;
-    std::vector<int> tile((b->seg_offsets[S] + tile_m - 1) / tile_m, 0);
-    for (int i = 0; i < S; ++i)
-        if (const int k = steps(i)) {
-            const int u = b->seg_offsets[i] / tile_m, v = (b->seg_offsets[i + 1] - 1) / tile_m;
-            tile[u] += k;
-            if (v != u) tile[v] += k;
-        }
-    for (int i = 0; i < S; ++i)
-        if (steps(i)) {
-            const int lo = b->seg_offsets[i], n = b->seg_offsets[i + 1] - lo;
-            if (tile[lo / tile_m] < least && tile[(lo + n - 1) / tile_m] < least) continue;
-            d.items.push_back(RowChunk{i, lo, n, d.rows});
-            d.rows += n;
-        }
-    return d;
-}
 std::vector<TileDelta> delta_tiles(const DeltaPlan& d, int num_m_tiles, int tile_m) {
     std::vector<TileDelta> v(d.items.empty() ? 0 : num_m_tiles, TileDelta{});
     for (const RowChunk& it : d.items)
@@ -636,10 +661,9 @@ WsLayout ws_layout(const symb_batch* b, const BatchInfo& bi, int op, bool full_b
     if (op != SYMB_OP_ADAPTER_GRAD) {
         const int N = op == SYMB_OP_FWD ? b->d_out : b->d_in, K = op == SYMB_OP_FWD ? b->d_in : b->d_out;
         const bool lora = bi.n_lora && (op == SYMB_OP_FWD || full_bwd);
-        const GemmPlan plan = gemm_plan(bi.T, N, K, (op == SYMB_OP_FWD) == conv1d, lora ? lora_steps(b) : LoraSteps{}, false, SIZE_MAX);
+        const GemmPlan plan = gemm_plan(b, N, K, (op == SYMB_OP_FWD) == conv1d, lora, false, true, SIZE_MAX);
         take(w.tp_off, w.tp_bytes, plan.split.bytes);
-        const int rows = lora ? delta_plan(b, plan, N).rows : 0;
-        take(w.de_off, w.de_bytes, (size_t)rows * N * 4);
+        take(w.de_off, w.de_bytes, (size_t)plan.terms.rows * N * 4);
     }
     w.total = std::max(small_end, cur);
     return w;
@@ -1398,8 +1422,8 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
         return SYMB_OK;
     }
 
-    const GemmPlan plan = gemm_plan(bi.T, b->d_out, b->d_in, b->weight_layout == SYMB_WEIGHT_CONV1D, bi.n_lora > 0 ? lora_steps(b) : LoraSteps{}, Ybase != nullptr,
-                                    !Ybase && h->opt_k_split && h->xcd_rule && ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
+    GemmPlan plan = gemm_plan(b, b->d_out, b->d_in, b->weight_layout == SYMB_WEIGHT_CONV1D, bi.n_lora > 0, Ybase != nullptr, !Ybase && h->opt_k_split && h->xcd_rule,
+                              ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
     const bool k_split = plan.split.parts > 1 && plan.variant != kTileMid;
     const int bm = tile_rows(plan.variant), bn = tile_cols(plan.variant);
     std::vector<int32_t> lo, hi;
@@ -1415,10 +1439,8 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     unsigned char* wsb = (unsigned char*)ws;
     std::vector<SegDesc> sd_gemm = sd;
     std::vector<int64_t> pk_off(bi.S, 0);
-    DeltaPlan delta;
+    DeltaPlan& delta = plan.terms;
     const size_t de_off = terms_offset(wl, plan);
-    if (bi.n_lora && ws_bytes > de_off) delta = delta_plan(b, plan, b->d_out);
-    if (!delta.items.empty() && ws_bytes < de_off + (size_t)delta.rows * b->d_out * 4) delta = DeltaPlan{};
     if (conv1d && bi.n_lora) {
         int64_t cur = 0;
         for (int i = 0; i < bi.S; ++i)
@@ -1660,8 +1682,8 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
         return SYMB_OK;
     }
 
-    const GemmPlan plan = gemm_plan(bi.T, b->d_in, b->d_out, b->weight_layout != SYMB_WEIGHT_CONV1D, lora ? lora_steps(b) : LoraSteps{}, dXbase != nullptr,
-                                    !dXbase && h->opt_k_split && h->xcd_rule && ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
+    GemmPlan plan = gemm_plan(b, b->d_in, b->d_out, b->weight_layout != SYMB_WEIGHT_CONV1D, lora, dXbase != nullptr, !dXbase && h->opt_k_split && h->xcd_rule,
+                              ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
     const bool k_split = plan.split.parts > 1 && plan.variant != kTileMid;
     const int bm = tile_rows(plan.variant), bn = tile_cols(plan.variant);
     std::vector<int32_t> lo, hi;
@@ -1698,10 +1720,8 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     // whose LoRA steps read the adapter side as [d_in][rank] rows: A_i^T, packed into the workspace.
     const bool conv1d = b->weight_layout == SYMB_WEIGHT_CONV1D;
     std::vector<SegDesc> sd_gemm = sd;
-    DeltaPlan delta;
+    DeltaPlan& delta = plan.terms;
     const size_t de_off = terms_offset(wl, plan);
-    if (lora && ws_bytes > de_off) delta = delta_plan(b, plan, b->d_in);
-    if (!delta.items.empty() && ws_bytes < de_off + (size_t)delta.rows * b->d_in * 4) delta = DeltaPlan{};
     std::vector<int64_t> pk_off(bi.S, 0), pa_off(bi.S, 0);
     {
         int64_t cur = 0, cura = 0;

@@ -60,3 +60,24 @@ def test_tall_tile(T, d_in, d_out, parts, ranks):
             call = lambda: sb.symb_base_linear_fwd(gh.handle(), plain, X, W, None, Y, Yb, buf)  # noqa: B023,E731
             assert launches(call, variant)[0] == 1 and launches(call, variant + 8)[0] == 0
             check_y(gh.bf16_to_f64(Y[rows]), off, oracle_ads(base), p["X"], p["W"], None, f"Y in {ws} bytes", rows=rows)
+
+
+@pytest.mark.parametrize("lens,d_in,d_out,room", [
+    ([1] * 2000, 4096, 4096, False),                     # no room for the terms: 256 steps in a tile of 256 rows
+    ([1] * 276 + [124], 3072, 11008, True)])             # the second tile's 20 steps are too few for memory beside 276 rows of terms
+def test_not_with_many_steps_left(lens, d_in, d_out, room):
+    """Steps of short segments that do not come from memory count in full: the 128x128 tile."""
+    p = make_problem(len(lens), d_in, d_out, lens, [L] * 276 + [N] if room else [L], [16])
+    off = p["off"]
+    dev = gh.upload_adapters(p["ads"], d_in, d_out, grads=False)
+    b = sb.Batch(d_in, d_out, off, dev.descs)
+    X, W = gh.to_dev(p["X"]), gh.to_dev(p["W"])
+    Y = torch.empty(p["T"], d_out, device="cuda", dtype=torch.bfloat16)
+    ws = gh.workspace(b, sb.SYMB_OP_FWD)
+    if not room:
+        ws = ws[:p["T"] * 2 * 16 * 2]                    # Hs alone
+    call = lambda: sb.symb_base_linear_fwd(gh.handle(), b, X, W, None, Y, None, ws)  # noqa: E731
+    full = 4 if room else 0
+    assert launches(call, 2 + full)[0] == 1 and launches(call, 8 + 2 + full)[0] == 0
+    rows = synth.sample_rows(off, 6, f"left{d_in}", block=128)[:64]
+    check_y(gh.bf16_to_f64(Y[rows]), off, oracle_ads(p["ads"]), p["X"], p["W"], None, "Y", rows=rows)
