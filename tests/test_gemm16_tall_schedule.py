@@ -1,6 +1,7 @@
 """The main loop of the 256x128 GEMM tile, run on the CPU as it is committed (gemm16_asm.hpp): its scalar instructions, load addresses and waits, with every
 load arriving as late as the waits allow.  Every MFMA must find the fragments of the stage it is at, and no load may leave the K range or land in a unit
-that is still being read.  No GPU needed."""
+that is still being read.  One wavefront is run for all four, which load a quarter of every unit each: what it waited for is there for the others, and what it has read is free for
+their loads, from the next barrier on.  No GPU needed."""
 import os
 import re
 
@@ -26,8 +27,9 @@ class Loop:
         self.order = [(first + n) % KF for n in range(KF)]
         self.s, self.scc, self.m0 = {}, 0, 0
         self.vm, self.lg, self.frag = [], [], {}      # loads and LDS reads on their way (oldest first), fragment halves by register
-        self.lds = {}                                 # (operand, unit, load) -> stage
-        self.barriers = self.step = 0
+        self.lds = {}                                 # (operand, unit, load) -> stage, barriers before it was waited for
+        self.read_at = {}                             # (operand, unit) -> barriers before its last read was waited for
+        self.barriers = 0
         self.mfma = []
 
     def val(self, x):
@@ -46,6 +48,8 @@ class Loop:
         addr = self.m0 + off
         unit, where = divmod(addr, UNIT_A) if which == "A" else divmod(addr - 3 * UNIT_A, UNIT_B)
         assert where == 1024 * j < sw and unit < (3 if which == "A" else 4), (which, addr)
+        assert not any(r[2:] == (which, unit) for r in self.lg), (which, unit)
+        assert self.read_at.get((which, unit), -1) < self.barriers, (which, unit)       # the other wavefronts have read it, too
         self.lds[(which, unit, j)] = None             # from its request on a unit holds neither the old nor the new stage
         self.vm.append((which, unit, j, at // step))
 
@@ -62,9 +66,10 @@ class Loop:
             assert (base - 3 * UNIT_A) % UNIT_B == 0 and unit < 4
             half = (off // 8192, off % 8192 // 4096) if self.nn else (self.ks[addr], q)
             need = [(which, unit, j) for j in range(NB)]
-        stages = {self.lds.get(k) for k in need}
-        assert len(stages) == 1 and None not in stages, (ins, stages)
-        self.lg.append((dst, (which, stages.pop(), half)))
+        held = [self.lds.get(k) for k in need]
+        assert None not in held and len({h[0] for h in held}) == 1, (ins, held)
+        assert all(h[1] < self.barriers for h in held), (ins, held)                     # the other wavefronts' loads are there, too
+        self.lg.append((dst, (which, held[0][0], half), which, unit))
         self.frag[dst] = None
 
     def run(self, lines):
@@ -114,9 +119,10 @@ class Loop:
                     while len(queue) > int(n):
                         x = queue.pop(0)
                         if what == "vmcnt":
-                            self.lds[x[:3]] = x[3]
+                            self.lds[x[:3]] = (x[3], self.barriers)
                         else:
                             self.frag[x[0]] = x[1]
+                            self.read_at[x[2:]] = self.barriers
             elif op == "s_barrier":
                 self.barriers += 1
                 assert not self.lg                    # everybody has read what this barrier gives away
@@ -142,6 +148,31 @@ def test_every_mfma_finds_its_stage(nn, KF):
     for first in sorted({x * KF // 8 for x in range(8)}):
         Loop(nn, KF, first, 128 * 40000 if nn else 128).run(lines)
     Loop(nn, KF, KF - 1, (1 << 32) - 128 if nn else 128).run(lines)           # a stage stride times KF beyond 32 bits
+
+
+@pytest.mark.parametrize("nn", [False, True])
+def test_a_missing_barrier_or_wait_is_seen(nn):
+    """The simulation itself: every barrier taken out, and every wait for loads or fragments loosened by one, must fail it."""
+    lines = _lines("SYMB_GEMM16T_LOOP_" + ("NN" if nn else "NT"))
+    barriers = [k for k, l in enumerate(lines) if l == "s_barrier"]
+    waits = [k for k, l in enumerate(lines) if "vmcnt" in l]
+    assert len(barriers) == 4 and len(waits) == 5
+
+    def fails(changed):
+        for KF in (1, 2, 3, 4, 17):
+            try:
+                Loop(nn, KF, 0, 128).run(changed)
+            except AssertionError:
+                return True
+        return False
+    assert not fails(lines)
+    for k in barriers:
+        assert fails(lines[:k] + lines[k + 1:]), k
+    for k, l in enumerate(lines):
+        for what, n in re.findall(r"(vmcnt|lgkmcnt)\((\d+)\)", l):
+            if (what, n) != ("lgkmcnt", "15"):           # (the largest there is: may be less than needed)
+                looser = l.replace(f"{what}({n})", f"{what}({int(n) + 1})")
+                assert fails(lines[:k] + [looser] + lines[k + 1:]), (k, looser)
 
 
 def test_compiler_code_leaves_the_accumulators_alone(device_asm):  # noqa: F811
