@@ -162,8 +162,21 @@ def measured_traffic(cfg: str, variant: int):
 
 
 def kernel_name(variant: int) -> str:
-    return "symb_gemm16_kernel<%d,%s,%s>" % (4 if variant & 2 else 8, "true" if variant & 1 else "false",
-                                             "false" if variant & 4 else "true")
+    nn, plain = "true" if variant & 1 else "false", "false" if variant & 4 else "true"
+    if variant & 16:
+        return f"symb_gemm_mid_kernel<{nn}>" + ("" if plain == "true" else " (full epilogue)")
+    if variant & 8:
+        return f"symb_gemm16t_kernel<{nn},{plain}>"
+    return "symb_gemm16_kernel<%d,%s,%s>" % (4 if variant & 2 else 8, nn, plain)
+
+
+def gemm_timing(h):
+    """{variant: (ms, launches, flops)} since the hook was enabled, every launch under one variant (the hook counts those of bits 3 and 4 without them, too)."""
+    from paper_2507_03220_amd import binding as sb
+    t = {v: sb.symb_debug_gemm_timing_read(h, v) for v in (*range(8), 10, 11, 14, 15, 18, 19, 22, 23)}
+    for v in (2, 3, 6, 7):
+        t[v] = tuple(x - y - z for x, y, z in zip(t[v], t[v + 8], t[v + 16]))
+    return t
 
 
 def timed_steps(runs, stream_obj, stream, steps: int):
@@ -263,7 +276,7 @@ def main() -> int:
     fl = {k: sum(r.flops()[k] for r in runs) for k in runs[0].flops()}
     tflops = fl["total"] / (ms_per_step * 1e-3) / 1e12
     tokens = wl.T
-    timing = {v: sb.symb_debug_gemm_timing_read(h, v) for v in range(8)}
+    timing = gemm_timing(h)
     sb.symb_debug_gemm_timing_enable(h, False)
     dom = max(timing, key=lambda v: timing[v][0])
     ms_tot, n_launch, fl_tot = timing[dom]

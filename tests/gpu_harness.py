@@ -137,11 +137,14 @@ def adapter_grad(off, ads: Sequence[HostAdapter], X, dY, Ybase=None, d_in=None, 
 
 def gemm_launches(call):
     """How often call() launches each GEMM instantiation: {variant: launches}, variants as in symb_debug_gemm_timing_read (bit 0: weight read
-    N-contiguous, bit 1: 128x128 tile, bit 2: full epilogue); empty if another kernel did the product."""
+    N-contiguous, bit 1: 128 columns wide or less, bit 2: full epilogue), each counted once: with bit 3 the 256x128 tile, with bit 4 the 32-row one, without
+    either the 128x128 (bit 1) or 256x256 one; empty if another kernel did the product."""
     sb.symb_debug_gemm_timing_enable(handle(), 1)
     try:
         call()
-        n = {v: sb.symb_debug_gemm_timing_read(handle(), v)[1] for v in range(8)}
+        n = {v: sb.symb_debug_gemm_timing_read(handle(), v)[1] for v in (*range(8), 10, 11, 14, 15, 18, 19, 22, 23)}
     finally:
         sb.symb_debug_gemm_timing_enable(handle(), 0)
+    for v in (2, 3, 6, 7):
+        n[v] -= n[v + 8] + n[v + 16]
     return {v: k for v, k in n.items() if k}

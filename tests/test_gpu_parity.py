@@ -408,8 +408,9 @@ def test_adapter_grad_can_reuse_dh_from_the_input_gradient_call():
     same(plain, both)
 
 
-@pytest.mark.parametrize("shape", [dict(d_in=264, d_out=392, lens=[150, 1, 70, 0, 33]),          # 128x128 tiles
-                                   dict(d_in=200, d_out=6208, lens=[700, 5, 795, 2, 40])])       # 256x256 tiles
+@pytest.mark.parametrize("shape", [dict(d_in=264, d_out=392, lens=[150, 1, 70, 0, 33], tile=22),         # 32-row tiles
+                                   dict(d_in=264, d_out=2056, lens=[700, 5, 195, 2, 40], tile=6),        # 128x128 tiles
+                                   dict(d_in=200, d_out=6208, lens=[700, 5, 795, 2, 40], tile=4)])       # 256x256 tiles
 def test_privacy_flow_noise_add_and_denoised_forward(shape):
     """Sec. 3.8: x + n bit-exact against the oracle's prepass; the noise effect (a bias-free forward of the
     noise rows) and the denoised forward (a stored noise effect taken off in the epilogue) each against the
@@ -450,7 +451,8 @@ def test_privacy_flow_noise_add_and_denoised_forward(shape):
     for q, i in enumerate(keep):
         saved[i] = saved_bits[int(noff[q]):int(noff[q + 1])]
     Y = torch.empty((T, d_out), device="cuda", dtype=torch.bfloat16)
-    sb.symb_base_linear_fwd_denoise(h, b, Xn, Wd, bd, [gh.to_dev(n) for n in saved], Y, gh.workspace(b, sb.SYMB_OP_FWD))
+    saved_dev, ws = [gh.to_dev(n) for n in saved], gh.workspace(b, sb.SYMB_OP_FWD)
+    assert gh.gemm_launches(lambda: sb.symb_base_linear_fwd_denoise(h, b, Xn, Wd, bd, saved_dev, Y, ws)) == {shape["tile"]: 1}
     torch.cuda.synchronize()
     Yr = oracle.forward_denoise(off, oads, Xn_ref, p["W"], p["bias"], saved)
     assert_close(gh.bf16_to_f64(Y), Yr, "denoised Y", out_bf16=True)
@@ -668,8 +670,8 @@ def test_large_tile_kernel_with_one_to_five_k_stages(d_in):
 
 @pytest.mark.parametrize("lens", [[1], [16], [9, 0, 8], [1, 1, 20, 1, 1, 24], [30, 1, 40, 29], [1] * 48, [50, 78]])
 def test_forward_of_a_handful_of_rows(lens):
-    """Batches of at most 16 rows (decode steps) take a kernel of their own that streams W once, larger
-    ones the 128x128 tiles with every tile split over K ranges: 1, 16, 17, 48, 100 and 128 rows; K with
+    """Batches of at most 64 rows (decode steps) take kernels of their own that stream W once, larger
+    ones 32-row tiles (the narrow layer) or 128x128 tiles with every tile split over K ranges (the wide one): 1, 16, 17, 48, 100 and 128 rows; K with
     a remainder, d_out not a multiple of 32; every adapter kind, ranks 1..128, bias."""
     kinds = [L, I, N, L, L, I]
     p = make_problem(90 + len(lens), 200, 392, lens, kinds, [1, 128, 24, 8, 100])

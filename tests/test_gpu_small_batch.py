@@ -216,17 +216,17 @@ def test_tile_and_split_rules_of_mid_sized_batches(T, d_in, d_out, tile, parts):
         check_y(gh.bf16_to_f64(res[0])[rows], p["off"], oads, p["X"], p["W"], p["bias"], "Y", rows=rows)
 
 
-@pytest.mark.parametrize("T,d_in,d_out,small", [
-    (2048, 4608, 4096, True), (2048, 4616, 4096, False), (1800, 512, 4096, True), (1024, 4096, 8192, True), (1024, 4104, 8192, False),
-    (512, 3072, 16384, True), (512, 4096, 16384, False), (3700, 512, 2056, True), (3840, 512, 2184, False), (1792, 8192, 4096, True)])
-def test_tile_size(T, d_in, d_out, small):
-    """Which tile a product runs in, around 128 tiles of 256x256 and 512 of 128x128."""
+@pytest.mark.parametrize("T,d_in,d_out,tile", [       # 0: 256x256, 2: 128x128, 2 + 8: 256x128
+    (2048, 4608, 4096, 10), (2048, 3064, 4096, 2), (2048, 4616, 4096, 0), (1800, 512, 4096, 2), (1024, 4096, 8192, 10), (1024, 3064, 8192, 2), (1024, 4104, 8192, 0),
+    (512, 3072, 16384, 10), (512, 3064, 16384, 2), (512, 4096, 16384, 0), (3700, 512, 2056, 2), (3840, 512, 2184, 0), (1792, 8192, 4096, 10)])
+def test_tile_size(T, d_in, d_out, tile):
+    """Which tile a product runs in, around 128 tiles of 256x256, 512 of 128x128 and an inner dimension of 3072."""
     X, W, Y = (torch.zeros(s, device="cuda", dtype=torch.bfloat16) for s in ((T, d_in), (d_out, d_in), (T, d_out)))
     for conv1d in (0, 1):
         b = sb.Batch(d_in, d_out, [0, T], [sb.Adapter()], conv1d)
         ws = gh.workspace(b, sb.SYMB_OP_FWD)
         ran = gh.gemm_launches(lambda: sb.symb_base_linear_fwd(gh.handle(), b, X, W, None, Y, None, ws))
-        assert ran == {conv1d + (2 if small else 0): 1}
+        assert ran == {conv1d + tile: 1}
 
 
 @pytest.mark.parametrize("d_in,d_out,tile", [(264, 392, 128), (2056, 264, 128), (200, 9480, 256)])     # whole, split over K, large tiles
