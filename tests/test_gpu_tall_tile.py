@@ -1,5 +1,6 @@
 """Products that take the 256x128 GEMM tile: whole and split over K, inner dimensions with and without a
 remainder of 64, ragged edges, every epilogue, LoRA steps of ranks 5 to 128, in both directions and weight layouts."""
+import numpy as np
 import pytest
 import torch
 
@@ -12,6 +13,64 @@ import test_gpu_parity as tp
 
 pytestmark = pytest.mark.gpu
 tp.gh, tp.sb = gh, sb                    # what its problem maker uses
+
+
+@pytest.mark.parametrize("T,d_in,d_out,tile,parts", [
+    (1000, 264, 2056, 2, 1), (250, 2056, 392, 2, 4), (1300, 3144, 4104, 10, 1), (700, 6152, 4104, 10, 2), (1000, 6152, 2056, 10, 3)])
+def test_forms_of_calls_in_tiles_of_128_columns(T, d_in, d_out, tile, parts):
+    """The 128x128 and 256x128 tiles, whole and in K parts, with terms of short segments, IA3 and the noise effect in the epilogue, IA3 of the input in the input gradient's, and
+    the same calls on a buffer per client, in another order in memory."""
+    lens = [1] * 80 + [T // 3, 0, 17, T // 4, T - T // 3 - T // 4 - 97]
+    rng = np.random.default_rng(T)
+
+    def pieces(M, width):                # a buffer per segment, the last segment's first
+        arena = torch.full((T, width), float("nan"), device="cuda", dtype=torch.bfloat16)
+        v = [arena[T - off[i + 1]:T - off[i]] if lens[i] else None for i in range(len(lens))]
+        for i in range(len(lens)):
+            if M is not None and lens[i]:
+                v[i].copy_(M[off[i]:off[i + 1]])
+        return v
+
+    def joined(v):
+        return torch.cat([x for x in v if x is not None])
+    plain = sb.Batch(d_in, d_out, [0, T], [sb.Adapter()])
+    need = sb.symb_workspace_bytes(plain, sb.SYMB_OP_FWD)
+    assert need == (-(-T // (256 if tile & 8 else 128)) * -(-d_out // 128) * parts * (256 if tile & 8 else 128) * 128 * 4 if parts > 1 else 0)
+    p = make_problem(T + d_in, d_in, d_out, lens, [L] * 80 + [L, N, I, N, L], [16])
+    off, oads = p["off"], oracle_ads(p["ads"])
+    rows = synth.sample_rows(off, 2, f"forms{T}", block=128)
+    neff = [synth.f32_to_bf16_bits(rng.standard_normal((1 if i % 2 else n, d_out)).astype(np.float32)) if n and i % 3 else None for i, n in enumerate(lens)]
+    dev = gh.upload_adapters(p["ads"], d_in, d_out, grads=False)
+    X, bias, nd = gh.to_dev(p["X"]), gh.to_dev(p["bias"]), [gh.to_dev(n) for n in neff]
+    for conv1d in (0, 1):
+        b = sb.Batch(d_in, d_out, off, dev.descs, conv1d)
+        W, ws = gh.weight_to_dev(p["W"], bool(conv1d)), gh.workspace(b, sb.SYMB_OP_FWD)
+        if not conv1d:
+            assert ws.numel() == need + (T * 2 * 16 * 2 + 255) // 256 * 256 + 80 * d_out * 4                   # partial tiles, Hs, the short segments' terms
+        Y, Yn = (torch.full((T, d_out), float("nan"), device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        xs, ys = pieces(X, d_in), pieces(None, d_out)
+        for call in (lambda: sb.symb_base_linear_fwd(gh.handle(), b, X, W, bias, Y, None, ws),
+                     lambda: sb.symb_base_linear_fwd_denoise(gh.handle(), b, X, W, bias, nd, Yn, ws),
+                     lambda: sb.symb_base_linear_fwd_seg(gh.handle(), b, xs, W, bias, ys, ws)):
+            assert gh.gemm_launches(call) == {conv1d + tile + 4: 1}
+        _, Yr = check_y(gh.bf16_to_f64(Y)[rows], off, oads, p["X"], p["W"], p["bias"], f"Y conv1d={conv1d}", rows=rows)
+        seg = np.searchsorted(off, rows, side="right") - 1
+        taken = np.stack([np.zeros(d_out) if neff[i] is None else synth.bf16_bits_to_f32(neff[i][0 if len(neff[i]) == 1 else t - off[i]]) for i, t in zip(seg, rows)])
+        assert_close(gh.bf16_to_f64(Yn)[rows], Yr - taken, f"denoised Y conv1d={conv1d}", out_bf16=True)
+        assert torch.equal(joined(ys).view(torch.int16), Y.view(torch.int16))
+    q = make_problem(T + d_out, d_out, d_in, lens, [L] * 80 + [L, N, 3, N, L], [16])          # its input gradient has the same product
+    qd = gh.upload_adapters(q["ads"], d_out, d_in, grads=False)
+    dY = gh.to_dev(q["dY"])
+    for conv1d in (0, 1):
+        b = sb.Batch(d_out, d_in, off, qd.descs, conv1d)
+        W, ws = gh.weight_to_dev(q["W"], bool(conv1d)), gh.workspace(b, sb.SYMB_OP_BWD_INPUT)
+        dX = torch.full((T, d_out), float("nan"), device="cuda", dtype=torch.bfloat16)
+        gs, xs = pieces(dY, d_in), pieces(None, d_out)
+        for call in (lambda: sb.symb_base_linear_bwd_input(gh.handle(), b, dY, W, dX, sb.SYMB_BWD_FULL, ws),
+                     lambda: sb.symb_base_linear_bwd_input_seg(gh.handle(), b, gs, W, xs, sb.SYMB_BWD_FULL, ws)):
+            assert gh.gemm_launches(call) == {1 - conv1d + tile + 4: 1}
+        check_dx(gh.bf16_to_f64(dX)[rows], off, oracle_ads(q["ads"]), q["dY"], q["W"], f"dX conv1d={conv1d}", rows=rows)
+        assert torch.equal(joined(xs).view(torch.int16), dX.view(torch.int16))
 
 
 def launches(call, variant):
