@@ -95,6 +95,13 @@ __device__ __forceinline__ uint4 ld_global_16(const bf16* p, bool ok) {
     return v;
 }
 
+// 8 bytes through a pointer that was read from memory: known to be global.
+__device__ __forceinline__ uint2 ld_global_8(const bf16* p) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 v = *(const __attribute__((address_space(1))) u32x2*)reinterpret_cast<const u32x2*>(p);
+    return make_uint2(v[0], v[1]);
+}
+
 template <int MBLK, int NBLK>
 struct Gemm16Tile {
     static_assert(NBLK == 4 ? MBLK == 4 || MBLK == 8 : NBLK == 8 && MBLK == 8, "256x256, 128x128 or 256x128 tile");
@@ -104,7 +111,7 @@ struct Gemm16Tile {
     static constexpr int UNIT_A = BM * 128, UNIT_B = BN * 128;   // one operand's 64-k stage
     static constexpr int C_PITCH = BN * 2 + 16, C_BYTES = BM * C_PITCH;
     static constexpr int SMEM = 3 * UNIT_A + (TALL ? 4 : 2) * UNIT_B;
-    static_assert(C_BYTES <= SMEM, "the staged output tile must fit the ring");
+    static_assert(C_BYTES + (TALL ? 24 * BM : 0) <= SMEM, "the staged output tile (and the pointers of its rows) must fit the ring");
 };
 
 // N-contiguous weight unit: [64 k][BN n] bf16, 16-byte chunk nc of row k stored at nc ^ swz.  The
@@ -189,9 +196,21 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
         const int s = seg_of_row(p.off, seg_lo, seg_hi, m);
         return p.a_seg[s] + (size_t)(m - p.off[s]) * p.K;
     };
+    // The 256x128 tile, one workgroup to a CU, looks the segment of a row up once, a thread for each, and hands what hangs on it to the others through LDS.  A lookup is a chain of
+    // dependent loads, and with one for every row that a lane loads, scales or stores nothing hid sixteen and more of them, one after the other: 408 rows of 4096 -> 11008 in 51
+    // segments, a buffer per client, some with IA3, 97.3 -> 75.1 us (128x128 tile 83.7); 2000 rows of 4608 -> 4096 with noise effects, in four segments, 82.4 -> 76.6.
+    int my_seg = 0;
+    const bool by_row = TT::TALL && (p.a_seg || p.c_seg || (!PLAIN && (p.neff || (p.epi_ia3 != 0 && p.tile_epi[tm] != 0))));
+    const int my_row = min(m0 + tid, p.M - 1);
+    if (by_row) my_seg = seg_of_row(p.off, seg_lo, seg_hi, my_row);
     const bf16* const a_tile = p.a_seg ? p.a_base : p.Aop + (size_t)m0 * p.K;
     const bf16* const b_tile = NN ? (p.Bop + n0) : (p.Bop + (size_t)n0 * p.K);
     const unsigned lds0 = (unsigned)(size_t)smem;          // LDS byte address of the dynamic segment
+    unsigned* const a_off = reinterpret_cast<unsigned*>(smem + TT::C_BYTES);         // 256x128 tile: where each row of A starts, from a_tile
+    auto a_offsets = [&]() __attribute__((always_inline)) {
+        a_off[tid] = (unsigned)(p.a_seg[my_seg] + (size_t)(my_row - p.off[my_seg]) * p.K - a_tile);
+        __syncthreads();
+    };
 
     // ---- register-staged 64-k tile (K remainder, LoRA term).  Chunk i of a thread sits 32 rows
     // (K-contiguous tiles) or KSTEP k-rows (N-contiguous weight tile) below chunk 0.
@@ -215,8 +234,10 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
     auto gload_tail = [&](int k0) __attribute__((always_inline)) {
         const bool kok = (k0 + lkc) < p.K;
 #pragma unroll
-        for (int i = 0; i < CA; ++i)
-            ra[i] = ld_global_16(a_row(min(m0 + lrow + i * RSTEP, p.M - 1)) + k0 + lkc, kok);
+        for (int i = 0; i < CA; ++i) {
+            const bf16* const row = TT::TALL && p.a_seg ? a_tile + a_off[lrow + i * RSTEP] : a_row(min(m0 + lrow + i * RSTEP, p.M - 1));
+            ra[i] = ld_global_16(row + k0 + lkc, kok);
+        }
 #pragma unroll
         for (int i = 0; i < CB; ++i) {
             if constexpr (!NN)
@@ -397,11 +418,14 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
         constexpr unsigned LOWER = TT::TALL ? 4096u : 0u;
         auto lower = [](int j) { return LOWER ? LOWER - 1024u * (unsigned)(j & 3) : 0u; };
         unsigned ab[MBLK], bb[NBLK];
+        if (TT::TALL && p.a_seg) a_offsets();
 #pragma unroll
         for (int j = 0; j < MBLK; ++j) {
             const int row = (wave * MBLK + j) * 8 + (lane >> 3), kc = (lane & 7) ^ swz_row(row);
-            ab[j] = ((unsigned)(a_row(min(m0 + row, p.M - 1)) - a_tile) + kc * 8) * 2u + lower(j);
+            const unsigned at = TT::TALL && p.a_seg ? a_off[row] : (unsigned)(a_row(min(m0 + row, p.M - 1)) - a_tile);
+            ab[j] = (at + kc * 8) * 2u + lower(j);
         }
+        if (TT::TALL && p.a_seg) __syncthreads();          // read by all before the first loads land there
 #pragma unroll
         for (int j = 0; j < NBLK; ++j) {
             if constexpr (!NN) {
@@ -457,6 +481,7 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
         __builtin_amdgcn_s_barrier();                      // everything landed and read before LDS is reused
     }
     if (last_part && KFT * 64 < p.K) {
+        if (TT::TALL && p.a_seg) a_offsets();
         gload_tail(KFT * 64);
         lds_store_a();
         lds_store_b();
@@ -467,6 +492,10 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
 
     // ---- output staging: the bf16 tile goes through LDS and leaves as whole 512-byte rows
     const unsigned c_lane = (unsigned)((wm0 + l15) * CP + (wn0 + lg * 4) * 2);   // this lane's C[.][.] of block (0, 0)
+    // 256x128 tile: each row's IA3 vector, noise effect and place in its client's buffer, behind the staged tile (set before the last stage_out)
+    const bf16** const row_scale = reinterpret_cast<const bf16**>(smem + TT::C_BYTES);
+    const bf16** const row_noise = row_scale + BM;
+    bf16** const row_out = reinterpret_cast<bf16**>(smem + TT::C_BYTES) + 2 * BM;
     auto stage_out = [&](bf16* __restrict__ dst, bool scale_ia3) __attribute__((always_inline)) {
         if (PLAIN || (!p.bias && !scale_ia3 && !p.neff)) {
             if constexpr (TT::TALL) asm volatile(SYMB_GEMM16T_STAGE_OUT : : "v"(lds0 + c_lane) : "memory", SYMB_GEMM16T_VCLOBBERS);
@@ -487,7 +516,10 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
                 const int m = m0 + wm0 + i * 16 + l15;
                 const bf16* lrow = nullptr;
                 const bf16* nrow = nullptr;
-                if ((scale_ia3 || p.neff) && m < p.M) {
+                if constexpr (TT::TALL) {
+                    if (scale_ia3) lrow = row_scale[m - m0];
+                    if (p.neff) nrow = row_noise[m - m0];
+                } else if ((scale_ia3 || p.neff) && m < p.M) {
                     const int s = seg_of_row(p.off, seg_lo, seg_hi, m);
                     if (scale_ia3 && p.seg[s].kind == p.epi_ia3) lrow = p.seg[s].A;
                     if (p.neff) {
@@ -496,6 +528,18 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
                     }
                 }
                 uint2 lv[NBLK], nv[NBLK];
+                if constexpr (TT::TALL) {                // four loads under one condition; columns past the last one repeat it, unstored
+#pragma unroll
+                    for (int j = 0; j < NBLK; ++j) nv[j] = make_uint2(0u, 0u), lv[j] = make_uint2(0x3f803f80u, 0x3f803f80u);
+                    if (nrow) {
+#pragma unroll
+                        for (int j = 0; j < NBLK; ++j) nv[j] = ld_global_8(nrow + min(nq0 + j * 16, p.N - 4));
+                    }
+                    if (lrow) {
+#pragma unroll
+                        for (int j = 0; j < NBLK; ++j) lv[j] = ld_global_8(lrow + min(nq0 + j * 16, p.N - 4));
+                    }
+                } else
 #pragma unroll
                 for (int j = 0; j < NBLK; ++j) {
                     const int n = nq0 + j * 16;
@@ -557,8 +601,12 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
             for (int r = r0; r < BM; r += RPP) {
                 const int m = m0 + r;
                 if (m < p.M && nok) {
-                    const int s = seg_of_row(p.off, seg_lo, seg_hi, m);
-                    bf16* rowp = p.c_seg[s] + (size_t)(m - p.off[s]) * p.N;
+                    bf16* rowp;
+                    if constexpr (TT::TALL) rowp = row_out[r];
+                    else {
+                        const int s = seg_of_row(p.off, seg_lo, seg_hi, m);
+                        rowp = p.c_seg[s] + (size_t)(m - p.off[s]) * p.N;
+                    }
                     *reinterpret_cast<uint4*>(rowp + n0 + col) = *reinterpret_cast<const uint4*>(smem + r * CP + col * 2);
                 }
             }
@@ -729,6 +777,19 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
                 });
             });
         }
+    }
+
+    if (by_row) {
+        const int at = my_row - p.off[my_seg];
+        if constexpr (!PLAIN) {
+            row_scale[tid] = p.seg[my_seg].kind == p.epi_ia3 ? p.seg[my_seg].A : nullptr;
+            if (p.neff) {
+                const NoiseDesc nd = p.neff[my_seg];
+                row_noise[tid] = nd.ptr ? nd.ptr + (size_t)(nd.rows == 1 ? 0 : at) * p.N : nullptr;
+            }
+        }
+        if (p.c_seg) row_out[tid] = p.c_seg[my_seg] + (size_t)at * p.N;
+        __syncthreads();
     }
 
     // ---- final output: bias, IA3 scale, noise effect, one rounding, whole-row stores
