@@ -421,6 +421,10 @@ LoraSteps lora_steps(const symb_batch* b, const DeltaPlan& terms) {
 // 11008 55.8 / 66.9 (the calls).  Not with LoRA steps beyond a quarter of the K stages: a tile of twice the
 // rows has up to twice as many, one after the other (batches whose terms do not come from memory, for want of room or by their number, count in full: 2000 one-token clients on
 // 4096 x 4096 with room for nothing optional keep 128x128 tiles of 128 steps each).
+// Where few columns stream many activation rows that do not lie on whole lines (K no multiple of 64), a launch has to fill the chip to keep as many
+// loads on their way as the 128x128 tiles: 4500 to 20000 rows, M >= 3 N, 128x128 tile's time over its, whole, K < 4300 1.03 to 1.26, above 0.81 to 1.03 up to 216 tiles (8770 rows
+// of 9176 -> 768 145 / 178 us, 4689 of 17872 -> 1216 255 / 300) and 1.02 to 1.28 from 220 on; in parts 0.89 to 1.02, median 0.97, up to K = 8000, 0.94 to 1.05 up to 10000, 1.0 to 1.6
+// above; on whole lines 0.95 to 1.4.
 // Small layers take the tiles of 32 rows (symb_gemm_mid_kernel) as long as these are one round of workgroups: time of the 128x128 tile over theirs, 13 300 products
 // of 65 to 1500 rows, medians by K, K-contiguous weight: 1.2 (K = 256), 1.3 to 1.37 (512), 1.3 to 1.46 (768), 1.4 to 1.57 (1024), 1.55 to 1.74 (1536) up to 256
 // workgroups, 0.9 to 1.0 with 257 to 512, 0.6 beyond; where the 128x128 tiles are split over K 1.23 to 1.34 up to K = 2048, 1.03 to 1.1 above;
@@ -444,7 +448,9 @@ GemmPlan gemm_plan(const symb_batch* b, int N, int K, bool nn, bool lora, bool w
     if (p.variant == kTile128 && M > 128 && K >= 3072 && 4 * small >= 7 * tall && !p.split.doubled) {
         const int parts = (int)(32 / std::max((tall + 7) / 8, 1L));      // of an XCD's tiles, in its 32 CUs
         const size_t bytes = (size_t)tall * parts * 256 * 128 * 4;
-        const bool whole = tall > 160 && tall <= 256, split = tall > 64 && tall <= 128 && K >= 6144 && bytes <= split_room;
+        const bool streamed = M >= 3 * N && K % 64 != 0;
+        const bool whole = tall > 160 && tall <= 256 && !(streamed && K >= 4500 && tall < 220);
+        const bool split = tall > 64 && tall <= 128 && K >= (streamed ? 8192 : 6144) && bytes <= split_room;
         GemmPlan t;
         t.variant = kTileTall;
         if (split) t.split = SplitPlan{parts, 0, (int)tall, bytes, false};

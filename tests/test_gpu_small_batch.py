@@ -218,7 +218,8 @@ def test_tile_and_split_rules_of_mid_sized_batches(T, d_in, d_out, tile, parts):
 
 @pytest.mark.parametrize("T,d_in,d_out,tile", [       # 0: 256x256, 2: 128x128, 2 + 8: 256x128
     (2048, 4608, 4096, 10), (2048, 3064, 4096, 2), (2048, 4616, 4096, 0), (1800, 512, 4096, 2), (1024, 4096, 8192, 10), (1024, 3064, 8192, 2), (1024, 4104, 8192, 0),
-    (512, 3072, 16384, 10), (512, 3064, 16384, 2), (512, 4096, 16384, 0), (3700, 512, 2056, 2), (3840, 512, 2184, 0), (1792, 8192, 4096, 10)])
+    (512, 3072, 16384, 10), (512, 3064, 16384, 2), (512, 4096, 16384, 0), (3700, 512, 2056, 2), (3840, 512, 2184, 0), (1792, 8192, 4096, 10),
+    (8770, 9176, 768, 2), (8770, 9216, 768, 10), (9600, 9176, 768, 10), (2100, 9176, 2816, 10)])          # many rows off the lines: from 220 tiles of 256x128 on, or with more columns
 def test_tile_size(T, d_in, d_out, tile):
     """Which tile a product runs in, around 128 tiles of 256x256, 512 of 128x128 and an inner dimension of 3072."""
     X, W, Y = (torch.zeros(s, device="cuda", dtype=torch.bfloat16) for s in ((T, d_in), (d_out, d_in), (T, d_out)))
