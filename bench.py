@@ -166,7 +166,7 @@ def kernel_name(variant: int) -> str:
     if variant & 16:
         return f"symb_gemm_mid_kernel<{nn}>" + ("" if plain == "true" else " (full epilogue)")
     if variant & 8:
-        return f"symb_gemm16t_kernel<{nn},{plain}>"
+        return f"symb_gemm16_kernel<4,{nn},{plain},8>"
     return "symb_gemm16_kernel<%d,%s,%s>" % (4 if variant & 2 else 8, nn, plain)
 
 

@@ -298,10 +298,10 @@ symb_status symb_adapter_grad_ex(symb_handle h, const symb_batch* b, const void*
  * Measurement hook (not part of the method): while enabled, every launch of the base
  * GEMM kernel is bracketed by a pair of HIP events on the caller's stream, so a bench
  * can read that kernel's own duration inside its timed region.  `variant` names the
- * instantiation symb_gemm16_kernel<NBLK, NN, PLAIN>: bit 0 = NN (the weight is read
+ * instantiation symb_gemm16_kernel<NBLK, NN, PLAIN, MBLK>: bit 0 = NN (the weight is read
  * N-contiguous: input gradient of an nn.Linear weight), bit 1 = a tile of 128 columns (NBLK 4, else
  * 256x256, NBLK 8), bit 2 = the full epilogue (PLAIN false); 0..7.  Tiles of 128 columns have 128 rows or, in
- * symb_gemm16t_kernel<NN, PLAIN>, 256; with bit 3 (10, 11, 14, 15) the launches of the latter alone are read, with bit 4
+ * symb_gemm16_kernel<4, NN, PLAIN, 8>, 256; with bit 3 (10, 11, 14, 15) the launches of the latter alone are read, with bit 4
  * (18, 19, 22, 23) those of symb_gemm_mid_kernel<NN>, whose tiles of 32 rows count among 2, 3, 6, 7 too.
  * read synchronises on the recorded events and returns the totals since the last
  * enable call (which clears them).  At most 4096 launches are recorded after an

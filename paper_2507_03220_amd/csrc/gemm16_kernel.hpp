@@ -11,7 +11,7 @@
 // and an epilogue with the optional bias, the optional store of the pre-adapter output, the IA3
 // per-channel scale of each row's own segment and the privacy flow's noise effect.
 //
-// One kernel on v_mfma_f32_16x16x32_bf16: 4 wavefronts (2x2), each MBLK x NBLK blocks of 16x16 of C.
+// One kernel template on v_mfma_f32_16x16x32_bf16: 4 wavefronts (2x2), each MBLK x NBLK blocks of 16x16 of C.
 // 8 x 8: 256x256 tile of the workgroup, all 256 accumulation registers per wavefront, 160 KiB of
 // LDS, for launches with enough such tiles to fill the chip.  4 x 4: 128x128 tile, 64 accumulation
 // registers, 80 KiB of LDS, two workgroups per CU, for everything smaller.  8 x 4: 256x128 tile, 128 accumulation
@@ -148,8 +148,11 @@ __device__ __forceinline__ void acc16_write4(float v0, float v1, float v2, float
 }
 
 // PLAIN: no bias, no IA3 scale, no noise effect, no pre-adapter output (checked by the host).
-template <int MBLK, int NBLK, bool NN, bool PLAIN>
-__device__ __forceinline__ void gemm16_tile(const GemmParams p) {
+// These kernels are 25 to 120 KB of code, and a product of few K stages runs through all of it for every tile: where it starts counts (7729 rows of 544 -> 10848, the same
+// instructions from three places 174 / 177 / 183 us; from multiples of 64 KiB 175, from multiples of 4 KiB 178).  Aligned, it does not depend on the kernels before it.
+template <int NBLK, bool NN, bool PLAIN, int MBLK = NBLK>
+__global__ void __launch_bounds__(256) __attribute__((aligned(65536)))
+symb_gemm16_kernel(const GemmParams p) {
     using TT = Gemm16Tile<MBLK, NBLK>;
     constexpr int BM = TT::BM, BN = TT::BN, NT = TT::NT, CP = TT::C_PITCH, WM = TT::WM, WN = TT::WN;
     constexpr int CA = BM * 8 / NT, CB = BN * 8 / NT;      // 16-byte chunks per thread of a register-staged tile
@@ -424,10 +427,7 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
             const int row = (wave * MBLK + j) * 8 + (lane >> 3), kc = (lane & 7) ^ swz_row(row);
             const unsigned at = TT::TALL && p.a_seg ? a_off[row] : (unsigned)(a_row(min(m0 + row, p.M - 1)) - a_tile);
             ab[j] = (at + kc * 8) * 2u + lower(j);
-        }
-        if (TT::TALL && p.a_seg) __syncthreads();          // read by all before the first loads land there
-#pragma unroll
-        for (int j = 0; j < NBLK; ++j) {
+            if (j >= NBLK) continue;
             if constexpr (!NN) {
                 const int row = (wave * NBLK + j) * 8 + (lane >> 3), kc = (lane & 7) ^ swz_row(row);
                 bb[j] = ((unsigned)(min(n0 + row, p.N - 1) - n0) * (unsigned)p.K + kc * 8) * 2u + lower(j);
@@ -437,6 +437,7 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
                 bb[j] = ((unsigned)krow * (unsigned)p.N + (unsigned)min(nc * 8, p.N - 8 - n0)) * 2u + lower(j);
             }
         }
+        if (TT::TALL && p.a_seg) __syncthreads();          // read by all before the first loads land there
         // In the 256x128 loop every XCD starts at another eighth of the K range and walks around its end: the XCDs' tiles read the same rows of one
         // operand, and in step all of them would wait for the same lines from HBM (397 rows of 4096 -> 11008: 56.8 us in step, 50.8 this way).
         const int first = TT::TALL ? (int)((blockIdx.x & 7) * (unsigned)KF / 8) : 0;
@@ -648,9 +649,9 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
             const unsigned rows = (unsigned)__builtin_amdgcn_readfirstlane(
                 (r_hi > m0 + wm0 && b_lo <= b_hi) ? (int)((ALL >> (MBLK - 1 - b_hi)) & (ALL << b_lo) & ALL) : 0);
 #pragma unroll
-            for (int i = 0; i < EC; ++i) *reinterpret_cast<uint4*>(sA + e_lds[HALF] + i * 8192) = ea[SET][i];
-#pragma unroll
-            for (int i = 0; i < EB; ++i) {
+            for (int i = 0; i < EC; ++i) {
+                *reinterpret_cast<uint4*>(sA + e_lds[HALF] + i * 8192) = ea[SET][i];
+                if (i >= EB) continue;
                 if constexpr (!NN) *reinterpret_cast<uint4*>(sB + e_lds[HALF] + i * 8192) = eb[SET][i];
                 else *reinterpret_cast<uint4*>(sB + b_lds0 + (HALF * 32 + i * KSTEP) * (BN * 2)) = eb[SET][i];
             }
@@ -794,20 +795,6 @@ __device__ __forceinline__ void gemm16_tile(const GemmParams p) {
 
     // ---- final output: bias, IA3 scale, noise effect, one rounding, whole-row stores
     stage_out(p.C, p.epi_ia3 != 0 && p.tile_epi[tm] != 0);
-}
-
-// The square tiles: 256x256 (NBLK 8) and 128x128 (NBLK 4).
-template <int NBLK, bool NN, bool PLAIN>
-__global__ void __launch_bounds__(256)
-symb_gemm16_kernel(const GemmParams p) {
-    gemm16_tile<NBLK, NBLK, NN, PLAIN>(p);
-}
-
-// The 256x128 tile.
-template <bool NN, bool PLAIN>
-__global__ void __launch_bounds__(256)
-symb_gemm16t_kernel(const GemmParams p) {
-    gemm16_tile<8, 4, NN, PLAIN>(p);
 }
 
 }  // namespace symb

@@ -829,8 +829,7 @@ symb_status launch_gemm16_t(symb_handle h, const GemmParams& gp, hipStream_t st)
     using TT = Gemm16Tile<MBLK, NBLK>;
     // instantiation number of the measurement hook: bit 0 = N-contiguous weight, bit 1 = tile of 128 columns, bit 2 = full epilogue, bit 3 = 256x128 tile
     constexpr int variant = (NN ? 1 : 0) | (NBLK == 4 ? 2 : 0) | (PLAIN ? 0 : 4) | (TT::TALL ? 8 : 0);
-    if constexpr (TT::TALL) return launch_gemm_fn(h, gp, st, symb_gemm16t_kernel<NN, PLAIN>, TT::BM, TT::BN, TT::NT, TT::SMEM, variant);
-    else return launch_gemm_fn(h, gp, st, symb_gemm16_kernel<NBLK, NN, PLAIN>, TT::BM, TT::BN, TT::NT, TT::SMEM, variant);
+    return launch_gemm_fn(h, gp, st, symb_gemm16_kernel<NBLK, NN, PLAIN, MBLK>, TT::BM, TT::BN, TT::NT, TT::SMEM, variant);
 }
 
 // Algorithmic work of one GEMM launch: 2 M N K plus the LoRA term of the segments that have their steps in it.

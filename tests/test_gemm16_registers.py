@@ -50,7 +50,7 @@ def _kernels(text):
 
 def test_compiler_code_never_touches_accumulation_registers(device_asm):
     ks = _kernels(device_asm)
-    assert len(ks) == 8, sorted(ks)               # {256x256, 128x128 tile} x {K-contiguous, N-contiguous weight} x {plain, full epilogue}
+    assert len(ks) == 12, sorted(ks)              # {256x256, 128x128, 256x128 tile} x {K-contiguous, N-contiguous weight} x {plain, full epilogue}
     for name, lines in ks.items():
         inside = [c for c, i in lines if i]
         outside = [c for c, i in lines if not i]
@@ -72,14 +72,19 @@ def test_no_kernel_uses_scratch_memory(device_asm):
 
 def test_kernel_descriptors_claim_the_whole_register_file(device_asm):
     # 256x256 tile: 256 architectural + 256 accumulation registers per lane, one wavefront per SIMD;
-    # 128x128 tile: 192 + 64, two wavefronts per SIMD (two workgroups of 80 KiB LDS per CU)
+    # 128x128 tile: 192 + 64, two wavefronts per SIMD (two workgroups of 80 KiB LDS per CU);
+    # 256x128 tile: the templates' 224 and whatever the compiler takes above them + 128, one wavefront per SIMD
     n = 0
     for m in re.finditer(r"\.amdhsa_kernel (_ZN4symb18symb_gemm16_kernel\w+)(.*?)\.end_amdhsa_kernel", device_asm, re.S):
         body, big = m.group(2), "ILi8E" in m.group(1)
+        n += 1
+        if "ILi4E" in m.group(1) and "ELi8EEE" in m.group(1):
+            free, accum = (int(re.search(r"\.amdhsa_%s (\d+)" % w, body).group(1)) for w in ("next_free_vgpr", "accum_offset"))
+            assert 224 <= accum <= 256 and accum + 128 == free, m.group(1)
+            continue
         assert re.search(r"\.amdhsa_next_free_vgpr %d\b" % (512 if big else 256), body), m.group(1)
         assert re.search(r"\.amdhsa_accum_offset %d\b" % (256 if big else 192), body), m.group(1)
-        n += 1
-    assert n == 8
+    assert n == 12
 
 
 def _regs(operand):
@@ -130,3 +135,8 @@ def test_results_of_assembly_issued_loads_are_untouched_until_their_wait(device_
                     touched |= _regs(tok)
             assert not (touched & pending), (m.group(1), s, sorted(touched & pending))
     assert checked > 50
+
+
+def test_gemm_kernels_start_on_64_kib(device_asm):
+    """Where their code starts counts for products of few K stages: it must not depend on the kernels before them."""
+    assert len(re.findall(r"\.p2align\s+16[^\n]*\n(?:[^\n]*@function\n)?_ZN4symb18symb_gemm16_kernel\w+:", device_asm)) == 12

@@ -177,7 +177,7 @@ def test_a_missing_barrier_or_wait_is_seen(nn):
 
 def test_compiler_code_leaves_the_accumulators_alone(device_asm):  # noqa: F811
     """As test_gemm16_registers.py has it for the square tiles; 128 accumulation registers, one wavefront per SIMD."""
-    kernels = re.findall(r"^(_ZN4symb19symb_gemm16t_kernel\w+):(.*?)^\.Lfunc_end", device_asm, re.S | re.M)
+    kernels = re.findall(r"^(_ZN4symb18symb_gemm16_kernelILi4E\w+ELi8EEE\w+):(.*?)^\.Lfunc_end", device_asm, re.S | re.M)
     assert len(kernels) == 4
     for name, body in kernels:
         inside = False
