@@ -342,7 +342,7 @@ __device__ __forceinline__ void skinny_chunk(const SkinnyParams& p, int chunk, u
 }
 
 template <int RB, bool DEEP, bool BT>
-__global__ void __launch_bounds__(256)
+SYMB_KERNEL void __launch_bounds__(256)
 symb_skinny_kernel(const SkinnyParams p) {
     __shared__ __align__(16) unsigned char smem[skinny_lds<RB, DEEP>()];
     skinny_chunk<RB, DEEP, BT>(p, blockIdx.x, smem);
@@ -369,7 +369,7 @@ struct PackParams {
     const int64_t* packed_off;
     int d_out;
 };
-__global__ void __launch_bounds__(256) symb_pack_bt_kernel(const PackParams p) {
+SYMB_KERNEL void __launch_bounds__(256) symb_pack_bt_kernel(const PackParams p) {
     const SegDesc sd = p.seg[blockIdx.y];
     if (sd.kind != KIND_LORA) return;
     const int j = blockIdx.x * 256 + threadIdx.x;
@@ -388,7 +388,7 @@ struct PackAtParams {
     const int64_t* packed_off;
     int d_in;
 };
-__global__ void __launch_bounds__(256) symb_pack_at_kernel(const PackAtParams p) {
+SYMB_KERNEL void __launch_bounds__(256) symb_pack_at_kernel(const PackAtParams p) {
     const SegDesc sd = p.seg[blockIdx.y];
     if (sd.kind != KIND_LORA) return;
     const int k = blockIdx.x * 256 + threadIdx.x;
@@ -574,7 +574,7 @@ __device__ __forceinline__ void lora_grad_walk(const GradParams& p, const GradIt
 }
 
 template <int RB, bool CMAJOR>
-__global__ void __launch_bounds__(256)
+SYMB_KERNEL void __launch_bounds__(256)
 symb_lora_grad_kernel(const GradParams p) {
     __shared__ __attribute__((aligned(16))) unsigned char sR[GradWalk<RB>::R_BYTES], sL[GradWalk<RB>::L_BYTES];
     const GradItem it = p.items[blockIdx.y];
@@ -765,7 +765,7 @@ __device__ __forceinline__ void lora_grad_wave(const GradParams& p, const GradIt
 // RB: rank blocks of the widest segment of the launch.  The segments' own ones decide what each workgroup runs (above rank 64 the other
 // kernel's walk): one launch lets the short walks of low ranks fill the CUs beside the long ones.
 template <int RB, bool CMAJOR>
-__global__ void __launch_bounds__(256)
+SYMB_KERNEL void __launch_bounds__(256)
 symb_lora_grad_wave_kernel(const GradParams p) {
     constexpr int WB = RB < 4 ? RB : 4;
     __shared__ __attribute__((aligned(16))) unsigned char smem[GradWave<WB>::BYTES];
@@ -786,7 +786,7 @@ symb_lora_grad_wave_kernel(const GradParams p) {
 // other's result, and a small call's time is its launches: training step of 4 x 64 tokens on 768 columns 46.9 -> 43.0 us.  wave: see grad_wave()
 // in the host code (without it ranks above 32, whose walk has blocks of 128 columns too).
 template <int RB>
-__global__ void __launch_bounds__(256)
+SYMB_KERNEL void __launch_bounds__(256)
 symb_lora_grad_pair_kernel(const SkinnyParams sp, int nchunks, const GradParams gp, int col_blocks, int wave) {
     constexpr int BYTES = skinny_lds<RB, true>() > GradWave<RB>::BYTES ? skinny_lds<RB, true>() : GradWave<RB>::BYTES;
     __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES];
@@ -849,7 +849,7 @@ __device__ __forceinline__ void grad_static_for(F&& f) {
 }
 
 template <int G>
-__global__ void __launch_bounds__(256)
+SYMB_KERNEL void __launch_bounds__(256)
 symb_lora_dhdb_kernel(const DhDbParams p) {
     constexpr int CT = 256, NI = CT / 64;
     constexpr int RPITCH = CT * 2 + 16, LPRW = CT / 8, NRC = GRAD_TT * LPRW / 256;
@@ -1018,7 +1018,7 @@ struct DhFinishParams {
     const RowChunk* chunks;
     const SegDesc* seg;
 };
-__global__ void __launch_bounds__(128)
+SYMB_KERNEL void __launch_bounds__(128)
 symb_dh_finish_kernel(const DhFinishParams p) {
     const RowChunk ch = p.chunks[blockIdx.x];
     const SegDesc sd = p.seg[ch.seg];
@@ -1055,7 +1055,7 @@ struct GradReduceParams {
     const float* partial;
     int ncols, cmajor, accumulate;
 };
-__global__ void __launch_bounds__(256) symb_grad_reduce_kernel(const GradReduceParams p) {
+SYMB_KERNEL void __launch_bounds__(256) symb_grad_reduce_kernel(const GradReduceParams p) {
     const GradReduceItem it = p.items[blockIdx.y];
     const SegDesc sd = p.seg[it.seg];
     const size_t n = (size_t)sd.rank * p.ncols;          // a multiple of 4: ncols is a multiple of 8
@@ -1098,7 +1098,7 @@ struct Ia3GradParams {
 constexpr int ia3_grad_cols(bool lng) { return lng ? 64 : 128; }
 constexpr int ia3_grad_threads(bool lng) { return lng ? 1024 : 256; }
 template <bool LONG>
-__global__ void __launch_bounds__(ia3_grad_threads(LONG)) symb_ia3_grad_kernel(const Ia3GradParams p) {
+SYMB_KERNEL void __launch_bounds__(ia3_grad_threads(LONG)) symb_ia3_grad_kernel(const Ia3GradParams p) {
     constexpr int COLS = ia3_grad_cols(LONG), THREADS = ia3_grad_threads(LONG), CHUNKS = COLS / 8, LN = THREADS / CHUNKS;
     constexpr int WL = 64 / CHUNKS, NW = THREADS / 64;   // token lanes per wavefront; wavefronts
     __shared__ float red[NW][COLS];
@@ -1176,7 +1176,7 @@ struct ScaleParams {
     const int32_t* off;       // device [S+1] (read only with in_seg)
 };
 // grid = (blocks of ROWPASS_COLS 16-byte columns, row chunks, SKINNY_ROWS / ROWPASS_ROWS); see the noise prepass below
-__global__ void __launch_bounds__(ROWPASS_COLS) symb_ia3_scale_rows_kernel(const ScaleParams p) {
+SYMB_KERNEL void __launch_bounds__(ROWPASS_COLS) symb_ia3_scale_rows_kernel(const ScaleParams p) {
     const RowChunk ch = p.chunks[blockIdx.y];
     const SegDesc sd = p.seg[ch.seg];
     const bool ia3 = sd.kind == p.kind;
@@ -1227,7 +1227,7 @@ struct NoiseAddParams {
     const NoiseDesc* noise;
 };
 // grid = (blocks of ROWPASS_COLS 16-byte columns, row chunks, SKINNY_ROWS / ROWPASS_ROWS)
-__global__ void __launch_bounds__(ROWPASS_COLS) symb_noise_add_kernel(const NoiseAddParams p) {
+SYMB_KERNEL void __launch_bounds__(ROWPASS_COLS) symb_noise_add_kernel(const NoiseAddParams p) {
     const RowChunk ch = p.chunks[blockIdx.y];
     const NoiseDesc nd = p.noise[ch.seg];
     const int r0 = blockIdx.z * ROWPASS_ROWS, nr = min(ch.nrows - r0, ROWPASS_ROWS), seg0 = p.off[ch.seg];
@@ -1271,7 +1271,7 @@ struct ScatterParams {
     bf16* const* out_seg;     // device [S]
     const int32_t* off;       // device [S+1]
 };
-__global__ void __launch_bounds__(256) symb_scatter_rows_kernel(const ScatterParams p) {
+SYMB_KERNEL void __launch_bounds__(256) symb_scatter_rows_kernel(const ScatterParams p) {
     const RowChunk ch = p.chunks[blockIdx.x];
     const int nchunk = p.width >> 3;
     bf16* const out = p.out_seg[ch.seg] - (size_t)p.off[ch.seg] * p.width;
@@ -1281,7 +1281,7 @@ __global__ void __launch_bounds__(256) symb_scatter_rows_kernel(const ScatterPar
     }
 }
 
-__global__ void __launch_bounds__(256) symb_fill_zero_kernel(float* dst, size_t n) {
+SYMB_KERNEL void __launch_bounds__(256) symb_fill_zero_kernel(float* dst, size_t n) {
     for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) dst[i] = 0.f;
 }
 

@@ -148,10 +148,8 @@ __device__ __forceinline__ void acc16_write4(float v0, float v1, float v2, float
 }
 
 // PLAIN: no bias, no IA3 scale, no noise effect, no pre-adapter output (checked by the host).
-// These kernels are 25 to 120 KB of code, and a product of few K stages runs through all of it for every tile: where it starts counts (7729 rows of 544 -> 10848, the same
-// instructions from three places 174 / 177 / 183 us; from multiples of 64 KiB 175, from multiples of 4 KiB 178).  Aligned, it does not depend on the kernels before it.
 template <int NBLK, bool NN, bool PLAIN, int MBLK = NBLK>
-__global__ void __launch_bounds__(256) __attribute__((aligned(65536)))
+SYMB_KERNEL void __launch_bounds__(256)
 symb_gemm16_kernel(const GemmParams p) {
     using TT = Gemm16Tile<MBLK, NBLK>;
     constexpr int BM = TT::BM, BN = TT::BN, NT = TT::NT, CP = TT::C_PITCH, WM = TT::WM, WN = TT::WN;

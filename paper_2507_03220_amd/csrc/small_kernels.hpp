@@ -438,7 +438,7 @@ __device__ __forceinline__ void small_direct(const SmallStreamParams& p, int t, 
 // adapter matrix is read N-contiguous (forward: the weight of a Conv1D layer, never A_i; input gradient: the weight of an
 // nn.Linear layer, always B_i).
 template <int MB, bool BASE_NN, bool SHRINK_NN, bool ONE>
-__global__ void __launch_bounds__(256)
+SYMB_KERNEL void __launch_bounds__(256)
 symb_small_stream_kernel(const SmallStreamParams p) {
     static_assert(!ONE || (MB == 1 && BASE_NN), "one buffer: see small_base_nbuf");
     constexpr int CB = small_cols(BASE_NN) / 16, NB = small_base_nbuf(MB, BASE_NN, ONE), SNB1 = small_shrink_nbuf(1), SNB = small_shrink_nbuf(MB);
@@ -488,7 +488,7 @@ symb_small_stream_kernel(const SmallStreamParams p) {
 // per wavefront.  One row, us with 64 columns / 32: 2048 x 2048 9.1 / 8.0, 3072 -> 768 10.3 / 8.5 (in K ranges), 4608 -> 2048 11.7 / 9.9, 1024 -> 8192 8.3 / 8.0,
 // but 4096 x 4096 12.5 / 14.9 and 16 rows of 256 -> 11008 7.6 / 8.2; 64 rows of 2048 x 2048 14.3 / 11.1.  grid = tiles; ranges, items and partial sums of p are not used.
 template <int MB>
-__global__ void __launch_bounds__(256)
+SYMB_KERNEL void __launch_bounds__(256)
 symb_small_narrow_kernel(const SmallStreamParams p) {
     constexpr int CB = SMALL_NARROW_COLS / 16, NBUF = MB == 4 ? 3 : 4;
     __shared__ __attribute__((aligned(16))) unsigned char smem[SmallTile<CB, MB, NBUF, false>::BYTES];
@@ -508,7 +508,7 @@ symb_small_narrow_kernel(const SmallStreamParams p) {
 // output, no terms computed beforehand.
 constexpr int MID_ROWS = 32;
 template <bool NN>
-__global__ void __launch_bounds__(256)
+SYMB_KERNEL void __launch_bounds__(256)
 symb_gemm_mid_kernel(const GemmParams p) {
     constexpr int MB = MID_ROWS / 16, CB = small_cols(NN) / 16, NBUF = NN ? 4 : 3;
     __shared__ __attribute__((aligned(16))) unsigned char smem[SmallTile<CB, MB, NBUF, NN>::BYTES];
@@ -728,7 +728,7 @@ __device__ __forceinline__ void small_finish_sums(const SmallFinishParams& p, co
 
 // grid = (blocks of 256 columns, rows); a thread finishes two columns of one row.
 template <bool BACKWARD>
-__global__ void __launch_bounds__(128)
+SYMB_KERNEL void __launch_bounds__(128)
 symb_small_finish_kernel(const SmallFinishParams p) {
     __shared__ __attribute__((aligned(16))) float hs[128], us[4096 + 128];
     const int t = blockIdx.y, c0 = blockIdx.x * 256, n = c0 + 2 * (int)threadIdx.x;
@@ -855,7 +855,7 @@ __device__ __forceinline__ void lora_delta(const LoraDeltaParams& p, const RowCh
         if (kq * 4 + q < it.nrows) *reinterpret_cast<float4*>(out + (size_t)q * p.N) = make_float4(acc[0][q], acc[1][q], acc[2][q], acc[3][q]);
 }
 template <bool BACKWARD>
-__global__ void __launch_bounds__(256)
+SYMB_KERNEL void __launch_bounds__(256)
 symb_lora_delta_kernel(const LoraDeltaParams p) {
     const RowChunk it = p.items[blockIdx.y];
     const SegDesc sd = p.seg[it.seg];

@@ -3,6 +3,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+// Kernels start on multiples of 4 KiB.  The large ones are up to 120 KB of code, and a product of few K stages runs through all of it for every tile: where it starts counts, and without
+// the alignment that depends on the sizes of all kernels before it.  7729 rows of 544 -> 10848 with IA3, the same instructions at three places 174, 181 and 183 us, aligned 177 (to 64 KiB 175
+// to 178); a training step of 16 rows on 4096 x 4096, six short kernels, 41.4 to 42.5, aligned 41.7 (the large ones to 64 KiB 42.4).
+#define SYMB_KERNEL __attribute__((aligned(4096))) __global__
+
 namespace symb {
 
 typedef __bf16 bf16;
