@@ -274,7 +274,7 @@ symb_gemm16_kernel(const GemmParams p) {
         }
         return false;
     };
-    // The parts of a K-split 128x128 tile share the tile's steps out: step number e_no (counted over the
+    // The parts of a K-split tile of 128 columns share the tile's steps out: step number e_no (counted over the
     // tile) belongs to part e_no % nparts.  Any part may take any step, the partial tiles are added up
     // anyway; left to the last part alone, a tile of many short segments had its steps one after the
     // other behind that part's share of K while the other parts were done (a call of 128 rows in 16
@@ -410,7 +410,7 @@ symb_gemm16_kernel(const GemmParams p) {
         for (int j = 0; j < 4; ++j) vA[j] = lds0 + frag_a(j >> 1, j & 1);
 #pragma unroll
         for (int j = 0; j < NVB; ++j) vB[j] = lds0 + (NN ? frag_b_nn(j % NBLK) : frag_b_nt((j >> 1) & 1, j & 1));
-        // Global byte offsets of this lane's NBLK loads per operand and stage.  One load instruction
+        // Global byte offsets of this lane's MBLK A and NBLK B loads per stage.  One load instruction
         // fills 1 KiB of consecutive LDS: 8 rows of a K-contiguous unit or 1024 / (2 BN) k-rows of the
         // N-contiguous unit; the lane -> chunk map is the inverse of the LDS swizzle.  Rows / columns
         // outside the problem are clamped onto the last valid one and never stored.
@@ -629,7 +629,7 @@ symb_gemm16_kernel(const GemmParams p) {
     // step k + 1 has passed the barrier of step k, which every wavefront reaches after its MFMAs of
     // step k - 1, the last reader of that half.
     // (ESETS steps are in flight: two on a K-contiguous weight and one on an N-contiguous one for the
-    // 256x256 tile, which has no registers left for more; one more each for the 128x128 tile.  Step k
+    // 256x256 tile, which has no registers left for more; one more each for the tiles of 128 columns.  Step k
     // uses set k % ESETS and half k % 2.)
     if (e_have[0]) {
         static_for<1, ESETS>([&](auto J) __attribute__((always_inline)) {

@@ -502,8 +502,9 @@ symb_small_narrow_kernel(const SmallStreamParams p) {
 
 // ---- The tiled product of small layers: tiles of 32 rows and 64 (weight read K-contiguous) or 128 columns, the four wavefronts of a workgroup
 // splitting K.  Such a launch is one chain of latencies (launch, first loads, K, epilogue); the 128x128 tile walks its K stages one behind the other and
-// leaves the chip to a dozen workgroups.  Here a wavefront's share of K up to 768 is in flight at once, and the LoRA steps (H and the adapter straight
-// from memory, dealt out over the wavefronts) run while it arrives.  256 rows of 768 x 768 with one rank-8 step
+// leaves the chip to a dozen workgroups.  Here up to 768 of K (the weight read N-contiguous: 512) are in flight at once, in the four wavefronts together, and the loads of the
+// LoRA steps (H and the adapter straight from memory, dealt out over the wavefronts) go out behind them: their latency is hidden, their matrix instructions
+// wait, as loads return in order, for the slices requested before.  256 rows of 768 x 768 with one rank-8 step
 // per tile, us: K-contiguous 11.7 -> 6.9, N-contiguous 11.5 -> 8.4 (11.4 with the element loads of A_i under a condition).  gemm_plan has the rule.  No pre-adapter
 // output, no terms computed beforehand.
 constexpr int MID_ROWS = 32;
