@@ -412,8 +412,9 @@ LoraSteps lora_steps(const symb_batch* b, const DeltaPlan& terms) {
 // full round of one per CU, whole or in two or three K parts, take that tile: it moves three quarters of the bytes per flop from L2 to LDS and waits out
 // HBM latency with two stages in flight.  Time of the 128x128 tile over its, medians over products of 65 to 4500 rows, operands from HBM, by its
 // tiles: whole, 161 to 256 tiles, 1.12 to 1.19 for K = 1000 to 2500, 1.17 to 1.3 above, 1.0 below; 129 to 160 tiles 0.94 to 1.1; two or three parts, 65 to 128 tiles,
-// 1.1 to 1.46 for K >= 3072 and 0.93 to 0.99 below; but inside calls, with their activations in cache and the partial tiles (up to 32 MiB) pushing weights out of it, 90 calls of all
-// flows: K = 3072 to 6000 0.85 to 1.05, median 0.96 (675 rows of 4096 x 4096, forward and input gradient, 78.4 / 88.4 us, 2178 of 4608 -> 1064 82.1 / 97.0), from 6144 on 0.95 to 1.48, median 1.14: from there on; fewer tiles 0.76 to 1.0 (and 1.15 in four parts of K > 5000).  Up to 128 rows half of every
+// 1.1 to 1.46 for K >= 3072 and 0.93 to 0.99 below; but inside calls, with their activations in cache and the partial tiles (up to 32 MiB) pushing weights out of it, 210 calls of all
+// flows: two parts of K = 3072 to 6000 0.81 to 1.13, median 0.97 (457 rows of 4096 -> 6144 and back 106 / 131, 861 of 3312 -> 4096 40 / 45.6), from 6144 on 0.95 to 1.48, median 1.14; three parts 0.93 to 1.14
+// up to 4700, 1.02 to 1.22 from there on; one row tile 0.95 to 1.05 below 4096, 0.95 to 1.21, median 1.09, from there on; fewer tiles 0.76 to 1.0 (and 1.15 in four parts of K > 5000).  Up to 128 rows half of every
 // such tile would be empty.  The parts are as many as fit an XCD's 32 CUs: 81 to 85 tiles in three parts are 33 workgroups on most XCDs, a second
 // round (84 tiles, us in two / three parts, 128x128 tile: 2993 rows of 4608 -> 856 42.2 / 59.4, 58.3; 2855 of 11192 -> 776 109.7 / 129.2, 130.3).  397 rows of 4096 -> 11008 with the adapters of
 // eleven clients 85.5 / 78 us, 16384 rows of 6144 -> 256 80.6 / 59.3.  Inside calls, behind the adapter passes, the whole ones of K < 3072 only break even (6000 rows of
@@ -423,8 +424,8 @@ LoraSteps lora_steps(const symb_batch* b, const DeltaPlan& terms) {
 // 4096 x 4096 with room for nothing optional keep 128x128 tiles of 128 steps each).
 // Where few columns stream many activation rows that do not lie on whole lines (K no multiple of 64), a launch has to fill the chip to keep as many
 // loads on their way as the 128x128 tiles: 4500 to 20000 rows, M >= 3 N, 128x128 tile's time over its, whole, K < 4300 1.03 to 1.26, above 0.81 to 1.03 up to 216 tiles (8770 rows
-// of 9176 -> 768 145 / 178 us, 4689 of 17872 -> 1216 255 / 300) and 1.02 to 1.28 from 220 on; in parts 0.89 to 1.02, median 0.97, up to K = 8000, 0.94 to 1.05 up to 10000, 1.0 to 1.6
-// above; on whole lines 0.95 to 1.4.
+// of 9176 -> 768 145 / 178 us, 4689 of 17872 -> 1216 255 / 300) and 1.02 to 1.28 from 220 on; in two parts 0.89 to 1.04 up to
+// K = 7000, 0.95 to 1.05 up to 10000, 1.0 to 1.6 above; on whole lines 0.95 to 1.4.
 // Small layers take the tiles of 32 rows (symb_gemm_mid_kernel) as long as these are one round of workgroups: time of the 128x128 tile over theirs, 13 300 products
 // of 65 to 1500 rows, medians by K, K-contiguous weight: 1.2 (K = 256), 1.3 to 1.37 (512), 1.3 to 1.46 (768), 1.4 to 1.57 (1024), 1.55 to 1.74 (1536) up to 256
 // workgroups, 0.9 to 1.0 with 257 to 512, 0.6 beyond; where the 128x128 tiles are split over K 1.23 to 1.34 up to K = 2048, 1.03 to 1.1 above;
@@ -450,7 +451,7 @@ GemmPlan gemm_plan(const symb_batch* b, int N, int K, bool nn, bool lora, bool w
         const size_t bytes = (size_t)tall * parts * 256 * 128 * 4;
         const bool streamed = M >= 3 * N && K % 64 != 0;
         const bool whole = tall > 160 && tall <= 256 && !(streamed && K >= 4500 && tall < 220);
-        const bool split = tall > 64 && tall <= 128 && K >= (streamed ? 8192 : 6144) && bytes <= split_room;
+        const bool split = tall > 64 && tall <= 128 && K >= (M <= 256 ? 4096 : parts == 3 ? 4700 : streamed ? 7168 : 6144) && bytes <= split_room;
         GemmPlan t;
         t.variant = kTileTall;
         if (split) t.split = SplitPlan{parts, 0, (int)tall, bytes, false};

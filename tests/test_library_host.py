@@ -176,9 +176,18 @@ def test_short_inner_dimensions_do_not_split_256x128_tiles():
     # 675 rows, 4096 wide: 96 tiles of 256x128 (192 of 128x128, whole); partial tiles pay from K = 6144 on
     for k, parts in ((4096, 0), (6136, 0), (6144, 2), (11008, 2)):
         assert sb.symb_workspace_bytes(sb.Batch(k, 4096, [0, 675], [sb.Adapter()]), sb.SYMB_OP_FWD) == 96 * parts * 256 * 128 * 4, k
-    # 5357 rows, 680 wide: 126 tiles, activation rows off the 128-byte lines (K no multiple of 64) from 8192 on
-    for k, parts in ((6136, 0), (6144, 2), (7136, 0), (7168, 2), (8184, 0), (8200, 2)):
+    # 5357 rows, 680 wide: 126 tiles, activation rows off the 128-byte lines (K no multiple of 64) from 7168 on
+    for k, parts in ((6136, 0), (6144, 2), (7136, 0), (7168, 2), (7176, 2)):
         assert sb.symb_workspace_bytes(sb.Batch(k, 680, [0, 5357], [sb.Adapter()]), sb.SYMB_OP_FWD) == 126 * parts * 256 * 128 * 4, k
+
+
+def test_one_row_tile_or_three_parts_split_sooner():
+    # 250 rows, 11008 wide: 86 tiles of 256x128 in two parts from K = 4096 on, else 172 of 128x128, whole
+    for k, parts in ((4088, 0), (4096, 2)):
+        assert sb.symb_workspace_bytes(sb.Batch(k, 11008, [0, 250], [sb.Adapter()]), sb.SYMB_OP_FWD) == 86 * parts * 256 * 128 * 4, k
+    # 1264 rows, 2048 wide: 80 tiles in three parts from K = 4700 on, else 160 of 128x128 in two
+    for k, tiles, parts, rows in ((4696, 160, 2, 128), (4704, 80, 3, 256)):
+        assert sb.symb_workspace_bytes(sb.Batch(k, 2048, [0, 1264], [sb.Adapter()]), sb.SYMB_OP_FWD) == tiles * parts * rows * 128 * 4, k
 
 
 def test_parts_of_a_k_split_on_narrow_layers():
