@@ -224,6 +224,7 @@ int gemm_variant(int M, int N, int K) {
     // small / big tiles: 2048 rows, 4096 wide, K = 4096 70 / 76, 4608 80 / 81, 5120 90 / 88, 8192 128 / 119; 8192 rows, 1024 wide, K = 4608 80 / 81; 1024 rows, 8192 wide,
     // K = 2048 42 / 55, 4096 77 / 77, 4608 87 / 81; 512 rows, 16384 wide, K = 2048 45 / 54, 4096 84 / 79; ragged: 1800 rows, 4096 wide, K = 4608 74 / 81;
     // 3700 rows, 2056 wide (135 big tiles, 493 small) K = 4096 65 / 79; 3840 rows, 2184 wide (135, 540) K = 2048 52 / 46.
+    // (The 256x128 tile, which gemm_plan puts in the small one's place, has not been weighed against the big one.)
     return small <= 512 && K <= (N <= 4096 ? 4608 : N <= 8192 ? 4096 : 3072) ? 2 : 3;
 }
 
