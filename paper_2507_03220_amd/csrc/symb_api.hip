@@ -450,7 +450,7 @@ GemmPlan gemm_plan(const symb_batch* b, int N, int K, bool nn, bool lora, bool w
     if (p.variant == kTile128 && M > 128 && K >= 3072 && 4 * small >= 7 * tall && !p.split.doubled) {
         const int parts = (int)(32 / std::max((tall + 7) / 8, 1L));      // of an XCD's tiles, in its 32 CUs
         const size_t bytes = (size_t)tall * parts * 256 * 128 * 4;
-        const bool streamed = M >= 3 * N && K % 64 != 0;
+        const bool streamed = M >= 3L * N && K % 64 != 0;
         const bool whole = tall > 160 && tall <= 256 && !(streamed && K >= 4500 && tall < 220);
         const bool split = tall > 64 && tall <= 128 && K >= (M <= 256 ? 4096 : parts == 3 ? 4700 : streamed ? 7168 : 6144) && bytes <= split_room;
         GemmPlan t;
