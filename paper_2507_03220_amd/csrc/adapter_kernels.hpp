@@ -20,7 +20,7 @@ struct RowChunk {
 //   forward shrink : L = X  [T][K=d_in],  R_i = A_i  [r][d_in]
 //   backward dH    : L = dY [T][K=d_out], R_i = B_i^T: read from B_i [d_out][r] as it lies (BT), or, where a rank is no multiple
 //                    of 4 or a B_i not 16-byte aligned, from a packed copy [rpad][d_out] (see pack kernel)
-// A workgroup owns 32 rows; its 4 wavefronts split K in interleaved slices, bring the rows in
+// A workgroup owns 32 rows (16 to 48 in launches of few rows); its 4 (8) wavefronts split K in interleaved slices, bring the rows in
 // through LDS (see SkinnyStage below), take the adapter rows from L2, and meet in LDS for the
 // final sum.  RB = max rank blocks of 16.
 // -------------------------------------------------------------------------------------------
@@ -37,32 +37,33 @@ struct SkinnyParams {
     const int32_t* off;       // device [S+1] (read only with L_seg)
 };
 
-constexpr int SKINNY_BLKS = 2;                         // 16-row MFMA blocks per wavefront
-constexpr int SKINNY_ROWS = 16 * SKINNY_BLKS;          // rows per workgroup
+constexpr int SKINNY_ROWS = 32;                        // rows per workgroup, unless launch_skinny chooses others
 
 // The skinny kernel's row stream.  A lane of an MFMA operand holds 16 bytes of one row, so fragment
 // loads straight from global memory touch 16 cache lines per 16 lanes, 16 bytes of each; the
 // memory pipeline then runs at a fraction of what whole-line requests reach.  Here every wavefront
-// brings its K slices (SKINNY_ROWS rows x SK elements) in through LDS DMA, whole rows of the slice
+// brings its K slices (the workgroup's rows x SK elements) in through LDS DMA, whole rows of the slice
 // per request, into NBUF buffers of its own (no workgroup barrier in the loop), and reads the
 // fragments from LDS.  The 16-byte chunks of a row are stored at chunk ^ f(row), so the 16 rows a
 // fragment read touches fall on different banks.  The adapter rows of a slice (from L2) come the same
 // way, into one more buffer.  Measured on 1.5 GB inputs: 4.0 -> 5.0 TB/s; 128-element slices are best
 // at rank <= 16, 64-element ones above (LDS for the adapter rows); a third buffer or a third workgroup
 // per CU changes nothing.
-template <int RB, int NBUF_ = 2, bool RDEEP_ = false>
+template <int RB, int NBUF_, bool RDEEP_, int BLKS_, int NW_>
 struct SkinnyStage {
-    static constexpr int SK = RB >= 2 ? 64 : 128;         // K elements per slice
+    static constexpr int BLKS = BLKS_, ROWS = 16 * BLKS;  // 16-row MFMA blocks
+    static constexpr int NW = NW_;                        // wavefronts
+    static constexpr int SK = RB >= 2 || NW > 4 ? 64 : 128;         // K elements per slice
     static constexpr int NBUF = NBUF_;                    // slices a wavefront keeps in LDS
     static constexpr bool RDEEP = RDEEP_;                 // the adapter rows are requested with their slice, NBUF deep as well
     static constexpr int ROW_BYTES = SK * 2;
     static constexpr int LPR = ROW_BYTES / 16;            // lanes (16-byte chunks) per row
     static constexpr int RPI = 64 / LPR;                  // rows per DMA request of one wavefront
-    static constexpr int DPS = SKINNY_ROWS / RPI;         // DMA requests per slice
-    static constexpr int SLICE = SKINNY_ROWS * ROW_BYTES;
+    static constexpr int DPS = ROWS / RPI;         // DMA requests per slice
+    static constexpr int SLICE = ROWS * ROW_BYTES;
     static constexpr int RSLICE = RB * 16 * ROW_BYTES;    // the adapter rows of one slice (one buffer)
     static constexpr int WAVE_BYTES = NBUF * SLICE + (RDEEP ? NBUF : 1) * RSLICE;
-    static constexpr int BYTES = 4 * WAVE_BYTES;
+    static constexpr int BYTES = NW * WAVE_BYTES;
     static_assert(SK == 64 || SK == 128, "a row of a slice is one or two 128-byte lines");
     __device__ static constexpr int swz(int r) { return (r / (16 / LPR)) & (LPR - 1); }
 };
@@ -86,19 +87,20 @@ __device__ __forceinline__ u32x4 ld_glb16(const bf16* p) {
 __device__ __forceinline__ int skinny_bt_swz(int r, int k) {
     return r == 128 ? ((((k >> 3) & 1) << 2) | (k & 3)) : r == 64 ? ((((k >> 3) & 1) << 1) | ((k >> 1) & 1)) : 0;
 }
-template <int RB, int NB, bool BT, class ST = SkinnyStage<RB>>
-__device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[SKINNY_BLKS], const bf16* (&rrow)[RB], const bool (&r_ok)[RB],
+template <int RB, int NB, bool BT, class ST>
+__device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[ST::BLKS], const bf16* (&rrow)[RB], const bool (&r_ok)[RB],
                                               const bf16* (&src)[ST::DPS], const bf16* rbase, int rrows,
-                                              unsigned char* wbuf, int K, int wave, int lane, floatx4 (&acc)[SKINNY_BLKS][RB]) {
+                                              unsigned char* wbuf, int K, int wave, int lane, floatx4 (&acc)[ST::BLKS][RB]) {
+    constexpr int BLKS = ST::BLKS, KSTEP = ST::NW * ST::SK;        // (K from one slice of a wavefront to its next)
     constexpr int NH = ST::SK / 32;                      // MFMA k-steps per slice
     constexpr int NRD = NB * 16 / ST::RPI;               // DMA requests for the adapter rows of a slice
     const int trow = lane & 15, kq = lane >> 4;
     unsigned char* const rbuf = wbuf + ST::NBUF * ST::SLICE;
-    unsigned foff[SKINNY_BLKS][NH], roff[NB][NH];        // fragment (b, h) / (j, h) of this lane within a slice buffer
+    unsigned foff[BLKS][NH], roff[NB][NH];        // fragment (b, h) / (j, h) of this lane within a slice buffer
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
 #pragma unroll
-        for (int b = 0; b < SKINNY_BLKS; ++b) {
+        for (int b = 0; b < BLKS; ++b) {
             const int r = b * 16 + trow;
             foff[b][h] = (unsigned)(size_t)wbuf + (unsigned)(r * ST::ROW_BYTES + (((h * 4 + kq) ^ ST::swz(r)) * 16));
         }
@@ -142,12 +144,12 @@ __device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[SKINNY_BLKS], 
     // complete: both buffers it read may be requested again.
     auto mul = [&](int buf) __attribute__((always_inline)) {
         typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-        u32x4 lv[SKINNY_BLKS][NH], rv[BT ? 1 : NB][NH];
+        u32x4 lv[BLKS][NH], rv[BT ? 1 : NB][NH];
         u32x2 rt[BT ? NB : 1][NH][2];
 #pragma unroll
         for (int h = 0; h < NH; ++h) {
 #pragma unroll
-            for (int b = 0; b < SKINNY_BLKS; ++b) asm volatile("ds_read_b128 %0, %1" : "=v"(lv[b][h]) : "v"(foff[b][h] + buf * ST::SLICE));
+            for (int b = 0; b < BLKS; ++b) asm volatile("ds_read_b128 %0, %1" : "=v"(lv[b][h]) : "v"(foff[b][h] + buf * ST::SLICE));
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
                 const unsigned at = roff[j][h] + (ST::RDEEP ? buf * ST::RSLICE : 0);
@@ -163,7 +165,7 @@ __device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[SKINNY_BLKS], 
 #pragma unroll
         for (int h = 0; h < NH; ++h) {
 #pragma unroll
-            for (int b = 0; b < SKINNY_BLKS; ++b) asm volatile("" : "+v"(lv[b][h]));
+            for (int b = 0; b < BLKS; ++b) asm volatile("" : "+v"(lv[b][h]));
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
                 if constexpr (BT) { asm volatile("" : "+v"(rt[j][h][0])); asm volatile("" : "+v"(rt[j][h][1])); }
@@ -179,54 +181,54 @@ __device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[SKINNY_BLKS], 
                 else raw = rv[j][h];
                 const bf16x8 rf = __builtin_bit_cast(bf16x8, r_ok[j] ? raw : u32x4{0u, 0u, 0u, 0u});
 #pragma unroll
-                for (int b = 0; b < SKINNY_BLKS; ++b)
+                for (int b = 0; b < BLKS; ++b)
                     acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rf, __builtin_bit_cast(bf16x8, lv[b][h]), acc[b][j], 0, 0, 0);
             }
     };
-    // ---- full slices of this wavefront: k = wave * SK + 4 SK s, s < ns, through LDS.  Slices 0 .. np-1
+    // ---- full slices of this wavefront: k = wave * SK + 4 (8) SK s, s < ns, through LDS.  Slices 0 .. np-1
     // are requested up front; iteration s requests slice s + np (while there is one) into the buffer
     // iteration s - 1 has finished reading, after the adapter rows of slice s: the memory counter
     // retires in order, so the wait for slice s and its adapter rows leaves exactly the newest slice's
     // DPS requests in flight.
     int k0 = wave * ST::SK;
-    const int ns = K >= k0 + ST::SK ? (K - k0 - ST::SK) / (4 * ST::SK) + 1 : 0;
+    const int ns = K >= k0 + ST::SK ? (K - k0 - ST::SK) / (KSTEP) + 1 : 0;
     const int np = ns < ST::NBUF - 1 ? ns : ST::NBUF - 1;
     for (int d = 0; d < np; ++d) {
-        dma(d, k0 + d * 4 * ST::SK);
-        if constexpr (ST::RDEEP) dma_r(d, k0 + d * 4 * ST::SK);
+        dma(d, k0 + d * KSTEP);
+        if constexpr (ST::RDEEP) dma_r(d, k0 + d * KSTEP);
     }
     int cur = 0, nxt = np;                               // buffer of slice s, of slice s + np
     int s = 0;
     for (; s + np < ns; ++s) {
         if constexpr (ST::RDEEP) {                       // slice and adapter rows together, NBUF - 1 of them in flight
-            dma(nxt, k0 + np * 4 * ST::SK);
-            dma_r(nxt, k0 + np * 4 * ST::SK);
+            dma(nxt, k0 + np * KSTEP);
+            dma_r(nxt, k0 + np * KSTEP);
             asm volatile("s_waitcnt vmcnt(%0)" : : "n"((ST::NBUF - 1) * (ST::DPS + NRD)) : "memory");
         } else {
             dma_r(0, k0);
-            dma(nxt, k0 + np * 4 * ST::SK);
+            dma(nxt, k0 + np * KSTEP);
             asm volatile("s_waitcnt vmcnt(%0)" : : "n"(ST::DPS) : "memory");
         }
         mul(cur);
         cur = cur + 1 == ST::NBUF ? 0 : cur + 1;
         nxt = nxt + 1 == ST::NBUF ? 0 : nxt + 1;
-        k0 += 4 * ST::SK;
+        k0 += KSTEP;
     }
     for (; s < ns; ++s) {                                // the last np slices: nothing left to request
         if constexpr (!ST::RDEEP) dma_r(0, k0);
         asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
         mul(cur);
         cur = cur + 1 == ST::NBUF ? 0 : cur + 1;
-        k0 += 4 * ST::SK;
+        k0 += KSTEP;
     }
     // ---- the slice that crosses the end of K: masked fragments straight from global memory
     if (k0 < K) {
 #pragma unroll
         for (int h = 0; h < NH; ++h) {
             const bool kok = (k0 + h * 32 + kq * 8) < K;
-            u32x4 lv[SKINNY_BLKS];
+            u32x4 lv[BLKS];
 #pragma unroll
-            for (int b = 0; b < SKINNY_BLKS; ++b) lv[b] = kok ? ld_glb16(lrow[b] + k0 + h * 32) : u32x4{0u, 0u, 0u, 0u};
+            for (int b = 0; b < BLKS; ++b) lv[b] = kok ? ld_glb16(lrow[b] + k0 + h * 32) : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
                 u32x4 rv = u32x4{0u, 0u, 0u, 0u};
@@ -240,7 +242,7 @@ __device__ __forceinline__ void skinny_stream(const bf16* (&lrow)[SKINNY_BLKS], 
                     }
                 }
 #pragma unroll
-                for (int b = 0; b < SKINNY_BLKS; ++b)
+                for (int b = 0; b < BLKS; ++b)
                     acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rv), __builtin_bit_cast(bf16x8, lv[b]), acc[b][j], 0, 0, 0);
             }
         }
@@ -254,28 +256,43 @@ __device__ __forceinline__ void skinny_stream_dispatch(int nb, Args&&... args) {
     else if constexpr (NB < RB) skinny_stream_dispatch<RB, BT, ST, NB + 1>(nb, args...);
 }
 
-// DEEP: three buffers with the adapter rows beside each slice, two slices in flight per wavefront.  For
-// launches of few chunks, where a workgroup has a compute unit to itself and its time is the chain of
-// memory latencies along K rather than bandwidth.
-template <int RB, bool DEEP>
-constexpr int skinny_lds() {                             // slice buffers of the 4 wavefronts; afterwards the partial sums of wavefronts 1..3
-    constexpr int slices = SkinnyStage<RB, DEEP ? 3 : 2, DEEP>::BYTES, red = 3 * SKINNY_ROWS * (RB * 16 + 4) * 4;
-    return slices > red ? slices : red;
-}
-template <int RB, bool DEEP, bool BT>
+// Slice buffers and wavefronts by the build of the kernel.  0: four wavefronts, two buffers.  4: three buffers with the adapter rows beside each slice,
+// two slices in flight per wavefront (dH beside dB in one launch).  Launches of at most one workgroup per CU take eight wavefronts and
+// BUILD = 1, 2 or 3 blocks of 16 rows, as few as that needs: such a launch is one chain of memory latencies along K, not bandwidth, and half of K per wavefront
+// and fewer rows shorten it.  As many slices in flight as 160 KiB hold; where the adapter rows leave no room for two of theirs they are requested with the slice that is
+// multiplied next.  At rank 128 only 16 rows fit that way.  Four wavefronts on 32 rows / this, us: 381 rows of ranks to 64, K = 4096 9.8 / 8.5; 2000 of rank 16, K = 4608 10.4 / 8.6;
+// 10240 of ranks to 64, K = 4096 31.8 / 27.5, against B_i 25.2 / 20.6; 1000 of ranks to 32, K = 11008, against B_i 24.0 / 17.7; 1300 of ranks to 128, K = 4096 27.4 / 24.1.  The rest is what a CU takes in
+// (64 bytes per clock: 1 MiB of a rank-128 adapter 8 us) and, before it, launch, descriptors and first lines.
+constexpr int SKINNY_DEEP = 4;
+constexpr int skinny_threads(int build) { return build >= 1 && build <= 3 ? 512 : 256; }
+constexpr bool skinny_has(int rb, int build) { return rb <= 4 || build <= 1; }
+template <int RB, int BUILD>
+struct SkinnyBuild {
+    static constexpr bool WIDE = BUILD >= 1 && BUILD <= 3;
+    static constexpr int BLKS = WIDE ? BUILD : 2, NW = WIDE ? 8 : 4;
+    static constexpr int KIB = WIDE ? 20 : 64, X = BLKS * 2, R = RB * 2;          // KiB of a wavefront, of its slice, of the adapter rows of it (SK = 64)
+    static constexpr bool RDEEP = BUILD == SKINNY_DEEP || (WIDE && 2 * (X + R) <= KIB);
+    static constexpr int NBUF = BUILD == SKINNY_DEEP ? 3 : !WIDE ? 2 : !RDEEP ? 2 : KIB / (X + R) < 4 ? KIB / (X + R) : 4;
+    using ST = SkinnyStage<RB, NBUF, RDEEP, BLKS, NW>;
+    static constexpr int RED = NW * ST::ROWS * (RB * 16 + 4) * 4;                 // the wavefronts' sums, afterwards
+    static constexpr int BYTES = ST::BYTES > RED ? ST::BYTES : RED;
+    static_assert(BYTES <= 160 << 10, "LDS of a CU");
+};
+template <int RB, int BUILD, bool BT>
 __device__ __forceinline__ void skinny_chunk(const SkinnyParams& p, int chunk, unsigned char* smem) {
-    using ST = SkinnyStage<RB, DEEP ? 3 : 2, DEEP>;
-    float (*red)[SKINNY_ROWS][RB * 16 + 4] = reinterpret_cast<float (*)[SKINNY_ROWS][RB * 16 + 4]>(smem);
+    using ST = typename SkinnyBuild<RB, BUILD>::ST;
+    constexpr int BLKS = ST::BLKS, ROWS = ST::ROWS;
+    float (*red)[ROWS][RB * 16 + 4] = reinterpret_cast<float (*)[ROWS][RB * 16 + 4]>(smem);
     const RowChunk ch = p.chunks[chunk];
     const SegDesc sd = p.seg[ch.seg];
     const int nb = sd.rpad >> 4;                         // rank blocks in use (uniform), 1..RB
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int trow = lane & 15, kq = lane >> 4;
     // rows past the chunk are clamped onto its last row; their results are never stored
-    const bf16* lrow[SKINNY_BLKS];
+    const bf16* lrow[BLKS];
     const bf16* const lbase = p.L_seg ? p.L_seg[ch.seg] - (size_t)p.off[ch.seg] * p.K : p.L;
 #pragma unroll
-    for (int b = 0; b < SKINNY_BLKS; ++b) lrow[b] = lbase + (size_t)(ch.row0 + min(b * 16 + trow, ch.nrows - 1)) * p.K + kq * 8;
+    for (int b = 0; b < BLKS; ++b) lrow[b] = lbase + (size_t)(ch.row0 + min(b * 16 + trow, ch.nrows - 1)) * p.K + kq * 8;
     const bf16* src[ST::DPS];
 #pragma unroll
     for (int i = 0; i < ST::DPS; ++i) {
@@ -292,60 +309,47 @@ __device__ __forceinline__ void skinny_chunk(const SkinnyParams& p, int chunk, u
         rrow[j] = rbase + (size_t)(r_ok[j] ? (j * 16 + trow) : 0) * p.K + kq * 8;
     }
 
-    floatx4 acc[SKINNY_BLKS][RB];
+    floatx4 acc[BLKS][RB];
 #pragma unroll
-    for (int b = 0; b < SKINNY_BLKS; ++b)
+    for (int b = 0; b < BLKS; ++b)
 #pragma unroll
         for (int j = 0; j < RB; ++j) acc[b][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     skinny_stream_dispatch<RB, BT, ST>(nb, lrow, rrow, r_ok, src, rbase, rrows, smem + wave * ST::WAVE_BYTES, p.K, wave, lane, acc);
     __syncthreads();                                     // every wavefront is done with its slice buffers
     // lane holds out[t = b*16 + trow][p = j*16 + 4*kq + q]
-    if (wave > 0) {
 #pragma unroll
-        for (int b = 0; b < SKINNY_BLKS; ++b)
+    for (int b = 0; b < BLKS; ++b)
 #pragma unroll
-            for (int j = 0; j < RB; ++j)
-                if (j < nb)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) red[wave - 1][b * 16 + trow][j * 16 + kq * 4 + q] = acc[b][j][q];
-    }
+        for (int j = 0; j < RB; ++j)
+            if (j < nb) *reinterpret_cast<floatx4*>(&red[wave][b * 16 + trow][j * 16 + kq * 4]) = acc[b][j];
     __syncthreads();
     // One row of `out` holds, for its own segment, rpad values rounded to bf16 followed by the
     // rpad rounding residuals (also bf16): value + residual carries ~16 significand bits on.
-    if (wave == 0) {
+    const int per = sd.rpad >> 2;                        // quads of ranks per row, dealt out over the threads; the wavefronts' sums in order
+    for (int e = tid; e < ch.nrows * per; e += 64 * ST::NW) {
+        const int t = e / per, pp = (e - t * per) * 4;
+        floatx4 v = *reinterpret_cast<const floatx4*>(&red[0][t][pp]);
 #pragma unroll
-        for (int b = 0; b < SKINNY_BLKS; ++b) {
-            const int t = b * 16 + trow;
-            if (t < ch.nrows) {
-                bf16* row = p.out + (size_t)(ch.row0 + t) * p.out_pitch;
-#pragma unroll
-                for (int j = 0; j < RB; ++j)
-                    if (j < nb) {
-                        const int pp = j * 16 + kq * 4;
-                        float v[4];
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            v[q] = sd.scale * (acc[b][j][q] + red[0][t][pp + q] + red[1][t][pp + q] + red[2][t][pp + q]);
-                        const unsigned h01 = pack2_bf16(v[0], v[1]), h23 = pack2_bf16(v[2], v[3]);
-                        uint2 hi2, lo2;
-                        hi2.x = h01;
-                        hi2.y = h23;
-                        lo2.x = pack2_bf16(v[0] - bf16_bits_to_f32((unsigned short)(h01 & 0xffffu)), v[1] - bf16_bits_to_f32((unsigned short)(h01 >> 16)));
-                        lo2.y = pack2_bf16(v[2] - bf16_bits_to_f32((unsigned short)(h23 & 0xffffu)), v[3] - bf16_bits_to_f32((unsigned short)(h23 >> 16)));
-                        *reinterpret_cast<uint2*>(row + pp) = hi2;
-                        *reinterpret_cast<uint2*>(row + sd.rpad + pp) = lo2;
-                    }
-            }
-        }
+        for (int w = 1; w < ST::NW; ++w) v += *reinterpret_cast<const floatx4*>(&red[w][t][pp]);
+        v *= sd.scale;
+        const unsigned h01 = pack2_bf16(v[0], v[1]), h23 = pack2_bf16(v[2], v[3]);
+        uint2 hi2, lo2;
+        hi2.x = h01;
+        hi2.y = h23;
+        lo2.x = pack2_bf16(v[0] - bf16_bits_to_f32((unsigned short)(h01 & 0xffffu)), v[1] - bf16_bits_to_f32((unsigned short)(h01 >> 16)));
+        lo2.y = pack2_bf16(v[2] - bf16_bits_to_f32((unsigned short)(h23 & 0xffffu)), v[3] - bf16_bits_to_f32((unsigned short)(h23 >> 16)));
+        bf16* const row = p.out + (size_t)(ch.row0 + t) * p.out_pitch + pp;
+        *reinterpret_cast<uint2*>(row) = hi2;
+        *reinterpret_cast<uint2*>(row + sd.rpad) = lo2;
     }
 }
 
-template <int RB, bool DEEP, bool BT>
-SYMB_KERNEL void __launch_bounds__(256)
+template <int RB, int BUILD, bool BT>
+SYMB_KERNEL void __launch_bounds__(skinny_threads(BUILD))
 symb_skinny_kernel(const SkinnyParams p) {
-    __shared__ __align__(16) unsigned char smem[skinny_lds<RB, DEEP>()];
-    skinny_chunk<RB, DEEP, BT>(p, blockIdx.x, smem);
+    __shared__ __align__(16) unsigned char smem[SkinnyBuild<RB, BUILD>::BYTES];
+    skinny_chunk<RB, BUILD, BT>(p, blockIdx.x, smem);
 }
 
 // Transposing LDS read of an MFMA fragment whose k axis runs down the rows of a column-contiguous tile.
@@ -788,10 +792,10 @@ symb_lora_grad_wave_kernel(const GradParams p) {
 template <int RB>
 SYMB_KERNEL void __launch_bounds__(256)
 symb_lora_grad_pair_kernel(const SkinnyParams sp, int nchunks, const GradParams gp, int col_blocks, int wave) {
-    constexpr int BYTES = skinny_lds<RB, true>() > GradWave<RB>::BYTES ? skinny_lds<RB, true>() : GradWave<RB>::BYTES;
+    constexpr int BYTES = SkinnyBuild<RB, SKINNY_DEEP>::BYTES > GradWave<RB>::BYTES ? SkinnyBuild<RB, SKINNY_DEEP>::BYTES : GradWave<RB>::BYTES;
     __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES];
     if ((int)blockIdx.x < nchunks) {
-        skinny_chunk<RB, true, true>(sp, blockIdx.x, smem);
+        skinny_chunk<RB, SKINNY_DEEP, true>(sp, blockIdx.x, smem);
         return;
     }
     const int g = blockIdx.x - nchunks, block = g % col_blocks;

@@ -867,25 +867,52 @@ symb_status launch_gemm(symb_handle h, const GemmParams& gp, hipStream_t st) {
     return plain ? launch_gemm16_t<4, 4, NN, true>(h, gp, st) : launch_gemm16_t<4, 4, NN, false>(h, gp, st);
 }
 
-// Up to one workgroup per compute unit the deep-prefetch build is used (where its buffers fit in LDS).
-template <int RB, bool BT>
-void launch_skinny_rb(const SkinnyParams& sp, int nchunks, bool deep_ok, hipStream_t st) {
-    if constexpr (RB <= 4) {
-        if (deep_ok && nchunks <= 256) {
-            hipLaunchKernelGGL((symb_skinny_kernel<RB, true, BT>), dim3(nchunks), dim3(256), 0, st, sp);
-            return;
-        }
+// Row chunks of a launch of the skinny kernel over `segs`, and the build that takes them (SkinnyBuild): chunks of 16, 32 or 48 rows where that is at most one
+// workgroup per compute unit, for the eight-wavefront builds; else 32 rows.
+struct SkinnyChunks {
+    int build = 0;
+    std::vector<RowChunk> items;
+};
+SkinnyChunks plan_skinny(symb_handle h, const symb_batch* b, const std::vector<int32_t>& segs, int max_rpad) {
+    SkinnyChunks c;
+    const int rb = max_rpad <= 16 ? 1 : max_rpad <= 32 ? 2 : max_rpad <= 64 ? 4 : 8;
+    for (int blks = 1; h->opt_skinny_deep && b->num_segments <= 4096 && blks <= 3 && !c.build && skinny_has(rb, blks); ++blks) {
+        long n = 0;
+        for (int i : segs) n += (b->seg_offsets[i + 1] - b->seg_offsets[i] + 16 * blks - 1) / (16 * blks);
+        if (n <= 256) c.build = blks;
     }
-    hipLaunchKernelGGL((symb_skinny_kernel<RB, false, BT>), dim3(nchunks), dim3(256), 0, st, sp);
+    const int rows = c.build ? 16 * c.build : kSkinnyRows;
+    for (int i : segs)
+        for (int r = b->seg_offsets[i]; r < b->seg_offsets[i + 1]; r += rows)
+            c.items.push_back(RowChunk{i, r, std::min(rows, b->seg_offsets[i + 1] - r), 0});
+    return c;
+}
+std::vector<int32_t> lora_segments(const symb_batch* b) {
+    std::vector<int32_t> v;
+    for (int i = 0; i < b->num_segments; ++i)
+        if (b->adapters[i].kind == SYMB_ADAPTER_LORA) v.push_back(i);
+    return v;
+}
+template <int RB, int BUILD, bool BT>
+void launch_skinny_build(const SkinnyParams& sp, int nchunks, hipStream_t st) {
+    if constexpr (skinny_has(RB, BUILD))
+        hipLaunchKernelGGL((symb_skinny_kernel<RB, BUILD, BT>), dim3(nchunks), dim3(skinny_threads(BUILD)), 0, st, sp);
+}
+template <int RB, bool BT>
+void launch_skinny_rb(const SkinnyParams& sp, const SkinnyChunks& c, hipStream_t st) {
+    const int n = (int)c.items.size();
+    if (c.build == 1) launch_skinny_build<RB, 1, BT>(sp, n, st);
+    else if (c.build == 2) launch_skinny_build<RB, 2, BT>(sp, n, st);
+    else if (c.build == 3) launch_skinny_build<RB, 3, BT>(sp, n, st);
+    else launch_skinny_build<RB, 0, BT>(sp, n, st);
 }
 template <bool BT>
-symb_status launch_skinny(symb_handle h, const SkinnyParams& sp, int nchunks, int max_rpad, hipStream_t st) {
-    if (nchunks == 0) return SYMB_OK;
-    const bool deep = h->opt_skinny_deep;
-    if (max_rpad <= 16) launch_skinny_rb<1, BT>(sp, nchunks, deep, st);
-    else if (max_rpad <= 32) launch_skinny_rb<2, BT>(sp, nchunks, deep, st);
-    else if (max_rpad <= 64) launch_skinny_rb<4, BT>(sp, nchunks, deep, st);
-    else launch_skinny_rb<8, BT>(sp, nchunks, deep, st);
+symb_status launch_skinny(symb_handle h, const SkinnyParams& sp, const SkinnyChunks& c, int max_rpad, hipStream_t st) {
+    if (c.items.empty()) return SYMB_OK;
+    if (max_rpad <= 16) launch_skinny_rb<1, BT>(sp, c, st);
+    else if (max_rpad <= 32) launch_skinny_rb<2, BT>(sp, c, st);
+    else if (max_rpad <= 64) launch_skinny_rb<4, BT>(sp, c, st);
+    else launch_skinny_rb<8, BT>(sp, c, st);
     SYMB_HIP(h, hipGetLastError());
     return SYMB_OK;
 }
@@ -899,15 +926,15 @@ bool reads_bt(const symb_batch* b) {
     return true;
 }
 // dH = s dY B of the rows in sp.chunks (sp: everything but the adapter side).
-symb_status launch_skinny_dh(symb_handle h, const symb_batch* b, SkinnyParams sp, bf16* packed, const int64_t* packed_off, int nchunks, int max_rpad, hipStream_t st) {
-    if (reads_bt(b)) return launch_skinny<true>(h, sp, nchunks, max_rpad, st);
+symb_status launch_skinny_dh(symb_handle h, const symb_batch* b, SkinnyParams sp, bf16* packed, const int64_t* packed_off, const SkinnyChunks& c, int max_rpad, hipStream_t st) {
+    if (reads_bt(b)) return launch_skinny<true>(h, sp, c, max_rpad, st);
     PackParams pp{sp.seg, packed, packed_off, b->d_out};
     hipLaunchKernelGGL(symb_pack_bt_kernel, dim3((b->d_out + 255) / 256, b->num_segments), dim3(256), 0, st, pp);
     SYMB_HIP(h, hipGetLastError());
     sp.packed = packed;
     sp.packed_off = packed_off;
     sp.use_packed = 1;
-    return launch_skinny<false>(h, sp, nchunks, max_rpad, st);
+    return launch_skinny<false>(h, sp, c, max_rpad, st);
 }
 
 template <int RB, bool CM>
@@ -1435,8 +1462,8 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     const int bm = tile_rows(plan.variant), bn = tile_cols(plan.variant);
     std::vector<int32_t> lo, hi;
     plan_row_tiles(b, bm, lo, hi);
-    std::vector<RowChunk> chunks, all_chunks;
-    plan_chunks(b, kSkinnyRows, SYMB_ADAPTER_LORA, chunks);
+    const SkinnyChunks chunks = plan_skinny(h, b, lora_segments(b), bi.max_rpad);
+    std::vector<RowChunk> all_chunks;
     // Input-major weight: the forward is the N-contiguous GEMM, whose LoRA steps read the adapter
     // side as [rank][d_out] rows: B_i^T, packed into the workspace; a second descriptor set points there.
     const bool conv1d = b->weight_layout == SYMB_WEIGHT_CONV1D;
@@ -1464,7 +1491,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
     const size_t o_hi = blob.add(hi.data(), hi.size());
     const std::vector<int32_t> tile_epi = plan_tile_kind(b, lo, hi, SYMB_ADAPTER_IA3);
     const size_t o_te = blob.add(tile_epi.data(), tile_epi.size());
-    const size_t o_ch = blob.add(chunks.data(), chunks.size());
+    const size_t o_ch = blob.add(chunks.items.data(), chunks.items.size());
     const size_t o_nd = blob.add(nd.data(), nd.size());
     const size_t o_pk = blob.add(pk_off.data(), pk_off.size());
     const size_t o_all = blob.add(all_chunks.data(), all_chunks.size());
@@ -1506,7 +1533,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
             sp.L_seg = (const bf16* const*)(dev + o_xs);
             sp.off = (const int32_t*)(dev + o_off);
         }
-        if ((st = launch_skinny<false>(h, sp, (int)chunks.size(), bi.max_rpad, s)) != SYMB_OK) return st;
+        if ((st = launch_skinny<false>(h, sp, chunks, bi.max_rpad, s)) != SYMB_OK) return st;
     }
     if (!delta.items.empty() && (st = launch_delta(h, false, (const SegDesc*)(dev + o_seg), (const RowChunk*)(dev + db.items), (int)delta.items.size(), b->d_out,
                                                    Hs, bi.max_rpad, (float*)(wsb + de_off), s)) != SYMB_OK) return st;
@@ -1695,8 +1722,9 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     const int bm = tile_rows(plan.variant), bn = tile_cols(plan.variant);
     std::vector<int32_t> lo, hi;
     plan_row_tiles(b, bm, lo, hi);
-    std::vector<RowChunk> chunks, all_chunks;
-    if (lora) plan_chunks(b, kSkinnyRows, SYMB_ADAPTER_LORA, chunks);
+    SkinnyChunks chunks;
+    if (lora && !take_dh) chunks = plan_skinny(h, b, lora_segments(b), bi.max_rpad);
+    std::vector<RowChunk> all_chunks;
     // Rows of IA3 segments enter the GEMM scaled by l_i: a scaled copy of those rows goes to the
     // workspace, and the GEMM takes every row from where it lies (per-row base pointers: the copy for
     // IA3 rows, the caller's dY for the others).  Lane offsets are 32 bits wide, so this needs all those
@@ -1750,7 +1778,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     const size_t o_hi = blob.add(hi.data(), hi.size());
     const std::vector<int32_t> tile_epi = plan_tile_kind(b, lo, hi, SYMB_ADAPTER_IA3_IN);
     const size_t o_te = blob.add(tile_epi.data(), tile_epi.size());
-    const size_t o_ch = blob.add(chunks.data(), chunks.size());
+    const size_t o_ch = blob.add(chunks.items.data(), chunks.items.size());
     const size_t o_all = blob.add(all_chunks.data(), all_chunks.size());
     const size_t o_pk = blob.add(pk_off.data(), pk_off.size());
     const size_t o_pa = blob.add(pa_off.data(), pa_off.size());
@@ -1786,7 +1814,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
             sp.L_seg = (const bf16* const*)(dev + o_gs);
             sp.off = (const int32_t*)(dev + o_off);
         }
-        if ((st = launch_skinny_dh(h, b, sp, (bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk), (int)chunks.size(), bi.max_rpad, s)) != SYMB_OK) return st;
+        if ((st = launch_skinny_dh(h, b, sp, (bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk), chunks, bi.max_rpad, s)) != SYMB_OK) return st;
     }
     bool a_from_seg = seg_io;
     if (ia3) {
@@ -1954,14 +1982,6 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
     };
     if (!any_lora && want_l.empty() && want_lin.empty()) return fill_zeros();
 
-    // Row chunks of the LoRA segments that want a gradient (Hs for dB, dH for dA).
-    std::vector<RowChunk> ch_h, ch_dh;
-    for (int i : want_b)
-        for (int r = b->seg_offsets[i]; r < b->seg_offsets[i + 1]; r += kSkinnyRows)
-            ch_h.push_back(RowChunk{i, r, std::min(kSkinnyRows, b->seg_offsets[i + 1] - r), 0});
-    for (int i : want_a)
-        for (int r = b->seg_offsets[i]; r < b->seg_offsets[i + 1]; r += kSkinnyRows)
-            ch_dh.push_back(RowChunk{i, r, std::min(kSkinnyRows, b->seg_offsets[i + 1] - r), 0});
     const std::vector<SegDesc> sd = make_segdesc(b);
     std::vector<int64_t> pk_off(bi.S, 0);
     {
@@ -1995,6 +2015,24 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
     std::vector<GradItem> it_a, it_b;
     std::vector<GradReduceItem> red_a, red_b;
     const int wave_rpad_b = plan_items(want_b, b->d_out, true, it_b, red_b), wave_rpad_a = plan_items(want_a, b->d_in, false, it_a, red_a);
+    // One pass over dY for dB and dH: when both gradients are wanted of the same segments, dH has to be
+    // computed here anyway, and the ranks fit one rank block.  The pass leaves dH in the workspace where an
+    // input-gradient call with SYMB_BWD_REUSE_DH (same batch, same dY, same workspace) takes it.
+    const bool one_pass = !reuse_dh && want_a == want_b && !want_b.empty() && bi.max_rpad == 16 && wl.dp_bytes;
+    // Small calls: dH beside dB in one launch (at most one workgroup per CU).
+    const int col_blocks = (b->d_out + GRAD_WAVE_CT - 1) / GRAD_WAVE_CT;
+    long long pair_groups = (long long)col_blocks * (long long)it_b.size();
+    for (int i : want_a) pair_groups += (b->seg_offsets[i + 1] - b->seg_offsets[i] + kSkinnyRows - 1) / kSkinnyRows;
+    const bool pair = !one_pass && !reuse_dh && !want_b.empty() && !want_a.empty() && b->d_out < GRAD_WIDE && (wave_rpad_b > 0 || grad_max_rpad > 32) &&
+                      grad_max_rpad <= GRAD_WAVE_RANK && h->opt_skinny_deep && reads_bt(b) && pair_groups <= 256;
+    // Row chunks of the LoRA segments that want a gradient (Hs for dB, dH for dA).
+    SkinnyChunks ch_h, ch_dh;
+    if (!reuse_hs) ch_h = plan_skinny(h, b, want_b, grad_max_rpad);
+    if (one_pass || pair) {
+        for (int i : want_a)
+            for (int r = b->seg_offsets[i]; r < b->seg_offsets[i + 1]; r += kSkinnyRows)
+                ch_dh.items.push_back(RowChunk{i, r, std::min(kSkinnyRows, b->seg_offsets[i + 1] - r), 0});
+    } else if (!reuse_dh) ch_dh = plan_skinny(h, b, want_a, grad_max_rpad);
     Blob blob;
     const size_t o_seg = blob.add(sd.data(), sd.size());
     const size_t o_off = blob.add(b->seg_offsets, (size_t)bi.S + 1);
@@ -2002,8 +2040,8 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
     const size_t o_itb = blob.add(it_b.data(), it_b.size());
     const size_t o_rda = blob.add(red_a.data(), red_a.size());
     const size_t o_rdb = blob.add(red_b.data(), red_b.size());
-    const size_t o_chh = blob.add(ch_h.data(), ch_h.size());
-    const size_t o_chd = blob.add(ch_dh.data(), ch_dh.size());
+    const size_t o_chh = blob.add(ch_h.items.data(), ch_h.items.size());
+    const size_t o_chd = blob.add(ch_dh.items.data(), ch_dh.items.size());
     const size_t o_pk = blob.add(pk_off.data(), pk_off.size());
     const size_t o_wl = blob.add(want_l.data(), want_l.size());
     const size_t o_wli = blob.add(want_lin.data(), want_lin.size());
@@ -2030,7 +2068,7 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
             sp.L_seg = (const bf16* const*)(dev + o_xs);
             sp.off = doff;
         }
-        return launch_skinny<false>(h, sp, (int)ch_h.size(), grad_max_rpad, s);
+        return launch_skinny<false>(h, sp, ch_h, grad_max_rpad, s);
     };
     auto skinny_dh = [&]() {                            // dH = s dY B of the segments that want dA
         SkinnyParams sp{};
@@ -2046,10 +2084,6 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
         }
         return sp;
     };
-    // One pass over dY for dB and dH: when both gradients are wanted of the same segments, dH has to be
-    // computed here anyway, and the ranks fit one rank block.  The pass leaves dH in the workspace where an
-    // input-gradient call with SYMB_BWD_REUSE_DH (same batch, same dY, same workspace) takes it.
-    const bool one_pass = !reuse_dh && want_a == want_b && !want_b.empty() && bi.max_rpad == 16 && wl.dp_bytes;
     bool have_dh = reuse_dh;
     if (one_pass) {
         if (!reuse_hs && (st = run_skinny_h()) != SYMB_OK) return st;
@@ -2062,22 +2096,18 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
                                      (int)red_b.size(), s)) != SYMB_OK) return st;
         DhFinishParams fp{(const float*)(wsb + wl.dp_off), groups, bi.T, (bf16*)(wsb + wl.dh_off), 2 * bi.max_rpad,
                           (const RowChunk*)(dev + o_chd), dseg};
-        hipLaunchKernelGGL(symb_dh_finish_kernel, dim3((unsigned)ch_dh.size()), dim3(128), 0, s, fp);
+        hipLaunchKernelGGL(symb_dh_finish_kernel, dim3((unsigned)ch_dh.items.size()), dim3(128), 0, s, fp);
         SYMB_HIP(h, hipGetLastError());
         have_dh = true;
     } else if (!want_b.empty()) {       // dB_i = s_i * dY_i^T H_i  ==  dY_i^T Hs_i
-        // small calls: dH beside dB in one launch (at most one workgroup per CU)
-        const int col_blocks = (b->d_out + GRAD_WAVE_CT - 1) / GRAD_WAVE_CT;
-        const bool pair = !have_dh && !want_a.empty() && b->d_out < GRAD_WIDE && (wave_rpad_b > 0 || grad_max_rpad > 32) && grad_max_rpad <= GRAD_WAVE_RANK && h->opt_skinny_deep && reads_bt(b) &&
-                          (long long)ch_dh.size() + (long long)col_blocks * (long long)it_b.size() <= 256;
         if (!reuse_hs && (st = run_skinny_h()) != SYMB_OK) return st;
         GradParams gp{(const bf16*)dY, (const bf16*)(wsb + wl.h_off), b->d_out, 2 * bi.max_rpad, doff, dseg,
                       (const GradItem*)(dev + o_itb), acc ? 1 : 0, seg_io ? (const bf16* const*)(dev + o_gs) : nullptr,
                       (float*)(wsb + wl.gr_off)};
         if (pair) {
-            const dim3 grid((unsigned)(ch_dh.size() + (size_t)col_blocks * it_b.size()));
+            const dim3 grid((unsigned)pair_groups);
             const SkinnyParams sp = skinny_dh();
-            auto launch = [&](auto kfn) { hipLaunchKernelGGL(kfn, grid, dim3(256), 0, s, sp, (int)ch_dh.size(), gp, col_blocks, wave_rpad_b > 0 ? 1 : 0); };
+            auto launch = [&](auto kfn) { hipLaunchKernelGGL(kfn, grid, dim3(256), 0, s, sp, (int)ch_dh.items.size(), gp, col_blocks, wave_rpad_b > 0 ? 1 : 0); };
             if (grad_max_rpad <= 16) launch(symb_lora_grad_pair_kernel<1>);
             else if (grad_max_rpad <= 32) launch(symb_lora_grad_pair_kernel<2>);
             else launch(symb_lora_grad_pair_kernel<4>);
@@ -2089,7 +2119,7 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
     }
     if (!want_a.empty()) {       // dA_i = dH_i^T X_i
         if (!have_dh) {
-            if ((st = launch_skinny_dh(h, b, skinny_dh(), (bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk), (int)ch_dh.size(), grad_max_rpad, s)) != SYMB_OK) return st;
+            if ((st = launch_skinny_dh(h, b, skinny_dh(), (bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk), ch_dh, grad_max_rpad, s)) != SYMB_OK) return st;
         }
         GradParams gp{(const bf16*)X, (const bf16*)(wsb + wl.dh_off), b->d_in, 2 * bi.max_rpad, doff, dseg,
                       (const GradItem*)(dev + o_ita), acc ? 1 : 0, seg_io ? (const bf16* const*)(dev + o_xs) : nullptr,

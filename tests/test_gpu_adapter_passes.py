@@ -68,3 +68,16 @@ def test_gradients_of_many_short_segments(lens, ranks):
         dAr, dBr = oracle.lora_grad(off, oads, p["X"], p["dY"], i)
         assert_close(d.dA.cpu().numpy(), dAr, f"dA[{i}]")
         assert_close(d.dB.cpu().numpy(), dBr, f"dB[{i}]")
+
+
+@pytest.mark.parametrize("T,ranks", [(4096, [16]), (4090, [32, 5]), (3000, [64, 100]), (4100, [8]), (8190, [20]), (5000, [40, 64]), (8200, [16]), (9000, [32, 12]), (12280, [64]), (12300, [48])])
+def test_shrink_by_its_number_of_rows(T, ranks):
+    """The builds of 16, 32 and 48 rows and the one of 32 rows that more rows take, at their edges; the wavefronts' slices of the inner dimensions: some, one or none whole,
+    and a remainder."""
+    for d_in, d_out in ((1096, 72), (72, 1608)):
+        lens = [T // 3, 1, T - T // 3 - 1]
+        p = make_problem(T + sum(ranks) + d_in, d_in, d_out, lens, [L], ranks)
+        Y, _ = gh.forward(p["off"], p["ads"], p["X"], p["W"], None, want_base=False)
+        _, Yr = oracle.forward(p["off"], oracle_ads(p["ads"]), p["X"], p["W"])
+        assert_close(gh.bf16_to_f64(Y), Yr, f"Y {T} rows", out_bf16=True)
+        _check(p, f"{T} rows, ranks {ranks}")
