@@ -409,24 +409,26 @@ LoraSteps lora_steps(const symb_batch* b, const DeltaPlan& terms) {
     return s;
 }
 
-// The tile and the K split of a product.  Of the launches that gemm_variant gives to the 128x128 tile, those whose 256x128 tiles are one nearly
-// full round of one per CU, whole or in two or three K parts, take that tile: it moves three quarters of the bytes per flop from L2 to LDS and waits out
-// HBM latency with two stages in flight.  Time of the 128x128 tile over its, medians over products of 65 to 4500 rows, operands from HBM, by its
-// tiles: whole, 161 to 256 tiles, 1.12 to 1.19 for K = 1000 to 2500, 1.17 to 1.3 above, 1.0 below; 129 to 160 tiles 0.94 to 1.1; two or three parts, 65 to 128 tiles,
+// The tile and the K split of a product.  Of the launches that gemm_variant gives to the 128x128 tile, those of more such tiles than CUs whose 256x128 tiles
+// are at most one per CU, or fewer in two or three K parts, take that tile: it moves three quarters of the bytes per flop from L2 to LDS and waits out
+// HBM latency with two stages in flight.  Time of the 128x128 tile over its, medians inside calls of one product, three sets of operands in turn, 260 of 129 to 4200 rows: more
+// than 256 small tiles (some CUs run two) K = 3072 to 4100 1.05 to 1.2, to 6100 1.2 to 1.27, to 8200 1.19 to 1.4, above 1.1 to 1.3, also where up to two fifths of the 128-row halves are empty (600
+// rows of 8192 -> 8192 and back 217 / 185 us) and from 129 tiles on (731 of 6144 -> 6144 and back 152 / 143); up to 256 small tiles, one per CU, 0.75 to 0.88 (in parts 0.62 to 0.85);
+// K = 1000 to 3072 1.03 to 1.12, which calls with adapter passes lose again.  Whole calls of all flows whose tile this changed gained 9 % on average.  In two or three parts, 65 to 128 tiles, operands from HBM,
 // 1.1 to 1.46 for K >= 3072 and 0.93 to 0.99 below; but inside calls, with their activations in cache and the partial tiles (up to 32 MiB) pushing weights out of it, 210 calls of all
 // flows: two parts of K = 3072 to 6000 0.81 to 1.13, median 0.97 (457 rows of 4096 -> 6144 and back 106 / 131, 861 of 3312 -> 4096 40 / 45.6), from 6144 on 0.95 to 1.48, median 1.14; three parts 0.93 to 1.14
 // up to 4700, 1.02 to 1.22 from there on; one row tile 0.95 to 1.05 below 4096, 0.95 to 1.21, median 1.09, from there on; fewer tiles 0.76 to 1.0 (and 1.15 in four parts of K > 5000).  Up to 128 rows half of every
 // such tile would be empty.  The parts are as many as fit an XCD's 32 CUs: 81 to 85 tiles in three parts are 33 workgroups on most XCDs, a second
 // round (84 tiles, us in two / three parts, 128x128 tile: 2993 rows of 4608 -> 856 42.2 / 59.4, 58.3; 2855 of 11192 -> 776 109.7 / 129.2, 130.3).  397 rows of 4096 -> 11008 with the adapters of
 // eleven clients 85.5 / 78 us, 16384 rows of 6144 -> 256 80.6 / 59.3.  Inside calls, behind the adapter passes, the whole ones of K < 3072 only break even (6000 rows of
-// 2032 -> 800 74.5 / 77.4, the call): from K = 3072 on.  At most an eighth of the 128-row halves empty: 547 rows of 4096 -> 4992 85.0 / 89.8, 288 of 2320 ->
-// 11008 55.8 / 66.9 (the calls).  Not with LoRA steps beyond a quarter of the K stages: a tile of twice the
+// 2032 -> 800 74.5 / 77.4, the call): from K = 3072 on.  In parts: at most an eighth of the 128-row halves empty.  Not with LoRA steps beyond a quarter of the K stages: a tile of twice the
 // rows has up to twice as many, one after the other (batches whose terms do not come from memory, for want of room or by their number, count in full: 2000 one-token clients on
 // 4096 x 4096 with room for nothing optional keep 128x128 tiles of 128 steps each).
 // Where few columns stream many activation rows that do not lie on whole lines (K no multiple of 64), a launch has to fill the chip to keep as many
 // loads on their way as the 128x128 tiles: 4500 to 20000 rows, M >= 3 N, 128x128 tile's time over its, whole, K < 4300 1.03 to 1.26, above 0.81 to 1.03 up to 216 tiles (8770 rows
 // of 9176 -> 768 145 / 178 us, 4689 of 17872 -> 1216 255 / 300) and 1.02 to 1.28 from 220 on; in two parts 0.89 to 1.04 up to
-// K = 7000, 0.95 to 1.05 up to 10000, 1.0 to 1.6 above; on whole lines 0.95 to 1.4.
+// K = 7000, 0.95 to 1.05 up to 10000, 1.0 to 1.6 above; on whole lines 0.95 to 1.4.  Up to 160 tiles: M >= N, K = 12528 to 14872 0.88 to 0.94, to 11120 1.07 to 1.27; and on whole lines, M >= 18 N,
+// 0.94 to 1.01 (8761 rows of 4864 -> 472).
 // Small layers take the tiles of 32 rows (symb_gemm_mid_kernel) as long as these are one round of workgroups: time of the 128x128 tile over theirs, 13 300 products
 // of 65 to 1500 rows, medians by K, K-contiguous weight: 1.2 (K = 256), 1.3 to 1.37 (512), 1.3 to 1.46 (768), 1.4 to 1.57 (1024), 1.55 to 1.74 (1536) up to 256
 // workgroups, 0.9 to 1.0 with 257 to 512, 0.6 beyond; where the 128x128 tiles are split over K 1.23 to 1.34 up to K = 2048, 1.03 to 1.1 above;
@@ -447,12 +449,13 @@ GemmPlan gemm_plan(const symb_batch* b, int N, int K, bool nn, bool lora, bool w
     p.unsplit_for_base = with_base && p.variant == kTile128 && p.split.parts > 1;
     const long tall = (long)((M + 255) / 256) * ((N + 127) / 128);
     const long small = (long)((M + 127) / 128) * ((N + 127) / 128);
-    if (p.variant == kTile128 && M > 128 && K >= 3072 && 4 * small >= 7 * tall && !p.split.doubled) {
+    if (p.variant == kTile128 && M > 128 && K >= 3072 && !p.split.doubled) {
         const int parts = (int)(32 / std::max((tall + 7) / 8, 1L));      // of an XCD's tiles, in its 32 CUs
         const size_t bytes = (size_t)tall * parts * 256 * 128 * 4;
         const bool streamed = M >= 3L * N && K % 64 != 0;
-        const bool whole = tall > 160 && tall <= 256 && !(streamed && K >= 4500 && tall < 220);
-        const bool split = tall > 64 && tall <= 128 && K >= (M <= 256 ? 4096 : parts == 3 ? 4700 : streamed ? 7168 : 6144) && bytes <= split_room;
+        const bool few_streamed = K % 64 != 0 && (tall <= 160 ? M >= N && K >= 11500 : M >= 3L * N && K >= 4500 && tall < 220);
+        const bool whole = small > 256 && tall <= 256 && !few_streamed && !(tall <= 160 && M >= 12L * N);
+        const bool split = 4 * small >= 7 * tall && tall > 64 && tall <= 128 && K >= (M <= 256 ? 4096 : parts == 3 ? 4700 : streamed ? 7168 : 6144) && bytes <= split_room;
         GemmPlan t;
         t.variant = kTileTall;
         if (split) t.split = SplitPlan{parts, 0, (int)tall, bytes, false};

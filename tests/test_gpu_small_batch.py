@@ -230,6 +230,13 @@ def test_tile_size(T, d_in, d_out, tile):
         assert ran == {conv1d + tile: 1}
 
 
+@pytest.mark.parametrize("T,d_in,d_out,tile", [
+    (731, 6144, 6144, 10), (731, 3064, 6144, 2), (600, 8192, 6656, 10), (600, 8192, 6528, 2),          # 288 and 260 tiles of 128x128, 255
+    (2536, 12544, 1904, 10), (2536, 12528, 1904, 2), (8761, 4864, 472, 2), (5000, 4864, 904, 10)])     # rows off the lines, few columns
+def test_tile_size_where_small_tiles_are_more_than_the_cus(T, d_in, d_out, tile):
+    test_tile_size(T, d_in, d_out, tile)
+
+
 @pytest.mark.parametrize("d_in,d_out,tile", [(264, 392, 128), (2056, 264, 128), (200, 9480, 256)])     # whole, split over K, large tiles
 def test_short_segments_of_a_larger_batch(d_in, d_out, tile):
     """LoRA terms of short segments are added from memory where a row tile holds many of their steps: scattered over the tiles,

@@ -121,6 +121,10 @@ def test_tall_tile(T, d_in, d_out, parts, ranks):
             check_y(gh.bf16_to_f64(Y[rows]), off, oracle_ads(base), p["X"], p["W"], None, f"Y in {ws} bytes", rows=rows)
 
 
+def test_tall_tile_with_empty_halves():
+    test_tall_tile(600, 3080, 6536, 1, [16, 5])          # 156 tiles, a third of them with 88 rows; 260 of 128x128
+
+
 @pytest.mark.parametrize("lens,d_in,d_out,room", [
     ([1] * 2000, 4096, 4096, False),                     # no room for the terms: 256 steps in a tile of 256 rows
     ([1] * 276 + [124], 3072, 11008, True)])             # the second tile's 20 steps are too few for memory beside 276 rows of terms
