@@ -607,12 +607,16 @@ struct SmallFinishParams {
     SmallRows rows;
 };
 // What a workgroup (128 threads, 256 columns of one row) adds to its columns' sums v0, v1: the partial sums of the K ranges, bias, and
-// the row's LoRA term.  Every load that does not depend on another goes out before the first wait: H's partial sums, the call's, and
-// the adapter matrix, which the workgroup reads together, 16 bytes per lane and NCH chunks per thread, unconditionally.
+// the row's LoRA term.  The partial sums of the first eight ranges, the call's and H's, are requested before the row's descriptor is there (SmallFirst); what hangs on
+// that one, the adapter matrix, goes out next; the workgroup reads it together, 16 bytes per lane and NCH chunks per thread, unconditionally.
 // (A thread per column would read B_i in 64 lines per load and A_i two bytes at a time, a chain of dozens of
 // loads at rank 128.)  NCH: 0 = no LoRA term; else 4, 8, 16, 32 for ranks to 16, 32, 64, 128; -1 = forward at a rank that is no multiple of 8.
+struct SmallFirst {
+    float2 c[8];
+    float h[8];
+};
 template <bool BACKWARD, int NCH>
-__device__ __forceinline__ void small_finish_sums(const SmallFinishParams& p, const SegDesc& sd, int t, int c0, float* hs, float* us, float& v0, float& v1) {
+__device__ __forceinline__ void small_finish_sums(const SmallFinishParams& p, const SegDesc& sd, int t, int c0, const SmallFirst& first, float* hs, float* us, float& v0, float& v1) {
     constexpr int NC = NCH > 0 ? NCH : 1;
     const int tid = threadIdx.x, n = c0 + 2 * tid, nc = min(n, p.N - 2);
     // Forward: the 256 columns' rows of B_i are one contiguous run, L chunks per column, chunk number x = 128 i + tid.  Input gradient:
@@ -636,20 +640,24 @@ __device__ __forceinline__ void small_finish_sums(const SmallFinishParams& p, co
             if (tid < sd.rpad) hv = bf16_bits_to_f32(row[tid]) + bf16_bits_to_f32(row[sd.rpad + tid]);
         } else {
             const float* const src = p.h_partial + (size_t)t * p.h_pitch + min(tid, sd.rank - 1);
-            for (int r = 0; r < p.h_ranges; r += 8) {    // eight loads in flight, the ones past the last range discarded
+#pragma unroll
+            for (int q = 0; q < 8; ++q) hv += q < p.h_ranges ? first.h[q] : 0.f;
+            for (int r = 8; r < p.h_ranges; r += 8) {    // eight loads in flight, the ones past the last range discarded
                 float a[8];
 #pragma unroll
                 for (int q = 0; q < 8; ++q) a[q] = src[(size_t)min(r + q, p.h_ranges - 1) * p.T * p.h_pitch];
 #pragma unroll
                 for (int q = 0; q < 8; ++q) hv += r + q < p.h_ranges ? a[q] : 0.f;
             }
-            hv = tid < sd.rank ? hv * sd.scale : 0.f;
+            hv = tid < sd.rank ? hv * sd.scale : 0.f;    // (past the rank h_partial holds anything)
         }
     }
     {
         const float* const src = p.partial + (size_t)t * p.N + nc;
         const size_t stride = (size_t)p.T * p.N;
-        for (int r = 0; r < p.ranges; r += 8) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) { v0 += q < p.ranges ? first.c[q].x : 0.f; v1 += q < p.ranges ? first.c[q].y : 0.f; }
+        for (int r = 8; r < p.ranges; r += 8) {
             float2 a[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) a[q] = *reinterpret_cast<const float2*>(src + (size_t)min(r + q, p.ranges - 1) * stride);
@@ -733,11 +741,22 @@ SYMB_KERNEL void __launch_bounds__(128)
 symb_small_finish_kernel(const SmallFinishParams p) {
     __shared__ __attribute__((aligned(16))) float hs[128], us[4096 + 128];
     const int t = blockIdx.y, c0 = blockIdx.x * 256, n = c0 + 2 * (int)threadIdx.x;
+    SmallFirst first;
+    {
+        const float* const c = p.partial + (size_t)t * p.N + min(n, p.N - 2);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) first.c[q] = *reinterpret_cast<const float2*>(c + (size_t)min(q, p.ranges - 1) * ((size_t)p.T * p.N));
+        // (without a LoRA term or with H there already: some floats of the call's sums)
+        const bool h = p.lora_term && p.h_partial;
+        const float* const src = h ? p.h_partial + (size_t)t * p.h_pitch + min((int)threadIdx.x, p.h_pitch - 1) : c;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) first.h[q] = src[h ? (size_t)min(q, p.h_ranges - 1) * ((size_t)p.T * p.h_pitch) : 0];
+    }
     const uint32_t at = p.rows.at[t];
     const int s = at >> 8, in_seg = at & 255;
     const SegDesc sd = p.seg[s];
     float v0 = 0.f, v1 = 0.f;
-    auto sums = [&](auto NCH) __attribute__((always_inline)) { small_finish_sums<BACKWARD, decltype(NCH)::value>(p, sd, t, c0, hs, us, v0, v1); };
+    auto sums = [&](auto NCH) __attribute__((always_inline)) { small_finish_sums<BACKWARD, decltype(NCH)::value>(p, sd, t, c0, first, hs, us, v0, v1); };
     // uniform over the workgroup (one row, one segment)
     if (!p.lora_term || sd.kind != KIND_LORA) sums(std::integral_constant<int, 0>{});
     else if (!BACKWARD && (sd.rank & 7)) sums(std::integral_constant<int, -1>{});

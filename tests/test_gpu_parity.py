@@ -1130,3 +1130,41 @@ def test_two_streams_share_one_handle():
     finally:
         torch.cuda.synchronize()
         sb.symb_destroy(h)
+
+
+def test_more_streams_than_share_events():
+    """One host thread, six streams through one handle, each with batches of its own, 48 in all (more than the ring has slots; tiles split over K
+    ranges, whose counters live there): a first stretch on one stream alone, whose last calls no event covers when the others come, then all of them in random
+    order, then one that comes last.  Every call gives the bits of its batch's first one."""
+    h = sb.symb_create(0)
+    try:
+        rng = np.random.default_rng(17)
+        d_in, d_out = 1032, 264
+        streams = [torch.cuda.Stream() for _ in range(6)]
+        probs = []
+        for k in range(48):
+            p = make_problem(900 + k, d_in, d_out, [int(x) for x in rng.choice([3, 17, 40, 64], size=3)], [L, I, N], [8, 16])
+            dev = gh.upload_adapters(p["ads"], d_in, d_out, grads=False)
+            p["dev"], p["batch"] = dev, sb.Batch(d_in, d_out, p["off"], dev.descs)
+            p["Xd"], p["Wd"], p["bd"] = gh.to_dev(p["X"]), gh.to_dev(p["W"]), gh.to_dev(p["bias"])
+            p["Y"] = torch.empty((p["T"], d_out), device="cuda", dtype=torch.bfloat16)
+            p["ws"] = gh.workspace(p["batch"], sb.SYMB_OP_FWD)
+            sb.symb_base_linear_fwd(gh.handle(), p["batch"], p["Xd"], p["Wd"], p["bd"], p["Y"], None, p["ws"], gh.stream_ptr())
+            p["first"] = p["Y"].view(torch.int16).clone()
+            probs.append(p)
+        torch.cuda.synchronize()
+        order = [0, 6, 12, 0, 6, 12, 18, 24, 30, 36, 0, 6, 0] + [int(x) for x in rng.integers(0, 48, 500) if x % 6 < 5] + [int(x) for x in rng.integers(0, 48, 100)]
+        for n, k in enumerate(order):
+            p, st = probs[k], streams[k % 6]
+            with torch.cuda.stream(st):
+                if n % 3 == 0:
+                    p["Y"].fill_(float("nan"))
+                sb.symb_base_linear_fwd(h, p["batch"], p["Xd"], p["Wd"], p["bd"], p["Y"], None, p["ws"], st.cuda_stream)
+                same = torch.equal if n % 11 == 0 else lambda a, b: True          # (a comparison waits for the stream)
+                assert same(p["Y"].view(torch.int16), p["first"]), (n, k)
+        torch.cuda.synchronize()
+        for k, p in enumerate(probs):
+            assert torch.equal(p["Y"].view(torch.int16), p["first"]), k
+    finally:
+        torch.cuda.synchronize()
+        sb.symb_destroy(h)
