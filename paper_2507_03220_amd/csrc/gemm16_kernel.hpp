@@ -111,7 +111,7 @@ struct Gemm16Tile {
     static constexpr int UNIT_A = BM * 128, UNIT_B = BN * 128;   // one operand's 64-k stage
     static constexpr int C_PITCH = BN * 2 + 16, C_BYTES = BM * C_PITCH;
     static constexpr int SMEM = 3 * UNIT_A + (TALL ? 4 : 2) * UNIT_B;
-    static_assert(C_BYTES + (TALL ? 24 * BM : 0) <= SMEM, "the staged output tile (and the pointers of its rows) must fit the ring");
+    static_assert(C_BYTES + 24 * BM <= SMEM, "the staged output tile (and the pointers of its rows) must fit the ring");
 };
 
 // N-contiguous weight unit: [64 k][BN n] bf16, 16-byte chunk nc of row k stored at nc ^ swz.  The
@@ -197,13 +197,14 @@ symb_gemm16_kernel(const GemmParams p) {
         const int s = seg_of_row(p.off, seg_lo, seg_hi, m);
         return p.a_seg[s] + (size_t)(m - p.off[s]) * p.K;
     };
-    // The 256x128 tile, one workgroup to a CU, looks the segment of a row up once, a thread for each, and hands what hangs on it to the others through LDS.  A lookup is a chain of
-    // dependent loads, and with one for every row that a lane loads, scales or stores nothing hid sixteen and more of them, one after the other: 408 rows of 4096 -> 11008 in 51
-    // segments, a buffer per client, some with IA3, 97.3 -> 75.1 us (128x128 tile 83.7); 2000 rows of 4608 -> 4096 with noise effects, in four segments, 82.4 -> 76.6.
+    // What hangs on the segment of a row is looked up once, a thread for each row, and handed to the others through LDS.  A lookup is a chain of
+    // dependent loads, and with one for every row that a lane loads, scales or stores nothing hid sixteen and more of them, one after the other: 256x128 tile, 408 rows of 4096 -> 11008 in 51
+    // segments, a buffer per client, some with IA3, 97.3 -> 75.1 us; 2000 rows of 4608 -> 4096 with noise effects, in four segments, 82.4 -> 76.6.  That tile looks up
+    // before its main loop, for the rows that it loads too; the others, which have no register to keep it in, behind theirs.
     int my_seg = 0;
-    const bool by_row = TT::TALL && (p.a_seg || p.c_seg || (!PLAIN && (p.neff || (p.epi_ia3 != 0 && p.tile_epi[tm] != 0))));
+    const bool by_row = (TT::TALL && p.a_seg) || p.c_seg || (!PLAIN && (p.neff || (p.epi_ia3 != 0 && p.tile_epi[tm] != 0)));
     const int my_row = min(m0 + tid, p.M - 1);
-    if (by_row) my_seg = seg_of_row(p.off, seg_lo, seg_hi, my_row);
+    if (TT::TALL && by_row) my_seg = seg_of_row(p.off, seg_lo, seg_hi, my_row);
     const bf16* const a_tile = p.a_seg ? p.a_base : p.Aop + (size_t)m0 * p.K;
     const bf16* const b_tile = NN ? (p.Bop + n0) : (p.Bop + (size_t)n0 * p.K);
     const unsigned lds0 = (unsigned)(size_t)smem;          // LDS byte address of the dynamic segment
@@ -491,18 +492,22 @@ symb_gemm16_kernel(const GemmParams p) {
 
     // ---- output staging: the bf16 tile goes through LDS and leaves as whole 512-byte rows
     const unsigned c_lane = (unsigned)((wm0 + l15) * CP + (wn0 + lg * 4) * 2);   // this lane's C[.][.] of block (0, 0)
-    // 256x128 tile: each row's IA3 vector, noise effect and place in its client's buffer, behind the staged tile (set before the last stage_out)
+    // each row's IA3 vector, noise effect and place in its client's buffer, behind the staged tile (set before the last stage_out)
     const bf16** const row_scale = reinterpret_cast<const bf16**>(smem + TT::C_BYTES);
     const bf16** const row_noise = row_scale + BM;
     bf16** const row_out = reinterpret_cast<bf16**>(smem + TT::C_BYTES) + 2 * BM;
-    auto stage_out = [&](bf16* __restrict__ dst, bool scale_ia3) __attribute__((always_inline)) {
-        if (PLAIN || (!p.bias && !scale_ia3 && !p.neff)) {
+    // FINAL: C; else the pre-adapter output, bias alone (never beside a noise effect)
+    auto stage_out = [&](auto FINALC, bf16* __restrict__ dst, bool scale_ia3) __attribute__((always_inline)) {
+        constexpr bool FINAL = decltype(FINALC)::value;
+        if (PLAIN || (!p.bias && (!FINAL || (!scale_ia3 && !p.neff)))) {
             if constexpr (TT::TALL) asm volatile(SYMB_GEMM16T_STAGE_OUT : : "v"(lds0 + c_lane) : "memory", SYMB_GEMM16T_VCLOBBERS);
             else if constexpr (NBLK == 8) asm volatile(SYMB_GEMM16_STAGE_OUT : : "v"(lds0 + c_lane) : "memory", SYMB_GEMM16_VCLOBBERS);
             else asm volatile(SYMB_GEMM16S_STAGE_OUT : : "v"(lds0 + c_lane) : "memory", SYMB_GEMM16S_VCLOBBERS);
         } else if constexpr (!PLAIN) {
-            // bias of this lane's column quads, once; IA3 vector and noise effect of each row's own
-            // segment per row block
+            // bias of this lane's column quads, once; IA3 vector and noise effect of each row's own segment per block of rows.  The loads of AHEAD blocks are on their way
+            // at a time, each unconditional (rows without read the weight, columns past the last one repeat it) and known at compile time, or the compiler's waits for
+            // one block's would take the next one's along: the privacy flow's call of 2000 rows of 4608 -> 4096 with noise effects
+            // 97.2 -> 90.3 us (with nothing on its way ahead, the loads of a block a chain of their own behind the one before), the mixed batch's training step 1490 -> 1454.
             const int nq0 = n0 + wn0 + lg * 4;
             uint2 bv[NBLK];
 #pragma unroll
@@ -510,72 +515,73 @@ symb_gemm16_kernel(const GemmParams p) {
                 const int n = nq0 + j * 16;
                 bv[j] = (p.bias && n < p.N) ? *reinterpret_cast<const uint2*>(p.bias + n) : make_uint2(0u, 0u);
             }
-            static_for<0, MBLK>([&](auto I) __attribute__((always_inline)) {
-                constexpr int i = decltype(I)::value;
-                const int m = m0 + wm0 + i * 16 + l15;
-                const bf16* lrow = nullptr;
-                const bf16* nrow = nullptr;
-                if constexpr (TT::TALL) {
-                    if (scale_ia3) lrow = row_scale[m - m0];
-                    if (p.neff) nrow = row_noise[m - m0];
-                } else if ((scale_ia3 || p.neff) && m < p.M) {
-                    const int s = seg_of_row(p.off, seg_lo, seg_hi, m);
-                    if (scale_ia3 && p.seg[s].kind == p.epi_ia3) lrow = p.seg[s].A;
-                    if (p.neff) {
-                        const NoiseDesc nd = p.neff[s];
-                        if (nd.ptr) nrow = nd.ptr + (size_t)(nd.rows == 1 ? 0 : m - p.off[s]) * p.N;
-                    }
-                }
-                uint2 lv[NBLK], nv[NBLK];
-                if constexpr (TT::TALL) {                // four loads under one condition; columns past the last one repeat it, unstored
+            auto blocks = [&](auto SCALEC, auto NOISEC) __attribute__((always_inline)) {
+                constexpr bool SCALE = decltype(SCALEC)::value, NOISE = decltype(NOISEC)::value;
+                constexpr int AHEAD = !SCALE && !NOISE ? 1 : NBLK == 8 ? 2 : 4;
+                uint2 lv[SCALE ? AHEAD : 1][NBLK], nv[NOISE ? AHEAD : 1][NBLK];
+                unsigned scaled = 0, noisy = 0;      // bit i: this lane's row of block i
+                auto fetch = [&](auto I) __attribute__((always_inline)) {
+                    constexpr int i = decltype(I)::value, at = i % AHEAD;
+                    const int r = wm0 + i * 16 + l15;
+                    if constexpr (SCALE) {
+                        const bf16* const q = row_scale[r];
+                        scaled |= q ? 1u << i : 0u;
 #pragma unroll
-                    for (int j = 0; j < NBLK; ++j) nv[j] = make_uint2(0u, 0u), lv[j] = make_uint2(0x3f803f80u, 0x3f803f80u);
-                    if (nrow) {
+                        for (int j = 0; j < NBLK; ++j) lv[at][j] = ld_global_8((q ? q : p.Bop) + min(nq0 + j * 16, p.N - 4));
+                    }
+                    if constexpr (NOISE) {
+                        const bf16* const q = row_noise[r];
+                        noisy |= q ? 1u << i : 0u;
 #pragma unroll
-                        for (int j = 0; j < NBLK; ++j) nv[j] = ld_global_8(nrow + min(nq0 + j * 16, p.N - 4));
+                        for (int j = 0; j < NBLK; ++j) nv[at][j] = ld_global_8((q ? q : p.Bop) + min(nq0 + j * 16, p.N - 4));
                     }
-                    if (lrow) {
-#pragma unroll
-                        for (int j = 0; j < NBLK; ++j) lv[j] = ld_global_8(lrow + min(nq0 + j * 16, p.N - 4));
-                    }
-                } else
-#pragma unroll
-                for (int j = 0; j < NBLK; ++j) {
-                    const int n = nq0 + j * 16;
-                    nv[j] = (nrow && n < p.N) ? *reinterpret_cast<const uint2*>(nrow + n) : make_uint2(0u, 0u);
-                    lv[j] = (lrow && n < p.N) ? *reinterpret_cast<const uint2*>(lrow + n) : make_uint2(0x3f803f80u, 0x3f803f80u);
-                }
-                static_for<0, NBLK>([&](auto J) __attribute__((always_inline)) {
-                    constexpr int j = decltype(J)::value;
-                    float v0, v1, v2, v3;
-                    acc16_read4<4 * (NBLK * i + j)>(v0, v1, v2, v3);
-                    if (p.bias) {
-                        v0 += bf16_bits_to_f32((unsigned short)(bv[j].x & 0xffffu));
-                        v1 += bf16_bits_to_f32((unsigned short)(bv[j].x >> 16));
-                        v2 += bf16_bits_to_f32((unsigned short)(bv[j].y & 0xffffu));
-                        v3 += bf16_bits_to_f32((unsigned short)(bv[j].y >> 16));
-                    }
-                    if (scale_ia3) {           // rows of other kinds carry ones (exact)
-                        v0 *= bf16_bits_to_f32((unsigned short)(lv[j].x & 0xffffu));
-                        v1 *= bf16_bits_to_f32((unsigned short)(lv[j].x >> 16));
-                        v2 *= bf16_bits_to_f32((unsigned short)(lv[j].y & 0xffffu));
-                        v3 *= bf16_bits_to_f32((unsigned short)(lv[j].y >> 16));
-                    }
-                    if (p.neff) {              // y = y_noisy - n_eff, still in fp32
-                        v0 -= bf16_bits_to_f32((unsigned short)(nv[j].x & 0xffffu));
-                        v1 -= bf16_bits_to_f32((unsigned short)(nv[j].x >> 16));
-                        v2 -= bf16_bits_to_f32((unsigned short)(nv[j].y & 0xffffu));
-                        v3 -= bf16_bits_to_f32((unsigned short)(nv[j].y >> 16));
-                    }
-                    uint2 o;
-                    o.x = pack2_bf16(v0, v1);
-                    o.y = pack2_bf16(v2, v3);
-                    *reinterpret_cast<uint2*>(smem + c_lane + i * 16 * CP + j * 32) = o;
+                };
+                if constexpr (SCALE || NOISE) static_for<0, AHEAD>([&](auto I) __attribute__((always_inline)) { fetch(I); });
+                static_for<0, MBLK>([&](auto I) __attribute__((always_inline)) {
+                    constexpr int i = decltype(I)::value, at = i % AHEAD;
+                    const bool sc = SCALE && (scaled >> i & 1), nz = NOISE && (noisy >> i & 1);
+                    static_for<0, NBLK>([&](auto J) __attribute__((always_inline)) {
+                        constexpr int j = decltype(J)::value;
+                        float v0, v1, v2, v3;
+                        acc16_read4<4 * (NBLK * i + j)>(v0, v1, v2, v3);
+                        if (p.bias) {
+                            v0 += bf16_bits_to_f32((unsigned short)(bv[j].x & 0xffffu));
+                            v1 += bf16_bits_to_f32((unsigned short)(bv[j].x >> 16));
+                            v2 += bf16_bits_to_f32((unsigned short)(bv[j].y & 0xffffu));
+                            v3 += bf16_bits_to_f32((unsigned short)(bv[j].y >> 16));
+                        }
+                        if constexpr (SCALE) {           // rows of other kinds: ones (exact)
+                            const uint2 l = make_uint2(sc ? lv[at][j].x : 0x3f803f80u, sc ? lv[at][j].y : 0x3f803f80u);
+                            v0 *= bf16_bits_to_f32((unsigned short)(l.x & 0xffffu));
+                            v1 *= bf16_bits_to_f32((unsigned short)(l.x >> 16));
+                            v2 *= bf16_bits_to_f32((unsigned short)(l.y & 0xffffu));
+                            v3 *= bf16_bits_to_f32((unsigned short)(l.y >> 16));
+                        }
+                        if constexpr (NOISE) {           // y = y_noisy - n_eff, still in fp32
+                            const uint2 q = make_uint2(nz ? nv[at][j].x : 0u, nz ? nv[at][j].y : 0u);
+                            v0 -= bf16_bits_to_f32((unsigned short)(q.x & 0xffffu));
+                            v1 -= bf16_bits_to_f32((unsigned short)(q.x >> 16));
+                            v2 -= bf16_bits_to_f32((unsigned short)(q.y & 0xffffu));
+                            v3 -= bf16_bits_to_f32((unsigned short)(q.y >> 16));
+                        }
+                        uint2 o;
+                        o.x = pack2_bf16(v0, v1);
+                        o.y = pack2_bf16(v2, v3);
+                        *reinterpret_cast<uint2*>(smem + c_lane + i * 16 * CP + j * 32) = o;
+                    });
+                    if constexpr ((SCALE || NOISE) && i + AHEAD < MBLK) fetch(std::integral_constant<int, i + AHEAD>{});
                 });
-            });
+            };
+            if constexpr (FINAL) {
+                if (p.neff) {
+                    if (scale_ia3) blocks(std::true_type{}, std::true_type{});
+                    else blocks(std::false_type{}, std::true_type{});
+                } else if (scale_ia3) blocks(std::true_type{}, std::false_type{});
+                else blocks(std::false_type{}, std::false_type{});
+            } else blocks(std::false_type{}, std::false_type{});
         }
         __syncthreads();
-        const bool to_seg = p.c_seg != nullptr && dst == p.C;   // the final output goes to the segments' own buffers
+        const bool to_seg = FINAL && p.c_seg != nullptr;        // the final output goes to the segments' own buffers
         constexpr int LPR = BN / 8;                  // lanes per row (16 bytes each)
         constexpr int RPP = 256 / LPR;               // rows per pass of the workgroup
         constexpr int NPASS = BM / RPP, BATCH = NPASS < 16 ? NPASS : 16;
@@ -600,13 +606,7 @@ symb_gemm16_kernel(const GemmParams p) {
             for (int r = r0; r < BM; r += RPP) {
                 const int m = m0 + r;
                 if (m < p.M && nok) {
-                    bf16* rowp;
-                    if constexpr (TT::TALL) rowp = row_out[r];
-                    else {
-                        const int s = seg_of_row(p.off, seg_lo, seg_hi, m);
-                        rowp = p.c_seg[s] + (size_t)(m - p.off[s]) * p.N;
-                    }
-                    *reinterpret_cast<uint4*>(rowp + n0 + col) = *reinterpret_cast<const uint4*>(smem + r * CP + col * 2);
+                    *reinterpret_cast<uint4*>(row_out[r] + n0 + col) = *reinterpret_cast<const uint4*>(smem + r * CP + col * 2);
                 }
             }
         }
@@ -615,7 +615,7 @@ symb_gemm16_kernel(const GemmParams p) {
     // ---- optional store of the pre-adapter output (accumulator + bias, before the LoRA term)
     if constexpr (!PLAIN) {
         if (p.Cbase) {
-            stage_out(p.Cbase, false);
+            stage_out(std::false_type{}, p.Cbase, false);
             __syncthreads();                         // LDS is reused by the LoRA tiles below
         }
     }
@@ -803,21 +803,25 @@ symb_gemm16_kernel(const GemmParams p) {
         }
     }
 
-    if (by_row) {
-        const int at = my_row - p.off[my_seg];
+    int row_at = (int)threadIdx.x;                   // (from the thread id again: the full 256x256 tile has no register to keep more in)
+    if (!TT::TALL) asm volatile("" : "+v"(row_at));
+    if (by_row && (BM == NT || row_at < BM)) {
+        const int row = TT::TALL ? my_row : min(m0 + row_at, p.M - 1);
+        if (!TT::TALL) my_seg = seg_of_row(p.off, seg_lo, seg_hi, row);
+        const int at = row - p.off[my_seg];
         if constexpr (!PLAIN) {
-            row_scale[tid] = p.seg[my_seg].kind == p.epi_ia3 ? p.seg[my_seg].A : nullptr;
+            row_scale[row_at] = p.seg[my_seg].kind == p.epi_ia3 ? p.seg[my_seg].A : nullptr;
             if (p.neff) {
                 const NoiseDesc nd = p.neff[my_seg];
-                row_noise[tid] = nd.ptr ? nd.ptr + (size_t)(nd.rows == 1 ? 0 : at) * p.N : nullptr;
+                row_noise[row_at] = nd.ptr ? nd.ptr + (size_t)(nd.rows == 1 ? 0 : at) * p.N : nullptr;
             }
         }
-        if (p.c_seg) row_out[tid] = p.c_seg[my_seg] + (size_t)at * p.N;
-        __syncthreads();
+        if (p.c_seg) row_out[row_at] = p.c_seg[my_seg] + (size_t)at * p.N;
     }
+    if (by_row) __syncthreads();
 
     // ---- final output: bias, IA3 scale, noise effect, one rounding, whole-row stores
-    stage_out(p.C, p.epi_ia3 != 0 && p.tile_epi[tm] != 0);
+    stage_out(std::true_type{}, p.C, p.epi_ia3 != 0 && p.tile_epi[tm] != 0);
 }
 
 }  // namespace symb
