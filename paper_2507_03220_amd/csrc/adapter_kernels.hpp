@@ -278,13 +278,11 @@ struct SkinnyBuild {
     static constexpr int BYTES = ST::BYTES > RED ? ST::BYTES : RED;
     static_assert(BYTES <= 160 << 10, "LDS of a CU");
 };
-template <int RB, int BUILD, bool BT>
-__device__ __forceinline__ void skinny_chunk(const SkinnyParams& p, int chunk, unsigned char* smem) {
-    using ST = typename SkinnyBuild<RB, BUILD>::ST;
+// The rows of one chunk: store(t, pp, value) gets ranks pp .. pp + 3 of its row t, as a bf16 value and its bf16 rounding residual, four of each packed.
+template <int RB, class ST, bool BT, class STORE>
+__device__ __forceinline__ void skinny_rows(const SkinnyParams& p, const RowChunk ch, const SegDesc sd, unsigned char* smem, STORE&& store) {
     constexpr int BLKS = ST::BLKS, ROWS = ST::ROWS;
     float (*red)[ROWS][RB * 16 + 4] = reinterpret_cast<float (*)[ROWS][RB * 16 + 4]>(smem);
-    const RowChunk ch = p.chunks[chunk];
-    const SegDesc sd = p.seg[ch.seg];
     const int nb = sd.rpad >> 4;                         // rank blocks in use (uniform), 1..RB
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int trow = lane & 15, kq = lane >> 4;
@@ -339,10 +337,20 @@ __device__ __forceinline__ void skinny_chunk(const SkinnyParams& p, int chunk, u
         hi2.y = h23;
         lo2.x = pack2_bf16(v[0] - bf16_bits_to_f32((unsigned short)(h01 & 0xffffu)), v[1] - bf16_bits_to_f32((unsigned short)(h01 >> 16)));
         lo2.y = pack2_bf16(v[2] - bf16_bits_to_f32((unsigned short)(h23 & 0xffffu)), v[3] - bf16_bits_to_f32((unsigned short)(h23 >> 16)));
-        bf16* const row = p.out + (size_t)(ch.row0 + t) * p.out_pitch + pp;
-        *reinterpret_cast<uint2*>(row) = hi2;
-        *reinterpret_cast<uint2*>(row + sd.rpad) = lo2;
+        store(t, pp, hi2, lo2);
     }
+}
+template <int RB, int BUILD, bool BT>
+__device__ __forceinline__ void skinny_chunk(const SkinnyParams& p, int chunk, unsigned char* smem) {
+    const RowChunk ch = p.chunks[chunk];
+    const SegDesc sd = p.seg[ch.seg];
+    bf16* const out = p.out + (size_t)ch.row0 * p.out_pitch;
+    const int pitch = p.out_pitch, rpad = sd.rpad;
+    skinny_rows<RB, typename SkinnyBuild<RB, BUILD>::ST, BT>(p, ch, sd, smem, [=](int t, int pp, uint2 hi, uint2 lo) __attribute__((always_inline)) {
+        bf16* const row = out + (size_t)t * pitch + pp;
+        *reinterpret_cast<uint2*>(row) = hi;
+        *reinterpret_cast<uint2*>(row + rpad) = lo;
+    });
 }
 
 template <int RB, int BUILD, bool BT>
@@ -812,6 +820,128 @@ symb_lora_grad_pair_kernel(const SkinnyParams sp, int nchunks, const GradParams 
     else if constexpr (RB >= 2) {
         if (sd.rpad <= 32) lora_grad_wave<2, true>(gp, it, sd, block, smem);
         else if constexpr (RB >= 4) lora_grad_wave<4, true>(gp, it, sd, block, smem);
+    }
+}
+
+// -------------------------------------------------------------------------------------------
+// dA, dB and dH of short segments (at most 64 tokens, ranks up to 16) in one launch.  Such a call is its launches: dA wants dH, so that beside dB in one launch (above) dH
+// still was a launch before dA's.  Here every workgroup of dA forms dH of its whole segment itself, (tokens + 16) d_out products' operands from L2, while its columns of X are on
+// their way; the first of a segment leaves it in the workspace.  A segment's tokens are at most two steps of the matrix cores: the eight wavefronts take 16 of the workgroup's 128 columns
+// each, with no sums between them.  Training step of 16 tokens, 4096 x 4096, 9.8 us in two launches, 7.1 here, the step 34.7 -> 31.0; of 4 x 64 tokens on
+// 768 columns 26.5 -> 25.7 (bound by the host's three calls).
+// -------------------------------------------------------------------------------------------
+constexpr int GRAD_SHORT_TOKENS = 64, GRAD_SHORT_CT = 128;
+struct GradShort {
+    using ST1 = SkinnyStage<1, 3, true, 1, 8>;           // up to 16 tokens
+    using ST2 = SkinnyStage<1, 2, true, 2, 8>;           // 32 at a time
+    static constexpr int STAGE = ST1::BYTES > ST2::BYTES ? ST1::BYTES : ST2::BYTES;
+    static constexpr int X_BYTES = GRAD_SHORT_TOKENS * GRAD_SHORT_CT * 2, L_BYTES = GRAD_SHORT_TOKENS * 64, BYTES = STAGE + X_BYTES + L_BYTES;
+    static_assert(8 * 32 * 20 * 4 <= STAGE, "the wavefronts' sums of dH");
+};
+template <bool CMAJOR>
+__device__ __forceinline__ void lora_grad_short(const GradParams& p, const SkinnyParams& sp, const GradItem& it, const SegDesc& sd, int block, unsigned char* smem) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    constexpr int CT = GRAD_SHORT_CT;
+    const int s = it.seg, t_lo = it.t_lo, n = it.t_hi - it.t_lo;
+    const bf16* const rbase = p.R_seg ? p.R_seg[s] - (size_t)p.off[s] * p.ncols : p.R;
+    const int c0 = block * CT, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l15 = lane & 15, kq = lane >> 4;
+    unsigned char* const sX = smem + GradShort::STAGE;   // [token][128 columns], 32-byte pieces of row t at piece ^ skinny_bt_swz
+    unsigned char* const sL = sX + GradShort::X_BYTES;   // [token][16 values | 16 residuals]
+    for (int i = wave; i * 4 < n; i += 8) {              // four rows of X (dY) per request; past the last token it again
+        const int t = i * 4 + (lane >> 4), slot = lane & 15;
+        const bf16* const src = rbase + (size_t)(t_lo + min(t, n - 1)) * p.ncols + min(c0 + ((slot ^ (skinny_bt_swz(CT, t) << 1)) * 8), p.ncols - 8);
+        __builtin_amdgcn_global_load_lds((glb_void_t*)src, (lds_void_t*)(sX + i * 1024), 16, 0, 0);
+    }
+    if constexpr (CMAJOR) {
+        for (int i = wave; i * 16 < n; i += 8)
+            __builtin_amdgcn_global_load_lds((glb_void_t*)(p.L + (size_t)(t_lo + min(i * 16 + (lane >> 2), n - 1)) * p.l_pitch + (lane & 3) * 8), (lds_void_t*)(sL + i * 1024), 16, 0, 0);
+    } else {
+        auto part = [&](auto STC, int at, int rows) __attribute__((always_inline)) {
+            using ST = typename decltype(STC)::type;
+            skinny_rows<1, ST, true>(sp, RowChunk{s, t_lo + at, rows, 0}, sd, smem, [&](int t, int pp, uint2 hi, uint2 lo) __attribute__((always_inline)) {
+                *reinterpret_cast<uint2*>(sL + (at + t) * 64 + pp * 2) = hi;
+                *reinterpret_cast<uint2*>(sL + (at + t) * 64 + 32 + pp * 2) = lo;
+                if (block) return;
+                bf16* const row = sp.out + (size_t)(t_lo + at + t) * sp.out_pitch + pp;
+                *reinterpret_cast<uint2*>(row) = hi;
+                *reinterpret_cast<uint2*>(row + 16) = lo;
+            });
+        };
+        if (n <= 16) part(std::enable_if<true, GradShort::ST1>{}, 0, n);
+        else
+            for (int at = 0; at < n; at += 32) {
+                if (at) __syncthreads();                 // the sums of the first 32 tokens are read
+                part(std::enable_if<true, GradShort::ST2>{}, at, min(n - at, 32));
+            }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    __syncthreads();
+    // fragment reads with a wait of their own (see the skinny kernel)
+    const int k0 = kq * 8 + (l15 >> 2);                  // first of the two transposing reads; the second is 4 tokens further
+    const unsigned roff = (unsigned)(size_t)sX + (unsigned)(k0 * CT * 2 + ((wave ^ skinny_bt_swz(CT, k0)) * 32) + (l15 & 3) * 8);
+    const unsigned loff = (unsigned)(size_t)sL + (unsigned)(k0 * 64 + (l15 & 3) * 8);
+    floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int t0 = 0; t0 < n; t0 += 32) {
+        u32x2 rt[2], lt[2][2];
+        const unsigned ra = roff + t0 * CT * 2, la = loff + t0 * 64;
+        asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(rt[0]) : "v"(ra));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:1024" : "=v"(rt[1]) : "v"(ra));
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(lt[half][0]) : "v"(la + half * 32));
+            asm volatile("ds_read_b64_tr_b16 %0, %1 offset:256" : "=v"(lt[half][1]) : "v"(la + half * 32));
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+        asm volatile("" : "+v"(rt[0])); asm volatile("" : "+v"(rt[1]));
+#pragma unroll
+        for (int half = 0; half < 2; ++half) { asm volatile("" : "+v"(lt[half][0])); asm volatile("" : "+v"(lt[half][1])); }
+        u32x4 rf = __builtin_shufflevector(rt[0], rt[1], 0, 1, 2, 3);
+        u32x4 lf[2] = {__builtin_shufflevector(lt[0][0], lt[0][1], 0, 1, 2, 3), __builtin_shufflevector(lt[1][0], lt[1][1], 0, 1, 2, 3)};
+        const int left = n - (t0 + kq * 8);              // a lane holds tokens t0 + 8 kq + 0..7: those past the end count as zero, in both operands
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const unsigned keep = 2 * q + 1 < left ? 0xffffffffu : 2 * q < left ? 0xffffu : 0u;
+            rf[q] &= keep;
+            lf[0][q] &= keep;
+            lf[1][q] &= keep;
+        }
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const bf16x8 l = __builtin_bit_cast(bf16x8, lf[half]), r = __builtin_bit_cast(bf16x8, rf);
+            acc = CMAJOR ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(l, r, acc, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_bf16(r, l, acc, 0, 0, 0);
+        }
+    }
+    if constexpr (CMAJOR) {                              // lane: column l15 of the wavefront's; registers: ranks 4 kq ..
+        const int c = c0 + wave * 16 + l15;
+        float* const dst = sd.dB + (size_t)c * sd.rank + kq * 4;
+        if (c >= p.ncols) return;
+        float old[4] = {0.f, 0.f, 0.f, 0.f};             // all four read before the first store
+        if (p.accumulate) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (kq * 4 + q < sd.rank) old[q] = dst[q];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (kq * 4 + q < sd.rank) dst[q] = old[q] + acc[q];
+    } else {                                             // lane: rank l15; registers: columns 4 kq ..
+        const int c = c0 + wave * 16 + kq * 4;
+        if (l15 >= sd.rank || c >= p.ncols) return;
+        floatx4* const dst = reinterpret_cast<floatx4*>(sd.dA + (size_t)l15 * p.ncols + c);
+        *dst = p.accumulate ? acc + *dst : acc;
+    }
+}
+// grid = (column blocks of dA) x segments, then (column blocks of dB) x segments; sp: the shrink of the backward, without chunks.
+SYMB_KERNEL void __launch_bounds__(512)
+symb_lora_grad_short_kernel(const SkinnyParams sp, const GradParams ga, int a_blocks, int a_groups, const GradParams gb, int b_blocks) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[GradShort::BYTES];
+    if ((int)blockIdx.x < a_groups) {
+        const GradItem it = ga.items[blockIdx.x / a_blocks];
+        lora_grad_short<false>(ga, sp, it, ga.seg[it.seg], blockIdx.x % a_blocks, smem);
+    } else {
+        const int g = blockIdx.x - a_groups;
+        const GradItem it = gb.items[g / b_blocks];
+        lora_grad_short<true>(gb, sp, it, gb.seg[it.seg], g % b_blocks, smem);
     }
 }
 

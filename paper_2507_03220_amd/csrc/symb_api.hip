@@ -2099,10 +2099,18 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
     for (int i : want_a) pair_groups += (b->seg_offsets[i + 1] - b->seg_offsets[i] + kSkinnyRows - 1) / kSkinnyRows;
     const bool pair = !one_pass && !reuse_dh && !want_b.empty() && !want_a.empty() && b->d_out < GRAD_WIDE && (wave_rpad_b > 0 || grad_max_rpad > 32) &&
                       grad_max_rpad <= GRAD_WAVE_RANK && h->opt_skinny_deep && reads_bt(b) && pair_groups <= 256;
+    // Short segments: dA, dB and dH in one launch, every workgroup of dA with a dH of its own; as long as what each reads for it (a CU takes in
+    // 64 bytes per clock: 512 KiB 4 us) is less than another launch and its chain, and all of them are one per CU.
+    const int a_blocks = (b->d_in + GRAD_SHORT_CT - 1) / GRAD_SHORT_CT, b_blocks = (b->d_out + GRAD_SHORT_CT - 1) / GRAD_SHORT_CT;
+    int longest = 0;
+    for (int i : want_a) longest = std::max(longest, b->seg_offsets[i + 1] - b->seg_offsets[i]);
+    const bool short_grads = !one_pass && !reuse_dh && !want_a.empty() && want_a == want_b && grad_max_rpad <= 16 && longest <= GRAD_SHORT_TOKENS && b->d_out < GRAD_WIDE &&
+                             (longest + 16) * (long long)b->d_out * 2 <= 512 << 10 && (a_blocks + b_blocks) * (long long)want_a.size() <= 256 && h->opt_skinny_deep && reads_bt(b);
     // Row chunks of the LoRA segments that want a gradient (Hs for dB, dH for dA).
     SkinnyChunks ch_h, ch_dh;
     if (!reuse_hs) ch_h = plan_skinny(h, b, want_b, grad_max_rpad);
-    if (one_pass || pair) {
+    if (short_grads) {
+    } else if (one_pass || pair) {
         for (int i : want_a)
             for (int r = b->seg_offsets[i]; r < b->seg_offsets[i + 1]; r += kSkinnyRows)
                 ch_dh.items.push_back(RowChunk{i, r, std::min(kSkinnyRows, b->seg_offsets[i + 1] - r), 0});
@@ -2173,6 +2181,14 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
         hipLaunchKernelGGL(symb_dh_finish_kernel, dim3((unsigned)ch_dh.items.size()), dim3(128), 0, s, fp);
         SYMB_HIP(h, hipGetLastError());
         have_dh = true;
+    } else if (short_grads) {
+        if (!reuse_hs && (st = run_skinny_h()) != SYMB_OK) return st;
+        const GradParams ga{(const bf16*)X, nullptr, b->d_in, 2 * bi.max_rpad, doff, dseg, (const GradItem*)(dev + o_ita), acc ? 1 : 0, seg_io ? (const bf16* const*)(dev + o_xs) : nullptr, nullptr};
+        const GradParams gb{(const bf16*)dY, (const bf16*)(wsb + wl.h_off), b->d_out, 2 * bi.max_rpad, doff, dseg, (const GradItem*)(dev + o_itb), acc ? 1 : 0,
+                            seg_io ? (const bf16* const*)(dev + o_gs) : nullptr, nullptr};
+        const int a_groups = a_blocks * (int)it_a.size();
+        hipLaunchKernelGGL(symb_lora_grad_short_kernel, dim3((unsigned)(a_groups + b_blocks * (int)it_b.size())), dim3(512), 0, s, skinny_dh(), ga, a_blocks, a_groups, gb, b_blocks);
+        SYMB_HIP(h, hipGetLastError());
     } else if (!want_b.empty()) {       // dB_i = s_i * dY_i^T H_i  ==  dY_i^T Hs_i
         if (!reuse_hs && (st = run_skinny_h()) != SYMB_OK) return st;
         GradParams gp{(const bf16*)dY, (const bf16*)(wsb + wl.h_off), b->d_out, 2 * bi.max_rpad, doff, dseg,
@@ -2191,7 +2207,7 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
         if ((st = launch_grad_reduce(h, GradReduceParams{dseg, (const GradReduceItem*)(dev + o_rdb), (const float*)(wsb + wl.gr_off), b->d_out, 1, acc ? 1 : 0},
                                      (int)red_b.size(), s)) != SYMB_OK) return st;
     }
-    if (!want_a.empty()) {       // dA_i = dH_i^T X_i
+    if (!want_a.empty() && !short_grads) {       // dA_i = dH_i^T X_i
         if (!have_dh) {
             if ((st = launch_skinny_dh(h, b, skinny_dh(), (bf16*)(wsb + wl.pk_off), (const int64_t*)(dev + o_pk), ch_dh, grad_max_rpad, s)) != SYMB_OK) return st;
         }

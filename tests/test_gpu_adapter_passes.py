@@ -2,13 +2,14 @@
 without the swizzle of ranks 64 and 128), slices and remainders of the inner dimension, launches of few and many chunks, and
 the packed copy that ranks that are no multiple of 4 still take."""
 import pytest
+import torch
 
 import gpu_harness as gh
 import oracle
 import test_gpu_parity as tp
 from helpers import assert_close, check_dx
 from paper_2507_03220_amd import binding as sb
-from test_gpu_parity import L, make_problem, oracle_ads
+from test_gpu_parity import L, N, make_problem, oracle_ads
 
 pytestmark = pytest.mark.gpu
 tp.gh, tp.sb = gh, sb                    # what its problem maker uses
@@ -81,3 +82,24 @@ def test_shrink_by_its_number_of_rows(T, ranks):
         _, Yr = oracle.forward(p["off"], oracle_ads(p["ads"]), p["X"], p["W"])
         assert_close(gh.bf16_to_f64(Y), Yr, f"Y {T} rows", out_bf16=True)
         _check(p, f"{T} rows, ranks {ranks}")
+
+
+@pytest.mark.parametrize("lens", [[1], [16], [17, 2], [32, 33], [64, 63, 0, 5], [65, 8]])                # (65: the launches of longer segments)
+@pytest.mark.parametrize("d_in,d_out,ranks", [(72, 136, [16, 4]), (264, 1096, [8, 12]), (136, 4040, [16])])
+def test_gradients_of_short_segments_in_one_launch(lens, d_in, d_out, ranks):
+    """Gradients, accumulated ones, and the input gradient on the dH that the call leaves behind."""
+    p = make_problem(sum(lens) + d_in, d_in, d_out, lens + [3], [L] * len(lens) + [N], ranks)
+    off, oads = p["off"], oracle_ads(p["ads"])
+    dev = gh.upload_adapters(p["ads"], d_in, d_out, grads=True)
+    b = sb.Batch(d_in, d_out, off, dev.descs)
+    X, dY, W = gh.to_dev(p["X"]), gh.to_dev(p["dY"]), gh.to_dev(p["W"])
+    ws = torch.empty(max(sb.symb_workspace_bytes(b, op) for op in (sb.SYMB_OP_FWD, sb.SYMB_OP_BWD_INPUT, sb.SYMB_OP_ADAPTER_GRAD)), device="cuda", dtype=torch.uint8)
+    dX = torch.full((p["T"], d_in), float("nan"), device="cuda", dtype=torch.bfloat16)
+    want = [oracle.lora_grad(off, oads, p["X"], p["dY"], i) for i in range(len(lens))]
+    for times, flags in ((1, sb.SYMB_GRAD_OVERWRITE), (2, sb.SYMB_GRAD_ACCUMULATE)):
+        sb.symb_adapter_grad(gh.handle(), b, X, dY, None, flags, ws)
+        for i, (dAr, dBr) in enumerate(want):
+            assert_close(dev.descs[i].dA.cpu().numpy(), times * dAr, f"dA[{i}]")
+            assert_close(dev.descs[i].dB.cpu().numpy(), times * dBr, f"dB[{i}]")
+    sb.symb_base_linear_bwd_input(gh.handle(), b, dY, W, dX, sb.SYMB_BWD_REUSE_DH, ws)
+    check_dx(gh.bf16_to_f64(dX), off, oads, p["dY"], p["W"], "dX")

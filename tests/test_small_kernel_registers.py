@@ -28,3 +28,9 @@ def test_lds_reads_are_untouched_until_their_wait(device_asm):  # noqa: F811
                 touched = set().union(*[_regs(t) for t in re.findall(r"v\[\d+:\d+\]|v\d+", rest)] or [set()])
                 assert not (touched & pending), (m.group(1), s)
     assert checked > 200
+
+
+def test_lds_reads_of_the_short_gradient_kernel(device_asm):  # noqa: F811
+    renamed = device_asm.replace("_ZN4symb27symb_lora_grad_short_kernel", "_ZN4symb26symb_lora_grad_wave_kernel")
+    assert renamed != device_asm
+    test_lds_reads_are_untouched_until_their_wait(renamed)
