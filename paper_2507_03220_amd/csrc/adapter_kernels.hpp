@@ -880,8 +880,9 @@ __device__ __forceinline__ void lora_grad_short(const GradParams& p, const Skinn
     const int k0 = kq * 8 + (l15 >> 2);                  // first of the two transposing reads; the second is 4 tokens further
     const unsigned roff = (unsigned)(size_t)sX + (unsigned)(k0 * CT * 2 + ((wave ^ skinny_bt_swz(CT, k0)) * 32) + (l15 & 3) * 8);
     const unsigned loff = (unsigned)(size_t)sL + (unsigned)(k0 * 64 + (l15 & 3) * 8);
-    floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+    floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};           // a sum per 32 tokens, added up: the bits of the kernel that deals them out over its wavefronts
     for (int t0 = 0; t0 < n; t0 += 32) {
+        floatx4 part = floatx4{0.f, 0.f, 0.f, 0.f};
         u32x2 rt[2], lt[2][2];
         const unsigned ra = roff + t0 * CT * 2, la = loff + t0 * 64;
         asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(rt[0]) : "v"(ra));
@@ -908,8 +909,9 @@ __device__ __forceinline__ void lora_grad_short(const GradParams& p, const Skinn
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             const bf16x8 l = __builtin_bit_cast(bf16x8, lf[half]), r = __builtin_bit_cast(bf16x8, rf);
-            acc = CMAJOR ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(l, r, acc, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_bf16(r, l, acc, 0, 0, 0);
+            part = CMAJOR ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(l, r, part, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_bf16(r, l, part, 0, 0, 0);
         }
+        acc += part;
     }
     if constexpr (CMAJOR) {                              // lane: column l15 of the wavefront's; registers: ranks 4 kq ..
         const int c = c0 + wave * 16 + l15;

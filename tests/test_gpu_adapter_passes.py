@@ -103,3 +103,7 @@ def test_gradients_of_short_segments_in_one_launch(lens, d_in, d_out, ranks):
             assert_close(dev.descs[i].dB.cpu().numpy(), times * dBr, f"dB[{i}]")
     sb.symb_base_linear_bwd_input(gh.handle(), b, dY, W, dX, sb.SYMB_BWD_REUSE_DH, ws)
     check_dx(gh.bf16_to_f64(dX), off, oads, p["dY"], p["W"], "dX")
+    sb.symb_adapter_grad(gh.handle(), b, X, dY, None, sb.SYMB_GRAD_OVERWRITE, ws)
+    once = [(d.dA.clone(), d.dB.clone()) for d in dev.descs[:len(lens)]]
+    sb.symb_adapter_grad(gh.handle(), b, X, dY, None, sb.SYMB_GRAD_OVERWRITE | sb.SYMB_GRAD_REUSE_DH | sb.SYMB_GRAD_REUSE_HS, ws)        # the two launches: the same bits
+    assert all(torch.equal(x, d.dA) and torch.equal(y, d.dB) for (x, y), d in zip(once, dev.descs))
