@@ -17,6 +17,7 @@
 
 #include "adapter_kernels.hpp"
 #include "gemm16_kernel.hpp"
+#include "narrow_kernel.hpp"
 #include "small_kernels.hpp"
 
 using namespace symb;
@@ -44,6 +45,7 @@ constexpr size_t kSlotBytes = (size_t)2 << 20;  // capacity of one descriptor bl
 constexpr int kSkinnyRows = SKINNY_ROWS;        // rows per skinny / scale work item
 constexpr int kStreams = 4, kSealCalls = 8;     // streams whose calls share events, calls per event while there is one such stream (seal_slot)
 constexpr int kMaxTimed = 4096;                 // GEMM launches recorded between two timing reads
+constexpr int kTimedNarrow = 32;                // symb_gemm_narrow_kernel's number in the measurement hook
 constexpr int kXccProbeGroups = 2048;           // workgroups of the XCD-rule measurement (8 rounds of 256)
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -1226,6 +1228,40 @@ symb_status run_small(symb_handle h, const symb_batch* b, const BatchInfo& bi, c
     return seal_slot(h, s);
 }
 
+// The forward of a narrow layer in one launch, shrink included (narrow_kernel.hpp): its chunks of rows, none if the call is not one for it.  One column tile
+// (N <= 256, above 128: half of it), stages of 64 k without a remainder, ranks to 16; one round of workgroups that is 60 % full, or more that are 85 %.  Two launches / this, us, 8 clients of ranks 8 and
+// 16, 256 columns: 9900 rows (62 % of a round) of K = 512 17.9 / 13.0, 2048 36.6 / 29.6, 6144 90.9 / 81.2, 11008 143 / 137; 13000 rows 18.8 / 13.5, 36.5 / 30.9, 106 / 84, 174 / 140; 20000 (62 % of two)
+// 23.9 / 23.7, 52.1 / 59.2, 146 / 160, 284 / 268; 30000 (92 %) 27.2 / 25.0, 67.1 / 63.9, 179 / 165, 317 / 281.
+std::vector<RowChunk> narrow_chunks(const symb_batch* b, const BatchInfo& bi) {
+    std::vector<RowChunk> v;
+    if (b->weight_layout != SYMB_WEIGHT_LINEAR || !bi.n_lora || bi.n_ia3in || bi.max_rpad > 16 || b->d_out <= NARROW_COLS / 2 || b->d_out > NARROW_COLS || b->d_in % 64 || bi.S > 4096) return v;
+    long n = 0;
+    for (int i = 0; i < bi.S; ++i) n += (b->seg_offsets[i + 1] - b->seg_offsets[i] + NARROW_ROWS - 1) / NARROW_ROWS;
+    if (n <= 256 ? 10 * n < 6 * 256 : 20 * n < 17 * 256 * ((n + 255) / 256)) return v;
+    plan_chunks(b, NARROW_ROWS, -1, v);
+    return v;
+}
+symb_status run_narrow(symb_handle h, const symb_batch* b, const BatchInfo& bi, const std::vector<RowChunk>& chunks, const void* X, const void* W, const void* bias, void* Y, bf16* h_rows, hipStream_t s) {
+    symb_status st;
+    const std::vector<SegDesc> sd = make_segdesc(b);
+    Blob blob;
+    const size_t o_seg = blob.add(sd.data(), sd.size());
+    const size_t o_ch = blob.add(chunks.data(), chunks.size());
+    unsigned char* dev = nullptr;
+    if ((st = upload(h, blob, s, &dev)) != SYMB_OK) return st;
+    const NarrowParams np{(const bf16*)X, (const bf16*)W, (const bf16*)bias, (bf16*)Y, h_rows, b->d_out, b->d_in, 2 * bi.max_rpad, (const RowChunk*)(dev + o_ch), (const SegDesc*)(dev + o_seg)};
+    const bool timed = h->timing && (int)h->timed.size() < kMaxTimed;
+    const size_t slot = h->timed.size();
+    if (timed) SYMB_HIP(h, hipEventRecord(h->tev[2 * slot], s));
+    hipLaunchKernelGGL(symb_gemm_narrow_kernel, dim3((unsigned)chunks.size()), dim3(256), 0, s, np);
+    SYMB_HIP(h, hipGetLastError());
+    if (timed) {
+        SYMB_HIP(h, hipEventRecord(h->tev[2 * slot + 1], s));
+        h->timed.push_back({kTimedNarrow, gemm_flops(b, sd, b->d_out, b->d_in, true)});
+    }
+    return seal_slot(h, s);
+}
+
 symb_status check_handle(symb_handle h) {
     if (!h) return fail(nullptr, SYMB_ERR_INVALID_ARG, "handle is null");
     if (hipSetDevice(h->device) != hipSuccess) return fail(h, SYMB_ERR_DEVICE, "hipSetDevice(%d) failed", h->device);
@@ -1358,7 +1394,8 @@ symb_status symb_debug_gemm_timing_read(symb_handle h, int32_t variant, double* 
     *launches = 0;
     *flops_total = 0.0;
     for (size_t i = 0; i < h->timed.size(); ++i) {
-        if ((variant >= 8 ? h->timed[i].variant : h->timed[i].variant & 7) != variant) continue;
+        const int v = h->timed[i].variant;
+        if ((variant >= 8 || v >= kTimedNarrow ? v : v & 7) != variant) continue;
         SYMB_HIP(h, hipEventSynchronize(h->tev[2 * i + 1]));
         float ms = 0.f;
         SYMB_HIP(h, hipEventElapsedTime(&ms, h->tev[2 * i], h->tev[2 * i + 1]));
@@ -1530,6 +1567,14 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
         return SYMB_OK;
     }
 
+    if (!seg_io && nd.empty() && !Ybase) {
+        const std::vector<RowChunk> chunks = narrow_chunks(b, bi);
+        if (!chunks.empty()) {
+            if ((st = run_narrow(h, b, bi, chunks, X, W, bias, Y, (bf16*)((unsigned char*)ws + wl.h_off), s)) != SYMB_OK) return st;
+            guard.completed = true;
+            return SYMB_OK;
+        }
+    }
     GemmPlan plan = gemm_plan(b, b->d_out, b->d_in, b->weight_layout == SYMB_WEIGHT_CONV1D, bi.n_lora > 0, Ybase != nullptr, !Ybase && h->opt_k_split && h->xcd_rule,
                               ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
     const bool k_split = plan.split.parts > 1 && plan.variant != kTileMid;
