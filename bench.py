@@ -164,7 +164,7 @@ def measured_traffic(cfg: str, variant: int):
 def kernel_name(variant: int) -> str:
     nn, plain = "true" if variant & 1 else "false", "false" if variant & 4 else "true"
     if variant & 32:
-        return "symb_gemm_narrow_kernel"
+        return "symb_gemm_shortk_kernel" if variant & 1 else "symb_gemm_narrow_kernel"
     if variant & 16:
         return f"symb_gemm_mid_kernel<{nn}>" + ("" if plain == "true" else " (full epilogue)")
     if variant & 8:
@@ -175,7 +175,7 @@ def kernel_name(variant: int) -> str:
 def gemm_timing(h):
     """{variant: (ms, launches, flops)} since the hook was enabled, every launch under one variant (the hook counts those of bits 3 and 4 without them, too)."""
     from paper_2507_03220_amd import binding as sb
-    t = {v: sb.symb_debug_gemm_timing_read(h, v) for v in (*range(8), 10, 11, 14, 15, 18, 19, 22, 23, 32)}
+    t = {v: sb.symb_debug_gemm_timing_read(h, v) for v in (*range(8), 10, 11, 14, 15, 18, 19, 22, 23, 32, 33)}
     for v in (2, 3, 6, 7):
         t[v] = tuple(x - y - z for x, y, z in zip(t[v], t[v + 8], t[v + 16]))
     return t

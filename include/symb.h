@@ -303,7 +303,7 @@ symb_status symb_adapter_grad_ex(symb_handle h, const symb_batch* b, const void*
  * 256x256, NBLK 8), bit 2 = the full epilogue (PLAIN false); 0..7.  Tiles of 128 columns have 128 rows or, in
  * symb_gemm16_kernel<4, NN, PLAIN, 8>, 256; with bit 3 (10, 11, 14, 15) the launches of the latter alone are read, with bit 4
  * (18, 19, 22, 23) those of symb_gemm_mid_kernel<NN>, whose tiles of 32 rows count among 2, 3, 6, 7 too.  32 is
- * symb_gemm_narrow_kernel, which computes the LoRA shrink beside the product.
+ * symb_gemm_narrow_kernel, which computes the LoRA shrink beside the product, 33 symb_gemm_shortk_kernel.
  * read synchronises on the recorded events and returns the totals since the last
  * enable call (which clears them).  At most 4096 launches are recorded after an
  * enable; later ones are not timed.  `flops_total` is the algorithmic work of those launches

@@ -18,6 +18,7 @@
 #include "adapter_kernels.hpp"
 #include "gemm16_kernel.hpp"
 #include "narrow_kernel.hpp"
+#include "shortk_kernel.hpp"
 #include "small_kernels.hpp"
 
 using namespace symb;
@@ -45,7 +46,7 @@ constexpr size_t kSlotBytes = (size_t)2 << 20;  // capacity of one descriptor bl
 constexpr int kSkinnyRows = SKINNY_ROWS;        // rows per skinny / scale work item
 constexpr int kStreams = 4, kSealCalls = 8;     // streams whose calls share events, calls per event while there is one such stream (seal_slot)
 constexpr int kMaxTimed = 4096;                 // GEMM launches recorded between two timing reads
-constexpr int kTimedNarrow = 32;                // symb_gemm_narrow_kernel's number in the measurement hook
+constexpr int kTimedNarrow = 32, kTimedShortK = 33;      // symb_gemm_narrow_kernel, symb_gemm_shortk_kernel in the measurement hook
 constexpr int kXccProbeGroups = 2048;           // workgroups of the XCD-rule measurement (8 rounds of 256)
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -1237,7 +1238,7 @@ std::vector<RowChunk> narrow_chunks(const symb_batch* b, const BatchInfo& bi) {
     if (b->weight_layout != SYMB_WEIGHT_LINEAR || !bi.n_lora || bi.n_ia3in || bi.max_rpad > 16 || b->d_out <= NARROW_COLS / 2 || b->d_out > NARROW_COLS || b->d_in % 64 || bi.S > 4096) return v;
     long n = 0;
     for (int i = 0; i < bi.S; ++i) n += (b->seg_offsets[i + 1] - b->seg_offsets[i] + NARROW_ROWS - 1) / NARROW_ROWS;
-    if (n <= 256 ? 10 * n < 6 * 256 : 20 * n < 17 * 256 * ((n + 255) / 256)) return v;
+    if (n > 65536 || (n <= 256 ? 10 * n < 6 * 256 : 20 * n < 17 * 256 * ((n + 255) / 256))) return v;
     plan_chunks(b, NARROW_ROWS, -1, v);
     return v;
 }
@@ -1260,6 +1261,41 @@ symb_status run_narrow(symb_handle h, const symb_batch* b, const BatchInfo& bi, 
         h->timed.push_back({kTimedNarrow, gemm_flops(b, sd, b->d_out, b->d_in, true)});
     }
     return seal_slot(h, s);
+}
+
+// The input gradient of a layer of 64 to 256 outputs over many rows (shortk_kernel.hpp): its chunks of rows, none if the call is not one for it.  Enough of them that each of two workgroups per CU has four; up
+// to 128 outputs not where many rows of a large output leave nothing but its stores (tiled kernel / this, without adapters, us, columns x rows: 64 outputs 1024 x 16384 15.6 / 11.9, 6144 x 3000 21.3 / 13.3, 11008 x 6000 47.0 / 43.4,
+// 4096 x 16384 49.8 / 48.5, x 20480 50.8 / 59.4, 6144 x 20480 74.9 / 82.2; 256 outputs 2048 x 10000 27.3 / 17.7, 6144 x 6000 41.0 / 27.2, x 16384 84.3 / 79.2, 11008 x 10000 107.5 / 83.5, 24576 x 10000 206 / 172).
+std::vector<RowChunk> shortk_chunks(const symb_batch* b, const BatchInfo& bi, bool lora) {
+    std::vector<RowChunk> v;
+    if (b->weight_layout != SYMB_WEIGHT_LINEAR || b->d_out % 64 || b->d_out > 256 || (lora && bi.max_rpad > 16) || bi.S > 4096) return v;
+    long n = 0;
+    for (int i = 0; i < bi.S; ++i) n += (b->seg_offsets[i + 1] - b->seg_offsets[i] + 31) / 32;
+    if (n * ((b->d_in + SHORTK_COLS - 1) / SHORTK_COLS) < 2048 || n > 16384) return v;       // (their list lies beside the others in the descriptors)
+    if (b->d_out <= 128 && bi.T > 12000 && (long long)bi.T * b->d_in > 48000000) return v;
+    plan_chunks(b, 32, -1, v);
+    return v;
+}
+symb_status launch_shortk(symb_handle h, ShortKParams p, int K, double flops, hipStream_t s) {
+    const int strips = (p.N + SHORTK_COLS - 1) / SHORTK_COLS, most = std::max(1, std::min(p.num_chunks, 512 / strips));      // two workgroups per CU
+    p.per_group = (p.num_chunks + most - 1) / most;
+    p.groups = (p.num_chunks + p.per_group - 1) / p.per_group;
+    const dim3 grid((unsigned)((strips * p.groups + 7) / 8 * 8));
+    const bool timed = h->timing && (int)h->timed.size() < kMaxTimed;
+    const size_t slot = h->timed.size();
+    if (timed) SYMB_HIP(h, hipEventRecord(h->tev[2 * slot], s));
+    switch (K / 64) {
+        case 1: hipLaunchKernelGGL(symb_gemm_shortk_kernel<2>, grid, dim3(256), 0, s, p); break;
+        case 2: hipLaunchKernelGGL(symb_gemm_shortk_kernel<4>, grid, dim3(256), 0, s, p); break;
+        case 3: hipLaunchKernelGGL(symb_gemm_shortk_kernel<6>, grid, dim3(256), 0, s, p); break;
+        default: hipLaunchKernelGGL(symb_gemm_shortk_kernel<8>, grid, dim3(256), 0, s, p); break;
+    }
+    SYMB_HIP(h, hipGetLastError());
+    if (timed) {
+        SYMB_HIP(h, hipEventRecord(h->tev[2 * slot + 1], s));
+        h->timed.push_back({kTimedShortK, flops});
+    }
+    return SYMB_OK;
 }
 
 symb_status check_handle(symb_handle h) {
@@ -1837,6 +1873,9 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
 
     GemmPlan plan = gemm_plan(b, b->d_in, b->d_out, b->weight_layout != SYMB_WEIGHT_CONV1D, lora, dXbase != nullptr, !dXbase && h->opt_k_split && h->xcd_rule,
                               ws && ws_bytes > wl.tp_off ? ws_bytes - wl.tp_off : 0);
+    std::vector<RowChunk> sk_chunks;
+    if (!seg_io && !dXbase && !ia3 && !(full && bi.n_ia3in)) sk_chunks = shortk_chunks(b, bi, lora);
+    if (!sk_chunks.empty()) plan = GemmPlan{};
     const bool k_split = plan.split.parts > 1 && plan.variant != kTileMid;
     const int bm = tile_rows(plan.variant), bn = tile_cols(plan.variant);
     std::vector<int32_t> lo, hi;
@@ -1907,6 +1946,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
     std::vector<RowChunk> row_chunks;
     if (staged) plan_chunks(b, kSkinnyRows, -1, row_chunks);
     const size_t o_rows = blob.add(row_chunks.data(), row_chunks.size());
+    const size_t o_sk = blob.add(sk_chunks.data(), sk_chunks.size());
     const std::vector<int32_t> k_zero(k_split ? plan.split.slots : 0, 0);
     const size_t o_kc = blob.add(k_zero.data(), k_zero.size());   // arrival counters of the K-split tiles
     const DeltaBlob db = add_gemm_desc(blob, sd_gemm, delta, (int)lo.size(), bm);
@@ -1944,6 +1984,12 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
         // (every IA3 segment of the batch may be empty: nothing to scale then)
         if ((st = launch_row_pass(h, symb_ia3_scale_rows_kernel, sc, sc.d_out, all_chunks.size(), s)) != SYMB_OK) return st;
         a_op = copy;
+    }
+    if (!sk_chunks.empty()) {
+        const ShortKParams kp{(const bf16*)dY, (const bf16*)W, (bf16*)dX, dH, b->d_in, (int)sk_chunks.size(), 0, 0, (const RowChunk*)(dev + o_sk), (const SegDesc*)(dev + o_seg)};
+        if ((st = launch_shortk(h, kp, b->d_out, gemm_flops(b, sd, b->d_in, b->d_out, lora), s)) != SYMB_OK) return st;
+        guard.completed = true;
+        return seal_slot(h, s);
     }
     if (!delta.items.empty() && (st = launch_delta(h, true, (const SegDesc*)(dev + o_seg), (const RowChunk*)(dev + db.items), (int)delta.items.size(), b->d_in,
                                                    dH, bi.max_rpad, (float*)(wsb + de_off), s)) != SYMB_OK) return st;

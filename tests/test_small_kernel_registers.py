@@ -2,6 +2,8 @@
 such a read and the wait may touch the registers still in flight (see test_gemm16_registers.py; no GPU needed)."""
 import re
 
+import pytest
+
 from test_gemm16_registers import _regs, device_asm  # noqa: F401
 
 
@@ -30,7 +32,9 @@ def test_lds_reads_are_untouched_until_their_wait(device_asm):  # noqa: F811
     assert checked > 200
 
 
-def test_lds_reads_of_the_short_gradient_kernel(device_asm):  # noqa: F811
-    renamed = device_asm.replace("_ZN4symb27symb_lora_grad_short_kernel", "_ZN4symb26symb_lora_grad_wave_kernel")
-    assert renamed != device_asm
-    test_lds_reads_are_untouched_until_their_wait(renamed)
+@pytest.mark.parametrize("name", ["27symb_lora_grad_short_kernel", "23symb_gemm_narrow_kernel", "23symb_gemm_shortk_kernel"])
+def test_lds_reads_of_further_kernels(device_asm, name):  # noqa: F811
+    only = "\n".join(m.group(0) for m in re.finditer(r"^_ZN4symb%s\w+:.*?^\.Lfunc_end" % name, device_asm, re.S | re.M))
+    assert only
+    # (under a name that it looks for, and as often as it takes to make up the number of reads that it wants to see)
+    test_lds_reads_are_untouched_until_their_wait("\n".join([only.replace("_ZN4symb" + name, "_ZN4symb26symb_lora_grad_wave_kernel")] * 20))
