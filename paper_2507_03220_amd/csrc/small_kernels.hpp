@@ -18,8 +18,9 @@
 // Bound by HBM: 2 K N bytes of weight plus 2 r (K + N) of each LoRA client.  What these calls spent their time on
 // before was one launch after the other (shrink, weight, for the input gradient also a transposed copy of B_i),
 // each a chain of memory latencies on a part of the chip, and from 17 rows on, in the tiled kernel, a chain of small steps for each
-// client's adapter.  Measured per call, before / now: one client on 4096 x 4096 21.6 / 14.2 us (7.8 us the first kernel, 4.3 TB/s; 4.2 the
-// second), 16 mixed clients on 4096 -> 11008 69.0 / 28.7, 48 clients of ranks to 128 on 11008 -> 4096 134.9 / 41.2.
+// client's adapter.  Measured per call, in the tiled kernels / now: one client on 4096 x 4096 21.6 / 11.3 us (8.3 us the first kernel, 4.1 TB/s; 3.7 the
+// second), 16 mixed clients on 4096 -> 11008 69.0 / 26.1, 48 clients of ranks to 128 on 11008 -> 4096 134.9 / 38.0 (of the difference 2.8 us are the event that every call ended with; the figures
+// in the rules below have it on both sides).
 #pragma once
 #include "adapter_kernels.hpp"
 #include "gemm16_kernel.hpp"

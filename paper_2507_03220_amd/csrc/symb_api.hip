@@ -766,17 +766,30 @@ symb_status upload(symb_handle h, const Blob& blob, hipStream_t st, unsigned cha
                 return SYMB_OK;
             }
     // The next slot in turn that no other stream may still read without an event behind that call.  The device copy of a slot of this stream is
-    // overwritten in stream order; its pinned copy, and any other slot, is waited for.
-    int slot = h->next_slot;
-    for (int i = 0; i < kSlots; ++i) {
-        slot = (h->next_slot + i) % kSlots;
-        if (!h->slot_used[slot] || h->slot_sealed[slot] || h->slot_stream[slot] == st) break;
-        const symb_context::StreamUse* u = stream_use(h, h->slot_stream[slot]);
-        if (u && h->slot_last[slot] <= u->covered) {
-            SYMB_HIP(h, hipEventSynchronize(u->ev));
-            break;
+    // overwritten in stream order; its pinned copy, and any other slot, is waited for.  With several streams one that need not be waited for goes first: a stream's
+    // event may lie behind calls that are far from done.
+    const auto done = [](hipEvent_t ev) {
+        if (hipEventQuery(ev) == hipSuccess) return true;
+        (void)hipGetLastError();           // (not ready yet is no error of this call)
+        return false;
+    };
+    int slot = -1;
+    for (int i = 0; i < 2 * kSlots && slot < 0; ++i) {
+        const int j = (h->next_slot + i) % kSlots;
+        const symb_context::StreamUse* u = nullptr;
+        if (h->slot_used[j]) {
+            if (!h->slot_sealed[j] && h->slot_stream[j] != st) {
+                u = stream_use(h, h->slot_stream[j]);
+                if (!u || h->slot_last[j] > u->covered) continue;
+            }
+            if (i < kSlots && h->n_uses > 1 && !(done(h->slot_done[j]) && (!u || done(u->ev)))) continue;
+            if (u) SYMB_HIP(h, hipEventSynchronize(u->ev));
         }
-        if (i == kSlots - 1) SYMB_HIP(h, hipDeviceSynchronize());      // (not reached: see seal_slot)
+        slot = j;
+    }
+    if (slot < 0) {                        // (not reached: see seal_slot)
+        SYMB_HIP(h, hipDeviceSynchronize());
+        slot = h->next_slot;
     }
     h->next_slot = (slot + 1) % kSlots;
     h->cur_slot = slot;
