@@ -44,7 +44,7 @@ thread_local std::string g_tls_error;
 constexpr int kSlots = 32;                      // descriptor ring depth (a training step of 7 projections makes 21 different blobs)
 constexpr size_t kSlotBytes = (size_t)2 << 20;  // capacity of one descriptor blob
 constexpr int kSkinnyRows = SKINNY_ROWS;        // rows per skinny / scale work item
-constexpr int kStreams = 4, kSealCalls = 8;     // streams whose calls share events, calls per event while there is one such stream (seal_slot)
+constexpr int kStreams = 2, kSealCalls = 8;     // streams whose calls share events, calls per event while there is one such stream (seal_slot)
 constexpr int kMaxTimed = 4096;                 // GEMM launches recorded between two timing reads
 constexpr int kTimedNarrow = 32, kTimedShortK = 33;      // symb_gemm_narrow_kernel, symb_gemm_shortk_kernel in the measurement hook
 constexpr int kXccProbeGroups = 2048;           // workgroups of the XCD-rule measurement (8 rounds of 256)
@@ -766,8 +766,8 @@ symb_status upload(symb_handle h, const Blob& blob, hipStream_t st, unsigned cha
                 return SYMB_OK;
             }
     // The next slot in turn that no other stream may still read without an event behind that call.  The device copy of a slot of this stream is
-    // overwritten in stream order; its pinned copy, and any other slot, is waited for.  With several streams one that need not be waited for goes first: a stream's
-    // event may lie behind calls that are far from done.
+    // overwritten in stream order; its pinned copy, and any other slot, is waited for.  A slot that hangs on another stream's event goes first only if that has come, as it may lie behind
+    // calls that are far from done; one used in the last eight calls only if there is no other, so that a stream that comes to the ring gets a share of it.
     const auto done = [](hipEvent_t ev) {
         if (hipEventQuery(ev) == hipSuccess) return true;
         (void)hipGetLastError();           // (not ready yet is no error of this call)
@@ -782,7 +782,7 @@ symb_status upload(symb_handle h, const Blob& blob, hipStream_t st, unsigned cha
                 u = stream_use(h, h->slot_stream[j]);
                 if (!u || h->slot_last[j] > u->covered) continue;
             }
-            if (i < kSlots && h->n_uses > 1 && !(done(h->slot_done[j]) && (!u || done(u->ev)))) continue;
+            if (i < kSlots && (h->slot_last[j] + 8 > h->seq || (u && !done(u->ev)))) continue;
             if (u) SYMB_HIP(h, hipEventSynchronize(u->ev));
         }
         slot = j;
@@ -826,8 +826,8 @@ struct CallGuard {
 
 // Ends a call: its slot is busy until everything enqueued so far on `st` has run (kernels read it).  An event costs 2.8 us on the stream, a quarter of a small call (one user's decode
 // step on 4096 x 4096 14.1 -> 11.3 us without, a training step of 16 rows 42.1 -> 33.8), and what it guards against, the slot's next batch, is in stream order for this
-// stream.  So only every kSealCalls-th call of a stream records one, which covers all before it; with more streams more often.  A slot
-// that another stream still reads without an event behind it is passed over (upload): at most 7 + 3 + 1 + 1 of them for the kStreams streams that
+// stream.  So only every kSealCalls-th call of a stream records one, which covers all before it; with two streams every fourth.  A slot
+// that another stream still reads without an event behind it is passed over (upload): at most 7 + 3 of them for the kStreams streams that
 // share events, whatever becomes of those.  Calls of further streams, and calls under capture, record the slot's own event, as all calls did.
 symb_status seal_slot(symb_handle h, hipStream_t st) {
     symb_context::StreamUse* u = stream_use(h, st);
