@@ -20,6 +20,7 @@
 #include "narrow_kernel.hpp"
 #include "shortk_kernel.hpp"
 #include "small_kernels.hpp"
+#include "symb_ring.hpp"
 
 using namespace symb;
 
@@ -41,10 +42,8 @@ namespace {
 
 thread_local std::string g_tls_error;
 
-constexpr int kSlots = 32;                      // descriptor ring depth (a training step of 7 projections makes 21 different blobs)
 constexpr size_t kSlotBytes = (size_t)2 << 20;  // capacity of one descriptor blob
 constexpr int kSkinnyRows = SKINNY_ROWS;        // rows per skinny / scale work item
-constexpr int kStreams = 2, kSealCalls = 8;     // streams whose calls share events, calls per event while there is one such stream (seal_slot)
 constexpr int kMaxTimed = 4096;                 // GEMM launches recorded between two timing reads
 constexpr int kTimedNarrow = 32, kTimedShortK = 33;      // symb_gemm_narrow_kernel, symb_gemm_shortk_kernel in the measurement hook
 constexpr int kXccProbeGroups = 2048;           // workgroups of the XCD-rule measurement (8 rounds of 256)
@@ -52,29 +51,35 @@ constexpr int kXccProbeGroups = 2048;           // workgroups of the XCD-rule me
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline int rpad_of(int r) { return (r + 15) / 16 * 16; }
 
+struct HipRuntime {                             // what the descriptor ring asks of HIP
+    using Stream = hipStream_t;
+    using Event = hipEvent_t;
+    using Status = hipError_t;
+    static Status record(Event ev, Stream st) { return hipEventRecord(ev, st); }
+    static Status wait(Event ev) { return hipEventSynchronize(ev); }
+    static Status wait_all() { return hipDeviceSynchronize(); }
+    static bool done(Event ev) {
+        if (hipEventQuery(ev) == hipSuccess) return true;
+        (void)hipGetLastError();                // (not ready yet is no error of this call)
+        return false;
+    }
+    static bool capturing(Stream st) {
+        hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+        (void)hipGetLastError();                // (the default stream beside a capture)
+        return true;
+    }
+};
+constexpr int kSlots = DescRing<HipRuntime>::kSlots;
+
 }  // namespace
 
 struct symb_context {
     int device = 0;
     unsigned char* host_ring = nullptr;   // pinned, kSlots * kSlotBytes
     unsigned char* dev_ring = nullptr;    // device, kSlots * kSlotBytes
-    hipEvent_t slot_done[kSlots] = {};    // recorded behind the slot's copy and, if slot_sealed, behind its last call
-    bool slot_used[kSlots] = {}, slot_sealed[kSlots] = {};
-    uint64_t seq = 0, slot_last[kSlots] = {};           // calls so far; the last one that read the slot
-    struct StreamUse {
-        hipStream_t stream;
-        hipEvent_t ev;                    // recorded behind call number `covered` or a later one of the stream
-        uint64_t covered;
-        int since;                        // calls since
-    } uses[kStreams] = {};
-    int n_uses = 0;
-    int next_slot = 0;                    // the slot the next new blob goes to (round robin)
-    int cur_slot = 0;                     // the slot this call's kernels read
-    // what each slot's device copy holds: a call whose blob is already there (same bytes, copied on
-    // the same stream) reads that copy instead of sending the bytes again
-    size_t slot_size[kSlots] = {};
-    uint64_t slot_hash[kSlots] = {};
-    hipStream_t slot_stream[kSlots] = {};
+    DescRing<HipRuntime> ring;
+    HipRuntime rt;
     int64_t desc_sent = 0, desc_in_place = 0;
     int call_slot = -1;                   // the slot this call's descriptors went to (-1: none yet)
     std::string error;
@@ -727,12 +732,6 @@ DeltaBlob add_gemm_desc(Blob& blob, std::vector<SegDesc>& sd_gemm, DeltaPlan& de
     return d;
 }
 
-symb_context::StreamUse* stream_use(symb_handle h, hipStream_t st) {
-    for (int i = 0; i < h->n_uses; ++i)
-        if (h->uses[i].stream == st) return &h->uses[i];
-    return nullptr;
-}
-
 symb_status upload(symb_handle h, const Blob& blob, hipStream_t st, unsigned char** dev_base) {
     if (blob.bytes.size() > kSlotBytes)
         return fail(h, SYMB_ERR_UNSUPPORTED, "batch descriptors need %zu bytes, capacity is %zu", blob.bytes.size(), kSlotBytes);
@@ -740,7 +739,6 @@ symb_status upload(symb_handle h, const Blob& blob, hipStream_t st, unsigned cha
     // a launch ends), so a batch that comes again with the same offsets, adapters and buffers -- the
     // next decode step of the same clients, the same projection in the next training step -- finds
     // its descriptors in place.  The pinned copy of a slot is what its device copy holds.
-    const bool reuse = h->opt_desc_reuse;
     const size_t n = blob.bytes.size();
     uint64_t hash = 0x9E3779B97F4A7C15ull ^ n;
     {
@@ -753,61 +751,21 @@ symb_status upload(symb_handle h, const Blob& blob, hipStream_t st, unsigned cha
         }
         for (; i < n; ++i) hash = (hash ^ blob.bytes[i]) * 0x100000001B3ull;
     }
-    if (reuse)
-        for (int j = 0; j < kSlots; ++j)
-            if (h->slot_used[j] && h->slot_size[j] == n && h->slot_hash[j] == hash && h->slot_stream[j] == st &&
-                memcmp(h->host_ring + (size_t)j * kSlotBytes, blob.bytes.data(), n) == 0) {
-                h->slot_last[j] = ++h->seq;
-                h->slot_sealed[j] = false;
-                h->cur_slot = j;
-                h->call_slot = j;
-                ++h->desc_in_place;
-                *dev_base = h->dev_ring + (size_t)j * kSlotBytes;
-                return SYMB_OK;
-            }
-    // The next slot in turn that no other stream may still read without an event behind that call.  The device copy of a slot of this stream is
-    // overwritten in stream order; its pinned copy, and any other slot, is waited for.  A slot that hangs on another stream's event goes first only if that has come, as it may lie behind
-    // calls that are far from done; one used in the last eight calls only if there is no other, so that a stream that comes to the ring gets a share of it.
-    const auto done = [](hipEvent_t ev) {
-        if (hipEventQuery(ev) == hipSuccess) return true;
-        (void)hipGetLastError();           // (not ready yet is no error of this call)
-        return false;
-    };
-    int slot = -1;
-    for (int i = 0; i < 2 * kSlots && slot < 0; ++i) {
-        const int j = (h->next_slot + i) % kSlots;
-        const symb_context::StreamUse* u = nullptr;
-        if (h->slot_used[j]) {
-            if (!h->slot_sealed[j] && h->slot_stream[j] != st) {
-                u = stream_use(h, h->slot_stream[j]);
-                if (!u || h->slot_last[j] > u->covered) continue;
-            }
-            if (i < kSlots && (h->slot_last[j] + 8 > h->seq || (u && !done(u->ev)))) continue;
-            if (u) SYMB_HIP(h, hipEventSynchronize(u->ev));
-        }
-        slot = j;
+    const int in_place = h->opt_desc_reuse ? h->ring.find(st, n, hash, [&](int j) { return memcmp(h->host_ring + (size_t)j * kSlotBytes, blob.bytes.data(), n) == 0; }) : -1;
+    if (in_place >= 0) {
+        h->call_slot = in_place;
+        ++h->desc_in_place;
+        *dev_base = h->dev_ring + (size_t)in_place * kSlotBytes;
+        return SYMB_OK;
     }
-    if (slot < 0) {                        // (not reached: see seal_slot)
-        SYMB_HIP(h, hipDeviceSynchronize());
-        slot = h->next_slot;
-    }
-    h->next_slot = (slot + 1) % kSlots;
-    h->cur_slot = slot;
-    h->call_slot = slot;
-    if (h->slot_used[slot]) SYMB_HIP(h, hipEventSynchronize(h->slot_done[slot]));
-    h->slot_used[slot] = false;            // until the copy is enqueued, the slot holds nothing a later call may reuse
+    SYMB_HIP(h, h->ring.take(h->rt, st));
+    const int slot = h->call_slot = h->ring.cur;
     unsigned char* hp = h->host_ring + (size_t)slot * kSlotBytes;
     unsigned char* dp = h->dev_ring + (size_t)slot * kSlotBytes;
     memcpy(hp, blob.bytes.data(), n);
     SYMB_HIP(h, hipMemcpyAsync(dp, hp, n, hipMemcpyHostToDevice, st));
     ++h->desc_sent;
-    h->slot_size[slot] = n;
-    h->slot_hash[slot] = hash;
-    h->slot_stream[slot] = st;
-    h->slot_used[slot] = true;
-    h->slot_sealed[slot] = false;
-    h->slot_last[slot] = ++h->seq;
-    SYMB_HIP(h, hipEventRecord(h->slot_done[slot], st));   // a call that fails before its kernels still leaves the slot guarded
+    SYMB_HIP(h, h->ring.sent(h->rt, st, n, hash));
     *dev_base = dp;
     return SYMB_OK;
 }
@@ -820,45 +778,12 @@ struct CallGuard {
     bool completed = false;
     explicit CallGuard(symb_handle h_) : h(h_) { h->call_slot = -1; }
     ~CallGuard() {
-        if (!completed && h->call_slot >= 0) h->slot_size[h->call_slot] = SIZE_MAX;
+        if (!completed && h->call_slot >= 0) h->ring.slot[h->call_slot].size = SIZE_MAX;
     }
 };
 
-// Ends a call: its slot is busy until everything enqueued so far on `st` has run (kernels read it).  An event costs 2.8 us on the stream, a quarter of a small call (one user's decode
-// step on 4096 x 4096 14.1 -> 11.3 us without, a training step of 16 rows 42.1 -> 33.8), and what it guards against, the slot's next batch, is in stream order for this
-// stream.  So only every kSealCalls-th call of a stream records one, which covers all before it; with two streams every fourth.  A slot
-// that another stream still reads without an event behind it is passed over (upload): at most 7 + 3 of them for the kStreams streams that
-// share events, whatever becomes of those.  Calls of further streams, and calls under capture, record the slot's own event, as all calls did.
 symb_status seal_slot(symb_handle h, hipStream_t st) {
-    symb_context::StreamUse* u = stream_use(h, st);
-    const auto held = [&](int i) {
-        for (int j = 0; i < h->n_uses && j < kSlots; ++j)
-            if (h->slot_used[j] && h->slot_stream[j] == h->uses[i].stream) return true;
-        return false;
-    };
-    for (int i = 0; i < kStreams && !u; ++i) {           // a place in the table: a free one, or one whose stream has no slot left
-        if (held(i)) continue;
-        u = &h->uses[i];
-        h->n_uses = std::max(h->n_uses, i + 1);
-        u->stream = st;
-        u->covered = 0;
-        u->since = 0;
-    }
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (u && hipStreamIsCapturing(st, &capture) != hipSuccess) {        // (the default stream beside a capture)
-        (void)hipGetLastError();
-        capture = hipStreamCaptureStatusActive;
-    }
-    if (!u || capture != hipStreamCaptureStatusNone) {
-        SYMB_HIP(h, hipEventRecord(h->slot_done[h->cur_slot], st));
-        h->slot_sealed[h->cur_slot] = true;
-        return SYMB_OK;
-    }
-    if (++u->since >= kSealCalls / h->n_uses) {
-        SYMB_HIP(h, hipEventRecord(u->ev, st));
-        u->covered = h->seq;
-        u->since = 0;
-    }
+    SYMB_HIP(h, h->ring.seal(h->rt, st));
     return SYMB_OK;
 }
 
@@ -1351,13 +1276,12 @@ symb_status symb_create(symb_handle* out, int device) {
         delete c;
         return fail(nullptr, SYMB_ERR_DEVICE, "descriptor staging allocation failed");
     }
-    for (int i = 0; i < kSlots; ++i) {
-        if (hipEventCreateWithFlags(&c->slot_done[i], hipEventDisableTiming) != hipSuccess) {
-            delete c;
+    for (auto& r : c->ring.slot)
+        if (hipEventCreateWithFlags(&r.done, hipEventDisableTiming) != hipSuccess) {
+            symb_destroy(c);
             return fail(nullptr, SYMB_ERR_DEVICE, "hipEventCreate failed");
         }
-    }
-    for (auto& u : c->uses)
+    for (auto& u : c->ring.uses)
         if (hipEventCreateWithFlags(&u.ev, hipEventDisableTiming) != hipSuccess) {
             symb_destroy(c);
             return fail(nullptr, SYMB_ERR_DEVICE, "hipEventCreate failed");
@@ -1459,12 +1383,12 @@ symb_status symb_destroy(symb_handle h) {
     if (!h) return SYMB_OK;
     (void)hipSetDevice(h->device);
     for (auto& e : h->tev) (void)hipEventDestroy(e);
-    for (int i = 0; i < kSlots; ++i) {
-        if (h->slot_used[i]) (void)hipEventSynchronize(h->slot_done[i]);
-        if (h->slot_done[i]) (void)hipEventDestroy(h->slot_done[i]);
+    for (auto& r : h->ring.slot) {
+        if (r.used) (void)hipEventSynchronize(r.done);
+        if (r.done) (void)hipEventDestroy(r.done);
     }
-    if (h->n_uses) (void)hipDeviceSynchronize();         // calls without an event of their own
-    for (auto& u : h->uses)
+    if (h->ring.n_uses) (void)hipDeviceSynchronize();    // calls without an event of their own
+    for (auto& u : h->ring.uses)
         if (u.ev) (void)hipEventDestroy(u.ev);
     if (h->dev_ring) (void)hipFree(h->dev_ring);
     if (h->host_ring) (void)hipHostFree(h->host_ring);
