@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -68,6 +69,12 @@ struct HipRuntime {                             // what the descriptor ring asks
         if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
         (void)hipGetLastError();                // (the default stream beside a capture)
         return true;
+    }
+    static uint64_t thread(Stream st) {
+        if (st != hipStreamPerThread) return 0;
+        static std::atomic<uint64_t> threads{0};
+        thread_local const uint64_t mine = ++threads;
+        return mine;
     }
 };
 constexpr int kSlots = DescRing<HipRuntime>::kSlots;
@@ -751,7 +758,7 @@ symb_status upload(symb_handle h, const Blob& blob, hipStream_t st, unsigned cha
         }
         for (; i < n; ++i) hash = (hash ^ blob.bytes[i]) * 0x100000001B3ull;
     }
-    const int in_place = h->opt_desc_reuse ? h->ring.find(st, n, hash, [&](int j) { return memcmp(h->host_ring + (size_t)j * kSlotBytes, blob.bytes.data(), n) == 0; }) : -1;
+    const int in_place = h->opt_desc_reuse ? h->ring.find(h->rt, st, n, hash, [&](int j) { return memcmp(h->host_ring + (size_t)j * kSlotBytes, blob.bytes.data(), n) == 0; }) : -1;
     if (in_place >= 0) {
         h->call_slot = in_place;
         ++h->desc_in_place;

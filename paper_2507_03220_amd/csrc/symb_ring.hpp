@@ -2,6 +2,7 @@
 // again.  Host code that reaches streams and events through Runtime alone, so that a program without a GPU can walk it:
 //   Stream, Event, Status (0 = success)
 //   Status record(Event, Stream), wait(Event), wait_all();  bool done(Event);  bool capturing(Stream)
+//   uint64_t thread(Stream)   0 if the handle names one queue, else (a queue of every thread's own) the calling thread's number, never given out again
 #pragma once
 #include <cstddef>
 #include <cstdint>
@@ -16,16 +17,22 @@ struct DescRing {
     static constexpr int kSlots = 32;                   // (a training step of 7 projections makes 21 different blobs)
     static constexpr int kStreams = 2, kSealCalls = 8;  // streams whose calls share events, calls per event while there is one such stream (seal)
 
+    struct Queue {                        // what work is in order on
+        Stream stream{};
+        uint64_t thread = 0;
+        bool operator==(const Queue& o) const { return stream == o.stream && thread == o.thread; }
+        bool operator!=(const Queue& o) const { return !(*this == o); }
+    };
     struct Slot {
         Event done{};                     // recorded behind the slot's copy and, if sealed, behind its last call
         bool used = false, sealed = false;
         uint64_t last = 0;                // the last call that read it
         size_t size = 0;                  // what its device copy holds: a call whose blob is already there (same bytes, copied on
-        uint64_t hash = 0;                // the same stream) reads that copy instead of sending the bytes again
-        Stream stream{};
+        uint64_t hash = 0;                // the same queue) reads that copy instead of sending the bytes again
+        Queue queue;
     } slot[kSlots];
     struct StreamUse {
-        Stream stream{};
+        Queue queue;
         Event ev{};                       // recorded behind call number `covered` or a later one of the stream
         uint64_t covered = 0;
         int since = 0;                    // calls since
@@ -35,17 +42,18 @@ struct DescRing {
     int next = 0;                         // the slot the next new blob goes to (round robin)
     int cur = 0;                          // the slot this call's kernels read
 
-    StreamUse* use_of(Stream st) {
+    StreamUse* use_of(const Queue& q) {
         for (int i = 0; i < n_uses; ++i)
-            if (uses[i].stream == st) return &uses[i];
+            if (uses[i].queue == q) return &uses[i];
         return nullptr;
     }
     // The slot that holds a blob already, -1 if none does.  same(i): slot i's pinned copy is that blob.
     template <class Same>
-    int find(Stream st, size_t n, uint64_t hash, Same&& same) {
+    int find(Runtime& rt, Stream st, size_t n, uint64_t hash, Same&& same) {
+        const Queue q{st, rt.thread(st)};
         for (int j = 0; j < kSlots; ++j) {
             Slot& s = slot[j];
-            if (!s.used || s.size != n || s.hash != hash || s.stream != st || !same(j)) continue;
+            if (!s.used || s.size != n || s.hash != hash || s.queue != q || !same(j)) continue;
             s.last = ++seq;
             s.sealed = false;
             cur = j;
@@ -58,14 +66,15 @@ struct DescRing {
     // overwritten in stream order; its pinned copy, and any other slot, is waited for.  A slot that hangs on another stream's event goes first only if that has come, as it may lie behind
     // calls that are far from done; one used in the last eight calls only if there is no other, so that a stream that comes to the ring gets a share of it.
     Status take(Runtime& rt, Stream st) {
+        const Queue q{st, rt.thread(st)};
         int at = -1;
         for (int i = 0; i < 2 * kSlots && at < 0; ++i) {
             const int j = (next + i) % kSlots;
             const Slot& s = slot[j];
             const StreamUse* u = nullptr;
             if (s.used) {
-                if (!s.sealed && s.stream != st) {
-                    u = use_of(s.stream);
+                if (!s.sealed && s.queue != q) {
+                    u = use_of(s.queue);
                     if (!u || s.last > u->covered) continue;
                 }
                 if (i < kSlots && (s.last + 8 > seq || (u && !rt.done(u->ev)))) continue;
@@ -95,7 +104,7 @@ struct DescRing {
         Slot& s = slot[cur];
         s.size = n;
         s.hash = hash;
-        s.stream = st;
+        s.queue = Queue{st, rt.thread(st)};
         s.used = true;
         s.sealed = false;
         s.last = ++seq;
@@ -105,19 +114,20 @@ struct DescRing {
     // step on 4096 x 4096 14.1 -> 11.3 us without, a training step of 16 rows 42.1 -> 33.8), and what it guards against, the slot's next batch, is in stream order for this
     // stream.  So only every kSealCalls-th call of a stream records one, which covers all before it; with two streams every fourth.  A slot
     // that another stream still reads without an event behind it is passed over (take): at most 7 + 3 of them for the kStreams streams that
-    // share events, whatever becomes of those.  Calls of further streams, and calls under capture, record the slot's own event, as all calls did.
+    // share events, whatever becomes of those.  Calls of further streams, of streams that every thread has its own of, and calls under capture, record the slot's own event, as all calls did.
     Status seal(Runtime& rt, Stream st) {
-        StreamUse* u = use_of(st);
+        const Queue q{st, rt.thread(st)};
+        StreamUse* u = use_of(q);
         const auto held = [&](int i) {
             for (int j = 0; i < n_uses && j < kSlots; ++j)
-                if (slot[j].used && slot[j].stream == uses[i].stream) return true;
+                if (slot[j].used && slot[j].queue == uses[i].queue) return true;
             return false;
         };
-        for (int i = 0; i < kStreams && !u; ++i) {       // a place in the table: a free one, or one whose stream has no slot left
+        for (int i = 0; i < kStreams && !u && !q.thread; ++i) {       // a place in the table: a free one, or one whose stream has no slot left
             if (held(i)) continue;
             u = &uses[i];
             if (n_uses < i + 1) n_uses = i + 1;
-            u->stream = st;
+            u->queue = q;
             u->covered = 0;
             u->since = 0;
         }

@@ -62,6 +62,7 @@ struct SimRuntime {
     Status wait_all() { ++w->full_waits; for (auto& q : w->queues) q.done = q.enqueued; return 0; }
     bool done(Event ev) { return w->over(w->events[ev]); }
     bool capturing(Stream st) { return w->graph.count(st) != 0; }
+    uint64_t thread(Stream st) { return st == World::PER_THREAD ? 1 + (uint64_t)w->thread : 0; }
 };
 using Ring = symb::DescRing<SimRuntime>;
 
@@ -94,7 +95,7 @@ struct Walk {
         const auto g = w.graph.find(st);
         const int graph = g == w.graph.end() ? 0 : g->second;
         const int q = w.queue(st);
-        int at = ring.find(st, 100, (uint64_t)batch, [&](int j) { return copy[j].pinned == batch; });
+        int at = ring.find(rt, st, 100, (uint64_t)batch, [&](int j) { return copy[j].pinned == batch; });
         if (at >= 0) {
             Copy& c = copy[at];
             expect(c.graph ? c.graph == graph : c.device == batch && (c.copied.queue == q || w.over(c.copied)), "in place, but the blob is not there");
@@ -144,6 +145,20 @@ static int run(const std::string& name) {
             }
         }
         k.expect(k.w.full_waits == 0, "waits for the whole device");
+    } else if (name == "per_thread") {                   // one handle value, a queue in every thread: other batches, the same ones, other streams beside them
+        streams(2);
+        for (int i = 0; i < 200; ++i) {
+            k.w.thread = 0;
+            k.call(World::PER_THREAD, 7);                // (a long one, say: nothing has run yet)
+            k.w.thread = 1;
+            for (int j = 0; j < Ring::kSlots; ++j) k.call(World::PER_THREAD, 100 + 50 * i + j);
+            k.call(World::PER_THREAD, 7);
+        }
+        for (int i = 0; i < 20000; ++i) {
+            k.w.thread = rnd(4);
+            const int st = rnd(4);
+            k.call(st < 2 ? World::PER_THREAD : 99 + st, rnd(i < 10000 ? 20 : 200));
+        }
     } else if (name == "failing_calls") {                // their slots stay guarded, and the ring does not run out of others
         streams(3);
         for (int i = 0; i < 20000; ++i) k.call(101 + rnd(3), rnd(100), rnd(4) != 0);

@@ -1168,3 +1168,52 @@ def test_more_streams_than_share_events():
     finally:
         torch.cuda.synchronize()
         sb.symb_destroy(h)
+
+
+def test_a_stream_of_every_threads_own():
+    """hipStreamPerThread is one handle value for a queue in every thread: two host threads, one call at a time, through one handle, with batches of their own and two that
+    both use, more than the ring has slots.  Every call gives the bits of its batch's first one."""
+    import threading
+    h = sb.symb_create(0)
+    per_thread = 2                       # hipStreamPerThread
+    try:
+        rng = np.random.default_rng(23)
+        d_in, d_out = 1032, 264
+        probs = []
+        for k in range(42):
+            p = make_problem(1300 + k, d_in, d_out, [int(x) for x in rng.choice([3, 17, 40, 64], size=3)], [L, I, N], [8, 16])
+            dev = gh.upload_adapters(p["ads"], d_in, d_out, grads=False)
+            p["dev"], p["batch"] = dev, sb.Batch(d_in, d_out, p["off"], dev.descs)
+            p["Xd"], p["Wd"], p["bd"] = gh.to_dev(p["X"]), gh.to_dev(p["W"]), gh.to_dev(p["bias"])
+            p["Y"] = [torch.empty((p["T"], d_out), device="cuda", dtype=torch.bfloat16) for _ in range(2)]
+            p["ws"] = [gh.workspace(p["batch"], sb.SYMB_OP_FWD) for _ in range(2)]
+            sb.symb_base_linear_fwd(gh.handle(), p["batch"], p["Xd"], p["Wd"], p["bd"], p["Y"][0], None, p["ws"][0], gh.stream_ptr())
+            p["first"] = p["Y"][0].view(torch.int16).clone()
+            for y in p["Y"]:
+                y.fill_(float("nan"))
+            probs.append(p)
+        torch.cuda.synchronize()
+        lock, failed = threading.Lock(), []
+
+        def work(me):
+            try:
+                for n in range(200):
+                    p = probs[(n * 7 + me) % 40 // 2 * 2 + me if n % 5 else 40 + n % 2]
+                    with lock:
+                        sb.symb_base_linear_fwd(h, p["batch"], p["Xd"], p["Wd"], p["bd"], p["Y"][me], None, p["ws"][me], per_thread)
+            except Exception as e:       # noqa: BLE001 (reported by the test's own thread)
+                failed.append(e)
+        threads = [threading.Thread(target=work, args=(me,)) for me in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        torch.cuda.synchronize()
+        assert not failed, failed
+        for k, p in enumerate(probs):
+            for me in range(2):
+                if k >= 40 or k % 2 == me:
+                    assert torch.equal(p["Y"][me].view(torch.int16), p["first"]), (k, me)
+    finally:
+        torch.cuda.synchronize()
+        sb.symb_destroy(h)
