@@ -45,7 +45,10 @@
  * void*; NULL = the default stream); calls return without synchronising.  Calls on
  * different streams may be in flight together as long as their output buffers and
  * workspaces are distinct.  Calls on one handle from several host threads must be
- * serialised by the caller.
+ * serialised by the caller.  hipStreamPerThread is the calling thread's own stream.
+ * A stream that calls of a handle were enqueued on must have finished them
+ * (hipStreamSynchronize) before it is destroyed, unless the handle goes first: a later
+ * stream may get the same hipStream_t, and the handle takes it for the same queue.
  *
  * Errors.  Every entry point returns a symb_status; nothing throws or aborts.  All
  * argument checks happen before the first launch: a failing call enqueues nothing,

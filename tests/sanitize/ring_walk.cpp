@@ -159,6 +159,13 @@ static int run(const std::string& name) {
             const int st = rnd(4);
             k.call(st < 2 ? World::PER_THREAD : 99 + st, rnd(i < 10000 ? 20 : 200));
         }
+    } else if (name == "recycled") {                     // streams that come and go, their handle values given out again
+        for (int i = 0; i < 3000; ++i) {
+            const int st = 101 + rnd(3);
+            if (k.w.live.count({st, -1})) k.w.destroy(st);
+            k.w.create(st);
+            for (int j = rnd(60); j > 0; --j) k.call(rnd(3) ? st : 0, rnd(40));
+        }
     } else if (name == "failing_calls") {                // their slots stay guarded, and the ring does not run out of others
         streams(3);
         for (int i = 0; i < 20000; ++i) k.call(101 + rnd(3), rnd(100), rnd(4) != 0);
