@@ -142,7 +142,9 @@ typedef struct symb_context* symb_handle;
  * A call's descriptors (about 170 bytes per segment plus 16 per row tile and row chunk; 36 more per row tile
  * for the terms of short LoRA segments, which a call without room for them does without) must fit
  * one slot: batches beyond roughly 12 000 segments are refused with SYMB_ERR_UNSUPPORTED before
- * anything is launched.  SYMB_ERR_DEVICE if HIP fails. */
+ * anything is launched.  Under HIP graph capture a call takes a slot too, and the graph's kernels read it at every
+ * replay; later calls with new descriptors overwrite the slots in turn.  So captured calls want a handle of their
+ * own, with at most 32 batches, for as long as their graphs are replayed.  SYMB_ERR_DEVICE if HIP fails. */
 symb_status symb_create(symb_handle* out, int device);
 symb_status symb_destroy(symb_handle h);
 

@@ -64,11 +64,15 @@ struct HipRuntime {                             // what the descriptor ring asks
         (void)hipGetLastError();                // (not ready yet is no error of this call)
         return false;
     }
-    static bool capturing(Stream st) {
+    static bool capture(Stream st, uint64_t* number) {
         hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+        unsigned long long id = 0;
+        if (hipStreamGetCaptureInfo(st, &s, &id) == hipSuccess) {
+            *number = s == hipStreamCaptureStatusNone ? 0 : id + 1;
+            return true;
+        }
         (void)hipGetLastError();                // (the default stream beside a capture)
-        return true;
+        return false;
     }
     static uint64_t thread(Stream st) {
         if (st != hipStreamPerThread) return 0;
@@ -758,21 +762,22 @@ symb_status upload(symb_handle h, const Blob& blob, hipStream_t st, unsigned cha
         }
         for (; i < n; ++i) hash = (hash ^ blob.bytes[i]) * 0x100000001B3ull;
     }
-    const int in_place = h->opt_desc_reuse ? h->ring.find(h->rt, st, n, hash, [&](int j) { return memcmp(h->host_ring + (size_t)j * kSlotBytes, blob.bytes.data(), n) == 0; }) : -1;
+    h->ring.begin(h->rt, st);
+    const int in_place = h->opt_desc_reuse ? h->ring.find(n, hash, [&](int j) { return memcmp(h->host_ring + (size_t)j * kSlotBytes, blob.bytes.data(), n) == 0; }) : -1;
     if (in_place >= 0) {
         h->call_slot = in_place;
         ++h->desc_in_place;
         *dev_base = h->dev_ring + (size_t)in_place * kSlotBytes;
         return SYMB_OK;
     }
-    SYMB_HIP(h, h->ring.take(h->rt, st));
+    SYMB_HIP(h, h->ring.take(h->rt));
     const int slot = h->call_slot = h->ring.cur;
     unsigned char* hp = h->host_ring + (size_t)slot * kSlotBytes;
     unsigned char* dp = h->dev_ring + (size_t)slot * kSlotBytes;
     memcpy(hp, blob.bytes.data(), n);
     SYMB_HIP(h, hipMemcpyAsync(dp, hp, n, hipMemcpyHostToDevice, st));
     ++h->desc_sent;
-    SYMB_HIP(h, h->ring.sent(h->rt, st, n, hash));
+    SYMB_HIP(h, h->ring.sent(h->rt, n, hash));
     *dev_base = dp;
     return SYMB_OK;
 }
@@ -789,8 +794,8 @@ struct CallGuard {
     }
 };
 
-symb_status seal_slot(symb_handle h, hipStream_t st) {
-    SYMB_HIP(h, h->ring.seal(h->rt, st));
+symb_status seal_slot(symb_handle h) {
+    SYMB_HIP(h, h->ring.seal(h->rt));
     return SYMB_OK;
 }
 
@@ -1154,7 +1159,7 @@ symb_status run_small(symb_handle h, const symb_batch* b, const BatchInfo& bi, c
     } else if (fwd) conv1d ? launch_small_stream<true, false>(sp, plan.one_buffer, s) : launch_small_stream<false, false>(sp, false, s);
     else conv1d ? launch_small_stream<false, true>(sp, false, s) : launch_small_stream<true, true>(sp, plan.one_buffer, s);
     SYMB_HIP(h, hipGetLastError());
-    if (plan.direct) return seal_slot(h, s);
+    if (plan.direct) return seal_slot(h);
 
     SmallFinishParams fp{};
     fp.partial = sp.partial;
@@ -1171,7 +1176,7 @@ symb_status run_small(symb_handle h, const symb_batch* b, const BatchInfo& bi, c
     fp.rows = rows;
     hipLaunchKernelGGL(fwd ? symb_small_finish_kernel<false> : symb_small_finish_kernel<true>, dim3((N + 255) / 256, bi.T), dim3(128), 0, s, fp);
     SYMB_HIP(h, hipGetLastError());
-    return seal_slot(h, s);
+    return seal_slot(h);
 }
 
 // The forward of a narrow layer in one launch, shrink included (narrow_kernel.hpp): its chunks of rows, none if the call is not one for it.  One column tile
@@ -1205,7 +1210,7 @@ symb_status run_narrow(symb_handle h, const symb_batch* b, const BatchInfo& bi, 
         SYMB_HIP(h, hipEventRecord(h->tev[2 * slot + 1], s));
         h->timed.push_back({kTimedNarrow, gemm_flops(b, sd, b->d_out, b->d_in, true)});
     }
-    return seal_slot(h, s);
+    return seal_slot(h);
 }
 
 // The input gradient of a layer of 64 to 256 outputs over many rows (shortk_kernel.hpp): its chunks of rows, none if the call is not one for it.  Enough of them that each of two workgroups per CU has four; up
@@ -1684,7 +1689,7 @@ static symb_status forward_impl(symb_handle h, const symb_batch* b, const void* 
         hipLaunchKernelGGL(symb_scatter_rows_kernel, dim3((unsigned)all_chunks.size()), dim3(256), 0, s, sc);
         SYMB_HIP(h, hipGetLastError());
     }
-    { guard.completed = true; return seal_slot(h, s); }
+    { guard.completed = true; return seal_slot(h); }
 }
 
 symb_status symb_base_linear_fwd(symb_handle h, const symb_batch* b, const void* X, const void* W, const void* bias,
@@ -1748,7 +1753,7 @@ symb_status symb_noise_add(symb_handle h, const symb_batch* b, const void* X, co
     NoiseAddParams np{(const bf16*)X, (bf16*)Xn, b->d_in, (const RowChunk*)(dev + o_ch), (const int32_t*)(dev + o_off),
                       (const NoiseDesc*)(dev + o_nd)};
     if ((st = launch_row_pass(h, symb_noise_add_kernel, np, b->d_in, chunks.size(), s)) != SYMB_OK) return st;
-    { guard.completed = true; return seal_slot(h, s); }
+    { guard.completed = true; return seal_slot(h); }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1933,7 +1938,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
         const ShortKParams kp{(const bf16*)dY, (const bf16*)W, (bf16*)dX, dH, b->d_in, (int)sk_chunks.size(), 0, 0, (const RowChunk*)(dev + o_sk), (const SegDesc*)(dev + o_seg)};
         if ((st = launch_shortk(h, kp, b->d_out, gemm_flops(b, sd, b->d_in, b->d_out, lora), s)) != SYMB_OK) return st;
         guard.completed = true;
-        return seal_slot(h, s);
+        return seal_slot(h);
     }
     if (!delta.items.empty() && (st = launch_delta(h, true, (const SegDesc*)(dev + o_seg), (const RowChunk*)(dev + db.items), (int)delta.items.size(), b->d_in,
                                                    dH, bi.max_rpad, (float*)(wsb + de_off), s)) != SYMB_OK) return st;
@@ -1982,7 +1987,7 @@ static symb_status backward_input_impl(symb_handle h, const symb_batch* b, const
         hipLaunchKernelGGL(symb_scatter_rows_kernel, dim3((unsigned)row_chunks.size()), dim3(256), 0, s, sc);
         SYMB_HIP(h, hipGetLastError());
     }
-    { guard.completed = true; return seal_slot(h, s); }
+    { guard.completed = true; return seal_slot(h); }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2263,7 +2268,7 @@ static symb_status adapter_grad_impl(symb_handle h, const symb_batch* b, const v
                          seg_io ? (const bf16* const*)(dev + o_xs) : nullptr, seg_io ? (const bf16* const*)(dev + o_ys) : nullptr};
         if ((st = launch_ia3_grad(h, b, ip, want_lin, s)) != SYMB_OK) return st;
     }
-    { guard.completed = true; return seal_slot(h, s); }
+    { guard.completed = true; return seal_slot(h); }
 }
 
 }  // extern "C"

@@ -1,7 +1,8 @@
 // The descriptor ring's bookkeeping: which slot a call's descriptors go to, which slot has them already, and what has to be waited for before a slot is written
 // again.  Host code that reaches streams and events through Runtime alone, so that a program without a GPU can walk it:
 //   Stream, Event, Status (0 = success)
-//   Status record(Event, Stream), wait(Event), wait_all();  bool done(Event);  bool capturing(Stream)
+//   Status record(Event, Stream), wait(Event), wait_all();  bool done(Event)
+//   bool capture(Stream, uint64_t* number)    number: of the capture that the stream is under, 0 if none; false: it cannot say
 //   uint64_t thread(Stream)   0 if the handle names one queue, else (a queue of every thread's own) the calling thread's number, never given out again
 #pragma once
 #include <cstddef>
@@ -30,6 +31,7 @@ struct DescRing {
         size_t size = 0;                  // what its device copy holds: a call whose blob is already there (same bytes, copied on
         uint64_t hash = 0;                // the same queue) reads that copy instead of sending the bytes again
         Queue queue;
+        uint64_t graph = 0;               // the copy belongs to that capture: only calls under it find it done
     } slot[kSlots];
     struct StreamUse {
         Queue queue;
@@ -41,22 +43,32 @@ struct DescRing {
     uint64_t seq = 0;                     // calls so far
     int next = 0;                         // the slot the next new blob goes to (round robin)
     int cur = 0;                          // the slot this call's kernels read
+    // this call's queue, capture, and whether it may do without an event of its own
+    Queue queue;
+    uint64_t graph = 0;
+    bool shares = false;
 
+    void begin(Runtime& rt, Stream st) {
+        queue = Queue{st, rt.thread(st)};
+        graph = 0;
+        shares = rt.capture(st, &graph) && !queue.thread;
+    }
     StreamUse* use_of(const Queue& q) {
         for (int i = 0; i < n_uses; ++i)
             if (uses[i].queue == q) return &uses[i];
         return nullptr;
     }
-    // The slot that holds a blob already, -1 if none does.  same(i): slot i's pinned copy is that blob.
+    // The slot that holds a blob already, -1 if none does.  same(i): slot i's pinned copy is that blob.  A call under capture leaves the slot as it is: its launches run
+    // when the graph does, and what guards the ordinary calls before it stays behind them.
     template <class Same>
-    int find(Runtime& rt, Stream st, size_t n, uint64_t hash, Same&& same) {
-        const Queue q{st, rt.thread(st)};
+    int find(size_t n, uint64_t hash, Same&& same) {
         for (int j = 0; j < kSlots; ++j) {
             Slot& s = slot[j];
-            if (!s.used || s.size != n || s.hash != hash || s.queue != q || !same(j)) continue;
+            if (!s.used || s.size != n || s.hash != hash || s.queue != queue || (s.graph && s.graph != graph) || !same(j)) continue;
+            cur = j;
+            if (graph) return j;
             s.last = ++seq;
             s.sealed = false;
-            cur = j;
             return j;
         }
         return -1;
@@ -64,16 +76,16 @@ struct DescRing {
     // A slot for a new blob, both of whose copies may be written from here on (the device copy in stream order): `cur`.
     // The next slot in turn that no other stream may still read without an event behind that call.  The device copy of a slot of this stream is
     // overwritten in stream order; its pinned copy, and any other slot, is waited for.  A slot that hangs on another stream's event goes first only if that has come, as it may lie behind
-    // calls that are far from done; one used in the last eight calls only if there is no other, so that a stream that comes to the ring gets a share of it.
-    Status take(Runtime& rt, Stream st) {
-        const Queue q{st, rt.thread(st)};
+    // calls that are far from done; one used in the last eight calls only if there is no other, so that a stream that comes to the ring gets a share of it.  A
+    // copy under capture runs with the graph, on whatever stream: no slot is in its order.
+    Status take(Runtime& rt) {
         int at = -1;
         for (int i = 0; i < 2 * kSlots && at < 0; ++i) {
             const int j = (next + i) % kSlots;
             const Slot& s = slot[j];
             const StreamUse* u = nullptr;
             if (s.used) {
-                if (!s.sealed && s.queue != q) {
+                if (!s.sealed && (graph || s.queue != queue)) {
                     u = use_of(s.queue);
                     if (!u || s.last > u->covered) continue;
                 }
@@ -100,45 +112,46 @@ struct DescRing {
         return Status{};
     }
     // The copy of a new blob to `cur` is enqueued.
-    Status sent(Runtime& rt, Stream st, size_t n, uint64_t hash) {
+    Status sent(Runtime& rt, size_t n, uint64_t hash) {
         Slot& s = slot[cur];
         s.size = n;
         s.hash = hash;
-        s.queue = Queue{st, rt.thread(st)};
+        s.queue = queue;
+        s.graph = graph;
         s.used = true;
-        s.sealed = false;
+        s.sealed = graph != 0;            // (no ordinary call reads it)
         s.last = ++seq;
-        return rt.record(s.done, st);      // a call that fails before its kernels still leaves the slot guarded
+        return rt.record(s.done, queue.stream);      // a call that fails before its kernels still leaves the slot guarded
     }
     // Ends a call: its slot is busy until everything enqueued so far on `st` has run (kernels read it).  An event costs 2.8 us on the stream, a quarter of a small call (one user's decode
     // step on 4096 x 4096 14.1 -> 11.3 us without, a training step of 16 rows 42.1 -> 33.8), and what it guards against, the slot's next batch, is in stream order for this
     // stream.  So only every kSealCalls-th call of a stream records one, which covers all before it; with two streams every fourth.  A slot
     // that another stream still reads without an event behind it is passed over (take): at most 7 + 3 of them for the kStreams streams that
-    // share events, whatever becomes of those.  Calls of further streams, of streams that every thread has its own of, and calls under capture, record the slot's own event, as all calls did.
-    Status seal(Runtime& rt, Stream st) {
-        const Queue q{st, rt.thread(st)};
-        StreamUse* u = use_of(q);
+    // share events, whatever becomes of those.  Calls of further streams, and of streams that every thread has its own of, record the slot's own event, as all calls did.
+    Status seal(Runtime& rt) {
+        if (graph) return Status{};
+        StreamUse* u = use_of(queue);
         const auto held = [&](int i) {
             for (int j = 0; i < n_uses && j < kSlots; ++j)
                 if (slot[j].used && slot[j].queue == uses[i].queue) return true;
             return false;
         };
-        for (int i = 0; i < kStreams && !u && !q.thread; ++i) {       // a place in the table: a free one, or one whose stream has no slot left
+        for (int i = 0; i < kStreams && !u && shares; ++i) {       // a place in the table: a free one, or one whose stream has no slot left
             if (held(i)) continue;
             u = &uses[i];
             if (n_uses < i + 1) n_uses = i + 1;
-            u->queue = q;
+            u->queue = queue;
             u->covered = 0;
             u->since = 0;
         }
-        if (!u || rt.capturing(st)) {
+        if (!u || !shares) {
             slot[cur].sealed = true;
-            return rt.record(slot[cur].done, st);
+            return rt.record(slot[cur].done, queue.stream);
         }
         if (++u->since >= kSealCalls / n_uses) {
             u->covered = seq;
             u->since = 0;
-            return rt.record(u->ev, st);
+            return rt.record(u->ev, queue.stream);
         }
         return Status{};
     }

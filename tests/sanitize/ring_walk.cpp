@@ -61,7 +61,11 @@ struct SimRuntime {
     Status wait(Event ev) { ++w->waits; w->finish(w->events[ev]); return 0; }
     Status wait_all() { ++w->full_waits; for (auto& q : w->queues) q.done = q.enqueued; return 0; }
     bool done(Event ev) { return w->over(w->events[ev]); }
-    bool capturing(Stream st) { return w->graph.count(st) != 0; }
+    bool capture(Stream st, uint64_t* number) {
+        const auto g = w->graph.find(st);
+        *number = g == w->graph.end() ? 0 : (uint64_t)g->second;
+        return true;
+    }
     uint64_t thread(Stream st) { return st == World::PER_THREAD ? 1 + (uint64_t)w->thread : 0; }
 };
 using Ring = symb::DescRing<SimRuntime>;
@@ -95,13 +99,14 @@ struct Walk {
         const auto g = w.graph.find(st);
         const int graph = g == w.graph.end() ? 0 : g->second;
         const int q = w.queue(st);
-        int at = ring.find(rt, st, 100, (uint64_t)batch, [&](int j) { return copy[j].pinned == batch; });
+        ring.begin(rt, st);
+        int at = ring.find(100, (uint64_t)batch, [&](int j) { return copy[j].pinned == batch; });
         if (at >= 0) {
             Copy& c = copy[at];
             expect(c.graph ? c.graph == graph : c.device == batch && (c.copied.queue == q || w.over(c.copied)), "in place, but the blob is not there");
         } else {
             ++sent;
-            expect(ring.take(rt, st) == 0, "no slot");
+            expect(ring.take(rt) == 0, "no slot");
             at = ring.cur;
             Copy& c = copy[at];
             expect(w.over(c.copied), "pinned copy written under the copy from it");
@@ -111,10 +116,10 @@ struct Walk {
             c.graph = graph;
             c.device = graph ? -1 : batch;
             c.copied = graph ? At{} : w.enqueue(st);
-            expect(ring.sent(rt, st, 100, (uint64_t)batch) == 0, "event");
+            expect(ring.sent(rt, 100, (uint64_t)batch) == 0, "event");
         }
         if (!graph) copy[at].readers.push_back(w.enqueue(st));       // its launches
-        if (ended) expect(ring.seal(rt, st) == 0, "event");
+        if (ended) expect(ring.seal(rt) == 0, "event");
         else ring.slot[at].size = (size_t)-1;
     }
 };
@@ -166,6 +171,27 @@ static int run(const std::string& name) {
             k.w.create(st);
             for (int j = rnd(60); j > 0; --j) k.call(rnd(3) ? st : 0, rnd(40));
         }
+    } else if (name == "capture") {                      // captured calls between ordinary ones, in place and with blobs of their own, two captures after one another
+        streams(4);
+        for (int i = 0; i < 400; ++i) {
+            const int st = 101 + i % 2, other = 103 + i % 2;
+            for (int j = rnd(20); j >= 0; --j) k.call(st, 1);
+            k.w.graph[st] = i + 1;
+            k.call(st, 1);
+            for (int j = 0; j < 3; ++j) k.call(st, 500 + 3 * i + j % 2);
+            k.w.graph.erase(st);
+            k.call(st, 500 + 3 * i);                     // (its copy is in the graph)
+            k.w.graph[st] = 1000 + i;
+            k.call(st, 501 + 3 * i);
+            k.w.graph.erase(st);
+            for (int j = 0; j < Ring::kSlots; ++j) k.call(i % 4 < 2 ? other : 0, 100000 + 100 * i + j);
+        }
+        for (int i = 0; i < 30000; ++i) {
+            const int st = 101 + rnd(4);
+            if (rnd(10) == 0 && !k.w.graph.erase(st)) k.w.graph[st] = 10000 + i;
+            k.call(st, rnd(60));
+        }
+        k.expect(k.w.full_waits == 0, "waits for the whole device");
     } else if (name == "failing_calls") {                // their slots stay guarded, and the ring does not run out of others
         streams(3);
         for (int i = 0; i < 20000; ++i) k.call(101 + rnd(3), rnd(100), rnd(4) != 0);

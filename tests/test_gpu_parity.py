@@ -1217,3 +1217,58 @@ def test_a_stream_of_every_threads_own():
     finally:
         torch.cuda.synchronize()
         sb.symb_destroy(h)
+
+
+def test_calls_under_capture():
+    """A graph with a call whose descriptors an ordinary call sent and two calls of a batch that it sends itself, replayed with eager calls and waits between; the ordinary call of
+    that batch on the same stream sends it again, as the copy is the graph's."""
+    h = sb.symb_create(0)
+    try:
+        d_in, d_out = 1032, 264
+        probs = []
+        for k, lens in enumerate([[40, 3, 300], [90, 64, 17], [5, 200, 33]]):
+            p = make_problem(1700 + k, d_in, d_out, lens, [L, I, N], [8, 16])
+            p["dev"] = gh.upload_adapters(p["ads"], d_in, d_out, grads=False)
+            p["batch"] = sb.Batch(d_in, d_out, p["off"], p["dev"].descs)
+            p["Xd"], p["Wd"], p["bd"] = gh.to_dev(p["X"]), gh.to_dev(p["W"]), gh.to_dev(p["bias"])
+            p["Y"] = torch.empty((p["T"], d_out), device="cuda", dtype=torch.bfloat16)
+            p["ws"] = gh.workspace(p["batch"], sb.SYMB_OP_FWD)
+            probs.append(p)
+        st = torch.cuda.Stream()
+
+        def call(p, stream=st):
+            sb.symb_base_linear_fwd(h, p["batch"], p["Xd"], p["Wd"], p["bd"], p["Y"], None, p["ws"], stream.cuda_stream)
+
+        torch.cuda.synchronize()
+        a, b, c = probs
+        for p in probs:
+            sb.symb_base_linear_fwd(gh.handle(), p["batch"], p["Xd"], p["Wd"], p["bd"], p["Y"], None, p["ws"], gh.stream_ptr())
+            p["first"] = p["Y"].view(torch.int16).clone()
+        torch.cuda.synchronize()
+        call(a)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            call(a)
+            call(b)
+            call(b)
+        assert sb.symb_debug_descriptor_stats(h) == (2, 2)
+        call(b)
+        assert sb.symb_debug_descriptor_stats(h) == (3, 2)
+        for n in range(4):
+            for p in probs:
+                p["Y"].fill_(float("nan"))
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            for p in (a, b):
+                assert torch.equal(p["Y"].view(torch.int16), p["first"]), n
+            call(c)
+            call(b)
+            call(a, torch.cuda.current_stream())
+            torch.cuda.synchronize()
+            for p in probs:
+                assert torch.equal(p["Y"].view(torch.int16), p["first"]), n
+    finally:
+        torch.cuda.synchronize()
+        sb.symb_destroy(h)
