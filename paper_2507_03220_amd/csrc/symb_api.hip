@@ -56,7 +56,11 @@ struct HipRuntime {                             // what the descriptor ring asks
     using Stream = hipStream_t;
     using Event = hipEvent_t;
     using Status = hipError_t;
-    static Status record(Event ev, Stream st) { return hipEventRecord(ev, st); }
+    static Status record(Event ev, Stream st) {
+        const hipError_t e = hipEventRecord(ev, st);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e;
+    }
     static Status wait(Event ev) { return hipEventSynchronize(ev); }
     static Status wait_all() { return hipDeviceSynchronize(); }
     static bool done(Event ev) {
@@ -64,15 +68,16 @@ struct HipRuntime {                             // what the descriptor ring asks
         (void)hipGetLastError();                // (not ready yet is no error of this call)
         return false;
     }
-    static bool capture(Stream st, uint64_t* number) {
+    static StreamState state(Stream st, uint64_t* capture) {
         hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
         unsigned long long id = 0;
-        if (hipStreamGetCaptureInfo(st, &s, &id) == hipSuccess) {
-            *number = s == hipStreamCaptureStatusNone ? 0 : id + 1;
-            return true;
+        const hipError_t e = hipStreamGetCaptureInfo(st, &s, &id);
+        if (e == hipSuccess) {
+            *capture = s == hipStreamCaptureStatusNone ? 0 : id + 1;
+            return StreamState::Known;
         }
-        (void)hipGetLastError();                // (the default stream beside a capture)
-        return false;
+        (void)hipGetLastError();
+        return e == hipErrorStreamCaptureImplicit ? StreamState::Unsure : StreamState::Gone;     // (HIP looks the handle up among its live streams)
     }
     static uint64_t thread(Stream st) {
         if (st != hipStreamPerThread) return 0;
@@ -1399,7 +1404,7 @@ symb_status symb_destroy(symb_handle h) {
         if (r.used) (void)hipEventSynchronize(r.done);
         if (r.done) (void)hipEventDestroy(r.done);
     }
-    if (h->ring.n_uses) (void)hipDeviceSynchronize();    // calls without an event of their own
+    (void)hipDeviceSynchronize();                        // calls without an event of their own
     for (auto& u : h->ring.uses)
         if (u.ev) (void)hipEventDestroy(u.ev);
     if (h->dev_ring) (void)hipFree(h->dev_ring);

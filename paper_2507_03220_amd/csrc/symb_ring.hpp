@@ -2,13 +2,15 @@
 // again.  Host code that reaches streams and events through Runtime alone, so that a program without a GPU can walk it:
 //   Stream, Event, Status (0 = success)
 //   Status record(Event, Stream), wait(Event), wait_all();  bool done(Event)
-//   bool capture(Stream, uint64_t* number)    number: of the capture that the stream is under, 0 if none; false: it cannot say
+//   StreamState state(Stream, uint64_t* capture)   capture: number of the one that the stream is under, 0 if none
 //   uint64_t thread(Stream)   0 if the handle names one queue, else (a queue of every thread's own) the calling thread's number, never given out again
 #pragma once
 #include <cstddef>
 #include <cstdint>
 
 namespace symb {
+
+enum class StreamState { Known, Unsure, Gone };         // Unsure: the default stream beside a capture; Gone: destroyed
 
 template <class Runtime>
 struct DescRing {
@@ -17,6 +19,7 @@ struct DescRing {
     using Status = typename Runtime::Status;
     static constexpr int kSlots = 32;                   // (a training step of 7 projections makes 21 different blobs)
     static constexpr int kStreams = 2, kSealCalls = 8;  // streams whose calls share events, calls per event while there is one such stream (seal)
+    static constexpr int kIdleCalls = 64;               // calls of others after which a stream is taken to have stopped
 
     struct Queue {                        // what work is in order on
         Stream stream{};
@@ -36,10 +39,10 @@ struct DescRing {
     struct StreamUse {
         Queue queue;
         Event ev{};                       // recorded behind call number `covered` or a later one of the stream
-        uint64_t covered = 0;
+        uint64_t covered = 0, last = 0;   // (last: its last call)
         int since = 0;                    // calls since
+        bool used = false, active = false;              // active: its calls share events; else an event is behind all that did
     } uses[kStreams];
-    int n_uses = 0;
     uint64_t seq = 0;                     // calls so far
     int next = 0;                         // the slot the next new blob goes to (round robin)
     int cur = 0;                          // the slot this call's kernels read
@@ -51,11 +54,11 @@ struct DescRing {
     void begin(Runtime& rt, Stream st) {
         queue = Queue{st, rt.thread(st)};
         graph = 0;
-        shares = rt.capture(st, &graph) && !queue.thread;
+        shares = rt.state(st, &graph) == StreamState::Known && !queue.thread;
     }
     StreamUse* use_of(const Queue& q) {
-        for (int i = 0; i < n_uses; ++i)
-            if (uses[i].queue == q) return &uses[i];
+        for (StreamUse& u : uses)
+            if (u.used && u.queue == q) return &u;
         return nullptr;
     }
     // The slot that holds a blob already, -1 if none does.  same(i): slot i's pinned copy is that blob.  A call under capture leaves the slot as it is: its launches run
@@ -97,9 +100,10 @@ struct DescRing {
             }
             at = j;
         }
-        if (at < 0) {                      // (not reached: see seal)
+        if (at < 0) {                      // (calls that failed behind their descriptors have no event: they may hold every slot in the end)
             const Status e = rt.wait_all();
             if (e != Status{}) return e;
+            for (Slot& s : slot) s.sealed = true;
             at = next;
         }
         next = (at + 1) % kSlots;
@@ -127,33 +131,50 @@ struct DescRing {
     // step on 4096 x 4096 14.1 -> 11.3 us without, a training step of 16 rows 42.1 -> 33.8), and what it guards against, the slot's next batch, is in stream order for this
     // stream.  So only every kSealCalls-th call of a stream records one, which covers all before it; with two streams every fourth.  A slot
     // that another stream still reads without an event behind it is passed over (take): at most 7 + 3 of them for the kStreams streams that
-    // share events, whatever becomes of those.  Calls of further streams, and of streams that every thread has its own of, record the slot's own event, as all calls did.
+    // share events.  Calls of further streams, and of streams that every thread has its own of, record the slot's own event, as all calls did.  A stream that has made no call for the last
+    // kIdleCalls gets an event behind its last one, which frees its slots and, once it has come, its place.
     Status seal(Runtime& rt) {
         if (graph) return Status{};
         StreamUse* u = use_of(queue);
-        const auto held = [&](int i) {
-            for (int j = 0; i < n_uses && j < kSlots; ++j)
-                if (slot[j].used && slot[j].queue == uses[i].queue) return true;
-            return false;
-        };
-        for (int i = 0; i < kStreams && !u && shares; ++i) {       // a place in the table: a free one, or one whose stream has no slot left
-            if (held(i)) continue;
-            u = &uses[i];
-            if (n_uses < i + 1) n_uses = i + 1;
-            u->queue = queue;
-            u->covered = 0;
-            u->since = 0;
+        int active = 0;
+        for (StreamUse& w : uses) {
+            if (w.active && &w != u && seq - w.last > kIdleCalls) retire(rt, w);
+            active += w.active;
         }
+        if (shares && !u)
+            for (StreamUse& w : uses)
+                if (!u && !w.active && (!w.used || rt.done(w.ev))) {
+                    for (Slot& s : slot)
+                        if (w.used && s.queue == w.queue && s.last <= w.covered) s.sealed = true;      // (over)
+                    u = &w;
+                    u->queue = queue;
+                    u->used = true;
+                    u->covered = 0;
+                }
         if (!u || !shares) {
             slot[cur].sealed = true;
             return rt.record(slot[cur].done, queue.stream);
         }
-        if (++u->since >= kSealCalls / n_uses) {
+        if (!u->active) {
+            u->active = true;
+            u->since = 0;
+            ++active;
+        }
+        u->last = seq;
+        if (++u->since >= kSealCalls / active) {
             u->covered = seq;
             u->since = 0;
             return rt.record(u->ev, queue.stream);
         }
         return Status{};
+    }
+    void retire(Runtime& rt, StreamUse& u) {
+        uint64_t number = 0;
+        const StreamState is = rt.state(u.queue.stream, &number);
+        if (is == StreamState::Unsure || number) return;               // (an event now would be the capture's, or disturb one)
+        if (is == StreamState::Known && rt.record(u.ev, u.queue.stream) != Status{}) return;
+        u.covered = seq;                                               // (of a stream that is gone all calls are over)
+        u.active = false;
     }
 };
 

@@ -61,10 +61,10 @@ struct SimRuntime {
     Status wait(Event ev) { ++w->waits; w->finish(w->events[ev]); return 0; }
     Status wait_all() { ++w->full_waits; for (auto& q : w->queues) q.done = q.enqueued; return 0; }
     bool done(Event ev) { return w->over(w->events[ev]); }
-    bool capture(Stream st, uint64_t* number) {
+    symb::StreamState state(Stream st, uint64_t* capture) {
         const auto g = w->graph.find(st);
-        *number = g == w->graph.end() ? 0 : (uint64_t)g->second;
-        return true;
+        *capture = g == w->graph.end() ? 0 : (uint64_t)g->second;
+        return w->queue(st) < 0 ? symb::StreamState::Gone : symb::StreamState::Known;
     }
     uint64_t thread(Stream st) { return st == World::PER_THREAD ? 1 + (uint64_t)w->thread : 0; }
 };
@@ -192,9 +192,34 @@ static int run(const std::string& name) {
             k.call(st, rnd(60));
         }
         k.expect(k.w.full_waits == 0, "waits for the whole device");
+    } else if (name == "idle" || name == "gone") {       // two streams that share events stop, or are destroyed; then others, one after the other, get their events and all of their slots
+        streams(9);
+        for (int st = 101; st <= 102; ++st)
+            for (int i = 0; i < 300; ++i) k.call(st, 100 * st + (i < 293 ? 0 : i));
+        if (name == "gone") k.w.destroy(101), k.w.destroy(102);
+        for (int st = 103; st <= 109; ++st) {
+            int sent = 0, records = 0;
+            for (int i = 0; i < 4000; ++i) {
+                if (i == 2000) sent = k.sent, records = k.w.records;
+                k.call(st, 100 * st + i % 30);
+                if (i % 100 == 0)
+                    for (auto& q : k.w.queues) q.done = q.enqueued;
+            }
+            k.expect(k.sent == sent && k.w.records == records + 2000 / 8, "one stream alone");
+        }
+        k.w.graph[109] = 1;                              // (stops under capture: no event behind its calls)
+        for (int i = 0; i < 4000; ++i) k.call(108, 77000 + i % 40);
+        k.w.graph.erase(109);
+        if (name == "idle")
+            for (int i = 0; i < 20000; ++i) k.call(101 + i / 100 % 9, rnd(50));
+        k.expect(k.w.full_waits == 0, "waits for the whole device");
     } else if (name == "failing_calls") {                // their slots stay guarded, and the ring does not run out of others
         streams(3);
         for (int i = 0; i < 20000; ++i) k.call(101 + rnd(3), rnd(100), rnd(4) != 0);
+        k.expect(k.w.full_waits == 0, "waits for the whole device");
+        for (int i = 0; i < 100; ++i) k.call(103, 5000 + i, false);      // (of the one that shares no events)
+        for (int i = 0; i < 1000; ++i) k.call(101, i);
+        k.expect(k.w.full_waits <= 1, "waits for the whole device");
     } else {
         std::fprintf(stderr, "no scenario %s\n", name.c_str());
         return 1;

@@ -15,7 +15,7 @@ def walk(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["one_stream", "streams", "per_thread", "recycled", "capture", "failing_calls"])
+@pytest.mark.parametrize("scenario", ["one_stream", "streams", "per_thread", "recycled", "capture", "idle", "gone", "failing_calls"])
 def test_walk(walk, scenario):
     r = subprocess.run([walk, scenario], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and f"{scenario} fails=0" in r.stdout, (r.stdout, r.stderr[-2000:])
