@@ -524,13 +524,15 @@ symb_gemm_mid_kernel(const GemmParams p) {
     };
     auto lora = [&](floatx4 (&acc)[CB][MB]) __attribute__((always_inline)) {
         if (!p.ext) return;
-        // step number n of a segment goes to wavefront n % 4: a row's sum does not depend on what else is in its tile
+        // Steps of the tile: number no goes to wavefront no % 4.  (By its number inside the segment, seven short clients of one step each are a chain on one wavefront, us
+        // of 256 rows of 768 x 768: forward 13.4 -> 15.3, input gradient 16.0 -> 20.7; 128 of 256 x 256 11.1 -> 12.7, 12.8 -> 17.6.)
+        int no = 0;
         for (int s = seg_lo; s <= seg_hi; ++s) {
             const SegDesc sd = p.seg[s];
             const int lo = max(p.off[s], m0), hi = min(min(p.off[s + 1], m0 + MID_ROWS), p.M);
             if (sd.kind != KIND_LORA || hi <= lo) continue;
-            for (int e = 0; e < 2 * sd.rpad; e += 32) {
-                if (((e >> 5) & 3) != wave) continue;
+            for (int e = 0; e < 2 * sd.rpad; e += 32, ++no) {
+                if ((no & 3) != wave) continue;
                 const int pk = e + kq * 8, pp = pk >= sd.rpad ? pk - sd.rpad : pk;     // both halves of the extended columns meet the same adapter matrix
                 // every load unconditional and in bounds, what does not belong to the step zeroed afterwards (under a condition each would be waited for)
                 u32x4 xv[MB], wv[CB];

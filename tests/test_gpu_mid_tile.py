@@ -49,3 +49,14 @@ def test_an_infinity_stays_out_of_other_blocks_of_rows():
     p["ads"][0].B[3] = 0x7f80
     got = gh.bf16_to_f64(gh.forward(p["off"], p["ads"], p["X"], p["W"], p["bias"], want_base=False)[0])
     assert not np.isfinite(got[:16, 3]).any() and np.isfinite(np.delete(got, 3, 1)).all() and np.isfinite(got[16:]).all()
+
+
+@pytest.mark.parametrize("lens", [[4] * 7 + [44], [1] * 7 + [58, 30], [16] * 5 + [3, 2]])
+def test_short_segments_that_share_a_tile(lens):
+    """As many as the tiles of 32 rows take: their LoRA steps are dealt out over the wavefronts."""
+    p = make_problem(len(lens) + sum(lens), 264, 200, lens, [L], [8, 16, 5])
+    for conv1d in (False, True):
+        n, (Y, _) = launches(lambda: gh.forward(p["off"], p["ads"], p["X"], p["W"], p["bias"], want_base=False, conv1d=conv1d), 16 + 4 + 2 + conv1d)
+        assert n == 1
+        check_y(gh.bf16_to_f64(Y), p["off"], oracle_ads(p["ads"]), p["X"], p["W"], p["bias"], f"Y conv1d={conv1d}")
+        check_dx(gh.bf16_to_f64(gh.backward_input(p["off"], p["ads"], p["dY"], p["W"], conv1d=conv1d)), p["off"], oracle_ads(p["ads"]), p["dY"], p["W"], "dX")
