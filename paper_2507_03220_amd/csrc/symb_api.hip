@@ -1187,13 +1187,24 @@ symb_status run_small(symb_handle h, const symb_batch* b, const BatchInfo& bi, c
 // The forward of a narrow layer in one launch, shrink included (narrow_kernel.hpp): its chunks of rows, none if the call is not one for it.  One column tile
 // (N <= 256, above 128: half of it), stages of 64 k without a remainder, ranks to 16; one round of workgroups that is 60 % full, or more that are 85 %.  Two launches / this, us, 8 clients of ranks 8 and
 // 16, 256 columns: 9900 rows (62 % of a round) of K = 512 17.9 / 13.0, 2048 36.6 / 29.6, 6144 90.9 / 81.2, 11008 143 / 137; 13000 rows 18.8 / 13.5, 36.5 / 30.9, 106 / 84, 174 / 140; 20000 (62 % of two)
-// 23.9 / 23.7, 52.1 / 59.2, 146 / 160, 284 / 268; 30000 (92 %) 27.2 / 25.0, 67.1 / 63.9, 179 / 165, 317 / 281.
+// 23.9 / 23.7, 52.1 / 59.2, 146 / 160, 284 / 268; 136 to 248 columns of K = 64 to 6144 1.05 to 1.9 times as fast in one round.
+// A chunk costs the whole weight whatever it holds, so beyond short inner dimensions, where the two launches' own latencies weigh more, its rows have to be there.  Two launches / this, segments of
+// 1 to 1000 rows, 256 columns, rank 8.  One round: K <= 1536 1.0 to 3.5; above, seven eighths of the rows there or 9600 of them 0.97 to 1.5, else 0.37 to 0.97 (160, 200, 256 one-token clients of
+// K = 6144 60.7 / 74.4, 58.5 / 76.4, 63.7 / 78.3).  More rounds: K <= 128 1.0 to 2.3; segments of one chunk each, K = 256 1.17 to 2.2, 512 up to 16 rows each 1.12 to 1.7, longer ones 0.9 to 1.1; K = 6144 and
+// 11008, filled, up to three rounds 1.0 to 1.16, four 0.97; everything else 0.2 to 1.05 (500 one-token clients of K = 6144 71.8 / 147.4).
 std::vector<RowChunk> narrow_chunks(const symb_batch* b, const BatchInfo& bi) {
     std::vector<RowChunk> v;
     if (b->weight_layout != SYMB_WEIGHT_LINEAR || !bi.n_lora || bi.n_ia3in || bi.max_rpad > 16 || b->d_out <= NARROW_COLS / 2 || b->d_out > NARROW_COLS || b->d_in % 64 || bi.S > 4096) return v;
-    long n = 0;
-    for (int i = 0; i < bi.S; ++i) n += (b->seg_offsets[i + 1] - b->seg_offsets[i] + NARROW_ROWS - 1) / NARROW_ROWS;
+    long n = 0, segments = 0;
+    for (int i = 0; i < bi.S; ++i) {
+        const int rows = b->seg_offsets[i + 1] - b->seg_offsets[i];
+        n += (rows + NARROW_ROWS - 1) / NARROW_ROWS;
+        segments += rows > 0;
+    }
     if (n > 65536 || (n <= 256 ? 10 * n < 6 * 256 : 20 * n < 17 * 256 * ((n + 255) / 256))) return v;
+    const bool filled = 8L * bi.T >= 7 * NARROW_ROWS * n;
+    if (n <= 256 ? b->d_in > 1536 && !filled && bi.T < 9600
+                 : b->d_in > 128 && !(n == segments && b->d_in <= (bi.T <= 16 * n ? 512 : 384)) && !(filled && b->d_in >= 6144 && n <= 768)) return v;
     plan_chunks(b, NARROW_ROWS, -1, v);
     return v;
 }

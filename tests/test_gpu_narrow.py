@@ -55,10 +55,14 @@ def test_forward_and_the_h_it_leaves(d_in, d_out, ranks):
     (27800, 64, 256, 8, 0), (27904, 64, 256, 8, 1),                                                          # 435 and 436
     (12000, 136, 256, 8, 0), (12000, 128, 128, 8, 0), (12000, 128, 264, 8, 0), (12000, 128, 256, 17, 0)])
 def test_which_calls_take_it(T, d_in, d_out, rank, want):
-    p = make_problem(T, d_in, d_out, [T], [L], [rank])
+    which_calls_take_it(T, d_in, d_out, rank, want, [T])
+
+
+def which_calls_take_it(T, d_in, d_out, rank, want, lens):
+    p = make_problem(T, d_in, d_out, lens, [L], [rank])
     dev = gh.upload_adapters(p["ads"], d_in, d_out, grads=False)
     X, W = gh.to_dev(p["X"]), gh.to_dev(p["W"])
-    rows = synth.sample_rows(p["off"], 20, f"takes{T}", block=512)
+    rows = synth.sample_rows(p["off"], 20 if len(lens) == 1 else 1, f"takes{T}", block=512)
     for conv1d, base in ((0, False), (0, True), (1, False)):
         b = sb.Batch(d_in, d_out, p["off"], dev.descs, conv1d)
         Wl = W if not conv1d else gh.weight_to_dev(p["W"], True)
@@ -67,3 +71,11 @@ def test_which_calls_take_it(T, d_in, d_out, rank, want):
         ws = gh.workspace(b, sb.SYMB_OP_FWD)
         assert narrow_launches(lambda: sb.symb_base_linear_fwd(gh.handle(), b, X, Wl, None, Y, Yb, ws)) == (want if not conv1d and not base else 0)  # noqa: B023
         check_y(gh.bf16_to_f64(Y)[rows], p["off"], oracle_ads(p["ads"]), p["X"], p["W"], None, "Y", rows=rows)
+
+
+@pytest.mark.parametrize("clients,tokens,d_in,want", [
+    (160, 1, 6144, 0), (200, 1, 6144, 0), (256, 1, 6144, 0), (500, 1, 6144, 0), (200, 16, 2048, 0), (160, 56, 1600, 1), (160, 55, 1600, 0), (250, 40, 1600, 1),
+    (200, 1, 1536, 1), (500, 16, 512, 1), (500, 17, 512, 0), (500, 17, 384, 1), (250, 72, 256, 0), (250, 72, 128, 1), (440, 56, 6144, 1), (440, 8, 6144, 0)])
+def test_which_calls_of_short_segments_take_it(clients, tokens, d_in, want):
+    """A chunk of rows costs the whole weight, so that chunks of a few rows are for short inner dimensions."""
+    which_calls_take_it(clients * tokens, d_in, 256, 8, want, [tokens] * clients)
