@@ -3,7 +3,7 @@
 // 256 outputs) and streams rows past them.
 //
 // Bound by the stores of dX.  16384 rows of 6144 <- 256, 201 MB of them: 84 us in 256x256 tiles,
-// 79 here with three outputs in turn (2.5 TB/s, what a copy writes), the training step 240 -> 219; 6000 rows 41.0 -> 27.2.  A workgroup is 4 wavefronts, 256 columns; its 32-row chunks (never across a segment)
+// 79 here with three outputs in turn (2.5 TB/s, what a copy writes), the training step 240 -> 219; 6000 rows 41.0 -> 27.2.  A workgroup is 4 wavefronts, 256 columns; its 32-row chunks (with adapters never across a segment)
 // come in by LDS DMA through a ring of three, one barrier per chunk, and every wavefront multiplies all 32 rows with its own columns.  Two workgroups per CU, so that one's stores run beside the
 // other's products.  The columns of a wavefront are dealt out so that a lane ends up with 16 consecutive ones of a row, 32 bytes: output goes to memory from the registers, whole
 // 128-byte lines per row between four lanes, with no staging.
@@ -20,7 +20,7 @@ struct ShortKParams {
     bf16* C;                  // dX [M][N]
     const bf16* h_rows;       // [M][32]: dH, 16 values and 16 residuals; null: no LoRA term
     int N, num_chunks, groups, per_group;
-    const RowChunk* chunks;   // device: at most 32 rows of one segment each; a workgroup takes per_group of them
+    const RowChunk* chunks;   // device: at most 32 rows each, with h_rows of one segment; a workgroup takes per_group of them
     const SegDesc* seg;       // LoRA segments: ranks up to 16
 };
 

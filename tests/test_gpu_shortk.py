@@ -55,3 +55,19 @@ def test_input_gradient(d_out, d_in, ranks):
 def test_calls_that_are_not_its(T, d_out, d_in, kinds, rank, conv1d):
     p = make_problem(T + d_out, d_in, d_out, [T - 1000, 1000], kinds, [rank])
     run(p, d_in, d_out, 0, conv1d=conv1d, tag=f"{T} {d_out} {kinds}")
+
+
+@pytest.mark.parametrize("clients,tokens,d_out,d_in,kind,want", [
+    (512, 1, 256, 11008, L, 0), (512, 1, 256, 11008, N, 0), (512, 1, 64, 6144, L, 1), (3000, 1, 64, 6144, N, 1), (500, 4, 256, 4096, L, 0), (512, 4, 64, 1024, L, 1), (128, 4, 128, 4096, L, 1),
+    (750, 8, 64, 4096, L, 1)])
+def test_which_calls_of_short_segments_take_it(clients, tokens, d_out, d_in, kind, want):
+    """A chunk of rows costs as much whatever it holds; without adapters it may cross segments."""
+    p = make_problem(clients + d_in, d_in, d_out, [tokens] * clients, [kind], [8])
+    dev = gh.upload_adapters(p["ads"], d_in, d_out, grads=False)
+    b = sb.Batch(d_in, d_out, p["off"], dev.descs)
+    W, dY = gh.to_dev(p["W"]), gh.to_dev(p["dY"])
+    dX = torch.full((p["T"], d_in), float("nan"), device="cuda", dtype=torch.bfloat16)
+    assert shortk_launches(lambda: sb.symb_base_linear_bwd_input(gh.handle(), b, dY, W, dX, sb.SYMB_BWD_FULL, gh.workspace(b, sb.SYMB_OP_BWD_INPUT))) == want
+    rows = synth.sample_rows([0, p["T"]], 100, f"short{clients}", block=64)
+    check_dx(gh.bf16_to_f64(dX)[rows], p["off"], oracle_ads(p["ads"]), p["dY"], p["W"], "dX", rows=rows)
+    assert not torch.isnan(dX.float()).any()
