@@ -2,8 +2,8 @@
 // the tiles' prologues and stores, one behind the other; here the inner dimension is short enough that a wavefront keeps its 64 columns of W in registers (128 of them at
 // 256 outputs) and streams rows past them.
 //
-// Bound by the stores of dX.  16384 rows of 6144 <- 256, 201 MB of them: 84 us in 256x256 tiles,
-// 79 here with three outputs in turn (2.5 TB/s, what a copy writes), the training step 240 -> 219; 6000 rows 41.0 -> 27.2.  A workgroup is 4 wavefronts, 256 columns; its 32-row chunks (with adapters never across a segment)
+// 16384 rows of 6144 <- 256, 201 MB of dX: 85 us in 256x256 tiles, 80 here with a wait for every chunk's stores, 73 with those left open (three sets of operands in turn); 6000 rows 39.2, 29.4, 26.1.  That is 2.8 TB/s
+// of stores: a kernel that only stores reaches 6.9, a copy writes 2.7, so the stores alone are not what bounds it; what does has not been measured.  A workgroup is 4 wavefronts, 256 columns; its 32-row chunks (with adapters never across a segment)
 // come in by LDS DMA through a ring of three, one barrier per chunk, and every wavefront multiplies all 32 rows with its own columns.  Two workgroups per CU, so that one's stores run beside the
 // other's products.  The columns of a wavefront are dealt out so that a lane ends up with 16 consecutive ones of a row, 32 bytes: output goes to memory from the registers, whole
 // 128-byte lines per row between four lanes, with no staging.
@@ -35,7 +35,8 @@ symb_gemm_shortk_kernel(const ShortKParams p) {
     constexpr int WK = KS < 4 ? KS : 4;                  // 32-k steps of the weight that pass through LDS at a time, a wavefront's 4 KiB each
     constexpr int SWZ = CPR % 16 == 0 ? 15 : 7;
     static_assert(KS % 2 == 0 && KS <= 8, "whole requests; the weight fits the registers");
-    constexpr int BYTES = NBUF * STAGE > 4 * WK * 4096 ? NBUF * STAGE : 4 * WK * 4096;
+    constexpr int H_AT = STAGE, BUF = STAGE + 32 * 64;   // a buffer: rows of dY, rows of dH
+    constexpr int BYTES = NBUF * BUF > 4 * WK * 4096 ? NBUF * BUF : 4 * WK * 4096;
     __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES];
     const int strips = (p.N + SHORTK_COLS - 1) / SHORTK_COLS, total = strips * p.groups, per_xcd = (total + 7) >> 3;
     const int lin = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
@@ -90,32 +91,41 @@ symb_gemm_shortk_kernel(const ShortKParams p) {
         srow[i] = r;
         src0[i] = p.G + ((pos & ~SWZ) | ((pos ^ r) & SWZ)) * 8;
     }
-    RowChunk cur = p.chunks[first];
+    // dH, eight rows of 64 bytes per wavefront, lanes 0 to 31: position pos of row r holds chunk pos ^ (r / 2) % 4
+    const int hrow = wave * 8 + ((lane & 31) >> 2);
+    const bf16* const hsrc = p.h_rows + ((lane & 3) ^ ((hrow >> 1) & 3)) * 8;
+    const bool h = p.h_rows != nullptr;
+    // (scalar loads: a vector load's wait would be one for all stores before it)
+    auto chunk = [&](int i) __attribute__((always_inline)) {
+        const __attribute__((address_space(4))) int* const c = (const __attribute__((address_space(4))) int*)reinterpret_cast<const int*>(p.chunks + min(i, last - 1));
+        return RowChunk{c[0], c[1], c[2], 0};
+    };
     auto dma = [&](int buf, const RowChunk& ch) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < REQ; ++i)
-            __builtin_amdgcn_global_load_lds((glb_void_t*)(src0[i] + (size_t)(ch.row0 + min(srow[i], ch.nrows - 1)) * K), (lds_void_t*)(smem + buf * STAGE + (wave * REQ + i) * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((glb_void_t*)(src0[i] + (size_t)(ch.row0 + min(srow[i], ch.nrows - 1)) * K), (lds_void_t*)(smem + buf * BUF + (wave * REQ + i) * 1024), 16, 0, 0);
+        if (h && lane < 32)
+            __builtin_amdgcn_global_load_lds((glb_void_t*)(hsrc + (size_t)(ch.row0 + min(hrow, ch.nrows - 1)) * 32), (lds_void_t*)(smem + buf * BUF + H_AT + wave * 512), 16, 0, 0);
     };
-    auto load_h = [&](const RowChunk& ch, u32x4 (&h)[2]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int b = 0; b < 2; ++b) h[b] = ld_glb16(p.h_rows + (size_t)(ch.row0 + min(b * 16 + l15, ch.nrows - 1)) * 32 + kq * 8);
-    };
-    u32x4 h[2] = {}, lf[4] = {};
+    u32x4 lf[4] = {};
     int seg = -1;
     bool lora = false;
+    RowChunk cur = chunk(first), next = chunk(first + 1), after = chunk(first + 2);
     dma(0, cur);
-    if (p.h_rows) load_h(cur, h);
-    RowChunk next = p.chunks[min(first + 1, last - 1)];
     if (first + 1 < last) dma(1, next);
+    // Stores that the last two chunks issued for certain: four each, where the chunk reaches into its second 16 rows and this wavefront's columns are all there.
+    const bool inside = n0 + 64 <= N;
+    bool four1 = false, four2 = false;
     int buf = 0;
     for (int it = first; it < last; ++it) {
-        const RowChunk after = p.chunks[min(it + 2, last - 1)];
+        const RowChunk later = chunk(it + 3);
         if (cur.seg != seg) {                            // (uniform) A_i: columns as in wf, ranks 8 (kq % 2) .. + 7, for both halves of the step
             seg = cur.seg;
             const SegDesc sd = p.seg[seg];
-            lora = p.h_rows && sd.kind == KIND_LORA;
+            lora = h && sd.kind == KIND_LORA;
             if (lora) {
-                const unsigned short* const a = reinterpret_cast<const unsigned short*>(sd.A);
+                const __attribute__((address_space(1))) unsigned short* const a =
+                    (const __attribute__((address_space(1))) unsigned short*)reinterpret_cast<const unsigned short*>(sd.A);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     const int n = min(n0 + shortk_col(c, l15), N - 1), q0 = (kq & 1) * 8;
@@ -128,10 +138,19 @@ symb_gemm_shortk_kernel(const ShortKParams p) {
                 }
             }
         }
-        // this wavefront's part of the chunk has landed (the newest requests may be the next one's, or stores behind them); behind the barrier everybody's has, and the buffer of
-        // the chunk before is free
-        if (it + 1 < last) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(REQ) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+        // This wavefront's part of the chunk has landed; behind the barrier everybody's has, and the buffer of the chunk before is free.  Behind its requests came the stores of the
+        // chunk two before, the next chunk's requests and the stores of the chunk before: those may stay open.  (Requests and stores are counted together and come back in order, so
+        // that a wait for fewer, or one that the compiler adds for a vector load of its own, is one for the stores just made.)
+        const bool more = it + 1 < last;
+        auto landed = [&](auto REQS) __attribute__((always_inline)) {
+            constexpr int R = decltype(REQS)::value;
+            if (four1 && four2) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(R + 8) : "memory");
+            else if (four1) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(R + 4) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(R) : "memory");
+        };
+        if (!more) landed(std::integral_constant<int, 0>{});
+        else if (h) landed(std::integral_constant<int, REQ + 1>{});
+        else landed(std::integral_constant<int, REQ>{});
         __builtin_amdgcn_s_barrier();
         const int nb = buf + 2 >= NBUF ? buf + 2 - NBUF : buf + 2;
         if (it + 2 < last) dma(nb, after);
@@ -140,7 +159,7 @@ symb_gemm_shortk_kernel(const ShortKParams p) {
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[b][c] = floatx4{0.f, 0.f, 0.f, 0.f};
-        const unsigned base = lds0 + (unsigned)(buf * STAGE + l15 * ROW);
+        const unsigned base = lds0 + (unsigned)(buf * BUF + l15 * ROW);
 #pragma unroll
         for (int g = 0; g < KS; g += 2) {
             u32x4 x[2][2];
@@ -165,13 +184,19 @@ symb_gemm_shortk_kernel(const ShortKParams p) {
                         acc[b][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[g + s][c]), __builtin_bit_cast(bf16x8, x[s][b]), acc[b][c], 0, 0, 0);
         }
         if (lora) {
+            u32x4 hv[2];
+            const unsigned hat = lds0 + (unsigned)(buf * BUF + H_AT + l15 * 64 + ((kq ^ ((l15 >> 1) & 3)) * 16));
+#pragma unroll
+            for (int b = 0; b < 2; ++b) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(hv[b]) : "v"(hat), "n"(b * 1024));
+            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+#pragma unroll
+            for (int b = 0; b < 2; ++b) asm volatile("" : "+v"(hv[b]));
 #pragma unroll
             for (int b = 0; b < 2; ++b)
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    acc[b][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, lf[c]), __builtin_bit_cast(bf16x8, h[b]), acc[b][c], 0, 0, 0);
+                    acc[b][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, lf[c]), __builtin_bit_cast(bf16x8, hv[b]), acc[b][c], 0, 0, 0);
         }
-        if (p.h_rows && it + 1 < last) load_h(next, h);
         // C[row b * 16 + l15][n0 + 16 kq ..]: block c holds columns 4 c .. + 3 of the lane's 16
         const int n = n0 + kq * 16;
 #pragma unroll
@@ -184,8 +209,11 @@ symb_gemm_shortk_kernel(const ShortKParams p) {
                 if (n + half * 8 < N) *reinterpret_cast<uint4*>(out + half * 8) = make_uint4(pack2_bf16(u[0], u[1]), pack2_bf16(u[2], u[3]), pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]));
             }
         }
+        four2 = four1;
+        four1 = inside && cur.nrows > 16;
         cur = next;
         next = after;
+        after = later;
         buf = buf + 1 == NBUF ? 0 : buf + 1;
     }
 }

@@ -1230,8 +1230,8 @@ symb_status run_narrow(symb_handle h, const symb_batch* b, const BatchInfo& bi, 
 }
 
 // The input gradient of a layer of 64 to 256 outputs over many rows (shortk_kernel.hpp): its chunks of rows, none if the call is not one for it.  Enough of them that each of two workgroups per CU has four; up
-// to 128 outputs not where many rows of a large output leave nothing but its stores (tiled kernel / this, without adapters, us, columns x rows: 64 outputs 1024 x 16384 15.6 / 11.9, 6144 x 3000 21.3 / 13.3, 11008 x 6000 47.0 / 43.4,
-// 4096 x 16384 49.8 / 48.5, x 20480 50.8 / 59.4, 6144 x 20480 74.9 / 82.2; 256 outputs 2048 x 10000 27.3 / 17.7, 6144 x 6000 41.0 / 27.2, x 16384 84.3 / 79.2, 11008 x 10000 107.5 / 83.5, 24576 x 10000 206 / 172).
+// to 128 outputs not where many rows of a large output leave nothing but its stores (tiled kernel / this, without adapters, us, columns x rows: 64 outputs 1024 x 16384 13.5 / 11.8, 6144 x 3000 18.8 / 13.0, 11008 x 6000 44.5 / 44.3,
+// 4096 x 16384 49.4 / 46.1, x 20480 49.8 / 55.3, 6144 x 20480 73.1 / 81.8; 256 outputs 2048 x 10000 25.4 / 17.8, 6144 x 6000 39.2 / 27.4, x 16384 85.3 / 74.3, 11008 x 10000 107.8 / 79.8, 24576 x 10000 205 / 164).
 // A chunk costs as much whatever it holds.  Tiled kernels / this, with the dH launch that both make, LoRA segments of 1 to 64 rows, 64 to 256 outputs, 1024 to 24576 columns: under four rows a chunk 1.04 to 1.5 up to 2.1
 // million chunks x columns, 0.94 to 1.2 to 3.2 million, 0.68 to 0.93 above (512 one-token clients of 11008 columns, 256 outputs, 96.8 / 141.6), but for 1.16 at 2048 of 24576; four rows and more 0.96 to 1.7,
 // but where 1000 rows and more fill 512 to 1280 chunks in all strips of columns together 0.82 to 1.02 (4096 columns x 500 clients of 4 47.9 / 58.2).  Without adapters a chunk may cross segments.

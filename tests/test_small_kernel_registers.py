@@ -38,3 +38,17 @@ def test_lds_reads_of_further_kernels(device_asm, name):  # noqa: F811
     assert only
     # (under a name that it looks for, and as often as it takes to make up the number of reads that it wants to see)
     test_lds_reads_are_untouched_until_their_wait("\n".join([only.replace("_ZN4symb" + name, "_ZN4symb26symb_lora_grad_wave_kernel")] * 20))
+
+
+def test_short_inner_dimension_kernel_leaves_its_stores_open(device_asm):  # noqa: F811
+    """Its loop waits once per chunk of rows, ahead of the barrier, for that chunk's requests: requests and stores are counted together, so that any other
+    wait in it (for a vector load, say) would be one for the output just stored."""
+    kernels = re.findall(r"^_ZN4symb23symb_gemm_shortk_kernel\w+:(.*?)^\.Lfunc_end", device_asm, re.S | re.M)
+    assert len(kernels) == 4
+    for text in kernels:
+        loop, stores = text[text.rindex("s_barrier"):], text.count("global_store_dwordx4")
+        assert stores == loop.count("global_store_dwordx4") == 4
+        assert not re.search(r"s_waitcnt[^\n]*vmcnt", loop), loop
+        before = text[:text.rindex("s_barrier")]
+        req = before.count("global_load_lds_dwordx4", before.rindex("s_barrier"))        # two chunks' requests, with dH
+        assert {f"vmcnt({n})" for n in (req // 2 + 8, req // 2 + 4, req // 2 + 7)} <= set(re.findall(r"vmcnt\(\d+\)", before))
