@@ -672,23 +672,21 @@ symb_gemm16_kernel(const GemmParams p) {
         __syncthreads();                             // LDS goes to the output tile / the arrival flag next
     }
 
-    // ---- K-split tile: every part but the last to arrive leaves its accumulators in the workspace (register order: 1 KiB
-    // per wavefront and 16x16 block); that one adds them to its own, all in part order (so the sum does not depend on who
-    // was last), and writes the tile.  A part counts itself in before it stores and again when its stores are complete; the last one waits for the
-    // others' second count.  The wait ends: whoever has counted itself in is running, stores and counts again without waiting for anybody.
-    // (Storing all parts and reading all of them back, the last one's too, was a store and its acknowledgement before every arrival and
-    // one more partial tile each way: a training step of 10240 rows of 4096 x 4096, both products with a split last round, 655 -> 641 us; mid-sized calls
-    // 1.6 to 2.8 % shorter.)
+    // ---- K-split tile: the parts leave their accumulators in the workspace (register order: 1 KiB
+    // per wavefront and 16x16 block); the one that arrives last adds all of them up in part order (so the sum does not depend on who
+    // was last) and writes the tile.  The smaller tiles' parts all store, then count themselves in; the last one reads the others' partial tiles (of more than four parts all of them, in one loop without a
+    // branch).  256x256 tiles, whose parts end at different times, behind whole tiles in a last round, and whose partial tiles are large, count in first (keep): all but the last store then and count again, the last
+    // one waits for that.  The wait ends: whoever has counted itself in is running, stores and counts again without waiting for anybody.  A store and its acknowledgement less for the last part, but two counts one behind the other
+    // for the rest.  Calls that store everything and read everything / as it is, geometric means: 256x256 tiles in two to four parts 1.01 to 1.1 (a training step of 10240 rows of 4096 x 4096 655 / 641 us);
+    // 256x128 tiles in two parts 1.04 (with two counts 1.02), three 1.02 (0.98); 128x128 tiles in two 1.03, three 1.02, four and more 0.98 to 1.0 (with two
+    // counts 1.01, 0.97, 0.94, 0.92 and, eight parts, 0.91: 112 rows of 4608 <- 4096 18.9 / 25.0 us).
     if (nparts > 1) {
         constexpr int PT = BM * BN;                  // floats per partial tile
         float* const tile_parts = p.partial + (size_t)slot * nparts * PT;
         int* const flag = reinterpret_cast<int*>(smem);
         constexpr int STORED = 1 << 16;              // second count: in the upper half of the counter
-        __syncthreads();                             // (the main loop's last reads of the LDS)
-        if (tid == 0) *flag = atomicAdd(p.k_count + slot, 1) & (STORED - 1);
-        __syncthreads();
-        const bool last_arrival = *flag == nparts - 1;
-        if (!last_arrival) {
+        constexpr bool keep = NBLK == 8;
+        auto store = [&]() __attribute__((always_inline)) {
             const unsigned lane_off = (unsigned)(wave * (MBLK * NBLK * 1024) + lane * 16);
             const unsigned long long mine = (unsigned long long)(tile_parts + (size_t)part * PT);
             if constexpr (TT::TALL) asm volatile(SYMB_GEMM16T_STORE_PARTIAL : : "v"(lane_off), "s"(mine) : "memory", SYMB_GEMM16T_VCLOBBERS);
@@ -700,11 +698,20 @@ symb_gemm16_kernel(const GemmParams p) {
             // stores are acknowledged by that L2 (write-through L1); the counter is bumped after that;
             // and the reader's L1 holds no line of the partial tiles (nobody read them in this launch).
             __syncthreads();
+        };
+        if (!keep) store();
+        else __syncthreads();                        // (the main loop's last reads of the LDS)
+        if (tid == 0) *flag = atomicAdd(p.k_count + slot, 1) & (STORED - 1);
+        __syncthreads();
+        const bool last_arrival = *flag == nparts - 1;
+        if (!last_arrival) {
+            if (!keep) return;
+            store();
             if (tid == 0) atomicAdd(p.k_count + slot, STORED);
             return;
         }
         if (tid == 0) {
-            while (__hip_atomic_load(p.k_count + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16 != nparts - 1) __builtin_amdgcn_s_sleep(1);
+            while (keep && __hip_atomic_load(p.k_count + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16 != nparts - 1) __builtin_amdgcn_s_sleep(1);
             // the last arrival leaves the counter as it found the launch: zero, for the next one
             __hip_atomic_store(p.k_count + slot, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -748,10 +755,10 @@ symb_gemm16_kernel(const GemmParams p) {
                 constexpr int g = decltype(G)::value;
                 float4 sum[16];
 #pragma unroll
-                for (int b = 0; b < 16; ++b) sum[b] = make_float4(-0.f, -0.f, -0.f, -0.f);      // (the neutral one: -0 + x = x for every x)
-                for (int q = 0; q < nparts; ++q) {
+                for (int b = 0; b < 16; ++b) sum[b] = keep ? make_float4(-0.f, -0.f, -0.f, -0.f) : src[(g * 16 + b) * 64];      // (the neutral one: -0 + x = x for every x)
+                for (int q = keep ? 0 : 1; q < nparts; ++q) {
                     float4 v[16];
-                    if (q != part) {
+                    if (!keep || q != part) {
 #pragma unroll
                         for (int b = 0; b < 16; ++b) v[b] = src[(size_t)q * (PT / 4) + (g * 16 + b) * 64];
                     } else {
