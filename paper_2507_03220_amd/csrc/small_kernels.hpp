@@ -98,9 +98,12 @@ constexpr int small_base_nbuf(int mb, bool nn, bool one = false) { return one ? 
 constexpr int small_shrink_nbuf(int mb) { return mb == 1 ? 4 : 2; }
 __device__ __forceinline__ int small_nn_swz(int k) { return (((k >> 3) & 1) << 2) | (k & 3); }
 
-// The wavefronts' sums meet in LDS; block b is added up in wavefront order and stored by wavefront b % 4.
-template <int CB, int MB, class STORE>
-__device__ __forceinline__ void small_sum(const floatx4 (&acc)[CB][MB], unsigned char* smem, STORE&& store) {
+// The wavefronts' sums meet in LDS; block b is added up in wavefront order and stored by wavefront b % 4.  beside(at): what else a wavefront leaves there, behind the sums.
+struct NothingBeside {
+    __device__ __forceinline__ void operator()(floatx4*) const {}
+};
+template <int CB, int MB, class STORE, class BESIDE = NothingBeside>
+__device__ __forceinline__ void small_sum(const floatx4 (&acc)[CB][MB], unsigned char* smem, STORE&& store, BESIDE&& beside = {}) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     floatx4* const red = reinterpret_cast<floatx4*>(smem);
     __syncthreads();                                     // every wavefront is done with what it had in LDS
@@ -108,6 +111,7 @@ __device__ __forceinline__ void small_sum(const floatx4 (&acc)[CB][MB], unsigned
     for (int c = 0; c < CB; ++c)
 #pragma unroll
         for (int m = 0; m < MB; ++m) red[((wave * CB + c) * MB + m) * 64 + lane] = acc[c][m];
+    beside(red + 4 * CB * MB * 64);
     __syncthreads();
 #pragma unroll
     for (int b = 0; b < CB * MB; ++b) {
@@ -522,64 +526,115 @@ symb_gemm_mid_kernel(const GemmParams p) {
         const int s = seg_of_row(p.off, seg_lo, seg_hi, m);
         return p.a_seg[s] + (size_t)(m - p.off[s]) * p.K;
     };
+    // LoRA steps, 32 of a segment's extended columns each, dealt out over the wavefronts so that a sum hangs on its own segment alone.  A segment of several goes by their number inside it.
+    // Segments of one step go by their number inside the tile, up to two to a wavefront; their operands wait in registers until the wavefronts' sums meet, and their terms, formed
+    // then, are added to the total, which does not depend on whose they were.  All by their number inside the segment, every one-step segment's first and only step is the first wavefront's, us: forward of 150 rows of
+    // 1024 -> 1536 in six such clients 13.0 -> 11.4, the training step 38.0 -> 33.9, of 200 rows of 768 x 768 in eight of ranks 8 to 32 34.4 -> 32.7; tiles with one client each pay
+    // for the second sum, 256 rows of 768 x 768 in four 25.4 -> 25.9.  (All by their number inside the tile, as fast, let a row's last bit hang on the tile's other segments.)
+    int end = min(m0 + MID_ROWS, p.M);
+    asm volatile("" : "+s"(end));                        // (a minimum of three is a vector instruction)
+    struct Seg {
+        const bf16* w;                                   // A_i [rank][N] (NN) or B_i [N][rank]
+        int rank, rpad, lo, hi;                          // rows of the tile; rpad 0: no adapter, or no rows
+    };
+    auto segment = [&](int s) __attribute__((always_inline)) {       // (scalar loads, all at once: vector loads would be waited for with the slices requested before them)
+        const __attribute__((address_space(4))) SegDesc* const sd = (const __attribute__((address_space(4))) SegDesc*)reinterpret_cast<const SegDesc*>(p.seg + s);
+        const __attribute__((address_space(4))) int* const off = (const __attribute__((address_space(4))) int*)reinterpret_cast<const int*>(p.off + s);
+        int kind = sd->kind, rank = sd->rank, rpad = sd->rpad, lo = off[0], hi = off[1];
+        const bf16* w = NN ? sd->A : sd->B;
+        asm volatile("" : "+s"(kind), "+s"(rank), "+s"(rpad), "+s"(lo), "+s"(hi), "+s"(w));
+        lo = max(lo, m0);
+        hi = min(hi, end);
+        return Seg{w, rank, kind == KIND_LORA && hi > lo ? rpad : 0, lo, hi};
+    };
+    struct Operands { u32x4 x[MB], w[CB]; };
+    // every load unconditional and in bounds, what does not belong to the step zeroed afterwards (under a condition each would be waited for)
+    auto fetch = [&](const Seg& sd, int e, Operands& o) __attribute__((always_inline)) {
+        const int rank = sd.rank, pk = e + kq * 8, pp = pk >= sd.rpad ? pk - sd.rpad : pk;         // both halves of the extended columns meet the same adapter matrix
+#pragma unroll
+        for (int m = 0; m < MB; ++m) o.x[m] = ld_glb16(p.ext + (size_t)min(max(m0 + m * 16 + l15, sd.lo), sd.hi - 1) * p.ext_pitch + pk);
+        if (!NN && (rank & 7) == 0) {
+#pragma unroll
+            for (int c = 0; c < CB; ++c) o.w[c] = ld_glb16(sd.w + (size_t)min(n0 + c * 16 + l15, p.N - 1) * rank + min(pp, rank - 8));
+        } else {                                         // A_i [rank][N] or B_i [N][rank], element by element
+            const __attribute__((address_space(1))) unsigned short* const w = (const __attribute__((address_space(1))) unsigned short*)reinterpret_cast<const unsigned short*>(sd.w);
+            unsigned el[CB][8];
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                const int n = min(n0 + c * 16 + l15, p.N - 1);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const int r = min(pp + q, rank - 1);
+                    el[c][q] = w[NN ? (size_t)r * p.N + n : (size_t)n * rank + r];
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                __builtin_amdgcn_sched_barrier(0);       // (every load before the first wait, then as they come)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) el[c][q] = pp + q < rank ? el[c][q] : 0u;
+                o.w[c] = u32x4{el[c][0] | el[c][1] << 16, el[c][2] | el[c][3] << 16, el[c][4] | el[c][5] << 16, el[c][6] | el[c][7] << 16};
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < CB; ++c) o.w[c] = pp < rank ? o.w[c] : u32x4{0u, 0u, 0u, 0u};
+    };
+    unsigned singles = 0, mine[2] = {0, 0};              // rows of segments of one step, of this wavefront's
+    Operands single[2];
     auto lora = [&](floatx4 (&acc)[CB][MB]) __attribute__((always_inline)) {
         if (!p.ext) return;
-        // Steps of the tile: number no goes to wavefront no % 4.  (By its number inside the segment, seven short clients of one step each are a chain on one wavefront, us
-        // of 256 rows of 768 x 768: forward 13.4 -> 15.3, input gradient 16.0 -> 20.7; 128 of 256 x 256 11.1 -> 12.7, 12.8 -> 17.6.)
-        int no = 0;
+        int no = 0, several = seg_hi + 1;                // the first segment of several steps
+        Seg own[2] = {}, sd_several = {};
         for (int s = seg_lo; s <= seg_hi; ++s) {
-            const SegDesc sd = p.seg[s];
-            const int lo = max(p.off[s], m0), hi = min(min(p.off[s + 1], m0 + MID_ROWS), p.M);
-            if (sd.kind != KIND_LORA || hi <= lo) continue;
-            for (int e = 0; e < 2 * sd.rpad; e += 32, ++no) {
-                if ((no & 3) != wave) continue;
-                const int pk = e + kq * 8, pp = pk >= sd.rpad ? pk - sd.rpad : pk;     // both halves of the extended columns meet the same adapter matrix
-                // every load unconditional and in bounds, what does not belong to the step zeroed afterwards (under a condition each would be waited for)
-                u32x4 xv[MB], wv[CB];
+            const Seg sd = segment(s);
+            if (!sd.rpad) continue;
+            if (sd.rpad > 16 || no == 8) {
+                if (several > seg_hi) { several = s; sd_several = sd; }
+                continue;
+            }
+            singles |= (unsigned)((1ull << (sd.hi - m0)) - (1ull << (sd.lo - m0)));
+            // (from the last wavefront down, as the others start with the first)
+            if (no == 3 - wave) own[0] = sd;
+            if (no == 7 - wave) own[1] = sd;
+            ++no;
+        }
 #pragma unroll
-                for (int m = 0; m < MB; ++m) xv[m] = ld_glb16(p.ext + (size_t)min(max(m0 + m * 16 + l15, lo), hi - 1) * p.ext_pitch + pk);
-                if (!NN && (sd.rank & 7) == 0) {
-#pragma unroll
-                    for (int c = 0; c < CB; ++c) wv[c] = ld_glb16(sd.B + (size_t)min(n0 + c * 16 + l15, p.N - 1) * sd.rank + min(pp, sd.rank - 8));
-                } else {                                 // A_i [rank][N] or B_i [N][rank], element by element
-                    const __attribute__((address_space(1))) unsigned short* const w =
-                        (const __attribute__((address_space(1))) unsigned short*)reinterpret_cast<const unsigned short*>(NN ? sd.A : sd.B);
-#pragma unroll
-                    for (int c = 0; c < CB; ++c) {
-                        const int n = min(n0 + c * 16 + l15, p.N - 1);
-                        unsigned e[8];
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            const int r = min(pp + q, sd.rank - 1);
-                            e[q] = w[NN ? (size_t)r * p.N + n : (size_t)n * sd.rank + r];
-                        }
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) e[q] = pp + q < sd.rank ? e[q] : 0u;
-                        wv[c] = u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
-                    }
-                }
+        for (int k = 0; k < 2; ++k)
+            if (own[k].rpad) {
+                mine[k] = (unsigned)((1ull << (own[k].hi - m0)) - (1ull << (own[k].lo - m0)));
+                fetch(own[k], 0, single[k]);
+            }
+        Seg sd = sd_several;
+        for (int s = several; s <= seg_hi;) {
+            const int lo = sd.lo, hi = sd.hi, steps = sd.rpad && !(singles >> (lo - m0) & 1) ? 2 * sd.rpad : 0;
+            for (int e = wave * 32; e < steps; e += 128) {
+                Operands o;
+                fetch(sd, e, o);
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
                     const int t = m0 + m * 16 + l15;
-                    xv[m] = t >= lo && t < hi ? xv[m] : u32x4{0u, 0u, 0u, 0u};
+                    asm volatile("" : "+v"(o.x[m]));     // (its load not under the condition below)
+                    o.x[m] = t >= lo && t < hi ? o.x[m] : u32x4{0u, 0u, 0u, 0u};
                 }
-#pragma unroll
-                for (int c = 0; c < CB; ++c) wv[c] = pp < sd.rank ? wv[c] : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
                     if (lo >= m0 + m * 16 + 16 || hi <= m0 + m * 16) continue;      // 16 rows of other segments
 #pragma unroll
                     for (int c = 0; c < CB; ++c)
-                        acc[c][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv[c]), __builtin_bit_cast(bf16x8, xv[m]), acc[c][m], 0, 0, 0);
+                        acc[c][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, o.w[c]), __builtin_bit_cast(bf16x8, o.x[m]), acc[c][m], 0, 0, 0);
                 }
             }
+            if (++s <= seg_hi) sd = segment(s);
         }
     };
     floatx4 acc[CB][MB];
     small_tile_of<CB, MB, NBUF, NN>(p.K, xrow, p.Bop + (NN ? (size_t)n0 : (size_t)n0 * p.K), NN ? p.N : p.K, p.N - n0, m0, min(MID_ROWS, p.M - m0), 0, 1, smem, acc, lora);
     const bool scale = p.epi_ia3 != 0 && p.tile_epi[tm] != 0;
+    static_assert(5 * CB * MB * 1024 <= SmallTile<CB, MB, NBUF, NN>::BYTES, "the wavefronts' sums and the terms fit the slice buffers");
+    const floatx4* const terms = reinterpret_cast<const floatx4*>(smem) + 4 * CB * MB * 64;
     small_sum<CB, MB>(acc, smem, [&](int r, int c, floatx4 v) __attribute__((always_inline)) {
         const int t = m0 + r, n = n0 + c;
+        if (singles >> r & 1) v += terms[((c >> 4) * MB + (r >> 4)) * 64 + lane];
         if (t >= p.M || n >= p.N) return;
         auto quad = [&](const bf16* q) __attribute__((always_inline)) {
             const uint2 b = *reinterpret_cast<const uint2*>(q);
@@ -595,6 +650,20 @@ symb_gemm_mid_kernel(const GemmParams p) {
             if (p.c_seg) out = p.c_seg[s] + (size_t)(t - p.off[s]) * p.N;
         }
         *reinterpret_cast<uint2*>(out + n) = make_uint2(pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]));
+    }, [&](floatx4* at) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (!mine[k]) continue;
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+                if (!(mine[k] >> (m * 16) & 0xffffu)) continue;
+#pragma unroll
+                for (int c = 0; c < CB; ++c) {
+                    const floatx4 v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, single[k].w[c]), __builtin_bit_cast(bf16x8, single[k].x[m]), floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    if (mine[k] >> (m * 16 + l15) & 1) at[(c * MB + m) * 64 + lane] = v;
+                }
+            }
+        }
     });
 }
 

@@ -60,3 +60,23 @@ def test_short_segments_that_share_a_tile(lens):
         assert n == 1
         check_y(gh.bf16_to_f64(Y), p["off"], oracle_ads(p["ads"]), p["X"], p["W"], p["bias"], f"Y conv1d={conv1d}")
         check_dx(gh.bf16_to_f64(gh.backward_input(p["off"], p["ads"], p["dY"], p["W"], conv1d=conv1d)), p["off"], oracle_ads(p["ads"]), p["dY"], p["W"], "dX")
+
+
+@pytest.mark.parametrize("lens,kinds,ranks,order", [
+    ([4, 7, 9, 12, 16, 5, 11, 40, 3, 24], [L, L, L, N, L, L, I, L, L, L], [8, 16, 5], [8, 2, 5, 0, 9, 3, 7, 1, 6, 4]),
+    ([4, 7, 40, 12, 24, 30], [L, L, L, N, L, L], [8, 16, 40, 33, 100], [5, 2, 0, 3, 4, 1])])
+def test_a_row_hangs_on_its_own_segment(lens, kinds, ranks, order):
+    """Clients that share tiles, in another order: every row has the same bits, in both directions and weight layouts."""
+    p = make_problem(31 + len(ranks), 264, 200, lens, kinds, ranks)
+    off = p["off"]
+    idx = np.concatenate([np.arange(off[i], off[i + 1]) for i in order])
+    noff = np.concatenate([[0], np.cumsum([lens[i] for i in order])]).astype(np.int32)
+    ads = [p["ads"][i] for i in order]
+    X, dY = np.ascontiguousarray(p["X"][idx]), np.ascontiguousarray(p["dY"][idx])
+    for conv1d in (False, True):
+        n, (Y, _) = launches(lambda: gh.forward(off, p["ads"], p["X"], p["W"], p["bias"], want_base=False, conv1d=conv1d), 16 + 4 + 2 + conv1d)
+        assert n == 1
+        again, _ = gh.forward(noff, ads, X, p["W"], p["bias"], want_base=False, conv1d=conv1d)
+        np.testing.assert_array_equal(gh.bf16_bits(again), gh.bf16_bits(Y)[idx])
+        dX = gh.backward_input(off, p["ads"], p["dY"], p["W"], conv1d=conv1d)
+        np.testing.assert_array_equal(gh.bf16_bits(gh.backward_input(noff, ads, dY, p["W"], conv1d=conv1d)), gh.bf16_bits(dX)[idx])
