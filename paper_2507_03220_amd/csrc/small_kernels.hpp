@@ -510,7 +510,7 @@ symb_small_narrow_kernel(const SmallStreamParams p) {
 // leaves the chip to a dozen workgroups.  Here up to 768 of K (the weight read N-contiguous: 512) are in flight at once, in the four wavefronts together, and the loads of the
 // LoRA steps (H and the adapter straight from memory, dealt out over the wavefronts) go out behind them: their latency is hidden, their matrix instructions
 // wait, as loads return in order, for the slices requested before.  256 rows of 768 x 768 with one rank-8 step
-// per tile, us: K-contiguous 11.7 -> 6.9, N-contiguous 11.5 -> 8.4 (11.4 with the element loads of A_i under a condition).  gemm_plan has the rule.  No pre-adapter
+// per tile, us: K-contiguous 11.7 -> 6.9, N-contiguous 11.5 -> 8.9 (11.4 with the element loads of A_i under a condition).  gemm_plan has the rule.  No pre-adapter
 // output, no terms computed beforehand.
 constexpr int MID_ROWS = 32;
 template <bool NN>
